@@ -15,12 +15,15 @@
 // denominator, 8 accumulator channels per lane) in fp32, in the log2 domain.
 // Rows, waves and finally splits are merged with the usual (max, sum,
 // accumulator) rescaling; the split that finishes last merges the partial
-// results of all splits of its head.  With grouped-query attention a work-group
-// of the dense path serves several query heads of one KV head per page load.
+// results of all splits of its head.
 //
-// Single-query attention is a matrix-vector product (about one flop per byte
-// read), far below the machine balance, so there is no MFMA here: the kernel is
-// bound by how fast HBM delivers the 8 KiB per selected (page, head).
+// With one query head per KV head this is a matrix-vector product (about one flop per
+// byte read): no matrix cores, the kernel is bound by how fast HBM delivers the 8 KiB per
+// selected (page, head).  With grouped-query attention up to eight query heads meet each
+// key and value; a work-group serves them all from one load on the matrix cores
+// (GroupState in quest_decode_core.h).  32 query / 8 KV heads, 4 sequences of up to 32k
+// tokens: a step takes 23 us instead of 40 us (2048-token budget; every query head loaded
+// its pages and selected its list alone), dense attention 70 us instead of 183 us.
 #include "quest_common.h"
 #include "quest_decode_core.h"
 #include "quest_team.h"
@@ -35,7 +38,6 @@ namespace {
 
 constexpr int kComputeUnits = 256;  // MI355X; only used to decide how finely to split
 constexpr int kDecWaves = 4;
-constexpr int kDecThreads = kDecWaves * kWave;
 // With the selection done in the same launch (see decode_split_kernel): 8 waves, the size
 // the selection is fastest at, and room in LDS for a page list of this many entries.
 constexpr int kSelWaves = 8;
@@ -70,6 +72,7 @@ struct DecodeArgs {
   int per_split;            // ceil(list_len / splits)
   int device_fences;        // QUEST_FLAG_DEVICE_FENCES: fences around the exchange as well
   int kv_heads, group;      // KV heads; query heads per KV head (num_heads = kv_heads * group)
+  int subs;                 // work-groups per KV head and split: ceil(group / kGroupHeads)
   int page_shift;           // log2(tokens per page)
   int unit_shift;           // log2(streaming units per page): 0 up to 16 tokens, 1 for 32, 2 for 64
   float scale_log2;         // sm_scale * log2(e)
@@ -81,9 +84,9 @@ struct DecodeArgs {
 // are handed over with device-scope stores and loads (quest_team.h), correct wherever
 // the splits run; the split that finishes last merges them, without a second launch.
 // kLoads: wave-wide 16-byte loads per unit of keys (and of values): 4, or 2 for 8-token
-// pages.  kG: query heads served by one work-group (they share the KV head, so a page is
-// loaded once for all of them): 1 unless grouped-query attention; a group of G heads is
-// served by G / kG work-groups per split.
+// pages.  kGroup: grouped-query attention: a work-group serves up to kGroupHeads query
+// heads of a KV head on the matrix cores, so a page is loaded (and a list selected) once
+// for all of them; units are 16 tokens for every page size (two 8-token pages).
 //
 // kSelItems > 0: the page list does not exist yet.  Every work-group first selects the
 // pages of its head itself from the scores (the same selection as quest_topk, kSelItems
@@ -91,15 +94,18 @@ struct DecodeArgs {
 // the list out.  The selection is repeated by every split of a head, which costs nothing
 // that matters (the compute units would idle meanwhile) and saves a launch and the trip
 // of the list through memory.
-template <int kLoads, int kG, int kWaves, int kSelItems>
+template <int kLoads, bool kGroup, int kWaves, int kSelItems>
 __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const DecodeArgs a) {
-  constexpr int kDecWaves = kWaves;
-  __shared__ float sm_acc[kDecWaves][kG][kHeadDim];
-  __shared__ float sm_m[kDecWaves][kG], sm_l[kDecWaves][kG];
+  constexpr int kThreads = kWaves * kWave;
+  constexpr int kSlots = kGroup ? kGroupHeads : 1;
+  constexpr int kStride = kGroup ? kGroupStride : kHeadDim;
+  constexpr bool kTwoPages = kGroup && kLoads == 2;  // pages per unit
+  __shared__ __align__(16) float sm_acc[kWaves][kSlots * kStride];
+  __shared__ float sm_m[kWaves][kSlots], sm_l[kWaves][kSlots];
   __shared__ uint32_t sm_before;
   // the selection's LDS only where there is a selection; the list as (logical page,
   // physical page) pairs
-  __shared__ typename std::conditional<(kSelItems > 0), TopkShared<kWaves * kWave>, char>::type sm_topk;
+  __shared__ typename std::conditional<(kSelItems > 0), TopkShared<kThreads>, char>::type sm_topk;
   __shared__ int2 sm_list[kSelItems > 0 ? kSelListCap : 1];
 
   // blockIdx.x = slot + 8 * split, blockIdx.y = group of 8 items: the linear work-group
@@ -108,14 +114,16 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   // front of the first load of every work-group.
   const int slot = blockIdx.x & 7;
   const int split = blockIdx.x >> 3;
-  const int item = blockIdx.y * 8 + slot;  // (sequence, KV head, kG query heads of its group)
-  const int subs = a.group / kG;           // work-groups per KV head and split: 1 without groups
+  const int item = blockIdx.y * 8 + slot;  // (sequence, KV head, query heads of its group)
+  const int subs = kGroup ? a.subs : 1;    // work-groups per KV head and split
   const int per_seq = a.kv_heads * subs;
   if (item >= a.batch * per_seq) return;
   const int b = a.batch == 1 ? 0 : item / per_seq;
   const int in_seq = item - b * per_seq;
   const int hk = subs == 1 ? in_seq : in_seq / subs;  // the KV head: its pages, its page list
-  const int h = hk * a.group + (in_seq - hk * subs) * kG;  // first query head served here
+  const int sub = in_seq - hk * subs;
+  const int h = hk * a.group + sub * kSlots;  // first query head served here
+  const int n_heads = kGroup ? min(kSlots, a.group - sub * kSlots) : 1;
   const size_t bh = (size_t)b * a.num_heads + h;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = lane_id();
@@ -123,21 +131,24 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   const int c = lane & 15;
   uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.counters + bh * kTeamWordStride);
 
-  // This wave's share of the page list: positions begin + wave + 4 i.  The list
-  // length used for the split (k_pages, or max_pages without a list) is known
-  // on the host, so list entries and page-table entries are fetched without
-  // waiting for seq_lens; entries past the valid pages are dropped afterwards.
+  // This wave's share of the page list: positions begin + wave + kWaves i (two pages per
+  // unit: pairs of positions).  The list length used for the split (k_pages, or max_pages
+  // without a list) is known on the host, so list entries and page-table entries are
+  // fetched without waiting for seq_lens; entries past the valid pages are dropped
+  // afterwards.
   const int begin = split * a.per_split;
   const int end = min(a.list_len, begin + a.per_split);
-  const int iters = (a.per_split + kDecWaves - 1) / kDecWaves;
+  const int iters = ((kTwoPages ? (a.per_split + 1) >> 1 : a.per_split) + kWaves - 1) / kWaves;
   const int32_t* idx_row =
       a.topk_idx ? a.topk_idx + ((size_t)b * a.kv_heads + hk) * a.k_pages : nullptr;
   const int32_t* pt = a.page_table + (size_t)b * a.max_pages;
+  const char* q = a.q + bh * (kHeadDim * 2);
   int seq_len;
-  uint4 qv[kG];
+  uint4 qv;
+  GroupState gs;
   if constexpr (kSelItems > 0) {
     const size_t row = (size_t)b * a.kv_heads + hk;
-    const bool writer = split == 0 && h == hk * a.group;  // one work-group per list writes it out
+    const bool writer = split == 0 && sub == 0;  // one work-group per list writes it out
     int32_t* out_row = a.topk_out + row * a.k_pages;
     // Behind the loads of the scores (loads complete in order, so nothing may be in front
     // of what the selection waits for): the page-table entries of this thread's pages,
@@ -149,10 +160,12 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
       for (int j = 0; j < kSelItems; ++j)
         my_phys[j] = pt[min((int)threadIdx.x * kSelItems + j, a.max_pages - 1)];
       seq_len = a.seq_lens[b];
-#pragma unroll
-      for (int g = 0; g < kG; ++g) qv[g] = ld16(a.q + (bh + g) * (kHeadDim * 2) + c * 16);
+      if constexpr (kGroup)
+        group_init(gs, q, n_heads, lane);
+      else
+        qv = ld16(q + c * 16);
     };
-    topk_block_put<kWaves * kWave, kSelItems>(
+    topk_block_put<kThreads, kSelItems>(
         sm_topk, a.scores + row * a.max_pages, a.seq_lens + b, a.max_pages, a.k_pages,
         [&](int pos, int page, int j, float) {
           int phys = 0;
@@ -171,17 +184,18 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     __syncthreads();
   } else {
     seq_len = a.seq_lens[b];
-#pragma unroll
-    for (int g = 0; g < kG; ++g) qv[g] = ld16(a.q + (bh + g) * (kHeadDim * 2) + c * 16);
+    if constexpr (kGroup)
+      group_init(gs, q, n_heads, lane);
+    else
+      qv = ld16(q + c * 16);
   }
 
-  Softmax st[kG];
+  Softmax st;
+  if constexpr (!kGroup) {
+    st.m = kNegBig;
+    st.l = 0.f;
 #pragma unroll
-  for (int g = 0; g < kG; ++g) {
-    st[g].m = kNegBig;
-    st[g].l = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) st[g].acc[j] = 0.f;
+    for (int j = 0; j < 8; ++j) st.acc[j] = 0.f;
   }
 
   // A page is streamed as 1 << unit_shift units of up to 16 tokens; lane i of a
@@ -192,30 +206,31 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     const int u = chunk + lane;
     const int e = u >> a.unit_shift;
     const int un_v = u & ((1 << a.unit_shift) - 1);
-    const int pos = begin + wave + kDecWaves * e;
-    int lp_v = -1, ph_v = 0;
-    if constexpr (kSelItems > 0) {
-      if (e < iters && pos < end) {
-        const int2 entry = sm_list[pos];
-        lp_v = entry.x, ph_v = entry.y;
+    // (logical, physical) page at position pos of the list; logical -1: nothing there
+    auto entry_at = [&](int pos, int& lp, int& ph) {
+      lp = -1, ph = 0;
+      if constexpr (kSelItems > 0) {
+        if (e < iters && pos < end) {
+          const int2 entry = sm_list[pos];
+          lp = entry.x, ph = entry.y;
+        }
+      } else {
+        if (e < iters && pos < end) lp = idx_row ? idx_row[pos] : pos;
+        if (lp >= 0 && lp < a.max_pages) ph = pt[lp];
       }
+      if (lp >= num_pages) lp = -1;
+    };
+    int lp_v, ph_v, lp2_v = -1, ph2_v = 0;
+    if constexpr (kTwoPages) {
+      const int pos = begin + 2 * (wave + kWaves * e);
+      entry_at(pos, lp_v, ph_v);
+      entry_at(pos + 1, lp2_v, ph2_v);
+      if (lp_v < 0) ph_v = 0;  // half a unit may be missing: it is read from page 0, and not used
+      if (lp2_v < 0) ph2_v = 0;
     } else {
-      if (e < iters && pos < end) lp_v = idx_row ? idx_row[pos] : pos;
-      if (lp_v >= 0 && lp_v < a.max_pages) ph_v = pt[lp_v];
+      entry_at(begin + wave + kWaves * e, lp_v, ph_v);
     }
-    if (lp_v >= num_pages) lp_v = -1;
 
-#define QUEST_LOAD_UNIT(regs, i)                                                               \
-  load_unit<kLoads>(regs, a.k_pool, a.v_pool, a.kv_heads, hk, seq_len, __builtin_amdgcn_readlane(lp_v, i), \
-                    __builtin_amdgcn_readlane(ph_v, i), __builtin_amdgcn_readlane(un_c, i),    \
-                    a.page_shift, lane)
-#define QUEST_FOLD(regs)                                  \
-  do {                                                    \
-    if (kG == 1)                                          \
-      fold_page(st[0], regs, qv[0], a.scale_log2, grp);   \
-    else                                                  \
-      fold_group(st, regs, qv, a.scale_log2, grp);        \
-  } while (0)
     // The units to stream are moved to the first n lanes (lists from the selection are
     // ascending and padded at the end, so normally they are there already; a caller's
     // list may have negative or out-of-range entries anywhere: those are skipped).
@@ -225,80 +240,117 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     // wait counts inside the loop are exact: a conditional load, or an index still
     // marked as in flight, makes it wait for everything outstanding at every step,
     // which leaves a single unit in flight.
-    const unsigned long long live = __ballot(lp_v >= 0);
+    const unsigned long long live = __ballot(lp_v >= 0 || lp2_v >= 0);
     const int n = __popcll(live);
     int un_c = un_v;
     if (live & (live + 1)) {  // not a prefix of the lanes: compact (wave-uniform branch)
-      const int to = lp_v >= 0 ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
+      const bool mine = lp_v >= 0 || lp2_v >= 0;
+      const int to = mine ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
                                       __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u)) : kWave - 1;
       // a dead lane's target is lane 63, which no live lane can have unless all 64 are
       // live (then this branch is not taken); its value there is never used (63 >= n)
       lp_v = __builtin_amdgcn_ds_permute(to * 4, lp_v);
       ph_v = __builtin_amdgcn_ds_permute(to * 4, ph_v);
       un_c = __builtin_amdgcn_ds_permute(to * 4, un_v);
+      if constexpr (kTwoPages) {
+        lp2_v = __builtin_amdgcn_ds_permute(to * 4, lp2_v);
+        ph2_v = __builtin_amdgcn_ds_permute(to * 4, ph2_v);
+      }
     }
     lp_v = settled(lp_v);
     ph_v = settled(ph_v);
-    PageRegsT<kLoads> ra, rb;
+    if constexpr (kTwoPages) {
+      lp2_v = settled(lp2_v);
+      ph2_v = settled(ph2_v);
+    }
+    using Regs = typename std::conditional<kGroup, GroupRegs, PageRegsT<kLoads>>::type;
+    auto load = [&](Regs& r, int i) {
+      const int lp = __builtin_amdgcn_readlane(lp_v, i);
+      const int ph = __builtin_amdgcn_readlane(ph_v, i);
+      if constexpr (!kGroup) {
+        load_unit<kLoads>(r, a.k_pool, a.v_pool, a.kv_heads, hk, seq_len, lp, ph,
+                          __builtin_amdgcn_readlane(un_c, i), a.page_shift, lane);
+      } else {
+        const auto row = [&](int p) { return (((size_t)p * a.kv_heads + hk) << a.page_shift) * kRowBytes; };
+        if constexpr (kTwoPages) {
+          const int lp2 = __builtin_amdgcn_readlane(lp2_v, i);
+          group_load<true>(r, a.k_pool, a.v_pool, row(ph),
+                           row(__builtin_amdgcn_readlane(ph2_v, i)) - 8 * kRowBytes, lane);
+          r.first = lp < 0 ? 0 : seq_len - lp * 8;
+          r.second = lp2 < 0 ? 0 : seq_len - lp2 * 8;
+        } else {
+          const int token = __builtin_amdgcn_readlane(un_c, i) * 16;
+          const size_t base = row(ph) + (size_t)token * kRowBytes;
+          group_load<false>(r, a.k_pool, a.v_pool, base, base, lane);
+          r.first = seq_len - (lp << a.page_shift) - token;
+          r.second = r.first - 8;
+        }
+      }
+    };
+    auto fold = [&](Regs& r) {
+      if constexpr (kGroup)
+        group_fold(gs, r, a.scale_log2, lane);
+      else
+        fold_page(st, r, qv, a.scale_log2, grp);
+    };
+    Regs ra, rb;
     if (n > 0) {
-      QUEST_LOAD_UNIT(ra, 0);
+      load(ra, 0);
       int j = 0;
       for (; j + 2 < n; j += 2) {
-        QUEST_LOAD_UNIT(rb, j + 1);
-        QUEST_FOLD(ra);
-        QUEST_LOAD_UNIT(ra, j + 2);
-        QUEST_FOLD(rb);
+        load(rb, j + 1);
+        fold(ra);
+        load(ra, j + 2);
+        fold(rb);
       }
       if (j + 1 < n) {
-        QUEST_LOAD_UNIT(rb, j + 1);
-        QUEST_FOLD(ra);
-        QUEST_FOLD(rb);
+        load(rb, j + 1);
+        fold(ra);
+        fold(rb);
       } else {
-        QUEST_FOLD(ra);
+        fold(ra);
       }
     }
-#undef QUEST_LOAD_UNIT
-#undef QUEST_FOLD
   }
 
-  // the four DPP rows of the wave, then the four waves of the group
-#pragma unroll
-  for (int g = 0; g < kG; ++g) {
-    merge_rows(st[g]);
+  // the lanes of the wave that share a channel, then the waves of the group
+  if constexpr (kGroup) {
+    group_finish(gs, sm_acc[wave], sm_m[wave], sm_l[wave], lane);
+  } else {
+    merge_rows(st);
     if (lane < 16) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) sm_acc[wave][g][c * 8 + j] = st[g].acc[j];
+      for (int j = 0; j < 8; ++j) sm_acc[wave][c * 8 + j] = st.acc[j];
       if (lane == 0) {
-        sm_m[wave][g] = st[g].m;
-        sm_l[wave][g] = st[g].l;
+        sm_m[wave][0] = st.m;
+        sm_l[wave][0] = st.l;
       }
     }
   }
   __syncthreads();
   const int t = threadIdx.x;
+  const int n_out = n_heads * kHeadDim;
   // ---- this split's result per query head: written out if it is the only split, else
   // published as a partial; the split that arrives last merges
-#pragma unroll
-  for (int g = 0; g < kG; ++g) {
+  for (int x = t; x < n_out; x += kThreads) {
+    const int g = kGroup ? x / kHeadDim : 0, ch = x & (kHeadDim - 1);
     float m_tot = sm_m[0][g];
 #pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) m_tot = fmaxf(m_tot, sm_m[w][g]);
+    for (int w = 1; w < kWaves; ++w) m_tot = fmaxf(m_tot, sm_m[w][g]);
     float l_tot = 0.f, acc = 0.f;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
+    for (int w = 0; w < kWaves; ++w) {
       const float f = __builtin_amdgcn_exp2f(sm_m[w][g] - m_tot);
       l_tot += sm_l[w][g] * f;
-      acc += sm_acc[w][g][t & (kHeadDim - 1)] * f;
+      acc += sm_acc[w][g * kStride + ch] * f;
     }
     if (a.splits == 1) {
-      if (t < kHeadDim) {
-        store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + t, acc / l_tot);
-        if (t == 0 && a.lse) a.lse[bh + g] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
-      }
+      store_out(a.out, a.out_is_fp16, bh * kHeadDim + x, acc / l_tot);
+      if (ch == 0 && a.lse) a.lse[bh + g] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
     } else {
       const size_t ps = (bh + g) * a.splits + split;
-      if (t < kHeadDim) dev_st(a.part_acc + ps * kHeadDim + t, acc);
-      if (t == 0) {
+      dev_st(a.part_acc + ps * kHeadDim + ch, acc);
+      if (ch == 0) {
         dev_st(a.part_ml + ps * 2 + 0, m_tot);
         dev_st(a.part_ml + ps * 2 + 1, l_tot);
       }
@@ -316,11 +368,11 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   // one pass over the splits in chunks of 8, all loads of a chunk in flight at once, with
   // a running maximum (the same rescaling as between pages); always in split order, so the
   // result does not depend on which split arrived last
-  if (t >= kHeadDim) return;
 #pragma unroll 1
-  for (int g = 0; g < kG; ++g) {
+  for (int x = t; x < n_out; x += kThreads) {
+    const int g = kGroup ? x / kHeadDim : 0, ch = x & (kHeadDim - 1);
     const float* ml = a.part_ml + (bh + g) * a.splits * 2;
-    const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + t;
+    const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + ch;
     float mx = kNegBig, l_all = 0.f, o = 0.f;
     for (int s0 = 0; s0 < a.splits; s0 += 8) {
       float2 pml[8];
@@ -345,8 +397,8 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
       }
       mx = cm;
     }
-    store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + t, o / l_all);
-    if (t == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
+    store_out(a.out, a.out_is_fp16, bh * kHeadDim + x, o / l_all);
+    if (ch == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
   }
 }
 
@@ -357,17 +409,8 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
 // the ~1000 work-groups that are resident at once, so that all splits of a head
 // start together and the merge reads few partial results.
 namespace {
-// Query heads one work-group serves.  Heads of a group share a KV head, so its pages can
-// be loaded once for several of them: that pays on the dense path (4x less traffic; 47 us
-// against 88 us at 32 query / 8 KV heads, 32k tokens).  With a short page list it does not:
-// fewer, heavier work-groups and a merge over more partials (13.9 us against 10.1 us), so
-// there every query head keeps its own work-groups and the later heads of a group find
-// the pages in L2.
-int heads_per_group(const quest_cache& c, int k_pages) {
-  if (k_pages > 0) return 1;
-  const int g = group_size(c);
-  return g % 4 == 0 ? 4 : g % 2 == 0 ? 2 : 1;
-}
+// Work-groups per KV head and split: a group of query heads is served kGroupHeads at a time.
+int subs_of(const quest_cache& c) { return (group_size(c) + kGroupHeads - 1) / kGroupHeads; }
 struct SplitPlan {
   int list_len, per_split, splits;
 };
@@ -376,7 +419,7 @@ SplitPlan plan_splits(const quest_cache& c, int k_pages) {
   SplitPlan p;
   p.list_len = k_pages > 0 ? (k_pages < c.max_pages_per_seq ? k_pages : c.max_pages_per_seq)
                            : c.max_pages_per_seq;
-  const long bh = (long)c.batch * c.num_heads / heads_per_group(c, k_pages);  // work items per split
+  const long items = (long)c.batch * kv_heads(c) * subs_of(c);  // work-groups per split
   // the knob is in pages of 16 tokens: the same bytes per split for every page size
   const int shift = page_shift_of(c.page_size);
   const long pps = shift >= 0 && ((long)pages_per_split << 4 >> shift) > 0
@@ -386,16 +429,15 @@ SplitPlan plan_splits(const quest_cache& c, int k_pages) {
   // few (sequence, head) items: shorter splits, down to one unit of 16 tokens per wave,
   // until there is a work-group for every compute unit
   const long unit = kDecWaves << 4 >> shift > 0 ? (long)(kDecWaves << 4 >> shift) : 1;
-  const long fill = (kComputeUnits + bh - 1) / bh;
+  const long fill = (kComputeUnits + items - 1) / items;
   const long finest = (p.list_len + unit - 1) / unit;
   if (splits < fill) splits = fill < finest ? fill : finest;
-  const long qh = (long)c.batch * c.num_heads;  // a work-group's weight grows with its heads
   // Work-groups in all: two per compute unit stream best once there is enough work
   // (deeper streams per wave, fewer partial results to merge: 58 us against 62 us per
   // step at 4 sequences of 32 heads, 104 against 109 at 8); a single sequence of 32 heads
   // is faster with four (dense path: 100 us against 105 us).
-  const long max_groups = qh <= 32 ? 4 * kComputeUnits : 2 * kComputeUnits;
-  const long cap = max_groups / qh > 0 ? max_groups / qh : 1;
+  const long max_groups = items <= 32 ? 4 * kComputeUnits : 2 * kComputeUnits;
+  const long cap = max_groups / items > 0 ? max_groups / items : 1;
   if (splits > cap) splits = cap;
   if (splits < 1) splits = 1;
   if (splits > kMaxTeamSize) splits = kMaxTeamSize;
@@ -458,23 +500,32 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.counters = (uint64_t*)workspace;
   a.part_acc = workspace ? (float*)((char*)workspace + counter_bytes(c)) : nullptr;
   a.part_ml = a.part_acc ? a.part_acc + n_part * kHeadDim : nullptr;
-  const int kg = heads_per_group(c, a.k_pages);
-  const long items8 = ((long)c.batch * c.num_heads / kg + 7) / 8;
+  const bool group = a.group > 1;
+  a.subs = subs_of(c);
+  const long items8 = ((long)c.batch * a.kv_heads * a.subs + 7) / 8;
   if (items8 > 65535) {
     set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items8 * 8);
     return QUEST_ERR_SHAPE;
   }
   const dim3 grid((unsigned)(8 * a.splits), (unsigned)items8);
+#define QUEST_LAUNCH(L, G, W, I) \
+  hipLaunchKernelGGL((decode_split_kernel<L, G, W, I>), grid, dim3((W) * kWave), 0, s, a)
+#define QUEST_LAUNCH_FOR_CACHE(W, I)                   \
+  do {                                                 \
+    if (c.page_size == 8) {                            \
+      if (group) QUEST_LAUNCH(2, true, W, I);          \
+      else QUEST_LAUNCH(2, false, W, I);               \
+    } else {                                           \
+      if (group) QUEST_LAUNCH(4, true, W, I);          \
+      else QUEST_LAUNCH(4, false, W, I);               \
+    }                                                  \
+  } while (0)
   if (select) {
     const int mp = c.max_pages_per_seq;
-    const dim3 block(kSelWaves * kWave);
-#define QUEST_SELECT_CASE(I)                                                                 \
-  if (mp <= kSelWaves * kWave * (I)) {                                                       \
-    if (c.page_size == 8)                                                                    \
-      hipLaunchKernelGGL((decode_split_kernel<2, 1, kSelWaves, I>), grid, block, 0, s, a);   \
-    else                                                                                     \
-      hipLaunchKernelGGL((decode_split_kernel<4, 1, kSelWaves, I>), grid, block, 0, s, a);   \
-    return check_launch("quest_select_decode");                                              \
+#define QUEST_SELECT_CASE(I)                           \
+  if (mp <= kSelWaves * kWave * (I)) {                 \
+    QUEST_LAUNCH_FOR_CACHE(kSelWaves, I);              \
+    return check_launch("quest_select_decode");        \
   }
     QUEST_SELECT_CASE(2)
     QUEST_SELECT_CASE(5)
@@ -483,18 +534,9 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     set_error("quest_select_decode: internal: no selecting kernel for max_pages_per_seq = %d", mp);
     return QUEST_ERR_SHAPE;
   }
-#define QUEST_DECODE_LAUNCH(L, G) \
-  hipLaunchKernelGGL((decode_split_kernel<L, G, kDecWaves, 0>), grid, dim3(kDecThreads), 0, s, a)
-  if (c.page_size == 8) {
-    if (kg == 4) QUEST_DECODE_LAUNCH(2, 4);
-    else if (kg == 2) QUEST_DECODE_LAUNCH(2, 2);
-    else QUEST_DECODE_LAUNCH(2, 1);
-  } else {
-    if (kg == 4) QUEST_DECODE_LAUNCH(4, 4);
-    else if (kg == 2) QUEST_DECODE_LAUNCH(4, 2);
-    else QUEST_DECODE_LAUNCH(4, 1);
-  }
-#undef QUEST_DECODE_LAUNCH
+  QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0);
+#undef QUEST_LAUNCH_FOR_CACHE
+#undef QUEST_LAUNCH
   return check_launch("quest_sparse_decode");
 }
 }  // namespace

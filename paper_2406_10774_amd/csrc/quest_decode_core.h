@@ -92,48 +92,6 @@ __device__ __forceinline__ void fold_page(Softmax& st, PageRegsT<kLoads>& r, con
   st.m = m_new;
 }
 
-// The same unit against kG query heads that share the KV head (grouped-query
-// attention): keys and values are loaded once, the values converted to fp32
-// once, and every head keeps its own online-softmax state.
-template <int kLoads, int kG>
-__device__ __forceinline__ void fold_group(Softmax (&st)[kG], PageRegsT<kLoads>& r,
-                                           const uint4 (&qv)[kG], float scale_log2, int grp) {
-  bool live[kLoads];
-  float vf[kLoads][8];
-#pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    live[i] = grp + 4 * i < r.n_valid;  // stale slots of a partial page contribute nothing
-    const uint4 v = live[i] ? r.v[i] : make_uint4(0, 0, 0, 0);
-    vf[i][0] = lo(v.x), vf[i][1] = hi(v.x), vf[i][2] = lo(v.y), vf[i][3] = hi(v.y);
-    vf[i][4] = lo(v.z), vf[i][5] = hi(v.z), vf[i][6] = lo(v.w), vf[i][7] = hi(v.w);
-  }
-#pragma unroll
-  for (int g = 0; g < kG; ++g) {
-    float z[kLoads];
-    float m_new = st[g].m;
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
-      z[i] = live[i] ? row16_sum(dot8(qv[g], r.k[i], 0.f)) * scale_log2 : -INFINITY;
-      m_new = fmaxf(m_new, z[i]);
-    }
-    const float alpha = __builtin_amdgcn_exp2f(st[g].m - m_new);
-    float p[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) p[i] = __builtin_amdgcn_exp2f(z[i] - m_new);
-    float p_sum = p[0] + p[1];
-    if (kLoads == 4) p_sum += p[kLoads - 2] + p[kLoads - 1];
-    st[g].l = st[g].l * alpha + p_sum;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float acc = st[g].acc[j] * alpha;
-#pragma unroll
-      for (int i = 0; i < kLoads; ++i) acc += p[i] * vf[i][j];
-      st[g].acc[j] = acc;
-    }
-    st[g].m = m_new;
-  }
-}
-
 // Merge the online-softmax states of the wave's four DPP rows (lanes 16 apart, then lanes
 // 32 apart); every lane ends up with the merged state of its channels.
 __device__ __forceinline__ float as_f(uint32_t u) { return __builtin_bit_cast(float, u); }
@@ -156,6 +114,164 @@ __device__ __forceinline__ void merge_rows_step(Softmax& st) {
 __device__ __forceinline__ void merge_rows(Softmax& st) {
   merge_rows_step<false>(st);
   merge_rows_step<true>(st);
+}
+
+// ---- Grouped-query attention: one wave, up to kGroupHeads query heads that share the KV
+// head, one unit of 16 tokens at a time (pages of 8 tokens: two pages), on the matrix
+// cores.  Per unit 4 v_mfma_f32_16x16x32_f16 give the logits (16 tokens x 16 columns) and
+// 8 v_mfma_f32_16x16x16_f16 add the weighted values.  At 4 heads the same work is about
+// 450 vector instructions per unit, 1720 cycles on a SIMD for 8 KiB; here it is 12 matrix
+// instructions and about 100 others, the same for 2 or 8 heads.
+//
+// Columns: column n belongs to query head n % 8 (heads past the group: a zero query), in
+// two copies.  The weights are fp32; columns 0-7 carry their value rounded to fp16 and
+// columns 8-15 the fp16 of what that leaves, so the products with the fp16 values keep 23
+// bits of every weight, and the copies are added at the end.  The exponent reference
+// stays about 14 below the largest logit, so the largest weight is about 2^14: fp16's
+// subnormal step then costs a weight at most 2^-39 of the largest.
+//
+// Operand layouts (lane l: c = l % 16, g = l / 16).  Logits: row m of the first operand is
+// token 4 (m % 4) + m / 4, so the result leaves lane (c, g) with column c, tokens 4i + g, i =
+// 0..3, which is what the second product wants as its second operand.  Values: load r
+// of a unit leaves lane (c, g) with token 4r + g, channels 8c..8c+7; half e of the four
+// loads is row c (channel 8c + e) of the first operand of the e-th product.  Nothing moves
+// between lanes.  The keys' 64-byte segments per token are no slower than whole rows: both
+// halves of a cache line are requested one instruction apart (gather of 65536 units 80 us
+// against 82 us).
+constexpr int kGroupHeads = 8;
+constexpr int kGroupStride = kHeadDim + 4;  // floats per head in LDS: lanes spread over the banks
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Tokens of a unit that hold data: tokens [0, first) of the first eight and, of the others,
+// [8, 8 + second); anything from below zero to above eight.
+struct GroupRegs {
+  uint4 k[4], v[4];
+  int first, second;
+};
+
+struct GroupState {
+  uint4 q[4];       // query of column c's head: channels 32j + 8g .. +7
+  f32x4_t acc[8];   // [e]: channels 8 (4g + i) + e of column c
+  float ref, l;     // exponent reference of the column (log2), this lane's share of its sum
+};
+
+__device__ __forceinline__ void group_init(GroupState& st, const char* __restrict__ q, int heads,
+                                           int lane) {
+  const int head = lane & (kGroupHeads - 1);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint4 v = ld16(q + (head < heads ? head : 0) * kRowBytes + j * 64 + (lane >> 4) * 16);
+    st.q[j] = head < heads ? v : make_uint4(0, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) st.acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  st.ref = kNegBig;
+  st.l = 0.f;
+}
+
+// base_a: byte offset of the unit's first token in the pools; base_b: offset that token 8
+// has minus 8 rows (the same as base_a unless a unit is two pages).
+template <bool kTwoPages>
+__device__ __forceinline__ void group_load(GroupRegs& r, const char* __restrict__ k_pool,
+                                           const char* __restrict__ v_pool, size_t base_a,
+                                           size_t base_b, int lane) {
+  const int m = lane & 15;
+  const int token = 4 * (m & 3) + (m >> 2);
+  const size_t base = kTwoPages && token >= 8 ? base_b : base_a;
+  const char* k = k_pool + base + token * kRowBytes + (lane >> 4) * 16;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) r.k[j] = ld16_stream(k + j * 64);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    r.v[i] = ld16_stream(v_pool + (kTwoPages && i >= 2 ? base_b : base_a) + i * 1024 + lane * 16);
+}
+
+__device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float scale_log2, int lane) {
+  const int g = lane >> 4;
+  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, r.k[j]),
+                                               __builtin_bit_cast(half8_t, st.q[j]), s, 0, 0, 0);
+  float z[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) z[i] = s[i] * scale_log2;
+  if (r.first < 8 || r.second < 8) {  // stale slots contribute nothing, whatever they hold
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int t = 4 * (i & 1) + g;  // token within its eight
+      if (t >= (i < 2 ? r.first : r.second)) {
+        z[i] = -INFINITY;
+        r.v[i] = make_uint4(0, 0, 0, 0);
+      }
+    }
+  }
+  float top = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+  LanePair p2 = pair_across16(as_u(top));
+  p2 = pair_across32(as_u(fmaxf(as_f(p2.first), as_f(p2.second))));
+  top = fmaxf(as_f(p2.first), as_f(p2.second));
+  // weights stay at or below 2^15: the reference moves only when a logit passes that
+  const bool move = top > st.ref + 15.f;
+  if (__ballot(move)) {
+    const float ref = move ? top - 14.f : st.ref;
+    const float alpha = __builtin_amdgcn_exp2f(st.ref - ref);
+    st.ref = ref;
+    st.l *= alpha;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.acc[e] *= alpha;
+  }
+  half4_t w;
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float p = __builtin_amdgcn_exp2f(z[i] - st.ref);
+    sum += p;
+    const _Float16 part = (_Float16)p;
+    w[i] = (lane & 8) ? (_Float16)(p - (float)part) : part;
+  }
+  st.l += sum;
+  // halves 2d and 2d + 1 of the four loads
+  auto pick = [&](uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t sel) {
+    const uint2 u = make_uint2(__builtin_amdgcn_perm(b, a, sel), __builtin_amdgcn_perm(d, c, sel));
+    return __builtin_bit_cast(half4_t, u);
+  };
+#define QUEST_PV(d, member)                                                                          \
+  st.acc[2 * d] = __builtin_amdgcn_mfma_f32_16x16x16f16(                                             \
+      pick(r.v[0].member, r.v[1].member, r.v[2].member, r.v[3].member, 0x05040100u), w,              \
+      st.acc[2 * d], 0, 0, 0);                                                                       \
+  st.acc[2 * d + 1] = __builtin_amdgcn_mfma_f32_16x16x16f16(                                         \
+      pick(r.v[0].member, r.v[1].member, r.v[2].member, r.v[3].member, 0x07060302u), w,              \
+      st.acc[2 * d + 1], 0, 0, 0);
+  QUEST_PV(0, x)
+  QUEST_PV(1, y)
+  QUEST_PV(2, z)
+  QUEST_PV(3, w)
+#undef QUEST_PV
+}
+
+// The wave's result: acc[head * kGroupStride + channel], ref[head], l[head] (LDS).
+__device__ __forceinline__ void group_finish(GroupState& st, float* acc, float* ref, float* l,
+                                             int lane) {
+  LanePair s = pair_across16(as_u(st.l));
+  s = pair_across32(as_u(as_f(s.first) + as_f(s.second)));
+  const int head = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = row_ror_add<8>(st.acc[e][i]);  // the two parts of the weights
+    if (head < kGroupHeads) {
+      float4* to = reinterpret_cast<float4*>(acc + head * kGroupStride + 8 * (4 * g + i));
+      to[0] = make_float4(v[0], v[1], v[2], v[3]);
+      to[1] = make_float4(v[4], v[5], v[6], v[7]);
+    }
+  }
+  if (lane < kGroupHeads) {
+    ref[lane] = st.ref;
+    l[lane] = as_f(s.first) + as_f(s.second);
+  }
 }
 
 __device__ __forceinline__ void store_out(void* out, int out_is_fp16, size_t idx, float v) {

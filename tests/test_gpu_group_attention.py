@@ -1,0 +1,71 @@
+"""Attention of query-head groups on the matrix cores (grouped-query attention) at the sizes
+where a unit, a wave's share or a split can go wrong: sequences that end inside every part
+of a 16-token unit, groups that are not a power of two or need two work-groups, single
+pages, page pairs of 8 tokens with one missing, lists with holes, values that are fp16
+subnormals; dense, over a given list, and over the list the launch selects itself."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import quest_oracle as O
+from paper_2406_10774_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def bound(k_pool, v_pool, q, table, lens, idx, scale):
+    """Largest deviation from exact arithmetic, per output value.  A logit is a sum of 128
+    exact products in fp32: off by at most 128 * 2^-24 * sum |q_i k_i| (times the scale); a
+    weight relative to the sum of weights doubles that.  The weights keep 23 bits (2^-22
+    for both), and fp32 sums over n tokens add 2 n 2^-24.  All relative to sum p |v|."""
+    spread, _ = O.sparse_decode(k_pool, np.abs(v_pool), q, table, lens, idx, scale)
+    logit = float(np.nanmax(np.abs(k_pool.astype(np.float32)).sum(-1))) * float(np.abs(q).max()) * scale
+    n = max(int(x) for x in lens)
+    return (2 * 128 * 2.0 ** -24 * logit + 2.0 ** -21 + 2 * n * 2.0 ** -24) * spread + 1e-30
+
+
+@pytest.mark.parametrize("kv_heads,group", [(1, 2), (3, 3), (2, 5), (2, 8), (1, 9), (2, 16)])
+@pytest.mark.parametrize("S", [8, 16, 64])
+def test_unit_edges(kv_heads, group, S):
+    from gpu_util import Layer
+    lens = (1, 3, 7, 8, 9, 15, 16, 17, 31, 33, 64, 65, S * 37 + 5, S * 40)
+    w = synth.Workload(700 + group, f"group-S{S}", len(lens), kv_heads, lens, token_budget=S * 7,
+                       planted_per_head=2, page_size=S, decode_steps=0)
+    table, N = synth.make_page_table(w, permute=True)
+    k_pool, v_pool, _ = synth.fill_pools(w, table, N)          # stale slots hold NaN
+    rng = np.random.default_rng([group, S])
+    v_pool[..., 3::16] = np.where(np.isnan(v_pool[..., 3::16]), np.nan,
+                                  rng.integers(-1023, 1024, v_pool[..., 3::16].shape) * 2.0 ** -24).astype(np.float16)
+    k_pool *= np.float16(0.25)
+    q = rng.standard_normal((w.batch, kv_heads * group, 128)).astype(np.float16)
+    cur = np.array(lens, np.int32)
+    layer = Layer(k_pool, v_pool, table, cur, num_q_heads=kv_heads * group)
+    layer.build_meta()
+    scale = 1 / math.sqrt(128)
+
+    def check(got, lse, idx, what):
+        want, want_lse = O.sparse_decode(k_pool, v_pool, q, table, cur, idx, scale)
+        off = np.abs(got - want)
+        assert (off <= bound(k_pool, v_pool, q, table, cur, idx, scale)).all(), (what, float(off.max()))
+        assert np.abs(lse - want_lse).max() <= 1e-4, what
+
+    got, lse = layer.decode(q, None, 0)
+    check(got, lse, None, "dense")
+    K = w.k_pages
+    meta = O.build_meta(k_pool, table, cur)
+    sc = O.estimate(meta, q, table, cur, S)
+    idx, _ = O.topk(sc, cur, S, K)
+    holes = idx.copy()
+    for b in range(w.batch):
+        if w.pages_of(b) > 3:
+            holes[b, :, 1] = -1
+            holes[b, :, 2] = w.pages_of(b)
+    clean = np.where(holes >= 0, holes, -1)
+    for b in range(w.batch):
+        clean[b][clean[b] >= w.pages_of(b)] = -1
+    got, lse = layer.decode(q, holes, K)
+    check(got, lse, clean, "list")
+    for k_pages in (1, K, 64):
+        idx, keff, got, lse = layer.select_decode(q, k_pages, scores=sc.astype(np.float32))
+        check(got, lse, idx, f"select {k_pages}")
