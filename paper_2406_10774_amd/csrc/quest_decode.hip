@@ -29,6 +29,7 @@
 #include "quest_team.h"
 #include "quest_topk_core.h"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -36,7 +37,7 @@ namespace quest {
 
 namespace {
 
-constexpr int kComputeUnits = 256;  // MI355X; only used to decide how finely to split
+constexpr long kComputeUnits = 256;  // MI355X; only used to decide how finely to split
 constexpr int kDecWaves = 4;
 // With the selection done in the same launch (see decode_split_kernel): 8 waves, the size
 // the selection is fastest at, and room in LDS for a page list of this many entries.
@@ -131,14 +132,14 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   const int c = lane & 15;
   uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.counters + bh * kTeamWordStride);
 
-  // This wave's share of the page list: positions begin + wave + kWaves i (two pages per
+  // This work-group's share of the page list: positions begin .. end - 1 (two pages per
   // unit: pairs of positions).  The list length used for the split (k_pages, or max_pages
   // without a list) is known on the host, so list entries and page-table entries are
   // fetched without waiting for seq_lens; entries past the valid pages are dropped
   // afterwards.
   const int begin = split * a.per_split;
   const int end = min(a.list_len, begin + a.per_split);
-  const int iters = ((kTwoPages ? (a.per_split + 1) >> 1 : a.per_split) + kWaves - 1) / kWaves;
+  const int entries = kTwoPages ? (a.per_split + 1) >> 1 : a.per_split;
   const int32_t* idx_row =
       a.topk_idx ? a.topk_idx + ((size_t)b * a.kv_heads + hk) * a.k_pages : nullptr;
   const int32_t* pt = a.page_table + (size_t)b * a.max_pages;
@@ -198,37 +199,38 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     for (int j = 0; j < 8; ++j) st.acc[j] = 0.f;
   }
 
-  // A page is streamed as 1 << unit_shift units of up to 16 tokens; lane i of a
-  // round holds unit i of this wave: list entry i >> unit_shift, unit i & mask.
-  const int units = iters << a.unit_shift;
+  // A page is streamed as 1 << unit_shift units of up to 16 tokens, which the waves take in
+  // turn (so that a split of few large pages still occupies all of them); lane i of a round
+  // holds unit i of this wave.
+  const int units = ((entries << a.unit_shift) + kWaves - 1) / kWaves;
   const int num_pages = (seq_len + (1 << a.page_shift) - 1) >> a.page_shift;
   for (int chunk = 0; chunk < units; chunk += kWave) {
-    const int u = chunk + lane;
+    const int u = wave + kWaves * (chunk + lane);
     const int e = u >> a.unit_shift;
     const int un_v = u & ((1 << a.unit_shift) - 1);
     // (logical, physical) page at position pos of the list; logical -1: nothing there
     auto entry_at = [&](int pos, int& lp, int& ph) {
       lp = -1, ph = 0;
       if constexpr (kSelItems > 0) {
-        if (e < iters && pos < end) {
+        if (pos < end) {
           const int2 entry = sm_list[pos];
           lp = entry.x, ph = entry.y;
         }
       } else {
-        if (e < iters && pos < end) lp = idx_row ? idx_row[pos] : pos;
+        if (pos < end) lp = idx_row ? idx_row[pos] : pos;
         if (lp >= 0 && lp < a.max_pages) ph = pt[lp];
       }
       if (lp >= num_pages) lp = -1;
     };
     int lp_v, ph_v, lp2_v = -1, ph2_v = 0;
     if constexpr (kTwoPages) {
-      const int pos = begin + 2 * (wave + kWaves * e);
+      const int pos = begin + 2 * e;
       entry_at(pos, lp_v, ph_v);
       entry_at(pos + 1, lp2_v, ph2_v);
       if (lp_v < 0) ph_v = 0;  // half a unit may be missing: it is read from page 0, and not used
       if (lp2_v < 0) ph2_v = 0;
     } else {
-      entry_at(begin + wave + kWaves * e, lp_v, ph_v);
+      entry_at(begin + e, lp_v, ph_v);
     }
 
     // The units to stream are moved to the first n lanes (lists from the selection are
@@ -404,43 +406,51 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
 
 }  // namespace
 
-// Number of splits of a head's page list.  A split holds at least 256 tokens (sixteen
-// pages of 16: four per wave, two in flight at a time), and the whole launch stays within
-// the ~1000 work-groups that are resident at once, so that all splits of a head
-// start together and the merge reads few partial results.
+// How finely the page lists are split.
 namespace {
 // Work-groups per KV head and split: a group of query heads is served kGroupHeads at a time.
 int subs_of(const quest_cache& c) { return (group_size(c) + kGroupHeads - 1) / kGroupHeads; }
 struct SplitPlan {
   int list_len, per_split, splits;
 };
-SplitPlan plan_splits(const quest_cache& c, int k_pages) {
-  constexpr int pages_per_split = 16;
-  SplitPlan p;
-  p.list_len = k_pages > 0 ? (k_pages < c.max_pages_per_seq ? k_pages : c.max_pages_per_seq)
-                           : c.max_pages_per_seq;
-  const long items = (long)c.batch * kv_heads(c) * subs_of(c);  // work-groups per split
-  // the knob is in pages of 16 tokens: the same bytes per split for every page size
-  const int shift = page_shift_of(c.page_size);
-  const long pps = shift >= 0 && ((long)pages_per_split << 4 >> shift) > 0
-                       ? ((long)pages_per_split << 4 >> shift)
-                       : 1;
-  long splits = (p.list_len + pps - 1) / pps;
-  // few (sequence, head) items: shorter splits, down to one unit of 16 tokens per wave,
-  // until there is a work-group for every compute unit
-  const long unit = kDecWaves << 4 >> shift > 0 ? (long)(kDecWaves << 4 >> shift) : 1;
-  const long fill = (kComputeUnits + items - 1) / items;
-  const long finest = (p.list_len + unit - 1) / unit;
-  if (splits < fill) splits = fill < finest ? fill : finest;
-  // Work-groups in all: two per compute unit stream best once there is enough work
-  // (deeper streams per wave, fewer partial results to merge: 58 us against 62 us per
-  // step at 4 sequences of 32 heads, 104 against 109 at 8); a single sequence of 32 heads
-  // is faster with four (dense path: 100 us against 105 us).
+// With a page list: one work-group per compute unit, no more.  A second one on the same
+// unit competes for its load path (about 25 KiB per us), repeats the selection and
+// adds a partial result to merge: 6 sequences of 32 heads, 2048-token budget, selecting
+// launch: 36.0 us with 1 split, 39.6 with 2, 42.5 with 4; 8 sequences 46.8 / 49.2 / 49.8;
+// 40 heads of one sequence 13.4 us with 6 splits, 14.7 with 8; 16 sequences of 8 KV heads
+// with 4 query heads each 29.2 us with 2 splits, 35.0 with 4.  Only when the items
+// themselves leave a second round that is nearly empty are three splits of each better: 9
+// sequences of 32 heads 64.5 us with 1, 57.7 with 3 (10 sequences: 65.7 and 60.3; 12: 69.4
+// and 72.5; at 512 tokens 1 is better everywhere).
+// Short lists: a split merges in about 2.3 us, so 256 tokens stay whole (7.5 us against
+// 7.9 us), 512 and 1024 tokens are worth 8 splits (8.4 us against 10.1 us), more tokens
+// 16 (8 heads, 4096 tokens: 10.4 us, 12.1 with 8 splits, 11.0 with 32), very long lists a
+// split per 256 tokens.
+long list_splits(long items, long tokens) {
+  if (items > kComputeUnits)
+    return items < kComputeUnits * 11 / 8 && tokens >= 1024 ? 3 : 1;
+  if (tokens <= 256) return 1;
+  const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
+  return std::min(kComputeUnits / items, useful);
+}
+// All pages: a split holds at least 256 tokens; two work-groups per compute unit stream
+// best once there is enough work, a single sequence of 32 heads is faster with four (100 us
+// against 105 us).
+long dense_splits(long items, long tokens) {
   const long max_groups = items <= 32 ? 4 * kComputeUnits : 2 * kComputeUnits;
-  const long cap = max_groups / items > 0 ? max_groups / items : 1;
-  if (splits > cap) splits = cap;
-  if (splits < 1) splits = 1;
-  if (splits > kMaxTeamSize) splits = kMaxTeamSize;
+  long splits = (tokens + 255) / 256;
+  const long fill = (kComputeUnits + items - 1) / items;
+  const long finest = (tokens + 16 * kDecWaves - 1) / (16 * kDecWaves);
+  if (splits < fill) splits = std::min(fill, finest);
+  return std::min(splits, std::max(max_groups / items, 1l));
+}
+SplitPlan plan_splits(const quest_cache& c, int k_pages) {
+  SplitPlan p;
+  p.list_len = k_pages > 0 ? std::min(k_pages, c.max_pages_per_seq) : c.max_pages_per_seq;
+  const long items = (long)c.batch * kv_heads(c) * subs_of(c);  // work-groups per split
+  const long tokens = (long)p.list_len * c.page_size;
+  long splits = k_pages > 0 ? list_splits(items, tokens) : dense_splits(items, tokens);
+  splits = std::min(splits, std::min<long>(p.list_len, kMaxTeamSize));
   p.per_split = (int)((p.list_len + splits - 1) / splits);
   p.splits = (p.list_len + p.per_split - 1) / p.per_split;  // no empty split
   return p;

@@ -13,7 +13,7 @@ namespace {
 
 // Every GPU the library runs on holds its own copy of this array until the process
 // ends.  Counters and split-K partial results never need more than about 0.8 MiB (the
-// launch keeps batch * heads * splits within ~1000 work-groups); the rest is for the
+// launch keeps items * splits near one work-group per compute unit); the rest is for the
 // candidates of the two-stage selection of rows from 16384 pages on (batch * KV heads *
 // chunks * k_pages * 8 bytes: 0.6 MiB for one sequence of 32 heads at 512k tokens with a
 // budget of 4096 tokens).
