@@ -77,7 +77,7 @@ int quest_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out
     return QUEST_ERR_NULL;
   }
   // with a page list: enough for quest_select_decode and quest_decode_step as well
-  *out_bytes = k_pages > 0 ? step_workspace_bytes(*cache, k_pages) : decode_workspace_bytes(*cache, 0);
+  *out_bytes = k_pages > 0 ? step_workspace_bytes(*cache, k_pages) : dense_workspace_bytes(*cache);
   return QUEST_OK;
 }
 
@@ -182,12 +182,15 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
     set_error("quest_sparse_decode: k_pages must be >= 1 with a page list (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  const size_t need = decode_workspace_bytes(*cache, topk_idx ? k_pages : 0);
+  const size_t need = topk_idx ? decode_workspace_bytes(*cache, k_pages) : dense_workspace_bytes(*cache);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) {
     set_error("quest_sparse_decode: workspace of %zu bytes needed, %zu given", need,
               workspace ? workspace_bytes : (size_t)0);
     return QUEST_ERR_WORKSPACE;
   }
+  if (topk_idx == nullptr)
+    return launch_dense_decode(*cache, q, sm_scale, out, out_is_fp16 != 0, lse, workspace,
+                               (hipStream_t)stream);
   return launch_sparse_decode(*cache, q, topk_idx, k_pages, sm_scale, out, out_is_fp16 != 0, lse,
                               workspace, (hipStream_t)stream);
 }

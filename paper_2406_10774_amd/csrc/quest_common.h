@@ -53,8 +53,10 @@ int launch_topk(const quest_cache& c, const float* scores, int k_pages, int32_t*
 size_t topk_scratch_bytes(const quest_cache& c, int k_pages);
 int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                         int32_t* k_eff, void* scratch, hipStream_t s);
-int decode_num_splits(const quest_cache& c, int k_pages);
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages);
+size_t dense_workspace_bytes(const quest_cache& c);
+int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
+                        float* lse, void* workspace, hipStream_t s);
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
                          hipStream_t s);

@@ -1,7 +1,7 @@
 // Sparse paged decode attention (Figure 5 stage 2 / Section 3.4 of arXiv
 // 2406.10774): ordinary softmax attention of one query per (sequence, head)
-// over the tokens of the selected pages only.  With no page list it runs over
-// every page: the dense baseline the paper compares against (Section 3.1).
+// over the tokens of the selected pages only.  Attention over every page is
+// quest_dense.hip.
 //
 // Split-K flash-decoding.  One work-group per (sequence, head, split); each work-group of
 // four waves owns a contiguous slice of the head's page list, its waves take
@@ -23,7 +23,7 @@
 // key and value; a work-group serves them all from one load on the matrix cores
 // (GroupState in quest_decode_core.h).  32 query / 8 KV heads, 4 sequences of up to 32k
 // tokens: a step takes 23 us instead of 40 us (2048-token budget; every query head loaded
-// its pages and selected its list alone), dense attention 70 us instead of 183 us.
+// its pages and selected its list alone).
 #include "quest_common.h"
 #include "quest_decode_core.h"
 #include "quest_team.h"
@@ -44,39 +44,15 @@ constexpr int kDecWaves = 4;
 constexpr int kSelWaves = 8;
 constexpr int kSelListCap = 2048;
 
-// The same value in a register that no load is outstanding for: the compiler waits for
-// `v` here, once, instead of before every later use it cannot order against other loads.
-__device__ __forceinline__ int settled(int v) {
-  int r;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
-  return r;
-}
-
-struct DecodeArgs {
-  const char* k_pool;
-  const char* v_pool;
-  const char* q;
-  const int32_t* page_table;
-  const int32_t* seq_lens;
-  const int32_t* topk_idx;  // nullptr: all pages (or: selected inside the launch, see scores)
+struct DecodeArgs : AttnArgs {
+  const int32_t* topk_idx;  // the page list [B][kv heads][k_pages] (nullptr: selected inside the launch)
   const float* scores;      // selection inside the launch: scores [B][kv heads][max_pages] ...
   int32_t* topk_out;        // ... the list is also written here [B][kv heads][k_pages] ...
   int32_t* k_eff;           // ... and K_b here (nullable)
   int policy;               // QUEST_FLAG_KEEP_* bits
-  float* part_acc;          // [B*H*splits][D]   un-normalised accumulators
-  float* part_ml;           // [B*H*splits][2]   running max (log2 domain), denominator
-  void* out;
-  float* lse;
-  uint64_t* counters;       // [B*H] arrival counters, one per 256-byte slot (quest_team.h); zero between launches
-  int batch, num_heads, max_pages, k_pages, splits, out_is_fp16;
-  int list_len;             // entries of the page list the splits divide: k_pages, or max_pages
+  int k_pages, splits;
+  int list_len;             // entries of the page list the splits divide
   int per_split;            // ceil(list_len / splits)
-  int device_fences;        // QUEST_FLAG_DEVICE_FENCES: fences around the exchange as well
-  int kv_heads, group;      // KV heads; query heads per KV head (num_heads = kv_heads * group)
-  int subs;                 // work-groups per KV head and split: ceil(group / kGroupHeads)
-  int page_shift;           // log2(tokens per page)
-  int unit_shift;           // log2(streaming units per page): 0 up to 16 tokens, 1 for 32, 2 for 64
-  float scale_log2;         // sm_scale * log2(e)
 };
 
 // All splits of one (sequence, head) get work-group ids that are equal modulo 8
@@ -84,10 +60,8 @@ struct DecodeArgs {
 // one die and their traffic stays in one L2.  Nothing depends on that: partial results
 // are handed over with device-scope stores and loads (quest_team.h), correct wherever
 // the splits run; the split that finishes last merges them, without a second launch.
-// kLoads: wave-wide 16-byte loads per unit of keys (and of values): 4, or 2 for 8-token
-// pages.  kGroup: grouped-query attention: a work-group serves up to kGroupHeads query
-// heads of a KV head on the matrix cores, so a page is loaded (and a list selected) once
-// for all of them; units are 16 tokens for every page size (two 8-token pages).
+// kLoads, kGroup: see HeadState; a work-group serves one query head, or up to kGroupHeads
+// of a KV head, so that a page is loaded (and a list selected) once for all of them.
 //
 // kSelItems > 0: the page list does not exist yet.  Every work-group first selects the
 // pages of its head itself from the scores (the same selection as quest_topk, kSelItems
@@ -97,10 +71,9 @@ struct DecodeArgs {
 // of the list through memory.
 template <int kLoads, bool kGroup, int kWaves, int kSelItems>
 __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const DecodeArgs a) {
+  using Head = HeadState<kLoads, kGroup>;
   constexpr int kThreads = kWaves * kWave;
-  constexpr int kSlots = kGroup ? kGroupHeads : 1;
-  constexpr int kStride = kGroup ? kGroupStride : kHeadDim;
-  constexpr bool kTwoPages = kGroup && kLoads == 2;  // pages per unit
+  constexpr int kSlots = Head::kSlots, kStride = Head::kStride;
   __shared__ __align__(16) float sm_acc[kWaves][kSlots * kStride];
   __shared__ float sm_m[kWaves][kSlots], sm_l[kWaves][kSlots];
   __shared__ uint32_t sm_before;
@@ -128,25 +101,19 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   const size_t bh = (size_t)b * a.num_heads + h;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = lane_id();
-  const int grp = lane >> 4;
-  const int c = lane & 15;
   uint32_t* arrivals = reinterpret_cast<uint32_t*>(a.counters + bh * kTeamWordStride);
 
   // This work-group's share of the page list: positions begin .. end - 1 (two pages per
-  // unit: pairs of positions).  The list length used for the split (k_pages, or max_pages
-  // without a list) is known on the host, so list entries and page-table entries are
-  // fetched without waiting for seq_lens; entries past the valid pages are dropped
-  // afterwards.
+  // unit: pairs of positions).  The list length is known on the host, so list entries and
+  // page-table entries are fetched without waiting for seq_lens; entries past the valid
+  // pages are dropped afterwards.
   const int begin = split * a.per_split;
   const int end = min(a.list_len, begin + a.per_split);
-  const int entries = kTwoPages ? (a.per_split + 1) >> 1 : a.per_split;
-  const int32_t* idx_row =
-      a.topk_idx ? a.topk_idx + ((size_t)b * a.kv_heads + hk) * a.k_pages : nullptr;
+  const int entries = Head::kTwoPages ? (a.per_split + 1) >> 1 : a.per_split;
   const int32_t* pt = a.page_table + (size_t)b * a.max_pages;
   const char* q = a.q + bh * (kHeadDim * 2);
   int seq_len;
-  uint4 qv;
-  GroupState gs;
+  Head st;
   if constexpr (kSelItems > 0) {
     const size_t row = (size_t)b * a.kv_heads + hk;
     const bool writer = split == 0 && sub == 0;  // one work-group per list writes it out
@@ -161,10 +128,7 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
       for (int j = 0; j < kSelItems; ++j)
         my_phys[j] = pt[min((int)threadIdx.x * kSelItems + j, a.max_pages - 1)];
       seq_len = a.seq_lens[b];
-      if constexpr (kGroup)
-        group_init(gs, q, n_heads, lane);
-      else
-        qv = ld16(q + c * 16);
+      st.init(sm_acc[wave], q, n_heads, lane);
     };
     topk_block_put<kThreads, kSelItems>(
         sm_topk, a.scores + row * a.max_pages, a.seq_lens + b, a.max_pages, a.k_pages,
@@ -185,150 +149,40 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     __syncthreads();
   } else {
     seq_len = a.seq_lens[b];
-    if constexpr (kGroup)
-      group_init(gs, q, n_heads, lane);
-    else
-      qv = ld16(q + c * 16);
-  }
-
-  Softmax st;
-  if constexpr (!kGroup) {
-    st.m = kNegBig;
-    st.l = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) st.acc[j] = 0.f;
+    st.init(sm_acc[wave], q, n_heads, lane);
   }
 
   // A page is streamed as 1 << unit_shift units of up to 16 tokens, which the waves take in
-  // turn (so that a split of few large pages still occupies all of them); lane i of a round
-  // holds unit i of this wave.
+  // turn (so that a split of few large pages still occupies all of them).
   const int units = ((entries << a.unit_shift) + kWaves - 1) / kWaves;
   const int num_pages = (seq_len + (1 << a.page_shift) - 1) >> a.page_shift;
-  for (int chunk = 0; chunk < units; chunk += kWave) {
-    const int u = wave + kWaves * (chunk + lane);
+  stream_units<kLoads, kGroup>(st, a, hk, seq_len, units, lane, [&](int i, int& lp, int& ph, int& un,
+                                                                    int& lp2, int& ph2) {
+    const int u = wave + kWaves * i;
     const int e = u >> a.unit_shift;
-    const int un_v = u & ((1 << a.unit_shift) - 1);
-    // (logical, physical) page at position pos of the list; logical -1: nothing there
-    auto entry_at = [&](int pos, int& lp, int& ph) {
-      lp = -1, ph = 0;
+    un = u & ((1 << a.unit_shift) - 1);
+    auto entry_at = [&](int pos, int& l, int& p) {
       if constexpr (kSelItems > 0) {
         if (pos < end) {
           const int2 entry = sm_list[pos];
-          lp = entry.x, ph = entry.y;
+          l = entry.x, p = entry.y;
         }
       } else {
-        if (pos < end) lp = idx_row ? idx_row[pos] : pos;
-        if (lp >= 0 && lp < a.max_pages) ph = pt[lp];
+        if (pos < end) l = a.topk_idx[((size_t)b * a.kv_heads + hk) * a.k_pages + pos];
+        if (l >= 0 && l < a.max_pages) p = pt[l];
       }
-      if (lp >= num_pages) lp = -1;
+      if (l >= num_pages) l = -1;
     };
-    int lp_v, ph_v, lp2_v = -1, ph2_v = 0;
-    if constexpr (kTwoPages) {
-      const int pos = begin + 2 * e;
-      entry_at(pos, lp_v, ph_v);
-      entry_at(pos + 1, lp2_v, ph2_v);
-      if (lp_v < 0) ph_v = 0;  // half a unit may be missing: it is read from page 0, and not used
-      if (lp2_v < 0) ph2_v = 0;
+    if constexpr (Head::kTwoPages) {
+      entry_at(begin + 2 * e, lp, ph);
+      entry_at(begin + 2 * e + 1, lp2, ph2);
     } else {
-      entry_at(begin + e, lp_v, ph_v);
+      entry_at(begin + e, lp, ph);
     }
-
-    // The units to stream are moved to the first n lanes (lists from the selection are
-    // ascending and padded at the end, so normally they are there already; a caller's
-    // list may have negative or out-of-range entries anywhere: those are skipped).
-    // Two units in flight per wave: the next one is requested before the current one is
-    // folded.  Every load inside the loop is unconditional and the index registers are
-    // detached from the loads that produced them (one wait here), so the compiler's
-    // wait counts inside the loop are exact: a conditional load, or an index still
-    // marked as in flight, makes it wait for everything outstanding at every step,
-    // which leaves a single unit in flight.
-    const unsigned long long live = __ballot(lp_v >= 0 || lp2_v >= 0);
-    const int n = __popcll(live);
-    int un_c = un_v;
-    if (live & (live + 1)) {  // not a prefix of the lanes: compact (wave-uniform branch)
-      const bool mine = lp_v >= 0 || lp2_v >= 0;
-      const int to = mine ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
-                                      __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u)) : kWave - 1;
-      // a dead lane's target is lane 63, which no live lane can have unless all 64 are
-      // live (then this branch is not taken); its value there is never used (63 >= n)
-      lp_v = __builtin_amdgcn_ds_permute(to * 4, lp_v);
-      ph_v = __builtin_amdgcn_ds_permute(to * 4, ph_v);
-      un_c = __builtin_amdgcn_ds_permute(to * 4, un_v);
-      if constexpr (kTwoPages) {
-        lp2_v = __builtin_amdgcn_ds_permute(to * 4, lp2_v);
-        ph2_v = __builtin_amdgcn_ds_permute(to * 4, ph2_v);
-      }
-    }
-    lp_v = settled(lp_v);
-    ph_v = settled(ph_v);
-    if constexpr (kTwoPages) {
-      lp2_v = settled(lp2_v);
-      ph2_v = settled(ph2_v);
-    }
-    using Regs = typename std::conditional<kGroup, GroupRegs, PageRegsT<kLoads>>::type;
-    auto load = [&](Regs& r, int i) {
-      const int lp = __builtin_amdgcn_readlane(lp_v, i);
-      const int ph = __builtin_amdgcn_readlane(ph_v, i);
-      if constexpr (!kGroup) {
-        load_unit<kLoads>(r, a.k_pool, a.v_pool, a.kv_heads, hk, seq_len, lp, ph,
-                          __builtin_amdgcn_readlane(un_c, i), a.page_shift, lane);
-      } else {
-        const auto row = [&](int p) { return (((size_t)p * a.kv_heads + hk) << a.page_shift) * kRowBytes; };
-        if constexpr (kTwoPages) {
-          const int lp2 = __builtin_amdgcn_readlane(lp2_v, i);
-          group_load<true>(r, a.k_pool, a.v_pool, row(ph),
-                           row(__builtin_amdgcn_readlane(ph2_v, i)) - 8 * kRowBytes, lane);
-          r.first = lp < 0 ? 0 : seq_len - lp * 8;
-          r.second = lp2 < 0 ? 0 : seq_len - lp2 * 8;
-        } else {
-          const int token = __builtin_amdgcn_readlane(un_c, i) * 16;
-          const size_t base = row(ph) + (size_t)token * kRowBytes;
-          group_load<false>(r, a.k_pool, a.v_pool, base, base, lane);
-          r.first = seq_len - (lp << a.page_shift) - token;
-          r.second = r.first - 8;
-        }
-      }
-    };
-    auto fold = [&](Regs& r) {
-      if constexpr (kGroup)
-        group_fold(gs, r, a.scale_log2, lane);
-      else
-        fold_page(st, r, qv, a.scale_log2, grp);
-    };
-    Regs ra, rb;
-    if (n > 0) {
-      load(ra, 0);
-      int j = 0;
-      for (; j + 2 < n; j += 2) {
-        load(rb, j + 1);
-        fold(ra);
-        load(ra, j + 2);
-        fold(rb);
-      }
-      if (j + 1 < n) {
-        load(rb, j + 1);
-        fold(ra);
-        fold(rb);
-      } else {
-        fold(ra);
-      }
-    }
-  }
+  });
 
   // the lanes of the wave that share a channel, then the waves of the group
-  if constexpr (kGroup) {
-    group_finish(gs, sm_acc[wave], sm_m[wave], sm_l[wave], lane);
-  } else {
-    merge_rows(st);
-    if (lane < 16) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) sm_acc[wave][c * 8 + j] = st.acc[j];
-      if (lane == 0) {
-        sm_m[wave][0] = st.m;
-        sm_l[wave][0] = st.l;
-      }
-    }
-  }
+  st.finish(sm_acc[wave], sm_m[wave], sm_l[wave], lane);
   __syncthreads();
   const int t = threadIdx.x;
   const int n_out = n_heads * kHeadDim;
@@ -408,8 +262,6 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
 
 // How finely the page lists are split.
 namespace {
-// Work-groups per KV head and split: a group of query heads is served kGroupHeads at a time.
-int subs_of(const quest_cache& c) { return (group_size(c) + kGroupHeads - 1) / kGroupHeads; }
 struct SplitPlan {
   int list_len, per_split, splits;
 };
@@ -433,23 +285,11 @@ long list_splits(long items, long tokens) {
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
   return std::min(kComputeUnits / items, useful);
 }
-// All pages: a split holds at least 256 tokens; two work-groups per compute unit stream
-// best once there is enough work, a single sequence of 32 heads is faster with four (100 us
-// against 105 us).
-long dense_splits(long items, long tokens) {
-  const long max_groups = items <= 32 ? 4 * kComputeUnits : 2 * kComputeUnits;
-  long splits = (tokens + 255) / 256;
-  const long fill = (kComputeUnits + items - 1) / items;
-  const long finest = (tokens + 16 * kDecWaves - 1) / (16 * kDecWaves);
-  if (splits < fill) splits = std::min(fill, finest);
-  return std::min(splits, std::max(max_groups / items, 1l));
-}
 SplitPlan plan_splits(const quest_cache& c, int k_pages) {
   SplitPlan p;
-  p.list_len = k_pages > 0 ? std::min(k_pages, c.max_pages_per_seq) : c.max_pages_per_seq;
-  const long items = (long)c.batch * kv_heads(c) * subs_of(c);  // work-groups per split
-  const long tokens = (long)p.list_len * c.page_size;
-  long splits = k_pages > 0 ? list_splits(items, tokens) : dense_splits(items, tokens);
+  p.list_len = std::min(k_pages, c.max_pages_per_seq);
+  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);  // work-groups per split
+  long splits = list_splits(items, (long)p.list_len * c.page_size);
   splits = std::min(splits, std::min<long>(p.list_len, kMaxTeamSize));
   p.per_split = (int)((p.list_len + splits - 1) / splits);
   p.splits = (p.list_len + p.per_split - 1) / p.per_split;  // no empty split
@@ -462,8 +302,6 @@ size_t counter_bytes(const quest_cache& c) {
 }  // namespace
 
 size_t decode_counter_bytes(const quest_cache& c) { return counter_bytes(c); }
-
-int decode_num_splits(const quest_cache& c, int k_pages) { return plan_splits(c, k_pages).splits; }
 
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
   const size_t splits = plan_splits(c, k_pages).splits;
@@ -479,39 +317,22 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
                   int out_is_fp16, float* lse, void* workspace, hipStream_t s) {
   const bool select = scores != nullptr;
   DecodeArgs a;
-  a.k_pool = (const char*)c.k_pool;
-  a.v_pool = (const char*)c.v_pool;
-  a.q = (const char*)q;
-  a.page_table = c.page_table;
-  a.seq_lens = c.seq_lens;
+  fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   a.topk_idx = topk_idx;
   a.scores = scores;
   a.topk_out = topk_out;
   a.k_eff = k_eff;
   a.policy = c.flags;
-  a.batch = c.batch;
-  a.num_heads = c.num_heads;
-  a.kv_heads = kv_heads(c);
-  a.group = group_size(c);
-  a.max_pages = c.max_pages_per_seq;
-  a.k_pages = (topk_idx || select) ? k_pages : 0;
-  const SplitPlan p = plan_splits(c, a.k_pages);
+  a.k_pages = k_pages;
+  const SplitPlan p = plan_splits(c, k_pages);
   a.splits = p.splits;
   a.list_len = p.list_len;
   a.per_split = p.per_split;
-  a.device_fences = (c.flags & QUEST_FLAG_DEVICE_FENCES) != 0;
-  a.out = out;
-  a.out_is_fp16 = out_is_fp16;
-  a.lse = lse;
-  a.scale_log2 = sm_scale * kLog2e;
-  a.page_shift = page_shift_of(c.page_size);
-  a.unit_shift = a.page_shift > 4 ? a.page_shift - 4 : 0;
   const size_t n_part = (size_t)c.batch * c.num_heads * a.splits;
   a.counters = (uint64_t*)workspace;
   a.part_acc = workspace ? (float*)((char*)workspace + counter_bytes(c)) : nullptr;
   a.part_ml = a.part_acc ? a.part_acc + n_part * kHeadDim : nullptr;
   const bool group = a.group > 1;
-  a.subs = subs_of(c);
   const long items8 = ((long)c.batch * a.kv_heads * a.subs + 7) / 8;
   if (items8 > 65535) {
     set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items8 * 8);

@@ -3,6 +3,8 @@
 // wave with an online softmax.  See quest_decode.hip for the scheme.
 #pragma once
 
+#include <type_traits>
+
 #include "quest_common.h"
 
 namespace quest {
@@ -135,9 +137,10 @@ __device__ __forceinline__ void merge_rows(Softmax& st) {
 // 0..3, which is what the second product wants as its second operand.  Values: load r
 // of a unit leaves lane (c, g) with token 4r + g, channels 8c..8c+7; half e of the four
 // loads is row c (channel 8c + e) of the first operand of the e-th product.  Nothing moves
-// between lanes.  The keys' 64-byte segments per token are no slower than whole rows: both
-// halves of a cache line are requested one instruction apart (gather of 65536 units 80 us
-// against 82 us).
+// between lanes.  Keys are loaded like values and turned into rows through LDS (4 KiB per
+// wave, the 16-byte chunks of token t exclusive-ored with t: no bank conflicts); loading
+// them as the operand wants them, 64 bytes of each token per load, halves what a
+// compute unit can load (%KLDS%).
 constexpr int kGroupHeads = 8;
 constexpr int kGroupStride = kHeadDim + 4;  // floats per head in LDS: lanes spread over the banks
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
@@ -152,13 +155,15 @@ struct GroupRegs {
 };
 
 struct GroupState {
+  char* stage;      // kRowBytes * 16 bytes of LDS of this wave
   uint4 q[4];       // query of column c's head: channels 32j + 8g .. +7
   f32x4_t acc[8];   // [e]: channels 8 (4g + i) + e of column c
   float ref, l;     // exponent reference of the column (log2), this lane's share of its sum
 };
 
-__device__ __forceinline__ void group_init(GroupState& st, const char* __restrict__ q, int heads,
-                                           int lane) {
+__device__ __forceinline__ void group_init(GroupState& st, char* stage, const char* __restrict__ q,
+                                           int heads, int lane) {
+  st.stage = stage;
   const int head = lane & (kGroupHeads - 1);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -173,28 +178,32 @@ __device__ __forceinline__ void group_init(GroupState& st, const char* __restric
 
 // base_a: byte offset of the unit's first token in the pools; base_b: offset that token 8
 // has minus 8 rows (the same as base_a unless a unit is two pages).
-template <bool kTwoPages>
 __device__ __forceinline__ void group_load(GroupRegs& r, const char* __restrict__ k_pool,
                                            const char* __restrict__ v_pool, size_t base_a,
                                            size_t base_b, int lane) {
-  const int m = lane & 15;
-  const int token = 4 * (m & 3) + (m >> 2);
-  const size_t base = kTwoPages && token >= 8 ? base_b : base_a;
-  const char* k = k_pool + base + token * kRowBytes + (lane >> 4) * 16;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) r.k[j] = ld16_stream(k + j * 64);
+  for (int i = 0; i < 4; ++i) r.k[i] = ld16_stream(k_pool + (i < 2 ? base_a : base_b) + i * 1024 + lane * 16);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    r.v[i] = ld16_stream(v_pool + (kTwoPages && i >= 2 ? base_b : base_a) + i * 1024 + lane * 16);
+  for (int i = 0; i < 4; ++i) r.v[i] = ld16_stream(v_pool + (i < 2 ? base_a : base_b) + i * 1024 + lane * 16);
 }
 
 __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float scale_log2, int lane) {
-  const int g = lane >> 4;
-  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+  const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, r.k[j]),
+  for (int i = 0; i < 4; ++i) {
+    const int t = 4 * i + g;
+    st16(st.stage + t * kRowBytes + ((c ^ t) << 4), r.k[i]);
+  }
+  __builtin_amdgcn_wave_barrier();  // LDS serves a wave in order; keep the compiler to it
+  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+  const int token = 4 * (c & 3) + (c >> 2);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint4 k = ld16(st.stage + token * kRowBytes + (((4 * j + g) ^ token) << 4));
+    s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, k),
                                                __builtin_bit_cast(half8_t, st.q[j]), s, 0, 0, 0);
+  }
+  __builtin_amdgcn_wave_barrier();
   float z[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) z[i] = s[i] * scale_log2;
@@ -271,6 +280,199 @@ __device__ __forceinline__ void group_finish(GroupState& st, float* acc, float* 
   if (lane < kGroupHeads) {
     ref[lane] = st.ref;
     l[lane] = as_f(s.first) + as_f(s.second);
+  }
+}
+
+// The same value in a register that no load is outstanding for: the compiler waits for
+// `v` here, once, instead of before every later use it cannot order against other loads.
+__device__ __forceinline__ int settled(int v) {
+  int r;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
+  return r;
+}
+
+// What every attention launch is given.
+struct AttnArgs {
+  const char* k_pool;
+  const char* v_pool;
+  const char* q;
+  const int32_t* page_table;
+  const int32_t* seq_lens;
+  float* part_acc;      // un-normalised accumulators of the partial results, [..][D]
+  float* part_ml;       // their running max (log2 domain) and denominator, [..][2]
+  void* out;
+  float* lse;
+  uint64_t* counters;   // arrival counters, one per 256-byte slot (quest_team.h); zero between launches
+  int batch, num_heads, max_pages, out_is_fp16;
+  int device_fences;    // QUEST_FLAG_DEVICE_FENCES: fences around the exchange as well
+  int kv_heads, group;  // KV heads; query heads per KV head (num_heads = kv_heads * group)
+  int subs;             // work-groups per KV head: ceil(group / kGroupHeads)
+  int page_shift;       // log2(tokens per page)
+  int unit_shift;       // log2(streaming units per page): 0 up to 16 tokens, 1 for 32, 2 for 64
+  float scale_log2;     // sm_scale * log2(e)
+};
+
+inline int attention_subs(const quest_cache& c) { return (group_size(c) + kGroupHeads - 1) / kGroupHeads; }
+
+// All but the workspace.
+inline void fill_attn_args(AttnArgs& a, const quest_cache& c, const void* q, float sm_scale, void* out,
+                           int out_is_fp16, float* lse) {
+  a.k_pool = (const char*)c.k_pool;
+  a.v_pool = (const char*)c.v_pool;
+  a.q = (const char*)q;
+  a.page_table = c.page_table;
+  a.seq_lens = c.seq_lens;
+  a.out = out;
+  a.lse = lse;
+  a.batch = c.batch;
+  a.num_heads = c.num_heads;
+  a.max_pages = c.max_pages_per_seq;
+  a.out_is_fp16 = out_is_fp16;
+  a.device_fences = (c.flags & QUEST_FLAG_DEVICE_FENCES) != 0;
+  a.kv_heads = kv_heads(c);
+  a.group = group_size(c);
+  a.subs = attention_subs(c);
+  a.page_shift = page_shift_of(c.page_size);
+  a.unit_shift = a.page_shift > 4 ? a.page_shift - 4 : 0;
+  a.scale_log2 = sm_scale * kLog2e;
+}
+
+// A wave's attention state: one query head on the vector unit, or up to kGroupHeads query
+// heads of a KV head on the matrix cores.
+// kLoads: wave-wide 16-byte loads per unit of keys (and of values) of one query head: 4, or
+// 2 for 8-token pages.  A group's unit is 16 tokens for every page size.
+template <int kLoads, bool kGroup>
+struct HeadState {
+  static constexpr int kSlots = kGroup ? kGroupHeads : 1;             // query heads
+  static constexpr int kStride = kGroup ? kGroupStride : kHeadDim;    // floats per head in LDS
+  static constexpr bool kTwoPages = kGroup && kLoads == 2;            // pages per unit
+  using Regs = typename std::conditional<kGroup, GroupRegs, PageRegsT<kLoads>>::type;
+  typename std::conditional<kGroup, GroupState, Softmax>::type st;
+  uint4 qv;
+
+  // q: vectors of the first of `heads` query heads; lds: the wave's kSlots * kStride floats,
+  // where finish may leave the result.  Loads only (and constants): what it sets is first
+  // used by fold.
+  __device__ __forceinline__ void init(float* lds, const char* q, int heads, int lane) {
+    if constexpr (kGroup) {
+      static_assert(kSlots * kStride * sizeof(float) >= 16 * kRowBytes, "keys of a unit");
+      group_init(st, reinterpret_cast<char*>(lds), q, heads, lane);
+    } else {
+      qv = ld16(q + (lane & 15) * 16);
+      st.m = kNegBig;
+      st.l = 0.f;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) st.acc[j] = 0.f;
+    }
+  }
+  __device__ __forceinline__ void load(Regs& r, const AttnArgs& a, int hk, int seq_len, int lp, int ph,
+                                       int unit, int lp2, int ph2, int lane) {
+    if constexpr (!kGroup) {
+      load_unit<kLoads>(r, a.k_pool, a.v_pool, a.kv_heads, hk, seq_len, lp, ph, unit, a.page_shift, lane);
+    } else {
+      const auto row = [&](int p) { return (((size_t)p * a.kv_heads + hk) << a.page_shift) * kRowBytes; };
+      if constexpr (kTwoPages) {
+        group_load(r, a.k_pool, a.v_pool, row(ph), row(ph2) - 8 * kRowBytes, lane);
+        r.first = lp < 0 ? 0 : seq_len - lp * 8;
+        r.second = lp2 < 0 ? 0 : seq_len - lp2 * 8;
+      } else {
+        const size_t base = row(ph) + (size_t)unit * (16 * kRowBytes);
+        group_load(r, a.k_pool, a.v_pool, base, base, lane);
+        r.first = seq_len - (lp << a.page_shift) - unit * 16;
+        r.second = r.first - 8;
+      }
+    }
+  }
+  __device__ __forceinline__ void fold(Regs& r, float scale_log2, int lane) {
+    if constexpr (kGroup)
+      group_fold(st, r, scale_log2, lane);
+    else
+      fold_page(st, r, qv, scale_log2, lane >> 4);
+  }
+  // The wave's result per query head: acc[head * kStride + channel], m[head], l[head] (LDS).
+  __device__ __forceinline__ void finish(float* acc, float* m, float* l, int lane) {
+    if constexpr (kGroup) {
+      group_finish(st, acc, m, l, lane);
+    } else {
+      merge_rows(st);
+      if (lane < 16) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[lane * 8 + j] = st.acc[j];
+        if (lane == 0) m[0] = st.m, l[0] = st.l;
+      }
+    }
+  }
+};
+
+// Stream `units` units through the wave.  at(i, lp, ph, unit, lp2, ph2) says, lane by lane,
+// what the wave's i-th unit is: logical and physical page (and those of the second page of
+// a pair) and the unit within the page; a negative logical page: nothing there.  at is asked
+// for 64 units at a time, one per lane.
+template <int kLoads, bool kGroup, class At>
+__device__ __forceinline__ void stream_units(HeadState<kLoads, kGroup>& st, const AttnArgs& a, int hk,
+                                             int seq_len, int units, int lane, At at) {
+  using Head = HeadState<kLoads, kGroup>;
+  for (int chunk = 0; chunk < units; chunk += kWave) {
+    int lp_v = -1, ph_v = 0, un_v = 0, lp2_v = -1, ph2_v = 0;
+    at(chunk + lane, lp_v, ph_v, un_v, lp2_v, ph2_v);
+    if (Head::kTwoPages) {
+      if (lp_v < 0) ph_v = 0;  // half a unit may be missing: it is read from page 0, and not used
+      if (lp2_v < 0) ph2_v = 0;
+    }
+    // The units to stream are moved to the first n lanes (lists from the selection are
+    // ascending and padded at the end, so normally they are there already; a caller's
+    // list may have negative or out-of-range entries anywhere: those are skipped).
+    // Two units in flight per wave: the next one is requested before the current one is
+    // folded.  Every load inside the loop is unconditional and the index registers are
+    // detached from the loads that produced them (one wait here), so the compiler's
+    // wait counts inside the loop are exact: a conditional load, or an index still
+    // marked as in flight, makes it wait for everything outstanding at every step,
+    // which leaves a single unit in flight.
+    const bool mine = lp_v >= 0 || lp2_v >= 0;
+    const unsigned long long live = __ballot(mine);
+    const int n = __popcll(live);
+    if (live & (live + 1)) {  // not a prefix of the lanes: compact (wave-uniform branch)
+      const int to = mine ? (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
+                                      __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u)) : kWave - 1;
+      // a dead lane's target is lane 63, which no live lane can have unless all 64 are
+      // live (then this branch is not taken); its value there is never used (63 >= n)
+      lp_v = __builtin_amdgcn_ds_permute(to * 4, lp_v);
+      ph_v = __builtin_amdgcn_ds_permute(to * 4, ph_v);
+      un_v = __builtin_amdgcn_ds_permute(to * 4, un_v);
+      if (Head::kTwoPages) {
+        lp2_v = __builtin_amdgcn_ds_permute(to * 4, lp2_v);
+        ph2_v = __builtin_amdgcn_ds_permute(to * 4, ph2_v);
+      }
+    }
+    lp_v = settled(lp_v);
+    ph_v = settled(ph_v);
+    if (Head::kTwoPages) {
+      lp2_v = settled(lp2_v);
+      ph2_v = settled(ph2_v);
+    }
+    auto load = [&](typename Head::Regs& r, int i) {
+      st.load(r, a, hk, seq_len, __builtin_amdgcn_readlane(lp_v, i), __builtin_amdgcn_readlane(ph_v, i),
+              __builtin_amdgcn_readlane(un_v, i), Head::kTwoPages ? __builtin_amdgcn_readlane(lp2_v, i) : -1,
+              Head::kTwoPages ? __builtin_amdgcn_readlane(ph2_v, i) : 0, lane);
+    };
+    typename Head::Regs ra, rb;
+    if (n > 0) {
+      load(ra, 0);
+      int j = 0;
+      for (; j + 2 < n; j += 2) {
+        load(rb, j + 1);
+        st.fold(ra, a.scale_log2, lane);
+        load(ra, j + 2);
+        st.fold(rb, a.scale_log2, lane);
+      }
+      if (j + 1 < n) {
+        load(rb, j + 1);
+        st.fold(ra, a.scale_log2, lane);
+        st.fold(rb, a.scale_log2, lane);
+      } else {
+        st.fold(ra, a.scale_log2, lane);
+      }
+    }
   }
 }
 

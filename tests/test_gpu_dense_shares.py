@@ -1,0 +1,53 @@
+"""Attention over every page: the line of pages of all sequences and heads that the launch cuts
+into equal shares, where the cutting can go wrong: fewer pages than shares, shares that hold
+many whole items, items over many shares, more than 64 sequences (one lane each while the
+line is measured), heads by fours and one by one, groups that need two work-groups.  Against
+the oracle; a second call on the same workspace gives the same bits."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import quest_oracle as O
+from paper_2406_10774_amd import synth
+from test_gpu_group_attention import bound
+
+pytestmark = pytest.mark.gpu
+
+RAGGED70 = tuple(1 + (i * 37) % 90 for i in range(70))
+
+
+@pytest.mark.parametrize("kv_heads,group,S,lens", [
+    (32, 1, 16, (1,)), (32, 1, 16, (3001,)), (32, 1, 8, (1999, 16)), (36, 1, 64, (700,)),
+    (4, 1, 16, RAGGED70), (3, 1, 16, (5003, 1, 17)), (1, 1, 16, (9001,)), (1, 1, 32, RAGGED70 * 2),
+    (8, 1, 8, (260, 3, 4100, 900)), (2, 9, 16, (2100, 5, 333)), (1, 4, 8, RAGGED70), (2, 4, 64, (6007,)),
+])
+def test_dense_shares(kv_heads, group, S, lens):
+    import torch
+    from gpu_util import Layer
+    from paper_2406_10774_amd import binding as Q
+    w = synth.Workload(740, "dense", len(lens), kv_heads, lens, token_budget=S, planted_per_head=1,
+                       page_size=S, decode_steps=0)
+    table, N = synth.make_page_table(w, permute=True)
+    k_pool, v_pool, _ = synth.fill_pools(w, table, N)
+    k_pool *= np.float16(0.25)
+    rng = np.random.default_rng(len(lens))
+    q = rng.standard_normal((w.batch, kv_heads * group, 128)).astype(np.float16)
+    cur = np.array(lens, np.int32)
+    scale = 1 / math.sqrt(128)
+    want, want_lse = O.sparse_decode(k_pool, v_pool, q, table, cur, None, scale)
+    limit = bound(k_pool, v_pool, q, table, cur, None, scale)
+    for flags in (0, Q.QUEST_FLAG_DEVICE_FENCES):
+        layer = Layer(k_pool, v_pool, table, cur, num_q_heads=kv_heads * group, flags=flags)
+        ws = torch.zeros(Q.quest_workspace_bytes(layer.cache, 0), dtype=torch.uint8, device=layer.dev)
+        got = []
+        for _ in range(2):
+            out = torch.full(q.shape, float("nan"), device=layer.dev)
+            lse = torch.full(q.shape[:2], float("nan"), device=layer.dev)
+            Q.quest_sparse_decode(layer.cache, layer.half(q), None, 0, scale, out, lse, ws)
+            torch.cuda.synchronize()
+            got.append((out.cpu().numpy(), lse.cpu().numpy()))
+        off = np.abs(got[0][0] - want)
+        assert (off <= limit).all(), float(off.max())
+        assert np.abs(got[0][1] - want_lse).max() <= 1e-4
+        assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
