@@ -18,35 +18,55 @@ namespace quest {
 namespace {
 
 constexpr int kEstWaves = 4;
+constexpr unsigned kLdsPerUnit = 160 * 1024;  // of a gfx950 compute unit
 
 // Grid: x = blocks of pages, y = sequence, z = head.  The metadata table is head-major
 // over the physical pages, so with the sequences' pages laid out one after the other
 // consecutive work-groups walk memory in order (6.05 TB/s against 5.5 TB/s with the
 // heads in y, at 16 sequences of 32k tokens).
-template <bool kAppend, int kIters>
+//
+// Large tables (kIters = 4): a wave asks for its page-table entries only once it has the
+// length, so that the waves of a ragged batch that lie past the end of a sequence leave
+// early (16 sequences of 8k to 64k tokens: 91.6 us against 93.3 us; one of 512k 80.2 against
+// 81.9).  In a small table a trip to memory more would show (4 sequences, 8 heads: 7.0 us
+// against 6.8 us).
+template <bool kAppend, int kIters, bool kGroup>
 __global__ __launch_bounds__(kEstWaves* kWave) void estimate_kernel(const EstimateArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  estimate_wave<kAppend, kIters>(a, blockIdx.y, blockIdx.z,
-                                 (blockIdx.x * kEstWaves + wave) * (4 * kIters));
+  const int base = (blockIdx.x * kEstWaves + wave) * (4 * kIters);
+  if (kIters == kEstIters && (long)base << a.page_shift >= a.seq_lens[blockIdx.y]) return;
+  estimate_wave<kAppend, kIters, kGroup>(a, blockIdx.y, blockIdx.z, base);
 }
 
-// Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a small
-// table (one sequence of 32 heads at 32k tokens is 32 MiB, a few microseconds) is scanned
-// faster by twice as many waves of half the size: 7.6 us against 7.9 us there, 8.7 us
-// with 32 pages per wave.
+// Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
+// table is scanned faster by twice as many waves of half the size: 8.3 us against 8.75 us
+// at 2049 pages of 32 heads, 13.6 against 14.2 at 4100, 23.0 against 23.4 at 8193; but 98.0
+// against 93.7 us for 16 sequences of 8k to 64k tokens (1.2 M pages).
 int est_iters(const quest_cache& c) {
-  return (long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (1l << 17) ? 2 : kEstIters;
+  return (long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (1l << 19) ? 2 : kEstIters;
+}
+
+template <bool kAppend, int kIters>
+void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
+  const int per_group = kEstWaves * 4 * kIters;
+  const dim3 grid((c.max_pages_per_seq + per_group - 1) / per_group, c.batch, kv_heads(c));
+  const dim3 block(kEstWaves * kWave);
+  // LDS that nobody uses: it keeps the work-groups of a compute unit at five.  A large table
+  // streams better that way than with more (512k tokens in order 80.2 us, 83.3 with six; two
+  // sequences of 400k 123.5 and 128.9; 16 ragged ones 91.6 and 94.7); small ones do not care.
+  const unsigned lds = kIters == kEstIters ? kLdsPerUnit / 5 : 0;
+  if (a.group > 1)
+    hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, true>), grid, block, lds, s, a);
+  else
+    hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, false>), grid, block, lds, s, a);
 }
 
 template <bool kAppend>
 void launch(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
-  const int iters = est_iters(c);
-  const int per_group = kEstWaves * 4 * iters;
-  dim3 grid((c.max_pages_per_seq + per_group - 1) / per_group, c.batch, kv_heads(c));
-  if (iters == 2)
-    hipLaunchKernelGGL((estimate_kernel<kAppend, 2>), grid, dim3(kEstWaves * kWave), 0, s, a);
+  if (est_iters(c) == 2)
+    launch_iters<kAppend, 2>(c, a, s);
   else
-    hipLaunchKernelGGL((estimate_kernel<kAppend, kEstIters>), grid, dim3(kEstWaves * kWave), 0, s, a);
+    launch_iters<kAppend, kEstIters>(c, a, s);
 }
 
 }  // namespace
