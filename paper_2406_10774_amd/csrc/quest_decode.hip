@@ -156,8 +156,8 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   // turn (so that a split of few large pages still occupies all of them).
   const int units = ((entries << a.unit_shift) + kWaves - 1) / kWaves;
   const int num_pages = (seq_len + (1 << a.page_shift) - 1) >> a.page_shift;
-  stream_units<kLoads, kGroup>(st, a, hk, seq_len, units, lane, [&](int i, int& lp, int& ph, int& un,
-                                                                    int& lp2, int& ph2) {
+  attend<kLoads, kGroup>(st, a, hk, seq_len, units, q, n_heads, sm_acc[wave], sm_m[wave], sm_l[wave], lane,
+                         [&](int i, int& lp, int& ph, int& un, int& lp2, int& ph2) {
     const int u = wave + kWaves * i;
     const int e = u >> a.unit_shift;
     un = u & ((1 << a.unit_shift) - 1);
@@ -181,8 +181,6 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     }
   });
 
-  // the lanes of the wave that share a channel, then the waves of the group
-  st.finish(sm_acc[wave], sm_m[wave], sm_l[wave], lane);
   __syncthreads();
   const int t = threadIdx.x;
   const int n_out = n_heads * kHeadDim;
@@ -247,7 +245,8 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
       o *= rescale;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float f = s0 + i < a.splits ? __builtin_amdgcn_exp2f(pml[i].x - cm) : 0.f;
+        if (s0 + i >= a.splits) continue;  // not a factor of zero: the values may be infinite
+        const float f = __builtin_amdgcn_exp2f(pml[i].x - cm);
         l_all += pml[i].y * f;
         o += pa[i] * f;
       }

@@ -138,9 +138,9 @@ __device__ __forceinline__ void merge_rows(Softmax& st) {
 // of a unit leaves lane (c, g) with token 4r + g, channels 8c..8c+7; half e of the four
 // loads is row c (channel 8c + e) of the first operand of the e-th product.  Nothing moves
 // between lanes.  Keys are loaded like values and turned into rows through LDS (4 KiB per
-// wave, the 16-byte chunks of token t exclusive-ored with t: no bank conflicts); loading
-// them as the operand wants them, 64 bytes of each token per load, halves what a
-// compute unit can load (%KLDS%).
+// wave, the 16-byte chunks of token t exclusive-ored with t: no bank conflicts); loaded as
+// the operand wants them, 64 bytes of each token per load, they held a compute unit to 30
+// KiB per us.
 constexpr int kGroupHeads = 8;
 constexpr int kGroupStride = kHeadDim + 4;  // floats per head in LDS: lanes spread over the banks
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
@@ -187,6 +187,12 @@ __device__ __forceinline__ void group_load(GroupRegs& r, const char* __restrict_
   for (int i = 0; i < 4; ++i) r.v[i] = ld16_stream(v_pool + (i < 2 ? base_a : base_b) + i * 1024 + lane * 16);
 }
 
+// LDS serves a wave in order; this keeps the compiler to it (no instruction).
+__device__ __forceinline__ void lds_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float scale_log2, int lane) {
   const int g = lane >> 4, c = lane & 15;
 #pragma unroll
@@ -194,7 +200,7 @@ __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float s
     const int t = 4 * i + g;
     st16(st.stage + t * kRowBytes + ((c ^ t) << 4), r.k[i]);
   }
-  __builtin_amdgcn_wave_barrier();  // LDS serves a wave in order; keep the compiler to it
+  lds_in_order();
   f32x4_t s = {0.f, 0.f, 0.f, 0.f};
   const int token = 4 * (c & 3) + (c >> 2);
 #pragma unroll
@@ -203,7 +209,7 @@ __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float s
     s = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, k),
                                                __builtin_bit_cast(half8_t, st.q[j]), s, 0, 0, 0);
   }
-  __builtin_amdgcn_wave_barrier();
+  lds_in_order();
   float z[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) z[i] = s[i] * scale_log2;
@@ -258,6 +264,17 @@ __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float s
   QUEST_PV(2, z)
   QUEST_PV(3, w)
 #undef QUEST_PV
+}
+
+// Whether every sum of the wave is finite.  Two parts of a weight times an infinite value are
+// not the weight times that value: one of them may be zero or negative.
+__device__ __forceinline__ bool group_finite(const GroupState& st) {
+  float s = st.l * 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = __builtin_fmaf(st.acc[e][i], 0.f, s);
+  return __ballot(s != 0.f) == 0;  // NaN if one of them is not
 }
 
 // The wave's result: acc[head * kGroupStride + channel], ref[head], l[head] (LDS).
@@ -474,6 +491,38 @@ __device__ __forceinline__ void stream_units(HeadState<kLoads, kGroup>& st, cons
       }
     }
   }
+}
+
+// The wave's `units` units (see stream_units) with its n_heads query heads q: what finish
+// leaves in LDS.  Where a group's sums are not finite, head by head on the vector unit.
+template <int kLoads, bool kGroup, class At>
+__device__ __forceinline__ void attend(HeadState<kLoads, kGroup>& st, const AttnArgs& a, int hk, int seq_len,
+                                       int units, const char* q, int n_heads, float* acc, float* m, float* l,
+                                       int lane, At at) {
+  stream_units<kLoads, kGroup>(st, a, hk, seq_len, units, lane, at);
+  if constexpr (kGroup) {
+    if (!group_finite(st.st)) {
+      constexpr bool kTwo = HeadState<kLoads, kGroup>::kTwoPages;
+#pragma unroll 1
+      for (int g = 0; g < n_heads; ++g) {
+        HeadState<kLoads, false> one;
+        one.init(nullptr, q + g * kRowBytes, 1, lane);
+        stream_units<kLoads, false>(one, a, hk, seq_len, kTwo ? 2 * units : units, lane,
+                                    [&](int i, int& lp, int& ph, int& un, int& lp2, int& ph2) {
+          if constexpr (kTwo) {
+            int lp_b = -1, ph_b = 0;
+            at(i >> 1, lp, ph, un, lp_b, ph_b);
+            if (i & 1) lp = lp_b, ph = ph_b;
+          } else {
+            at(i, lp, ph, un, lp2, ph2);
+          }
+        });
+        one.finish(acc + g * HeadState<kLoads, kGroup>::kStride, m + g, l + g, lane);
+      }
+      return;
+    }
+  }
+  st.finish(acc, m, l, lane);
 }
 
 __device__ __forceinline__ void store_out(void* out, int out_is_fp16, size_t idx, float v) {

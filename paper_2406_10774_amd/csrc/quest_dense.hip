@@ -120,8 +120,9 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
     const int first = kBlock > 1 ? 0 : wave;
     const int entries = Head::kTwoPages ? (n_pages + 1) >> 1 : n_pages;
     const int units = ((entries << a.unit_shift) - first + kStep - 1) / kStep;
-    stream_units<kLoads, kGroup>(st, a, hk, seq_len, units, lane, [&](int i, int& lp, int& ph, int& un,
-                                                                      int& lp2, int& ph2) {
+    attend<kLoads, kGroup>(st, a, hk, seq_len, units, a.q + bh * kRowBytes, n_heads,
+                           sm_acc + wave * kSlots * kStride, sm_m + wave * kSlots, sm_l + wave * kSlots, lane,
+                           [&](int i, int& lp, int& ph, int& un, int& lp2, int& ph2) {
       const int u = first + kStep * i;
       const int e = u >> a.unit_shift;
       un = u & ((1 << a.unit_shift) - 1);
@@ -135,7 +136,6 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
         entry_at(e, lp, ph);
       }
     });
-    st.finish(sm_acc + wave * kSlots * kStride, sm_m + wave * kSlots, sm_l + wave * kSlots, lane);
     __syncthreads();
 
     // ---- the part's result: to the output if it is the whole item, else to a slot
@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
             for (int j = 0; j < 4; ++j) o[j] *= rescale;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              const float f = k0 + i * ways < parts ? __builtin_amdgcn_exp2f(ml[i].x - cm) : 0.f;
+              if (k0 + i * ways >= parts) continue;  // not a factor of zero: the values may be infinite
+              const float f = __builtin_amdgcn_exp2f(ml[i].x - cm);
               l_all += ml[i].y * f;
               o[0] += pa[i].x * f;
               o[1] += pa[i].y * f;

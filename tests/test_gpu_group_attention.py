@@ -2,7 +2,7 @@
 where a unit, a wave's share or a split can go wrong: sequences that end inside every part
 of a 16-token unit, groups that are not a power of two or need two work-groups, single
 pages, page pairs of 8 tokens with one missing, lists with holes, values that are fp16
-subnormals; dense, over a given list, and over the list the launch selects itself."""
+subnormals, infinite or not numbers; dense, over a given list, and over the list the launch selects itself."""
 import math
 
 import numpy as np
@@ -69,3 +69,39 @@ def test_unit_edges(kv_heads, group, S):
     for k_pages in (1, K, 64):
         idx, keff, got, lse = layer.select_decode(q, k_pages, scores=sc.astype(np.float32))
         check(got, lse, idx, f"select {k_pages}")
+
+
+@pytest.mark.parametrize("group,S", [(1, 16), (4, 16), (4, 8), (9, 64)])
+def test_infinite_and_nan_values(group, S):
+    """An infinite value is infinite in the output wherever its weight is not zero, a NaN is NaN;
+    every other channel and head comes out as without them."""
+    from gpu_util import Layer
+    lens = (S * 9 + 3, S * 3, 200)
+    kv_heads = 2
+    w = synth.Workload(760 + group, "non-finite", len(lens), kv_heads, lens, token_budget=S * 64, planted_per_head=0,
+                       page_size=S, decode_steps=0)
+    table, N = synth.make_page_table(w, permute=True)
+    k_pool, v_pool, _ = synth.fill_pools(w, table, N)
+    k_pool *= np.float16(0.125)                                # weights of one order of magnitude or two
+    plain = v_pool.copy()
+    bad = ((0, 0, 4, np.inf), (0, 1, 9, -np.inf), (1, 0, 17, np.nan), (2, 1, 127, np.inf))
+    for b, h, ch, x in bad:
+        for at in (5, lens[b] - 1):
+            v_pool[table[b, at // S], h, at % S, ch] = x
+    q = np.random.default_rng(group).standard_normal((w.batch, kv_heads * group, 128)).astype(np.float16)
+    cur = np.array(lens, np.int32)
+    layer = Layer(k_pool, v_pool, table, cur, num_q_heads=kv_heads * group)
+    scale = 1 / math.sqrt(128)
+    want, want_lse = O.sparse_decode(k_pool, plain, q, table, cur, None, scale)
+    limit = bound(k_pool, plain, q, table, cur, None, scale)
+    for b, h, ch, x in bad:
+        want[b, h * group:(h + 1) * group, ch] = x
+    K = w.k_pages                                              # every page of every sequence
+    every = np.where(np.arange(K) < np.array([w.pages_of(b) for b in range(w.batch)])[:, None, None],
+                     np.arange(K), -1) + np.zeros((w.batch, kv_heads, K), np.int64)
+    sc = np.zeros((w.batch, kv_heads, table.shape[1]), np.float32)
+    for got, lse in (layer.decode(q, None, 0), layer.decode(q, every, K), layer.select_decode(q, K, scores=sc)[2:]):
+        odd = ~np.isfinite(want)
+        assert np.array_equal(got[odd], want[odd], equal_nan=True)
+        assert (np.abs(got - want)[~odd] <= limit[~odd]).all()
+        assert np.abs(lse - want_lse).max() <= 1e-4
