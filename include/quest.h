@@ -129,7 +129,10 @@ typedef struct quest_cache {
  * each split); for rows of 16384 pages or more also the candidates of the
  * two-stage selection that quest_select_decode and quest_decode_step then use
  * (the best k_pages of every 4096-page chunk of a row, when there are at most
- * 8192 of them per row).  *out_bytes may be 0.
+ * 8192 of them per row).  *out_bytes may be 0.  Without a workspace (NULL, or a
+ * smaller one) attention over at most 64 tokens per head, or of more than 256
+ * (sequence, query head) pairs, runs with one work-group for each head or group
+ * of heads; other calls are refused, and so are those that keep candidates.
  * A workspace must be zero-filled once, after it is allocated and before its
  * first use (e.g. hipMemset); every call leaves the counters at zero again, so
  * the same workspace serves later calls, sparse or dense, on the same cache
@@ -259,10 +262,11 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
  * serving loops, test harnesses.  Same arguments, launches and results as
  * quest_decode_step, but the decode workspace lives in a static device array of
  * the library (4 MiB per GPU, held until the process ends) instead of caller
- * memory.  The call allocates and frees nothing.  Shapes whose workspace
- * (quest_step_workspace_bytes) exceeds 4 MiB are refused with
- * QUEST_ERR_WORKSPACE.  The call first enqueues a small kernel that zeroes the
- * arrival counters it is going to use (the array keeps the previous call's
+ * memory.  The call allocates and frees nothing.  Shapes whose two-stage
+ * selection (quest_topk_workspace_bytes) needs more than 4 MiB are refused with
+ * QUEST_ERR_WORKSPACE; where the attention's splits do not fit as well, there is
+ * one per head or group of heads.  The call first enqueues a small kernel that
+ * zeroes the arrival counters it is going to use (the array keeps the previous call's
  * contents).  All calls on one GPU share the one array: calls that overlap in
  * time on the same GPU (different streams, or graphs replayed concurrently) race;
  * serialise them, or use quest_decode_step with a workspace per stream.  The

@@ -65,6 +65,29 @@ int check_cache(const quest_cache* c, const char* who) {
 
 using namespace quest;
 
+namespace {
+
+// Attention with many query heads, or over few tokens, needs no workspace: one split of every
+// (sequence, head) is an ordinary launch there.  It takes one, of the size the query function
+// gives, for its faster form.  (Candidates of the two-stage selection have to be kept.)
+bool workspace_optional(const quest_cache& c, int32_t k_pages) {
+  const int64_t heads = (int64_t)c.batch * c.num_heads;
+  const int64_t pages = k_pages > 0 && k_pages < c.max_pages_per_seq ? k_pages : c.max_pages_per_seq;
+  const int64_t tokens = pages * c.page_size;
+  return heads > 256 || tokens <= 64 || (tokens <= 256 && heads == 256);
+}
+
+// The bytes a call may use; refused (false) where it needs more than it was given.
+bool check_workspace(const quest_cache& c, int32_t k_pages, size_t need, size_t candidates,
+                     const void* workspace, size_t* bytes, const char* who) {
+  if (workspace == nullptr) *bytes = 0;
+  if (*bytes >= need || (candidates == 0 && workspace_optional(c, k_pages))) return true;
+  set_error("%s: workspace of %zu bytes needed, %zu given", who, need, *bytes);
+  return false;
+}
+
+}  // namespace
+
 extern "C" {
 
 const char* quest_last_error(void) { return g_error; }
@@ -183,16 +206,13 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
     return QUEST_ERR_SHAPE;
   }
   const size_t need = topk_idx ? decode_workspace_bytes(*cache, k_pages) : dense_workspace_bytes(*cache);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) {
-    set_error("quest_sparse_decode: workspace of %zu bytes needed, %zu given", need,
-              workspace ? workspace_bytes : (size_t)0);
+  if (!check_workspace(*cache, topk_idx ? k_pages : 0, need, 0, workspace, &workspace_bytes, "quest_sparse_decode"))
     return QUEST_ERR_WORKSPACE;
-  }
   if (topk_idx == nullptr)
     return launch_dense_decode(*cache, q, sm_scale, out, out_is_fp16 != 0, lse, workspace,
-                               (hipStream_t)stream);
+                               workspace_bytes, (hipStream_t)stream);
   return launch_sparse_decode(*cache, q, topk_idx, k_pages, sm_scale, out, out_is_fp16 != 0, lse,
-                              workspace, (hipStream_t)stream);
+                              workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int quest_select_decode(const quest_cache* cache, const void* q, const float* scores,
@@ -211,13 +231,11 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
     return QUEST_ERR_SHAPE;
   }
   const size_t need = step_workspace_bytes(*cache, k_pages);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) {
-    set_error("quest_select_decode: workspace of %zu bytes needed, %zu given", need,
-              workspace ? workspace_bytes : (size_t)0);
+  if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
+                       "quest_select_decode"))
     return QUEST_ERR_WORKSPACE;
-  }
   return launch_select_decode(*cache, q, scores, k_pages, sm_scale, topk_idx, k_eff, out,
-                              out_is_fp16 != 0, lse, workspace, (hipStream_t)stream);
+                              out_is_fp16 != 0, lse, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes) {
@@ -256,11 +274,9 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
     return QUEST_ERR_SHAPE;
   }
   const size_t need = step_workspace_bytes(*cache, k_pages);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need)) {
-    set_error("quest_decode_step: workspace of %zu bytes needed, %zu given", need,
-              workspace ? workspace_bytes : (size_t)0);
+  if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
+                       "quest_decode_step"))
     return QUEST_ERR_WORKSPACE;
-  }
   return launch_decode_step(*cache, k_new, v_new, k_pool_write != 0, q, k_pages, sm_scale, scores,
                             topk_idx, k_eff, out, out_is_fp16 != 0, lse, workspace, workspace_bytes,
                             (hipStream_t)stream);

@@ -55,16 +55,19 @@ int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, 
                         int32_t* k_eff, void* scratch, hipStream_t s);
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages);
 size_t dense_workspace_bytes(const quest_cache& c);
+// With a workspace smaller than that an attention launch gives every (sequence, head) to one
+// work-group, which needs none.
 int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
-                        float* lse, void* workspace, hipStream_t s);
+                        float* lse, void* workspace, size_t workspace_bytes, hipStream_t s);
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
-                         hipStream_t s);
+                         size_t workspace_bytes, hipStream_t s);
 
 bool select_decode_supported(const quest_cache& c, int k_pages);
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
-                         int out_is_fp16, float* lse, void* workspace, hipStream_t s);
+                         int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
+                         hipStream_t s);
 
 size_t step_workspace_bytes(const quest_cache& c, int k_pages);
 // Leading part of a decode workspace: the arrival counters (must be zero before a launch).

@@ -313,7 +313,8 @@ namespace {
 // the caller has checked select_decode_supported.
 int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, const float* scores,
                   int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale, void* out,
-                  int out_is_fp16, float* lse, void* workspace, hipStream_t s) {
+                  int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
+                  hipStream_t s) {
   const bool select = scores != nullptr;
   DecodeArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
@@ -323,7 +324,8 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.k_eff = k_eff;
   a.policy = c.flags;
   a.k_pages = k_pages;
-  const SplitPlan p = plan_splits(c, k_pages);
+  SplitPlan p = plan_splits(c, k_pages);
+  if (p.splits > 1 && workspace_bytes < decode_workspace_bytes(c, k_pages)) p.splits = 1, p.per_split = p.list_len;
   a.splits = p.splits;
   a.list_len = p.list_len;
   a.per_split = p.per_split;
@@ -333,8 +335,9 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.part_ml = a.part_acc ? a.part_acc + n_part * kHeadDim : nullptr;
   const bool group = a.group > 1;
   const long items8 = ((long)c.batch * a.kv_heads * a.subs + 7) / 8;
-  if (items8 > 65535) {
-    set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items8 * 8);
+  const long heads8 = ((long)c.batch * c.num_heads + 7) / 8;
+  if (heads8 > 65535) {  // items8 <= heads8
+    set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", heads8 * 8);
     return QUEST_ERR_SHAPE;
   }
   const dim3 grid((unsigned)(8 * a.splits), (unsigned)items8);
@@ -373,9 +376,9 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
 
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
-                         hipStream_t s) {
+                         size_t workspace_bytes, hipStream_t s) {
   return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, k_pages, sm_scale, out, out_is_fp16,
-                       lse, workspace, s);
+                       lse, workspace, workspace_bytes, s);
 }
 
 // Selection and attention in one launch: while a row of scores fits the in-register
@@ -389,17 +392,21 @@ bool select_decode_supported(const quest_cache& c, int k_pages) {
 
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
-                         int out_is_fp16, float* lse, void* workspace, hipStream_t s) {
+                         int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
+                         hipStream_t s) {
   if (select_decode_supported(c, k_pages))
     return launch_decode(c, q, nullptr, scores, topk_idx, k_eff, k_pages, sm_scale, out, out_is_fp16,
-                         lse, workspace, s);
-  // very long rows: selection in two stages, candidates behind the attention's workspace
-  const int r = topk_scratch_bytes(c, k_pages) > 0
-                    ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff,
-                                          (char*)workspace + decode_workspace_bytes(c, k_pages), s)
-                    : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
+                         lse, workspace, workspace_bytes, s);
+  // very long rows: selection in two stages, candidates behind the attention's workspace (the
+  // candidates alone if there is no room for both)
+  const size_t candidates = topk_scratch_bytes(c, k_pages);
+  const size_t attention = workspace_bytes >= step_workspace_bytes(c, k_pages) ? decode_workspace_bytes(c, k_pages) : 0;
+  const int r = candidates > 0 ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff,
+                                                     (char*)workspace + attention, s)
+                               : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
   if (r != QUEST_OK) return r;
-  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, workspace, s);
+  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, workspace,
+                              candidates > 0 ? attention : workspace_bytes, s);
 }
 
 }  // namespace quest

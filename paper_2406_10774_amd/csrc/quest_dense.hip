@@ -29,7 +29,6 @@ namespace quest {
 
 namespace {
 
-
 constexpr int waves_of(bool group) { return group ? 8 : 4; }
 // Work-groups at most, of the 256 compute units: the memory system moves more with fewer
 // streams as long as they can carry it (2 layers of 32 heads, 32k tokens: 187 us with 128
@@ -39,6 +38,7 @@ constexpr int most_shares(bool group) { return group ? 224 : 192; }
 
 struct DenseArgs : AttnArgs {
   int shares;  // work-groups; partial results of share w are slots 2w and 2w + 1
+  int whole;   // no workspace: every work-group takes one item
 };
 
 // Query heads of one item and of one slot.
@@ -66,33 +66,40 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
   auto pages_of = [&](int len) { return (max(len, 0) + (1 << a.page_shift) - 1) >> a.page_shift; };
 
   // ---- this work-group's share [off, end) of the line, and the sequence it begins in
-  int64_t total = 0;
-  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-    const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-    total += __builtin_amdgcn_readlane(wave_incl_scan(p, lane), kWave - 1);
-  }
-  total *= blocks;
-  const int64_t shares = total < a.shares ? total : a.shares;  // none is empty
   const int64_t w = blockIdx.x;
-  if (w >= shares) return;
-  int64_t off = w * total / shares;
-  const int64_t end = (w + 1) * total / shares;
-  const int64_t begin = off;
-  auto share_of = [&](int64_t at) { return (int)(((at + 1) * shares - 1) / total); };
+  int64_t total = 0, shares = 1, off, end;
   int64_t base = 0;  // where sequence b begins
   int b = 0;
-  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-    const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-    const int upto = wave_incl_scan(p, lane);
-    const int64_t after = base + (int64_t)__builtin_amdgcn_readlane(upto, kWave - 1) * blocks;
-    if (off < after) {
-      const int k = __popcll(__ballot(b0 + lane < a.batch && base + (int64_t)upto * blocks <= off));
-      b = b0 + k;
-      base += k > 0 ? (int64_t)__builtin_amdgcn_readlane(upto, k > 0 ? k - 1 : 0) * blocks : 0;
-      break;
+  if (a.whole) {
+    b = (int)(w / blocks);
+    const int64_t pages = pages_of(a.seq_lens[b]);
+    off = (w - (int64_t)b * blocks) * pages;
+    end = off + pages;
+  } else {
+    for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+      const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
+      total += __builtin_amdgcn_readlane(wave_incl_scan(p, lane), kWave - 1);
     }
-    base = after;
+    total *= blocks;
+    shares = total < a.shares ? total : a.shares;  // none is empty
+    if (w >= shares) return;
+    off = w * total / shares;
+    end = (w + 1) * total / shares;
+    for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+      const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
+      const int upto = wave_incl_scan(p, lane);
+      const int64_t after = base + (int64_t)__builtin_amdgcn_readlane(upto, kWave - 1) * blocks;
+      if (off < after) {
+        const int k = __popcll(__ballot(b0 + lane < a.batch && base + (int64_t)upto * blocks <= off));
+        b = b0 + k;
+        base += k > 0 ? (int64_t)__builtin_amdgcn_readlane(upto, k > 0 ? k - 1 : 0) * blocks : 0;
+        break;
+      }
+      base = after;
+    }
   }
+  const int64_t begin = off;
+  auto share_of = [&](int64_t at) { return (int)(((at + 1) * shares - 1) / total); };
 
   while (off < end) {
     // ---- one item, or the part of it that lies in the share
@@ -274,24 +281,31 @@ size_t dense_workspace_bytes(const quest_cache& c) {
 }
 
 int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
-                        float* lse, void* workspace, hipStream_t s) {
+                        float* lse, void* workspace, size_t workspace_bytes, hipStream_t s) {
   DenseArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
-  a.shares = dense_shares(c);
+  const int block = four_heads(c) ? 4 : 1;
+  const long items = (long)c.batch * a.kv_heads * a.subs / block;
+  if (items > 8 * 65535l) {
+    set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items * block);
+    return QUEST_ERR_SHAPE;
+  }
+  a.whole = workspace_bytes < dense_workspace_bytes(c);
+  a.shares = a.whole ? (int)items : dense_shares(c);
   a.counters = (uint64_t*)workspace;
-  a.part_acc = (float*)((char*)workspace + counter_bytes(c));
-  a.part_ml = a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
+  a.part_acc = a.whole ? nullptr : (float*)((char*)workspace + counter_bytes(c));
+  a.part_ml = a.whole ? nullptr : a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
   const dim3 grid((unsigned)a.shares);
 #define QUEST_DENSE_LAUNCH(L, G, B)                                                              \
   hipLaunchKernelGGL((dense_kernel<L, G, B, waves_of(G)>), grid, dim3(waves_of(G) * kWave), \
                      0, s, a)
   if (c.page_size == 8) {
     if (a.group > 1) QUEST_DENSE_LAUNCH(2, true, 1);
-    else if (four_heads(c)) QUEST_DENSE_LAUNCH(2, false, 4);
+    else if (block == 4) QUEST_DENSE_LAUNCH(2, false, 4);
     else QUEST_DENSE_LAUNCH(2, false, 1);
   } else {
     if (a.group > 1) QUEST_DENSE_LAUNCH(4, true, 1);
-    else if (four_heads(c)) QUEST_DENSE_LAUNCH(4, false, 4);
+    else if (block == 4) QUEST_DENSE_LAUNCH(4, false, 4);
     else QUEST_DENSE_LAUNCH(4, false, 1);
   }
 #undef QUEST_DENSE_LAUNCH

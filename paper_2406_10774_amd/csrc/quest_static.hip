@@ -12,11 +12,12 @@ namespace quest {
 namespace {
 
 // Every GPU the library runs on holds its own copy of this array until the process
-// ends.  Counters and split-K partial results never need more than about 0.8 MiB (the
-// launch keeps items * splits near one work-group per compute unit); the rest is for the
-// candidates of the two-stage selection of rows from 16384 pages on (batch * KV heads *
-// chunks * k_pages * 8 bytes: 0.6 MiB for one sequence of 32 heads at 512k tokens with a
-// budget of 4096 tokens).
+// ends.  Counters and split-K partial results take up to about 1.3 MiB (the launch keeps
+// items * splits near one work-group per compute unit), 5.1 MiB for 257 to 351 groups of
+// query heads, which get three splits each; the rest is for the candidates of the
+// two-stage selection of rows from 16384 pages on (batch * KV heads * chunks * k_pages * 8
+// bytes: 0.6 MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens).
+// Where there is no room for both, the attention runs without splits.
 constexpr size_t kScratchBytes = 4u << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -64,26 +65,28 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
                               int k_pool_write, const void* q, int k_pages, float sm_scale,
                               float* scores, int32_t* topk_idx, int32_t* k_eff, void* out,
                               int out_is_fp16, float* lse, hipStream_t s) {
-  const size_t need = step_workspace_bytes(c, k_pages);
-  if (need > kScratchBytes) {
+  const size_t candidates = topk_scratch_bytes(c, k_pages);
+  if (candidates > kScratchBytes) {
     set_error("quest_decode_step_static: this shape needs %zu bytes of scratch, the static buffer "
-              "holds %zu; use quest_decode_step with a workspace", need, kScratchBytes);
+              "holds %zu; use quest_decode_step with a workspace", candidates, kScratchBytes);
     return QUEST_ERR_WORKSPACE;
   }
   void* ws = nullptr;
   int r = scratch_pointer(&ws);
   if (r != QUEST_OK) return r;
   // counters exist when the attention runs in several splits; they are then the first
-  // bytes of its workspace (<= need <= kScratchBytes)
-  const size_t words = decode_workspace_bytes(c, k_pages) ? decode_counter_bytes(c) / sizeof(uint32_t) : 0;
-  if (need > 0 && words > 0) {
+  // bytes of its workspace
+  const size_t need = step_workspace_bytes(c, k_pages);
+  const bool fits = need <= kScratchBytes;
+  if (fits && decode_workspace_bytes(c, k_pages) > 0) {
+    const size_t words = decode_counter_bytes(c) / sizeof(uint32_t);
     hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t*)ws, words);
     r = check_launch("quest_decode_step_static");
     if (r != QUEST_OK) return r;
   }
   return launch_decode_step(c, k_new, v_new, k_pool_write, q, k_pages, sm_scale, scores, topk_idx,
-                            k_eff, out, out_is_fp16, lse, ws, need, s);
+                            k_eff, out, out_is_fp16, lse, ws, fits ? need : candidates, s);
 }
 
 }  // namespace quest

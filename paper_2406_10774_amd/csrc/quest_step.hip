@@ -29,12 +29,11 @@ int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_ne
                        const void* q, int k_pages, float sm_scale, float* scores, int32_t* topk_idx,
                        int32_t* k_eff, void* out, int out_is_fp16, float* lse, void* workspace,
                        size_t workspace_bytes, hipStream_t s) {
-  (void)workspace_bytes;  // checked by the caller
   int r = k_new ? launch_append_estimate(c, k_new, v_new, k_pool_write, q, scores, s)
                 : launch_estimate(c, q, scores, s);
   if (r != QUEST_OK) return r;
   return launch_select_decode(c, q, scores, k_pages, sm_scale, topk_idx, k_eff, out, out_is_fp16, lse,
-                              workspace, s);
+                              workspace, workspace_bytes, s);
 }
 
 }  // namespace quest
