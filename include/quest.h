@@ -126,10 +126,10 @@ typedef struct quest_cache {
  * path of quest_sparse_decode over all pages).  Pure host function.
  * The workspace holds one arrival counter per (sequence, head) and the split-K
  * partial results (running max, denominator and un-normalised accumulator of
- * each split); for rows of 16384 pages or more also the candidates of the
- * two-stage selection that quest_select_decode and quest_decode_step then use
- * (the best k_pages of every 4096-page chunk of a row, when there are at most
- * 8192 of them per row).  *out_bytes may be 0.  Without a workspace (NULL, or a
+ * each split); for rows of more than 5120 pages also the candidates that
+ * quest_select_decode and quest_decode_step select from there (the best k_pages
+ * of every chunk of 2048 or 4096 pages of a row, when there are at most 8192 of
+ * them per row; below 16384 pages a workspace without room for them will do).  *out_bytes may be 0.  Without a workspace (NULL, or a
  * smaller one) attention over at most 64 tokens per head, or of more than 256
  * (sequence, query head) pairs, runs with one work-group for each head or group
  * of heads; other calls are refused, and so are those that keep candidates.
@@ -261,7 +261,7 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
  * that runs under HIP graph capture in a harness that forbids hipMalloc, tight
  * serving loops, test harnesses.  Same arguments, launches and results as
  * quest_decode_step, but the decode workspace lives in a static device array of
- * the library (4 MiB per GPU, held until the process ends) instead of caller
+ * the library (8 MiB per GPU, held until the process ends) instead of caller
  * memory.  The call allocates and frees nothing.  Shapes whose two-stage
  * selection (quest_topk_workspace_bytes) needs more than 4 MiB are refused with
  * QUEST_ERR_WORKSPACE; where the attention's splits do not fit as well, there is

@@ -230,7 +230,9 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
     set_error("quest_select_decode: k_pages must be >= 1 (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  const size_t need = step_workspace_bytes(*cache, k_pages);
+  // (shorter rows do without candidates)
+  const size_t need = topk_scratch_bytes(*cache, k_pages) > 0 ? step_workspace_bytes(*cache, k_pages)
+                                                              : decode_workspace_bytes(*cache, k_pages);
   if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
                        "quest_select_decode"))
     return QUEST_ERR_WORKSPACE;
@@ -273,7 +275,9 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
     set_error("quest_decode_step: k_pages must be >= 1 (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  const size_t need = step_workspace_bytes(*cache, k_pages);
+  // (shorter rows do without candidates)
+  const size_t need = topk_scratch_bytes(*cache, k_pages) > 0 ? step_workspace_bytes(*cache, k_pages)
+                                                              : decode_workspace_bytes(*cache, k_pages);
   if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
                        "quest_decode_step"))
     return QUEST_ERR_WORKSPACE;

@@ -49,7 +49,20 @@ int launch_append_estimate(const quest_cache& c, const void* k_new, const void* 
 int launch_topk(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                 int32_t* k_eff, hipStream_t s);
 // Scratch for the two-stage selection of very long rows (0: not used for this shape), and
-// the selection itself; the scratch need not be initialised.
+// the selection itself; the scratch need not be initialised.  launch_topk_chunks: the first
+// stage alone, in chunks of 2048 or 4096 pages, with candidate_bytes of scratch.
+struct Candidates {
+  const float* score;   // [B][kv heads][row_len]
+  const int32_t* page;
+  int row_len, chunk_pages;
+};
+constexpr int kSmallChunk = 2048, kLargeChunk = 4096;
+inline long candidates_per_row(const quest_cache& c, int k_pages, int chunk_pages) {
+  return ((long)c.max_pages_per_seq + chunk_pages - 1) / chunk_pages * k_pages;
+}
+size_t candidate_bytes(const quest_cache& c, int k_pages, int chunk_pages);
+int launch_topk_chunks(const quest_cache& c, const float* scores, int k_pages, int chunk_pages,
+                       void* scratch, Candidates* out, hipStream_t s);
 size_t topk_scratch_bytes(const quest_cache& c, int k_pages);
 int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                         int32_t* k_eff, void* scratch, hipStream_t s);
@@ -64,6 +77,11 @@ int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* top
                          size_t workspace_bytes, hipStream_t s);
 
 bool select_decode_supported(const quest_cache& c, int k_pages);
+// Candidates quest_select_decode keeps in its workspace when there is room for them; without
+// it does with topk_scratch_bytes.
+size_t select_candidate_bytes(const quest_cache& c, int k_pages);
+// Where they lie: never on the counters, which other calls with this workspace may need zero.
+size_t candidate_offset(const quest_cache& c, int k_pages);
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,

@@ -49,6 +49,9 @@ struct DecodeArgs : AttnArgs {
   const float* scores;      // selection inside the launch: scores [B][kv heads][max_pages] ...
   int32_t* topk_out;        // ... the list is also written here [B][kv heads][k_pages] ...
   int32_t* k_eff;           // ... and K_b here (nullable)
+  const int32_t* cand_page; // their pages, if the scores are those of candidates
+  int row_len;              // entries of a row of scores: max_pages, or candidates
+  int chunk_pages;          // pages that k_pages candidates stand for
   int policy;               // QUEST_FLAG_KEEP_* bits
   int k_pages, splits;
   int list_len;             // entries of the page list the splits divide
@@ -69,7 +72,10 @@ struct DecodeArgs : AttnArgs {
 // the list out.  The selection is repeated by every split of a head, which costs nothing
 // that matters (the compute units would idle meanwhile) and saves a launch and the trip
 // of the list through memory.
-template <int kLoads, bool kGroup, int kWaves, int kSelItems>
+//
+// kCand: the scores are those of candidates that a launch before has picked from the chunks
+// of a longer row, each with its page.
+template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand>
 __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const DecodeArgs a) {
   using Head = HeadState<kLoads, kGroup>;
   constexpr int kThreads = kWaves * kWave;
@@ -122,30 +128,37 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     // of what the selection waits for): the page-table entries of this thread's pages,
     // which travel with their scores so that the list needs no look-up afterwards, and
     // what the attention needs besides the pages.
-    int my_phys[kSelItems];
+    // (of candidates: their logical pages)
+    int mine[kSelItems];
+    const int32_t* per_score = kCand ? a.cand_page + row * a.row_len : pt;
     auto more_loads = [&] {
 #pragma unroll
       for (int j = 0; j < kSelItems; ++j)
-        my_phys[j] = pt[min((int)threadIdx.x * kSelItems + j, a.max_pages - 1)];
+        mine[j] = per_score[min((int)threadIdx.x * kSelItems + j, a.row_len - 1)];
       seq_len = a.seq_lens[b];
       st.init(sm_acc[wave], q, n_heads, lane);
     };
-    topk_block_put<kThreads, kSelItems>(
-        sm_topk, a.scores + row * a.max_pages, a.seq_lens + b, a.max_pages, a.k_pages,
-        [&](int pos, int page, int j, float) {
-          int phys = 0;
-          if (j >= 0) {
+    auto put = [&](int pos, int entry, int j, float) {
+      int of = kCand ? -1 : 0;
+      if (j >= 0) {
 #pragma unroll
-            for (int jj = 0; jj < kSelItems; ++jj)
-              if (jj == j) phys = my_phys[jj];
-          } else if (page >= 0) {
-            phys = pt[page];
-          }
-          sm_list[pos] = make_int2(page, phys);
-          if (writer) out_row[pos] = page;
-        },
-        (writer && hk == 0 && a.k_eff != nullptr) ? a.k_eff + b : nullptr,
-        WholeRow{a.page_shift, a.policy}, more_loads);
+        for (int jj = 0; jj < kSelItems; ++jj)
+          if (jj == j) of = mine[jj];
+      } else if (entry >= 0) {
+        of = per_score[entry];
+      }
+      const int page = kCand ? of : entry;
+      sm_list[pos] = make_int2(page, of);
+      if (writer) out_row[pos] = page;
+    };
+    int32_t* k_eff = (writer && hk == 0 && a.k_eff != nullptr) ? a.k_eff + b : nullptr;
+    const float* scores = a.scores + row * a.row_len;
+    if constexpr (kCand)
+      topk_block_put<kThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
+                                          CandidateRow{a.page_shift, a.policy, a.k_pages, a.chunk_pages}, more_loads);
+    else
+      topk_block_put<kThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
+                                          WholeRow{a.page_shift, a.policy}, more_loads);
     __syncthreads();
   } else {
     seq_len = a.seq_lens[b];
@@ -166,6 +179,7 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
         if (pos < end) {
           const int2 entry = sm_list[pos];
           l = entry.x, p = entry.y;
+          if (kCand && l >= 0) p = pt[l];
         }
       } else {
         if (pos < end) l = a.topk_idx[((size_t)b * a.kv_heads + hk) * a.k_pages + pos];
@@ -309,17 +323,20 @@ size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
 }
 
 namespace {
-// scores != nullptr: select inside the launch (topk_out, k_eff receive the list and K_b);
-// the caller has checked select_decode_supported.
+// scores != nullptr: select inside the launch (topk_out, k_eff receive the list and K_b), or
+// among the candidates if there are some; the caller has checked that it can.
 int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, const float* scores,
-                  int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale, void* out,
+                  const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale, void* out,
                   int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
                   hipStream_t s) {
-  const bool select = scores != nullptr;
+  const bool select = scores != nullptr || cand != nullptr;
   DecodeArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   a.topk_idx = topk_idx;
-  a.scores = scores;
+  a.scores = cand ? cand->score : scores;
+  a.cand_page = cand ? cand->page : nullptr;
+  a.row_len = cand ? cand->row_len : c.max_pages_per_seq;
+  a.chunk_pages = cand ? cand->chunk_pages : 0;
   a.topk_out = topk_out;
   a.k_eff = k_eff;
   a.policy = c.flags;
@@ -341,33 +358,33 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     return QUEST_ERR_SHAPE;
   }
   const dim3 grid((unsigned)(8 * a.splits), (unsigned)items8);
-#define QUEST_LAUNCH(L, G, W, I) \
-  hipLaunchKernelGGL((decode_split_kernel<L, G, W, I>), grid, dim3((W) * kWave), 0, s, a)
-#define QUEST_LAUNCH_FOR_CACHE(W, I)                   \
+#define QUEST_LAUNCH(L, G, W, I, C) \
+  hipLaunchKernelGGL((decode_split_kernel<L, G, W, I, C>), grid, dim3((W) * kWave), 0, s, a)
+#define QUEST_LAUNCH_FOR_CACHE(W, I, C)                \
   do {                                                 \
     if (c.page_size == 8) {                            \
-      if (group) QUEST_LAUNCH(2, true, W, I);          \
-      else QUEST_LAUNCH(2, false, W, I);               \
+      if (group) QUEST_LAUNCH(2, true, W, I, C);       \
+      else QUEST_LAUNCH(2, false, W, I, C);            \
     } else {                                           \
-      if (group) QUEST_LAUNCH(4, true, W, I);          \
-      else QUEST_LAUNCH(4, false, W, I);               \
+      if (group) QUEST_LAUNCH(4, true, W, I, C);       \
+      else QUEST_LAUNCH(4, false, W, I, C);            \
     }                                                  \
   } while (0)
   if (select) {
-    const int mp = c.max_pages_per_seq;
-#define QUEST_SELECT_CASE(I)                           \
-  if (mp <= kSelWaves * kWave * (I)) {                 \
-    QUEST_LAUNCH_FOR_CACHE(kSelWaves, I);              \
-    return check_launch("quest_select_decode");        \
+#define QUEST_SELECT_CASE(I)                                      \
+  if (a.row_len <= kSelWaves * kWave * (I)) {                     \
+    if (cand) QUEST_LAUNCH_FOR_CACHE(kSelWaves, I, true);         \
+    else QUEST_LAUNCH_FOR_CACHE(kSelWaves, I, false);             \
+    return check_launch("quest_select_decode");                   \
   }
     QUEST_SELECT_CASE(2)
     QUEST_SELECT_CASE(5)
     QUEST_SELECT_CASE(8)
 #undef QUEST_SELECT_CASE
-    set_error("quest_select_decode: internal: no selecting kernel for max_pages_per_seq = %d", mp);
+    set_error("quest_select_decode: internal: no selecting kernel for rows of %d scores", a.row_len);
     return QUEST_ERR_SHAPE;
   }
-  QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0);
+  QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0, false);
 #undef QUEST_LAUNCH_FOR_CACHE
 #undef QUEST_LAUNCH
   return check_launch("quest_sparse_decode");
@@ -377,7 +394,7 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
                          size_t workspace_bytes, hipStream_t s) {
-  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, k_pages, sm_scale, out, out_is_fp16,
+  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, nullptr, k_pages, sm_scale, out, out_is_fp16,
                        lse, workspace, workspace_bytes, s);
 }
 
@@ -390,23 +407,60 @@ bool select_decode_supported(const quest_cache& c, int k_pages) {
          c.max_pages_per_seq <= kSelWaves * kWave * 8 && k_pages <= kSelListCap;
 }
 
+namespace {
+// Longer rows: a launch picks candidates from the chunks of the rows, and the attention launch
+// selects among those, as long as they are as few as the scores of a short row.  A step of
+// 32 heads: 49.6 us instead of 55.6 us at 12500 pages (Top-K of whole rows and attention over
+// its list), 45.5 instead of 48.0 us at 8193, 106.3 instead of 108.2 us at 32769 (Top-K in two
+// stages); 8 KV heads of 8 query heads 27.0 instead of 29.8 us at 6125.  At 5000 pages the Top-K
+// of whole rows is 0.4 us faster.  Chunks of 4096 pages where 2048 leave too many candidates
+// (8193 pages 46.6 us).
+constexpr int kCandFromPages = 5121;
+int chunk_to_select_from(const quest_cache& c, int k_pages) {
+  if ((c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) || c.max_pages_per_seq < kCandFromPages || k_pages > kSelListCap)
+    return 0;
+  for (const int chunk : {kSmallChunk, kLargeChunk})
+    if (candidates_per_row(c, k_pages, chunk) <= kSelWaves * kWave * 8 && candidate_bytes(c, k_pages, chunk) > 0)
+      return chunk;
+  return 0;
+}
+}  // namespace
+
+size_t select_candidate_bytes(const quest_cache& c, int k_pages) {
+  const int chunk = chunk_to_select_from(c, k_pages);
+  return chunk ? candidate_bytes(c, k_pages, chunk) : select_decode_supported(c, k_pages) ? 0 : topk_scratch_bytes(c, k_pages);
+}
+
+size_t candidate_offset(const quest_cache& c, int k_pages) {
+  return std::max(decode_workspace_bytes(c, k_pages), counter_bytes(c));
+}
+
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
                          hipStream_t s) {
   if (select_decode_supported(c, k_pages))
-    return launch_decode(c, q, nullptr, scores, topk_idx, k_eff, k_pages, sm_scale, out, out_is_fp16,
-                         lse, workspace, workspace_bytes, s);
-  // very long rows: selection in two stages, candidates behind the attention's workspace (the
-  // candidates alone if there is no room for both)
-  const size_t candidates = topk_scratch_bytes(c, k_pages);
-  const size_t attention = workspace_bytes >= step_workspace_bytes(c, k_pages) ? decode_workspace_bytes(c, k_pages) : 0;
-  const int r = candidates > 0 ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff,
-                                                     (char*)workspace + attention, s)
-                               : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
+    return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, sm_scale, out,
+                         out_is_fp16, lse, workspace, workspace_bytes, s);
+  // candidates behind the attention's workspace, or alone if there is no room for both and
+  // they cannot be done without
+  const bool both = workspace_bytes >= step_workspace_bytes(c, k_pages);
+  const bool alone = !both && topk_scratch_bytes(c, k_pages) > 0;
+  void* scratch = (char*)workspace + (both ? candidate_offset(c, k_pages) : 0);
+  const size_t rest = both ? decode_workspace_bytes(c, k_pages) : alone ? 0 : workspace_bytes;
+  int r;
+  const int chunk = chunk_to_select_from(c, k_pages);
+  if (both && chunk) {
+    Candidates cand;
+    r = launch_topk_chunks(c, scores, k_pages, chunk, scratch, &cand, s);
+    if (r != QUEST_OK) return r;
+    return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, sm_scale, out,
+                         out_is_fp16, lse, workspace, rest, s);
+  }
+  r = topk_scratch_bytes(c, k_pages) > 0 ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff, scratch, s)
+                                         : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
   if (r != QUEST_OK) return r;
-  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, workspace,
-                              candidates > 0 ? attention : workspace_bytes, s);
+  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, workspace, rest, s);
 }
 
 }  // namespace quest

@@ -15,10 +15,11 @@ namespace {
 // ends.  Counters and split-K partial results take up to about 1.3 MiB (the launch keeps
 // items * splits near one work-group per compute unit), 5.1 MiB for 257 to 351 groups of
 // query heads, which get three splits each; the rest is for the candidates of the
-// two-stage selection of rows from 16384 pages on (batch * KV heads * chunks * k_pages * 8
-// bytes: 0.6 MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens).
+// selection of rows from 5121 pages on (batch * KV heads * chunks * k_pages * 8 bytes: 0.6
+// MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens).
 // Where there is no room for both, the attention runs without splits.
-constexpr size_t kScratchBytes = 4u << 20;
+constexpr size_t kScratchBytes = 8u << 20;
+constexpr size_t kMostCandidates = 4u << 20;  // of the two-stage selection
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -66,9 +67,9 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
                               float* scores, int32_t* topk_idx, int32_t* k_eff, void* out,
                               int out_is_fp16, float* lse, hipStream_t s) {
   const size_t candidates = topk_scratch_bytes(c, k_pages);
-  if (candidates > kScratchBytes) {
-    set_error("quest_decode_step_static: this shape needs %zu bytes of scratch, the static buffer "
-              "holds %zu; use quest_decode_step with a workspace", candidates, kScratchBytes);
+  if (candidates > kMostCandidates) {
+    set_error("quest_decode_step_static: this shape's selection needs %zu bytes of scratch, the static "
+              "buffer has %zu for it; use quest_decode_step with a workspace", candidates, kMostCandidates);
     return QUEST_ERR_WORKSPACE;
   }
   void* ws = nullptr;
@@ -76,9 +77,10 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
   if (r != QUEST_OK) return r;
   // counters exist when the attention runs in several splits; they are then the first
   // bytes of its workspace
-  const size_t need = step_workspace_bytes(c, k_pages);
-  const bool fits = need <= kScratchBytes;
-  if (fits && decode_workspace_bytes(c, k_pages) > 0) {
+  const size_t attention = decode_workspace_bytes(c, k_pages), need = step_workspace_bytes(c, k_pages);
+  const size_t bytes = need <= kScratchBytes ? need
+                       : candidates == 0 && attention <= kScratchBytes ? attention : candidates;
+  if (attention > 0 && (bytes == need || bytes == attention)) {
     const size_t words = decode_counter_bytes(c) / sizeof(uint32_t);
     hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t*)ws, words);
@@ -86,7 +88,7 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
     if (r != QUEST_OK) return r;
   }
   return launch_decode_step(c, k_new, v_new, k_pool_write, q, k_pages, sm_scale, scores, topk_idx,
-                            k_eff, out, out_is_fp16, lse, ws, fits ? need : candidates, s);
+                            k_eff, out, out_is_fp16, lse, ws, bytes, s);
 }
 
 }  // namespace quest

@@ -22,7 +22,8 @@
 namespace quest {
 
 size_t step_workspace_bytes(const quest_cache& c, int k_pages) {
-  return decode_workspace_bytes(c, k_pages) + topk_scratch_bytes(c, k_pages);
+  const size_t candidates = select_candidate_bytes(c, k_pages);
+  return (candidates > 0 ? candidate_offset(c, k_pages) : decode_workspace_bytes(c, k_pages)) + candidates;
 }
 
 int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write,

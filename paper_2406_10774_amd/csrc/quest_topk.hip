@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
 
 // ---- Selection in two stages for very long rows.  One work-group per row is bound by
 // what one compute unit can issue (about 0.75 us per key and thread at 1024 threads);
-// here the row is cut into chunks of kChunkPages pages, a work-group per chunk selects
+// here the row is cut into chunks of 2048 or 4096 pages, a work-group per chunk selects
 // the chunk's own best K pages (the K best of the row are among them, ties included:
 // fewer than K pages of the chunk rank above any of them), and a second launch selects
 // among the candidates.  Candidates are stored densely in page order (every chunk
@@ -141,56 +141,47 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
 // positions in the candidate row order like pages do: equal scores still go to the
 // lower page, page 0 is candidate 0 and the newest page is the last candidate whenever
 // the policy flags keep them in their chunks.
-constexpr int kChunkThreads = 1024;  // 16 waves x 4 keys: 0.3 us faster than 8 waves x 8 keys
-constexpr int kChunkItems = 4;
-constexpr int kChunkPages = kChunkThreads * kChunkItems;
+constexpr int kChunkItems = 4;  // keys per thread: 16 waves x 4 keys are 0.3 us faster than 8 waves x 8 keys
 
 struct ChunkOfRow {
-  int page_shift, policy, chunk;
+  int page_shift, policy, chunk, chunk_pages;
   __device__ __forceinline__ RowShape operator()(int seq_len) const {
     const int pages = (seq_len + (1 << page_shift) - 1) >> page_shift;
-    const int local = min(max(pages - chunk * kChunkPages, 0), kChunkPages);
+    const int local = min(max(pages - chunk * chunk_pages, 0), chunk_pages);
     int pol = 0;
     if (chunk == 0) pol |= policy & QUEST_FLAG_KEEP_FIRST_PAGE;
-    if (local > 0 && (chunk + 1) * kChunkPages >= pages) pol |= policy & QUEST_FLAG_KEEP_NEWEST_PAGE;
+    if (local > 0 && (chunk + 1) * chunk_pages >= pages) pol |= policy & QUEST_FLAG_KEEP_NEWEST_PAGE;
     return {local, pol};
   }
 };
 
-__global__ __launch_bounds__(kChunkThreads) void topk_chunk_kernel(
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void topk_chunk_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ seq_lens,
     float* __restrict__ cand_score, int32_t* __restrict__ cand_page, int num_heads, int max_pages,
     int k_pages, int num_chunks, int page_shift, int policy) {
-  __shared__ TopkShared<kChunkThreads> sm;
+  constexpr int kPages = kThreads * kChunkItems;
+  __shared__ TopkShared<kThreads> sm;
   // chunk-major launch order: the last chunk of a row, often a short one, must not take
   // the place of a full one on a compute unit that is still free
   const int h = blockIdx.x;
   const int chunk = blockIdx.y;
   const int b = blockIdx.z;
   const size_t bh = (size_t)b * num_heads + h;
-  const float* row = scores + bh * max_pages + (size_t)chunk * kChunkPages;
+  const float* row = scores + bh * max_pages + (size_t)chunk * kPages;
   const size_t at = (bh * num_chunks + chunk) * k_pages;
   float* out_score = cand_score + at;
   int32_t* out_page = cand_page + at;
-  topk_block_put<kChunkThreads, kChunkItems>(
-      sm, row, seq_lens + b, min(kChunkPages, max_pages - chunk * kChunkPages), k_pages,
+  topk_block_put<kThreads, kChunkItems>(
+      sm, row, seq_lens + b, min(kPages, max_pages - chunk * kPages), k_pages,
       [=](int pos, int page, int j, float score) {
         if (page >= 0) {
-          out_page[pos] = page + chunk * kChunkPages;
+          out_page[pos] = page + chunk * kPages;
           out_score[pos] = j >= 0 ? score : row[page];
         }
       },
-      nullptr, ChunkOfRow{page_shift, policy, chunk}, [] {});
+      nullptr, ChunkOfRow{page_shift, policy, chunk, kPages}, [] {});
 }
-
-struct CandidateRow {
-  int page_shift, policy, k_pages;
-  __device__ __forceinline__ RowShape operator()(int seq_len) const {
-    const int pages = (seq_len + (1 << page_shift) - 1) >> page_shift;
-    const int full = pages / kChunkPages;
-    return {full * k_pages + min(k_pages, pages - full * kChunkPages), policy};
-  }
-};
 
 template <int kThreads, int kItems>
 __global__ __launch_bounds__(kThreads) void topk_candidates_kernel(
@@ -220,7 +211,7 @@ __global__ __launch_bounds__(kThreads) void topk_candidates_kernel(
         }
         out[pos] = page;
       },
-      (h == 0 && k_eff != nullptr) ? k_eff + b : nullptr, CandidateRow{page_shift, policy, k_pages},
+      (h == 0 && k_eff != nullptr) ? k_eff + b : nullptr, CandidateRow{page_shift, policy, k_pages, kLargeChunk},
       [&] {
 #pragma unroll
         for (int jj = 0; jj < kItems; ++jj)
@@ -275,29 +266,46 @@ int launch_topk(const quest_cache& c, const float* scores, int k_pages, int32_t*
 constexpr int kChunkedFromPages = 16384;
 constexpr int kMaxCandidates = 512 * 16;
 
-static int num_chunks(const quest_cache& c) {
-  return (c.max_pages_per_seq + kChunkPages - 1) / kChunkPages;
+size_t candidate_bytes(const quest_cache& c, int k_pages, int chunk_pages) {
+  const long cand = candidates_per_row(c, k_pages, chunk_pages);
+  if (k_pages < 1 || k_pages > chunk_pages || cand > kMaxCandidates || 2 * cand > c.max_pages_per_seq) return 0;
+  return (size_t)c.batch * kv_heads(c) * cand * (sizeof(float) + sizeof(int32_t));
 }
 
 size_t topk_scratch_bytes(const quest_cache& c, int k_pages) {
-  const long cand = (long)num_chunks(c) * k_pages;
-  if (c.max_pages_per_seq < kChunkedFromPages || k_pages < 1 || k_pages > kChunkPages ||
-      cand > kMaxCandidates || 2 * cand > c.max_pages_per_seq)
-    return 0;
-  return (size_t)c.batch * kv_heads(c) * cand * (sizeof(float) + sizeof(int32_t));
+  return c.max_pages_per_seq < kChunkedFromPages ? 0 : candidate_bytes(c, k_pages, kLargeChunk);
+}
+
+int launch_topk_chunks(const quest_cache& c, const float* scores, int k_pages, int chunk_pages,
+                       void* scratch, Candidates* out, hipStream_t s) {
+  const int chunks = (c.max_pages_per_seq + chunk_pages - 1) / chunk_pages;
+  float* cand_score = (float*)scratch;
+  out->row_len = chunks * k_pages;
+  out->chunk_pages = chunk_pages;
+  out->score = cand_score;
+  int32_t* cand_page = (int32_t*)(cand_score + (size_t)c.batch * kv_heads(c) * out->row_len);
+  out->page = cand_page;
+  const dim3 grid(kv_heads(c), chunks, c.batch);
+#define QUEST_CHUNKS(T)                                                                           \
+  hipLaunchKernelGGL((topk_chunk_kernel<T>), grid, dim3(T), 0, s, scores, c.seq_lens, cand_score, \
+                     cand_page, kv_heads(c), c.max_pages_per_seq, k_pages, chunks,                \
+                     page_shift_of(c.page_size), c.flags)
+  if (chunk_pages == kSmallChunk)
+    QUEST_CHUNKS(kSmallChunk / kChunkItems);
+  else
+    QUEST_CHUNKS(kLargeChunk / kChunkItems);
+#undef QUEST_CHUNKS
+  return check_launch("quest_select_decode");
 }
 
 int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                         int32_t* k_eff, void* scratch, hipStream_t s) {
-  const int chunks = num_chunks(c);
-  const int row_len = chunks * k_pages;
-  float* cand_score = (float*)scratch;
-  int32_t* cand_page = (int32_t*)(cand_score + (size_t)c.batch * kv_heads(c) * row_len);
-  hipLaunchKernelGGL(topk_chunk_kernel, dim3(kv_heads(c), chunks, c.batch), dim3(kChunkThreads), 0, s,
-                     scores, c.seq_lens, cand_score, cand_page, kv_heads(c), c.max_pages_per_seq,
-                     k_pages, chunks, page_shift_of(c.page_size), c.flags);
-  int r = check_launch("quest_select_decode");
+  Candidates cand;
+  const int r = launch_topk_chunks(c, scores, k_pages, kLargeChunk, scratch, &cand, s);
   if (r != QUEST_OK) return r;
+  const int row_len = cand.row_len;
+  const float* cand_score = cand.score;
+  const int32_t* cand_page = cand.page;
 #define QUEST_CAND_CASE(I)                                                                       \
   if (row_len <= 512 * (I)) {                                                                    \
     hipLaunchKernelGGL((topk_candidates_kernel<512, I>), dim3(kv_heads(c), c.batch), dim3(512), 0, \

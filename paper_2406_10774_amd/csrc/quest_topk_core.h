@@ -122,6 +122,16 @@ struct WholeRow {
   }
 };
 
+// The row holds the scores of the candidates that the chunks of the row left.
+struct CandidateRow {
+  int page_shift, policy, k_pages, chunk_pages;
+  __device__ __forceinline__ RowShape operator()(int seq_len) const {
+    const int pages = (seq_len + (1 << page_shift) - 1) >> page_shift;
+    const int full = pages / chunk_pages;
+    return {full * k_pages + min(k_pages, pages - full * chunk_pages), policy};
+  }
+};
+
 // Selection for one row of scores by one work-group of kThreads threads (all of
 // them must call).  shape(seq_len) describes the row (it has room for max_pages
 // entries); put(position, page, j, score) receives the list: positions 0 .. k_pages-1,
