@@ -34,7 +34,9 @@ constexpr int waves_of(bool group) { return group ? 8 : 4; }
 // streams as long as they can carry it (2 layers of 32 heads, 32k tokens: 187 us with 128
 // work-groups, 172.7 with 192, 174.5 with 224, 175.7 with 256, 189 with 512; 32 query / 8 KV
 // heads, 4 ragged sequences: 133, 114.0, 113.3, 115.1, 127).
-constexpr int most_shares(bool group) { return group ? 224 : 192; }
+// Pages of 8 tokens leave a wave half the bytes in flight (one sequence of 42k tokens, 32 heads:
+// 113.7 us with 192, 104.9 with 256, 115.9 with 384).
+int most_shares(const quest_cache& c) { return group_size(c) > 1 ? 224 : c.page_size == 8 ? 256 : 192; }
 
 struct DenseArgs : AttnArgs {
   int shares;  // work-groups; partial results of share w are slots 2w and 2w + 1
@@ -264,7 +266,7 @@ int dense_shares(const quest_cache& c) {
   const bool group = group_size(c) > 1;
   const double heads = (double)c.batch * kv_heads(c) * attention_subs(c);
   const double units = heads * c.max_pages_per_seq * c.page_size / 16;
-  const double shares = std::min<double>(units / (4 * waves_of(group)), most_shares(group));
+  const double shares = std::min<double>(units / (4 * waves_of(group)), most_shares(c));
   return std::max(16, (int)((shares + 15) / 16) * 16);
 }
 

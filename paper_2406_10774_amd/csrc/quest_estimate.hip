@@ -41,9 +41,10 @@ __global__ __launch_bounds__(kEstWaves* kWave) void estimate_kernel(const Estima
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
 // table is scanned faster by twice as many waves of half the size: 8.3 us against 8.75 us
 // at 2049 pages of 32 heads, 13.6 against 14.2 at 4100, 23.0 against 23.4 at 8193; but 98.0
-// against 93.7 us for 16 sequences of 8k to 64k tokens (1.2 M pages).
+// against 93.7 us for 16 sequences of 8k to 64k tokens (1.2 M pages), and the calls of a layer
+// 56.0 against 54.0 us for 2 sequences and 8 KV heads (0.49 M pages).
 int est_iters(const quest_cache& c) {
-  return (long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (1l << 19) ? 2 : kEstIters;
+  return (long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (3l << 17) ? 2 : kEstIters;
 }
 
 template <bool kAppend, int kIters>
