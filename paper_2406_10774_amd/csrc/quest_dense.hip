@@ -40,7 +40,7 @@ int most_shares(const quest_cache& c) { return group_size(c) > 1 ? 224 : c.page_
 
 struct DenseArgs : AttnArgs {
   int shares;  // work-groups; partial results of share w are slots 2w and 2w + 1
-  int whole;   // no workspace: every work-group takes one item
+  int cuts;    // parts that every item is cut into, a work-group each; 0: equal shares of the line
 };
 
 // Query heads of one item and of one slot.
@@ -72,11 +72,16 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
   int64_t total = 0, shares = 1, off, end;
   int64_t base = 0;  // where sequence b begins
   int b = 0;
-  if (a.whole) {
-    b = (int)(w / blocks);
-    const int64_t pages = pages_of(a.seq_lens[b]);
-    off = (w - (int64_t)b * blocks) * pages;
-    end = off + pages;
+  int parts_each = 0;
+  if (a.cuts) {
+    const int item = (int)w / a.cuts, part = (int)w - item * a.cuts;
+    b = item / blocks;
+    const int pages = pages_of(a.seq_lens[b]);
+    parts_each = min(a.cuts, pages);  // none is empty
+    if (part >= parts_each) return;
+    off = end = (int64_t)(item - b * blocks) * pages;
+    off += (int)((int64_t)part * pages / parts_each);
+    end += (int)((int64_t)(part + 1) * pages / parts_each);
   } else {
     for (int b0 = 0; b0 < a.batch; b0 += kWave) {
       const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
@@ -182,7 +187,8 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
       }
     }
     if (!whole) {
-      const int from = share_of(item_at), parts = share_of(item_at + pages - 1) - from + 1;
+      const int from = a.cuts ? (int)w / a.cuts * a.cuts : share_of(item_at);
+      const int parts = a.cuts ? parts_each : share_of(item_at + pages - 1) - from + 1;
       uint32_t* arrivals = reinterpret_cast<uint32_t*>(
           a.counters + ((size_t)b * blocks + block) * kTeamWordStride);
       wait_stores();
@@ -260,9 +266,25 @@ bool four_heads(const quest_cache& c) {
   return group_size(c) == 1 && kv_heads(c) % 4 == 0 && (long)c.batch * kv_heads(c) >= 32;
 }
 
+long dense_items(const quest_cache& c) {
+  return (long)c.batch * kv_heads(c) * attention_subs(c) / (four_heads(c) ? 4 : 1);
+}
+
+// Little work: every item in as many parts, because a share that ends one item and begins the
+// next hands over twice, one after the other (launches of 6 sequences of 900 tokens, 8 heads: 13.0
+// us in equal shares, 10.9 in parts; 8 heads of 3000 tokens 8.9 and 7.7; 4 sequences of 900, 32
+// query / 8 KV heads 16.2 and 11.5).  At
+// most eight units per wave, so that ragged sequences cannot make one part long; two at least.
+int dense_cuts(const quest_cache& c) {
+  const long units = (long)c.max_pages_per_seq * c.page_size / 16 / (four_heads(c) ? 1 : waves_of(group_size(c) > 1));
+  const long cuts = std::max(1l, std::min(256 / dense_items(c), units / 2));
+  return dense_items(c) <= 256 && units <= 8 * cuts ? (int)cuts : 0;
+}
+
 // Work-groups: four units of 16 tokens per wave at least (a part costs about 2 us to hand
 // over and merge), of the longest work the page table has room for.
 int dense_shares(const quest_cache& c) {
+  if (const int cuts = dense_cuts(c)) return (int)dense_items(c) * cuts;
   const bool group = group_size(c) > 1;
   const double heads = (double)c.batch * kv_heads(c) * attention_subs(c);
   const double units = heads * c.max_pages_per_seq * c.page_size / 16;
@@ -287,16 +309,17 @@ int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, voi
   DenseArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   const int block = four_heads(c) ? 4 : 1;
-  const long items = (long)c.batch * a.kv_heads * a.subs / block;
+  const long items = dense_items(c);
   if (items > 8 * 65535l) {
     set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items * block);
     return QUEST_ERR_SHAPE;
   }
-  a.whole = workspace_bytes < dense_workspace_bytes(c);
-  a.shares = a.whole ? (int)items : dense_shares(c);
+  const bool whole = workspace_bytes < dense_workspace_bytes(c);  // no workspace: every work-group takes one item
+  a.cuts = whole ? 1 : dense_cuts(c);
+  a.shares = whole ? (int)items : dense_shares(c);
   a.counters = (uint64_t*)workspace;
-  a.part_acc = a.whole ? nullptr : (float*)((char*)workspace + counter_bytes(c));
-  a.part_ml = a.whole ? nullptr : a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
+  a.part_acc = whole ? nullptr : (float*)((char*)workspace + counter_bytes(c));
+  a.part_ml = whole ? nullptr : a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
   const dim3 grid((unsigned)a.shares);
 #define QUEST_DENSE_LAUNCH(L, G, B)                                                              \
   hipLaunchKernelGGL((dense_kernel<L, G, B, waves_of(G)>), grid, dim3(waves_of(G) * kWave), \

@@ -1,7 +1,7 @@
 """Attention over every page: the line of pages of all sequences and heads that the launch cuts
 into equal shares, where the cutting can go wrong: fewer pages than shares, shares that hold
 many whole items, items over many shares, more than 64 sequences (one lane each while the
-line is measured), heads by fours and one by one, groups that need two work-groups.  Against
+line is measured), little work in parts of each item, heads by fours and one by one, groups that need two work-groups.  Against
 the oracle; a second call on the same workspace gives the same bits."""
 import math
 
@@ -20,6 +20,7 @@ RAGGED70 = tuple(1 + (i * 37) % 90 for i in range(70))
 @pytest.mark.parametrize("kv_heads,group,S,lens", [
     (32, 1, 16, (1,)), (32, 1, 16, (3001,)), (32, 1, 8, (1999, 16)), (36, 1, 64, (700,)),
     (4, 1, 16, RAGGED70), (3, 1, 16, (5003, 1, 17)), (1, 1, 16, (9001,)), (1, 1, 32, RAGGED70 * 2),
+    (32, 1, 16, (700, 5)), (8, 1, 32, (903, 1, 32, 738)), (8, 4, 16, (900, 17, 500)),
     (8, 1, 8, (260, 3, 4100, 900)), (2, 9, 16, (2100, 5, 333)), (1, 4, 8, RAGGED70), (2, 4, 64, (6007,)),
 ])
 def test_dense_shares(kv_heads, group, S, lens):
