@@ -121,18 +121,30 @@ typedef struct quest_cache {
                                  else a divisor of num_heads (see below)     */
 } quest_cache;
 
-/* Bytes of device workspace quest_sparse_decode, quest_select_decode and
- * quest_decode_step need for this cache and k_pages (k_pages <= 0: the dense
- * path of quest_sparse_decode over all pages).  Pure host function.
+/* Bytes of device workspace for quest_sparse_decode, quest_select_decode and
+ * quest_decode_step on this cache: one size for every call on the cache shape
+ * (batch, heads, page size, row length), sparse or dense.  It does not depend on
+ * k_pages.  Pure host function.
  * The workspace holds one arrival counter per (sequence, head) and the split-K
  * partial results (running max, denominator and un-normalised accumulator of
  * each split); for rows of more than 5120 pages also the candidates that
  * quest_select_decode and quest_decode_step select from there (the best k_pages
- * of every chunk of 2048 or 4096 pages of a row, when there are at most 8192 of
- * them per row; below 16384 pages a workspace without room for them will do).  *out_bytes may be 0.  Without a workspace (NULL, or a
- * smaller one) attention over at most 64 tokens per head, or of more than 256
- * (sequence, query head) pairs, runs with one work-group for each head or group
- * of heads; other calls are refused, and so are those that keep candidates.
+ * of every chunk of 2048 or 4096 pages of a row: up to 4096 of them, from 16384
+ * pages on 8192, and never more than half of the row).  With
+ * QUEST_FLAG_SEPARATE_LAUNCHES rows of fewer than 16384 pages keep none; a
+ * workspace of that size serves calls without the flag too, which then select
+ * without candidates.
+ * A smaller workspace, or NULL, is accepted (status QUEST_OK) where one
+ * work-group for each head, or group of up to eight query heads of a KV head, can
+ * do the attention:
+ *   - any call over at most 64 tokens per head, of more than 256 (sequence, query
+ *     head) pairs, or of 256 pairs over at most 256 tokens;
+ *   - calls with a list of one page or of at most 256 tokens, and with longer lists
+ *     those of 129 or more (sequence, group) pairs (but not of 257 to 351 pairs
+ *     over 1024 tokens or more).
+ * Tokens are min(k_pages, max_pages_per_seq) * page_size.  Other calls refuse it, and
+ * so do quest_select_decode and quest_decode_step where
+ * quest_topk_workspace_bytes(cache, k_pages) is not 0.
  * A workspace must be zero-filled once, after it is allocated and before its
  * first use (e.g. hipMemset); every call leaves the counters at zero again, so
  * the same workspace serves later calls, sparse or dense, on the same cache
@@ -213,7 +225,7 @@ int quest_topk_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t
  * softmax over splits of the page list; the split that finishes last merges
  * them.  out is fp32
  * if out_is_fp16 == 0, else fp16 (rounded once, from the fp32 result).
- * workspace: at least quest_workspace_bytes(cache, topk_idx ? k_pages : 0). */
+ * workspace: quest_workspace_bytes(cache, k_pages) bytes. */
 int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* topk_idx,
                         int32_t k_pages, float sm_scale, void* out, int32_t out_is_fp16,
                         float* lse, void* workspace, size_t workspace_bytes, void* stream);
@@ -228,7 +240,7 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
  * max_pages_per_seq <= 4096 and QUEST_FLAG_SEPARATE_LAUNCHES is not set; else
  * the selection and the attention as launches of their own (the selection in
  * two stages for very long rows, see quest_workspace_bytes).
- * workspace: at least quest_workspace_bytes(cache, k_pages). */
+ * workspace: quest_workspace_bytes(cache, k_pages) bytes. */
 int quest_select_decode(const quest_cache* cache, const void* q, const float* scores,
                         int32_t k_pages, float sm_scale, int32_t* topk_idx, int32_t* k_eff,
                         void* out, int32_t out_is_fp16, float* lse, void* workspace,
@@ -242,8 +254,8 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * accumulated over a different split of the page list (so equal within fp32
  * rounding, not bit for bit).  scores and topk_idx are outputs and also the
  * buffers the phases hand to each other, so they must be provided.
- * workspace: at least quest_step_workspace_bytes(cache, k_pages) bytes (the
- * same size as quest_workspace_bytes gives for k_pages), zero-filled once after
+ * workspace: quest_step_workspace_bytes(cache, k_pages) bytes (the same size as
+ * quest_workspace_bytes gives), zero-filled once after
  * allocation (same rule as for quest_sparse_decode; one buffer may serve both
  * calls); calls sharing a workspace must not overlap in time.
  * The call enqueues the estimate, then what quest_select_decode enqueues: two
@@ -259,13 +271,16 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
 
 /* quest_decode_step for callers that cannot allocate or carry a workspace: code
  * that runs under HIP graph capture in a harness that forbids hipMalloc, tight
- * serving loops, test harnesses.  Same arguments, launches and results as
+ * serving loops, test harnesses.  Same arguments and results as
  * quest_decode_step, but the decode workspace lives in a static device array of
  * the library (8 MiB per GPU, held until the process ends) instead of caller
  * memory.  The call allocates and frees nothing.  Shapes whose two-stage
  * selection (quest_topk_workspace_bytes) needs more than 4 MiB are refused with
- * QUEST_ERR_WORKSPACE; where the attention's splits do not fit as well, there is
- * one per head or group of heads.  The call first enqueues a small kernel that
+ * QUEST_ERR_WORKSPACE.  The launches are those of quest_decode_step with a workspace
+ * of 8 MiB: where candidates of 2048-page chunks do not fit they come from
+ * 4096-page chunks or from the two-stage selection, and where the partial results
+ * do not fit beside those, a head or group has one split (out and lse then differ
+ * in the order of their fp32 sums).  The call first enqueues a small kernel that
  * zeroes the arrival counters it is going to use (the array keeps the previous call's
  * contents).  All calls on one GPU share the one array: calls that overlap in
  * time on the same GPU (different streams, or graphs replayed concurrently) race;

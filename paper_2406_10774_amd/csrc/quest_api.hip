@@ -77,13 +77,26 @@ bool workspace_optional(const quest_cache& c, int32_t k_pages) {
   return heads > 256 || tokens <= 64 || (tokens <= 256 && heads == 256);
 }
 
-// The bytes a call may use; refused (false) where it needs more than it was given.
-bool check_workspace(const quest_cache& c, int32_t k_pages, size_t need, size_t candidates,
-                     const void* workspace, size_t* bytes, const char* who) {
-  if (workspace == nullptr) *bytes = 0;
-  if (*bytes >= need || (candidates == 0 && workspace_optional(c, k_pages))) return true;
-  set_error("%s: workspace of %zu bytes needed, %zu given", who, need, *bytes);
-  return false;
+// The parts of a caller's workspace; refused (false) where a call needs more than it was given.
+// selects: the call selects its pages as well; very long rows then have candidates to keep.
+bool take_workspace(const quest_cache& c, int32_t k_pages, bool selects, void* workspace, size_t bytes,
+                    Workspace* w, const char* who) {
+  if (workspace == nullptr) bytes = 0;
+  const size_t candidates = selects ? topk_scratch_bytes(c, k_pages) : 0;
+  const size_t need = candidates > 0 ? attention_workspace_bytes(c) + candidates
+                      : k_pages > 0  ? decode_workspace_bytes(c, k_pages)
+                                     : dense_workspace_bytes(c);
+  if (bytes < need && (candidates > 0 || !workspace_optional(c, k_pages))) {
+    set_error("%s: workspace of %zu bytes needed, %zu given", who, need, bytes);
+    return false;
+  }
+  const size_t attention = bytes < attention_workspace_bytes(c) ? bytes : attention_workspace_bytes(c);
+  *w = {workspace, attention, (char*)workspace + attention, bytes - attention};
+  return true;
+}
+
+size_t workspace_bytes_of(const quest_cache& c) {
+  return attention_workspace_bytes(c) + selection_workspace_bytes(c);
 }
 
 }  // namespace
@@ -99,8 +112,8 @@ int quest_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out
     set_error("quest_workspace_bytes: out_bytes is NULL");
     return QUEST_ERR_NULL;
   }
-  // with a page list: enough for quest_select_decode and quest_decode_step as well
-  *out_bytes = k_pages > 0 ? step_workspace_bytes(*cache, k_pages) : dense_workspace_bytes(*cache);
+  (void)k_pages;  // one size for every call on the cache shape
+  *out_bytes = workspace_bytes_of(*cache);
   return QUEST_OK;
 }
 
@@ -205,14 +218,14 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
     set_error("quest_sparse_decode: k_pages must be >= 1 with a page list (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  const size_t need = topk_idx ? decode_workspace_bytes(*cache, k_pages) : dense_workspace_bytes(*cache);
-  if (!check_workspace(*cache, topk_idx ? k_pages : 0, need, 0, workspace, &workspace_bytes, "quest_sparse_decode"))
+  Workspace w;
+  if (!take_workspace(*cache, topk_idx ? k_pages : 0, false, workspace, workspace_bytes, &w, "quest_sparse_decode"))
     return QUEST_ERR_WORKSPACE;
   if (topk_idx == nullptr)
-    return launch_dense_decode(*cache, q, sm_scale, out, out_is_fp16 != 0, lse, workspace,
-                               workspace_bytes, (hipStream_t)stream);
+    return launch_dense_decode(*cache, q, sm_scale, out, out_is_fp16 != 0, lse, w.attention,
+                               w.attention_bytes, (hipStream_t)stream);
   return launch_sparse_decode(*cache, q, topk_idx, k_pages, sm_scale, out, out_is_fp16 != 0, lse,
-                              workspace, workspace_bytes, (hipStream_t)stream);
+                              w.attention, w.attention_bytes, (hipStream_t)stream);
 }
 
 int quest_select_decode(const quest_cache* cache, const void* q, const float* scores,
@@ -230,14 +243,11 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
     set_error("quest_select_decode: k_pages must be >= 1 (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  // (shorter rows do without candidates)
-  const size_t need = topk_scratch_bytes(*cache, k_pages) > 0 ? step_workspace_bytes(*cache, k_pages)
-                                                              : decode_workspace_bytes(*cache, k_pages);
-  if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
-                       "quest_select_decode"))
+  Workspace w;
+  if (!take_workspace(*cache, k_pages, true, workspace, workspace_bytes, &w, "quest_select_decode"))
     return QUEST_ERR_WORKSPACE;
   return launch_select_decode(*cache, q, scores, k_pages, sm_scale, topk_idx, k_eff, out,
-                              out_is_fp16 != 0, lse, workspace, workspace_bytes, (hipStream_t)stream);
+                              out_is_fp16 != 0, lse, w, (hipStream_t)stream);
 }
 
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes) {
@@ -251,7 +261,7 @@ int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t
     set_error("quest_step_workspace_bytes: k_pages must be >= 1 (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  *out_bytes = step_workspace_bytes(*cache, k_pages);
+  *out_bytes = workspace_bytes_of(*cache);
   return QUEST_OK;
 }
 
@@ -275,15 +285,11 @@ int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v
     set_error("quest_decode_step: k_pages must be >= 1 (got %d)", k_pages);
     return QUEST_ERR_SHAPE;
   }
-  // (shorter rows do without candidates)
-  const size_t need = topk_scratch_bytes(*cache, k_pages) > 0 ? step_workspace_bytes(*cache, k_pages)
-                                                              : decode_workspace_bytes(*cache, k_pages);
-  if (!check_workspace(*cache, k_pages, need, topk_scratch_bytes(*cache, k_pages), workspace, &workspace_bytes,
-                       "quest_decode_step"))
+  Workspace w;
+  if (!take_workspace(*cache, k_pages, true, workspace, workspace_bytes, &w, "quest_decode_step"))
     return QUEST_ERR_WORKSPACE;
   return launch_decode_step(*cache, k_new, v_new, k_pool_write != 0, q, k_pages, sm_scale, scores,
-                            topk_idx, k_eff, out, out_is_fp16 != 0, lse, workspace, workspace_bytes,
-                            (hipStream_t)stream);
+                            topk_idx, k_eff, out, out_is_fp16 != 0, lse, w, (hipStream_t)stream);
 }
 
 int quest_decode_step_static(const quest_cache* cache, const void* k_new, const void* v_new,

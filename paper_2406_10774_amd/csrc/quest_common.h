@@ -57,6 +57,9 @@ struct Candidates {
   int row_len, chunk_pages;
 };
 constexpr int kSmallChunk = 2048, kLargeChunk = 4096;
+// quest_topk selects in two stages from this many pages on, among this many candidates at most.
+constexpr int kChunkedFromPages = 16384;
+constexpr int kMaxCandidates = 512 * 16;
 inline long candidates_per_row(const quest_cache& c, int k_pages, int chunk_pages) {
   return ((long)c.max_pages_per_seq + chunk_pages - 1) / chunk_pages * k_pages;
 }
@@ -66,10 +69,23 @@ int launch_topk_chunks(const quest_cache& c, const float* scores, int k_pages, i
 size_t topk_scratch_bytes(const quest_cache& c, int k_pages);
 int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                         int32_t* k_eff, void* scratch, hipStream_t s);
+// What a launch over a list of k_pages, or over all pages, uses.  With less an attention
+// launch gives every (sequence, head) to one work-group, which needs none.
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages);
 size_t dense_workspace_bytes(const quest_cache& c);
-// With a workspace smaller than that an attention launch gives every (sequence, head) to one
-// work-group, which needs none.
+// A caller's workspace: the attention's part, then the candidates'.  Both sizes are those of
+// the cache shape, enough for every call on it (a size that followed k_pages would have to
+// follow every border of the split and chunk rules, up and down).
+size_t attention_workspace_bytes(const quest_cache& c);
+size_t selection_workspace_bytes(const quest_cache& c);
+// The parts as a call is given them.  Candidates never lie on the counters, which other calls
+// with this workspace need zero.
+struct Workspace {
+  void* attention;
+  size_t attention_bytes;
+  void* selection;
+  size_t selection_bytes;
+};
 int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
                         float* lse, void* workspace, size_t workspace_bytes, hipStream_t s);
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
@@ -77,23 +93,16 @@ int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* top
                          size_t workspace_bytes, hipStream_t s);
 
 bool select_decode_supported(const quest_cache& c, int k_pages);
-// Candidates quest_select_decode keeps in its workspace when there is room for them; without
-// it does with topk_scratch_bytes.
-size_t select_candidate_bytes(const quest_cache& c, int k_pages);
-// Where they lie: never on the counters, which other calls with this workspace may need zero.
-size_t candidate_offset(const quest_cache& c, int k_pages);
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
-                         int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
-                         hipStream_t s);
+                         int out_is_fp16, float* lse, const Workspace& workspace, hipStream_t s);
 
-size_t step_workspace_bytes(const quest_cache& c, int k_pages);
 // Leading part of a decode workspace: the arrival counters (must be zero before a launch).
 size_t decode_counter_bytes(const quest_cache& c);
 int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write,
                        const void* q, int k_pages, float sm_scale, float* scores, int32_t* topk_idx,
-                       int32_t* k_eff, void* out, int out_is_fp16, float* lse, void* workspace,
-                       size_t workspace_bytes, hipStream_t s);
+                       int32_t* k_eff, void* out, int out_is_fp16, float* lse, const Workspace& workspace,
+                       hipStream_t s);
 int launch_decode_step_static(const quest_cache& c, const void* k_new, const void* v_new,
                               int k_pool_write, const void* q, int k_pages, float sm_scale,
                               float* scores, int32_t* topk_idx, int32_t* k_eff, void* out,

@@ -298,12 +298,14 @@ long list_splits(long items, long tokens) {
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
   return std::min(kComputeUnits / items, useful);
 }
+long most_splits(const quest_cache& c, int list_len) {
+  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);  // work-groups per split
+  return std::min(list_splits(items, (long)list_len * c.page_size), std::min<long>(list_len, kMaxTeamSize));
+}
 SplitPlan plan_splits(const quest_cache& c, int k_pages) {
   SplitPlan p;
   p.list_len = std::min(k_pages, c.max_pages_per_seq);
-  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);  // work-groups per split
-  long splits = list_splits(items, (long)p.list_len * c.page_size);
-  splits = std::min(splits, std::min<long>(p.list_len, kMaxTeamSize));
+  const long splits = most_splits(c, p.list_len);
   p.per_split = (int)((p.list_len + splits - 1) / splits);
   p.splits = (p.list_len + p.per_split - 1) / p.per_split;  // no empty split
   return p;
@@ -316,10 +318,20 @@ size_t counter_bytes(const quest_cache& c) {
 
 size_t decode_counter_bytes(const quest_cache& c) { return counter_bytes(c); }
 
-size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
-  const size_t splits = plan_splits(c, k_pages).splits;
+namespace {
+size_t split_bytes(const quest_cache& c, size_t splits) {
   if (splits == 1) return 0;
   return counter_bytes(c) + (size_t)c.batch * c.num_heads * splits * (kHeadDim + 2) * sizeof(float);
+}
+}  // namespace
+
+size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
+  return split_bytes(c, plan_splits(c, k_pages).splits);
+}
+
+// most_splits of the longest list there is: no shorter one has more.
+size_t attention_workspace_bytes(const quest_cache& c) {
+  return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, c.max_pages_per_seq)));
 }
 
 namespace {
@@ -416,51 +428,46 @@ namespace {
 // of whole rows is 0.4 us faster.  Chunks of 4096 pages where 2048 leave too many candidates
 // (8193 pages 46.6 us).
 constexpr int kCandFromPages = 5121;
-int chunk_to_select_from(const quest_cache& c, int k_pages) {
+constexpr int kMostSelected = kSelWaves * kWave * 8;  // candidates of a row that a launch can select among
+int chunk_to_select_from(const quest_cache& c, int k_pages, size_t room) {
   if ((c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) || c.max_pages_per_seq < kCandFromPages || k_pages > kSelListCap)
     return 0;
   for (const int chunk : {kSmallChunk, kLargeChunk})
-    if (candidates_per_row(c, k_pages, chunk) <= kSelWaves * kWave * 8 && candidate_bytes(c, k_pages, chunk) > 0)
+    if (candidates_per_row(c, k_pages, chunk) <= kMostSelected && candidate_bytes(c, k_pages, chunk) > 0 &&
+        candidate_bytes(c, k_pages, chunk) <= room)
       return chunk;
   return 0;
 }
 }  // namespace
 
-size_t select_candidate_bytes(const quest_cache& c, int k_pages) {
-  const int chunk = chunk_to_select_from(c, k_pages);
-  return chunk ? candidate_bytes(c, k_pages, chunk) : select_decode_supported(c, k_pages) ? 0 : topk_scratch_bytes(c, k_pages);
-}
-
-size_t candidate_offset(const quest_cache& c, int k_pages) {
-  return std::max(decode_workspace_bytes(c, k_pages), counter_bytes(c));
+// The most candidates that a row can have (candidate_bytes): at most half of its pages.
+size_t selection_workspace_bytes(const quest_cache& c) {
+  const bool select = c.max_pages_per_seq >= kCandFromPages && !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES);
+  const size_t most = c.max_pages_per_seq >= kChunkedFromPages ? kMaxCandidates : select ? kMostSelected : 0;
+  return (size_t)c.batch * kv_heads(c) * std::min<size_t>(most, c.max_pages_per_seq / 2) * (sizeof(float) + sizeof(int32_t));
 }
 
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
-                         int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
-                         hipStream_t s) {
+                         int out_is_fp16, float* lse, const Workspace& w, hipStream_t s) {
   if (select_decode_supported(c, k_pages))
     return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, sm_scale, out,
-                         out_is_fp16, lse, workspace, workspace_bytes, s);
-  // candidates behind the attention's workspace, or alone if there is no room for both and
-  // they cannot be done without
-  const bool both = workspace_bytes >= step_workspace_bytes(c, k_pages);
-  const bool alone = !both && topk_scratch_bytes(c, k_pages) > 0;
-  void* scratch = (char*)workspace + (both ? candidate_offset(c, k_pages) : 0);
-  const size_t rest = both ? decode_workspace_bytes(c, k_pages) : alone ? 0 : workspace_bytes;
+                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
   int r;
-  const int chunk = chunk_to_select_from(c, k_pages);
-  if (both && chunk) {
+  if (const int chunk = chunk_to_select_from(c, k_pages, w.selection_bytes)) {
     Candidates cand;
-    r = launch_topk_chunks(c, scores, k_pages, chunk, scratch, &cand, s);
+    r = launch_topk_chunks(c, scores, k_pages, chunk, w.selection, &cand, s);
     if (r != QUEST_OK) return r;
     return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, sm_scale, out,
-                         out_is_fp16, lse, workspace, rest, s);
+                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
   }
-  r = topk_scratch_bytes(c, k_pages) > 0 ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff, scratch, s)
-                                         : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
+  const size_t two_stages = topk_scratch_bytes(c, k_pages);
+  r = two_stages > 0 && two_stages <= w.selection_bytes
+          ? launch_topk_chunked(c, scores, k_pages, topk_idx, k_eff, w.selection, s)
+          : launch_topk(c, scores, k_pages, topk_idx, k_eff, s);
   if (r != QUEST_OK) return r;
-  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, workspace, rest, s);
+  return launch_sparse_decode(c, q, topk_idx, k_pages, sm_scale, out, out_is_fp16, lse, w.attention,
+                              w.attention_bytes, s);
 }
 
 }  // namespace quest

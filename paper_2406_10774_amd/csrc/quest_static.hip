@@ -13,11 +13,12 @@ namespace {
 
 // Every GPU the library runs on holds its own copy of this array until the process
 // ends.  Counters and split-K partial results take up to about 1.3 MiB (the launch keeps
-// items * splits near one work-group per compute unit), 5.1 MiB for 257 to 351 groups of
+// items * splits near one work-group per compute unit), 4.9 MiB for 257 to 351 groups of eight
 // query heads, which get three splits each; the rest is for the candidates of the
-// selection of rows from 5121 pages on (batch * KV heads * chunks * k_pages * 8 bytes: 0.6
-// MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens).
-// Where there is no room for both, the attention runs without splits.
+// selection of rows from 5121 pages on (batch * KV heads * chunks * k_pages * 8 bytes: 1.1
+// MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens, in chunks of
+// 2048 pages).  Candidates of such chunks that do not fit are picked from chunks of 4096, and
+// where those of a two-stage selection do not fit either, the attention runs without splits.
 constexpr size_t kScratchBytes = 8u << 20;
 constexpr size_t kMostCandidates = 4u << 20;  // of the two-stage selection
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -75,12 +76,11 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
   void* ws = nullptr;
   int r = scratch_pointer(&ws);
   if (r != QUEST_OK) return r;
+  size_t attention = decode_workspace_bytes(c, k_pages);
+  if (attention + candidates > kScratchBytes) attention = 0;
   // counters exist when the attention runs in several splits; they are then the first
   // bytes of its workspace
-  const size_t attention = decode_workspace_bytes(c, k_pages), need = step_workspace_bytes(c, k_pages);
-  const size_t bytes = need <= kScratchBytes ? need
-                       : candidates == 0 && attention <= kScratchBytes ? attention : candidates;
-  if (attention > 0 && (bytes == need || bytes == attention)) {
+  if (attention > 0) {
     const size_t words = decode_counter_bytes(c) / sizeof(uint32_t);
     hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s,
                        (uint32_t*)ws, words);
@@ -88,7 +88,8 @@ int launch_decode_step_static(const quest_cache& c, const void* k_new, const voi
     if (r != QUEST_OK) return r;
   }
   return launch_decode_step(c, k_new, v_new, k_pool_write, q, k_pages, sm_scale, scores, topk_idx,
-                            k_eff, out, out_is_fp16, lse, ws, bytes, s);
+                            k_eff, out, out_is_fp16, lse,
+                            Workspace{ws, attention, (char*)ws + attention, kScratchBytes - attention}, s);
 }
 
 }  // namespace quest

@@ -22,20 +22,15 @@
 
 namespace quest {
 
-size_t step_workspace_bytes(const quest_cache& c, int k_pages) {
-  const size_t candidates = select_candidate_bytes(c, k_pages);
-  return (candidates > 0 ? candidate_offset(c, k_pages) : decode_workspace_bytes(c, k_pages)) + candidates;
-}
-
 int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write,
                        const void* q, int k_pages, float sm_scale, float* scores, int32_t* topk_idx,
-                       int32_t* k_eff, void* out, int out_is_fp16, float* lse, void* workspace,
-                       size_t workspace_bytes, hipStream_t s) {
+                       int32_t* k_eff, void* out, int out_is_fp16, float* lse, const Workspace& workspace,
+                       hipStream_t s) {
   int r = k_new ? launch_append_estimate(c, k_new, v_new, k_pool_write, q, scores, s)
                 : launch_estimate(c, q, scores, s);
   if (r != QUEST_OK) return r;
   return launch_select_decode(c, q, scores, k_pages, sm_scale, topk_idx, k_eff, out, out_is_fp16, lse,
-                              workspace, workspace_bytes, s);
+                              workspace, s);
 }
 
 }  // namespace quest

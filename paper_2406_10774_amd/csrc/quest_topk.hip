@@ -261,11 +261,6 @@ int launch_topk(const quest_cache& c, const float* scores, int k_pages, int32_t*
   return check_launch("quest_topk");
 }
 
-// Rows from kChunkedFromPages pages on are selected in two stages when the caller
-// brings scratch memory for the candidates (quest_select_decode, quest_decode_step).
-constexpr int kChunkedFromPages = 16384;
-constexpr int kMaxCandidates = 512 * 16;
-
 size_t candidate_bytes(const quest_cache& c, int k_pages, int chunk_pages) {
   const long cand = candidates_per_row(c, k_pages, chunk_pages);
   if (k_pages < 1 || k_pages > chunk_pages || cand > kMaxCandidates || 2 * cand > c.max_pages_per_seq) return 0;

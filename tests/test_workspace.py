@@ -1,0 +1,90 @@
+"""One workspace serves every call on a cache shape, as quest.h says: dense or with any list
+length, with and without QUEST_FLAG_SEPARATE_LAUNCHES, whichever call its size was asked for.
+The host decides that before anything is launched; on a machine without a GPU an accepted call
+then ends with QUEST_ERR_HIP."""
+import ctypes
+import random
+
+import pytest
+
+from paper_2406_10774_amd import binding
+
+WORKSPACE, HIP = -4, -5
+
+
+def on_host_only():
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the pointers of these calls point nowhere")
+
+
+def make_cache(batch, kv_heads, group, page_size, pages, flags=0):
+    return binding.quest_cache(batch=batch, num_heads=kv_heads * group, head_dim=128, page_size=page_size,
+                               max_pages_per_seq=pages, flags=flags, num_phys_pages=64, k_pool=0x1000,
+                               v_pool=0x1000, meta=0x1000, page_table=0x1000, seq_lens=0x1000,
+                               num_kv_heads=kv_heads if group > 1 else 0)
+
+
+def size_of(c, k_pages, step=False):
+    lib, out = binding.load(), ctypes.c_size_t(0)
+    query = lib.quest_step_workspace_bytes if step else lib.quest_workspace_bytes
+    assert query(ctypes.byref(c), k_pages, ctypes.byref(out)) == 0
+    return out.value
+
+
+def call(kind, c, k_pages, nbytes):
+    lib, r, p = binding.load(), ctypes.byref(c), 0x1000
+    ws = p if nbytes else None
+    if kind == "dense":
+        return lib.quest_sparse_decode(r, p, None, 0, 1.0, p, 0, None, ws, nbytes, None)
+    if kind == "list":
+        return lib.quest_sparse_decode(r, p, p, k_pages, 1.0, p, 0, None, ws, nbytes, None)
+    if kind == "select":
+        return lib.quest_select_decode(r, p, p, k_pages, 1.0, p, None, p, 0, None, ws, nbytes, None)
+    return lib.quest_decode_step(r, None, None, 0, p, k_pages, 1.0, p, p, None, p, 0, None, ws, nbytes, None)
+
+
+@pytest.mark.parametrize("pages,asked,used,asked_flags", [
+    (16384, 600, 500, 0), (20000, 600, 400, 0), (24000, 400, 330, 0), (16384, 256, 256, 1), (32769, 4000, 3, 0),
+    (16384, 0, 300, 0), (2048, 25, 24, 0), (2048, 16, 128, 0), (128, 0, 100, 0), (40000, 5, 1600, 0),
+])
+@pytest.mark.parametrize("kind", ["dense", "list", "select", "step"])
+def test_one_workspace_for_all_list_lengths(kind, pages, asked, used, asked_flags):
+    on_host_only()
+    for kv_heads, group in ((32, 1), (4, 8), (1, 1)):
+        nbytes = size_of(make_cache(1, kv_heads, group, 16, pages, asked_flags), asked)
+        if pages < 16384 and asked_flags == 0:
+            assert nbytes == size_of(make_cache(1, kv_heads, group, 16, pages), used)
+        assert call(kind, make_cache(1, kv_heads, group, 16, pages), used, nbytes) == HIP
+
+
+def test_one_workspace_on_drawn_shapes():
+    on_host_only()
+    rng = random.Random(7)
+    spread = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    for _ in range(4000):
+        shape = (spread(1, 64), rng.choice([1, 2, 8, 12, 29, 32, 40]), rng.choice([1, 1, 2, 4, 5, 8, 9]),
+                 rng.choice([8, 16, 32, 64]), spread(1, 70000))
+        asked, used = rng.choice([0, spread(1, 4200)]), spread(1, 4200)
+        flags = rng.choice([0, 1]), rng.choice([0, 1])
+        kind = rng.choice(["dense", "list", "select", "step"])
+        nbytes = size_of(make_cache(*shape, flags[0]), asked, step=asked > 0 and rng.random() < 0.5)
+        assert call(kind, make_cache(*shape, flags[1]), used, nbytes) == HIP, (shape, asked, used, flags, kind)
+
+
+@pytest.mark.parametrize("kind,batch,kv_heads,group,page_size,pages,k_pages,accepted", [
+    ("dense", 1, 32, 1, 16, 4, 0, True), ("dense", 1, 32, 1, 16, 5, 0, False), ("dense", 8, 32, 1, 16, 16, 0, True),
+    ("dense", 8, 32, 1, 16, 17, 0, False), ("dense", 9, 29, 1, 16, 2048, 0, True), ("dense", 9, 8, 4, 16, 2048, 0, True),
+    ("list", 1, 32, 1, 16, 2048, 16, True), ("list", 1, 32, 1, 16, 2048, 17, False),
+    ("list", 1, 32, 1, 64, 2048, 1, True), ("list", 4, 32, 1, 16, 2048, 128, False),
+    ("list", 129, 1, 1, 16, 2048, 128, True), ("list", 257, 1, 2, 16, 2048, 128, True),
+    ("select", 1, 32, 1, 16, 2048, 17, False), ("step", 1, 32, 1, 16, 2048, 16, True),
+    ("step", 1, 32, 1, 16, 16384, 16, False), ("step", 9, 32, 1, 16, 16384, 16, False),
+    ("step", 9, 32, 1, 16, 16383, 64, True),
+])
+def test_calls_without_a_workspace(kind, batch, kv_heads, group, page_size, pages, k_pages, accepted):
+    """The rule that quest.h states for a workspace of no or too few bytes."""
+    on_host_only()
+    c = make_cache(batch, kv_heads, group, page_size, pages)
+    for nbytes in (0, 64):
+        assert call(kind, c, k_pages, nbytes) == (HIP if accepted else WORKSPACE)
