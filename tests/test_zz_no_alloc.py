@@ -82,3 +82,52 @@ def test_static_scratch_refuses_shapes_beyond_its_size():
     with pytest.raises(Q.QuestError) as err:
         Q.quest_decode_step_static(cache, None, None, False, q, 512, 0.1, scores, idx, out)
     assert err.value.status == -4
+
+
+@pytest.mark.parametrize("batch,kv_heads,group,pages,k_pages,lens", [
+    # candidates of 2048-page chunks do not fit behind the splits' partial results: chunks of 4096
+    (9, 29, 1, 32768, 250, (32768 * 16, 3, 2048 * 16, 4096 * 16 + 1, 30000 * 16, 249 * 16, 16, 9000, 100000)),
+    # nor does the attention's part beside the two-stage selection: no splits, separate launches
+    (39, 9, 8, 16384, 360, tuple(1 + i * 16384 * 16 // 39 for i in range(39))),
+    # eight sequences of 32 heads, which leave the whole array to the candidates
+    (8, 32, 1, 32768, 256, tuple(32768 * 16 - i * 70001 for i in range(8))),
+])
+def test_static_scratch_at_its_limits(batch, kv_heads, group, pages, k_pages, lens):
+    """Selections that fill the static array: the list is that of quest_decode_step, out and lse
+    equal up to fp32 sums of n = 16 k_pages tokens in another order (2 n 2^-24 times |v| < 6); a
+    call with splits that follows finds its counters at zero."""
+    import torch
+    from paper_2406_10774_amd import binding as Q
+    dev, N = "cuda:0", 64
+    gen = torch.Generator(device=dev).manual_seed(pages)
+    half = dict(dtype=torch.float16, device=dev, generator=gen)
+    k_pool, v_pool = (torch.randn((N, kv_heads, 16, 128), **half) for _ in range(2))
+    meta = torch.zeros((kv_heads, N, 2, 128), dtype=torch.float16, device=dev)
+    table = torch.randint(0, N, (batch, pages), dtype=torch.int32, device=dev, generator=gen)
+    q = torch.randn((batch, kv_heads * group, 128), **half)
+    seq = torch.tensor(lens, dtype=torch.int32, device=dev)
+    cache = Q.Cache(k_pool, v_pool, meta, table, seq, num_heads=kv_heads * group)
+    Q.quest_build_meta(cache)
+    scores = torch.zeros((batch, kv_heads, pages), device=dev)
+    scale = 1 / math.sqrt(128)
+
+    def run(step):
+        idx = torch.full((batch, kv_heads, k_pages), -7, dtype=torch.int32, device=dev)
+        keff = torch.full((batch,), -7, dtype=torch.int32, device=dev)
+        out = torch.full(q.shape, float("nan"), device=dev)
+        lse = torch.full(q.shape[:2], float("nan"), device=dev)
+        step(idx, keff, out, lse)
+        torch.cuda.synchronize()
+        return idx, keff, out, lse
+
+    ws = torch.zeros(Q.quest_step_workspace_bytes(cache, k_pages), dtype=torch.uint8, device=dev)
+    want = run(lambda idx, keff, out, lse: Q.quest_decode_step(
+        cache, None, None, False, q, k_pages, scale, scores, idx, out, ws, k_eff=keff, lse=lse))
+    for _ in range(2):                     # the second on what the first left in the array
+        got = run(lambda idx, keff, out, lse: Q.quest_decode_step_static(
+            cache, None, None, False, q, k_pages, scale, scores, idx, out, k_eff=keff, lse=lse))
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        bound = 2 * 16 * k_pages * 2.0 ** -24
+        assert float((got[2] - want[2]).abs().max()) <= bound * 6
+        assert float((got[3] - want[3]).abs().max()) <= bound + 1e-6
+    _one_step(synth.Workload(73, "static-after", 1, 4, (16 * 90 + 7,), 16 * 24, 2, decode_steps=4))
