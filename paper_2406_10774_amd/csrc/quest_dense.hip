@@ -65,7 +65,10 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int lane = lane_id();
   const int blocks = a.kv_heads * a.subs / kBlock;  // items per sequence
-  auto pages_of = [&](int len) { return (max(len, 0) + (1 << a.page_shift) - 1) >> a.page_shift; };
+  // (a length past the end of the row, which a caller must not pass, reads no further than the row)
+  auto pages_of = [&](int len) {
+    return min((max(len, 0) + (1 << a.page_shift) - 1) >> a.page_shift, a.max_pages);
+  };
 
   // ---- this work-group's share [off, end) of the line, and the sequence it begins in
   const int64_t w = blockIdx.x;

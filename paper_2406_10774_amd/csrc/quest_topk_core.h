@@ -175,7 +175,7 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads>& sm,
   for (int i = tid; i < (kCopies0 + 3) * 256; i += kThreads) (&hist[0][0])[i] = 0;
 
   const RowShape row_shape = shape(seq_len);
-  const int num_pages = row_shape.num_pages;
+  const int num_pages = min(row_shape.num_pages, max_pages);  // whatever the length says: no entry past the row
   const int K = min(k_pages, num_pages);
   if (tid == 0 && k_eff_slot != nullptr) *k_eff_slot = K;
   if (K == num_pages) {  // everything is selected: identity list, padded with -1
