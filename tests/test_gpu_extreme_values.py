@@ -143,3 +143,49 @@ def test_a_single_token_returns_its_value_bit_for_bit():
     got, _ = layer.decode(q, idx, 1)
     want = v_pool[table[0, 0], :, 0].astype(np.float32)[None]
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("group", [3, 8, 9])
+def test_groups_of_query_heads_with_subnormal_and_huge_operands(salted, group):
+    """The same keys and values under groups of query heads, on the matrix cores, estimate included."""
+    from gpu_util import Layer, score_tolerance
+    w, table, k_pool, v_pool, _, lens, _ = salted
+    rng = np.random.default_rng(group)
+    H = w.num_heads * group
+    q = rng.standard_normal((w.batch, H, 128)).astype(np.float16)
+    q[..., 0:8] = subnormals(rng, q[..., 0:8].shape)
+    q[..., 8:16] = extremes(rng, q[..., 8:16].shape)
+    q[..., 16:24] = subnormals(rng, q[..., 16:24].shape)
+    layer = Layer(k_pool, v_pool, table, lens, num_q_heads=H)
+    layer.build_meta()
+    meta = O.build_meta(k_pool, table, lens)
+    sc = O.estimate(meta, q, table, lens, w.page_size)
+    tol = score_tolerance(meta, q, table, lens, w.page_size)
+    got = layer.estimate(q)
+    for b in range(w.batch):
+        P = w.pages_of(b)
+        assert (np.abs(got[b, :, :P] - sc[b, :, :P]) <= tol[b, :, :P]).all(), b
+    scale = 1 / math.sqrt(128)
+    idx, _ = O.topk(sc, lens, w.page_size, w.k_pages)
+    for pages in (idx, None):
+        want, want_lse = O.sparse_decode(k_pool, v_pool, q, table, lens, pages, scale)
+        got, lse = layer.decode(q, pages, w.k_pages)
+        assert np.abs(got - want).max() <= ATTN_TOL
+        assert np.abs(lse - want_lse).max() <= ATTN_TOL
+
+
+@pytest.mark.parametrize("group", [2, 9])
+def test_a_single_token_returns_its_value_to_every_head_of_a_group(group):
+    from gpu_util import Layer
+    w = synth.Workload(99, "one-token", 1, 2, (1,), token_budget=16, planted_per_head=0, decode_steps=1)
+    table, N = synth.make_page_table(w, permute=False)
+    k_pool, v_pool, _ = synth.fill_pools(w, table, N)
+    rng = np.random.default_rng(99)
+    v_pool[table[0, 0], :, 0, 0:32] = subnormals(rng, (2, 32))
+    v_pool[table[0, 0], :, 0, 32:48] = extremes(rng, (2, 16))
+    q = rng.standard_normal((1, 2 * group, 128)).astype(np.float16)
+    layer = Layer(k_pool, v_pool, table, np.array(w.seq_lens, np.int32), num_q_heads=2 * group)
+    want = v_pool[table[0, 0], :, 0].astype(np.float32).repeat(group, 0)[None]
+    for idx in (np.zeros((1, 2, 1), np.int32), None):
+        got, _ = layer.decode(q, idx, 1)
+        assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
