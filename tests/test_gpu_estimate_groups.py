@@ -1,0 +1,59 @@
+"""The estimate for groups of query heads over large tables (more than 393216 entries: 16 pages per
+wave), which nothing else reaches with groups, and over small ones: groups that are no
+multiple of the four queries loaded at a time, ragged lengths that end inside and between a
+wave's pages, rows that are no multiple of a work-group's pages.  Pages repeat a few physical
+ones, so that the pools stay small.  Scores against the oracle; the append against the calls one
+by one, bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import quest_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kv_heads,group,S,pages,lens", [
+    (8, 5, 16, 13013, (13013 * 16, 13000 * 16 + 1, 16 * 64 + 5, 1)),
+    (8, 9, 8, 49217, (49217 * 8 - 3,)),
+    (4, 4, 64, 33001, (33001 * 64, 40 * 64, 7 * 64 + 63)),
+    (2, 2, 16, 24601, (24601 * 16 - 1, 16 * 15, 16 * 16, 16 * 16 + 1, 24577 * 16, 16 * 63, 100, 24601 * 16)),
+    (8, 5, 16, 333, (333 * 16, 100, 16 * 17 + 2)), (3, 9, 32, 1027, (1027 * 32 - 5, 32 * 8, 1)),
+    (2, 6, 8, 61, (61 * 8, 33)),
+])
+def test_scores(kv_heads, group, S, pages, lens):
+    import torch
+    from gpu_util import Layer, score_tolerance
+    B, N = len(lens), 40
+    rng = np.random.default_rng(pages)
+    k_pool = rng.standard_normal((N, kv_heads, S, 128)).astype(np.float16)
+    v_pool = np.zeros_like(k_pool)
+    q = rng.standard_normal((B, kv_heads * group, 128)).astype(np.float16)
+    # the newest token's page is a physical page of its own: the others hold whole pages
+    table = rng.integers(B, N, (B, pages)).astype(np.int32)
+    cur = np.array(lens, np.int32)
+    table[np.arange(B), (cur - 1) // S] = np.arange(B)
+    k_new, v_new = (rng.standard_normal((B, kv_heads, 128)).astype(np.float16) for _ in range(2))
+    meta = np.stack([k_pool.astype(np.float32).min(2), k_pool.astype(np.float32).max(2)], 2).astype(np.float16)
+    meta = np.ascontiguousarray(meta.transpose(1, 0, 2, 3))               # [heads][pages][2][D]
+
+    def layer():
+        x = Layer(k_pool, v_pool, table, cur, num_q_heads=kv_heads * group)
+        x.meta.copy_(x.half(meta))
+        return x
+
+    one = layer()
+    one.append(k_new, v_new, write=True)
+    got = one.estimate(q)
+    after = one.np16(one.meta)
+    want = O.estimate(after, q, table, cur, S)
+    tol = score_tolerance(after, q, table, cur, S)
+    for b in range(B):
+        P = -(-int(cur[b]) // S)
+        assert (np.abs(got[b, :, :P] - want[b, :, :P]) <= tol[b, :, :P]).all(), b
+        assert np.isnan(got[b, :, P:]).all(), b                           # not written
+    both = layer()
+    fused = both.append_estimate(k_new, v_new, q)
+    assert np.array_equal(fused.view(np.uint32), got.view(np.uint32))
+    assert np.array_equal(both.np16(both.meta).view(np.uint16), after.view(np.uint16))
+    for a, b in ((both.k_pool, one.k_pool), (both.v_pool, one.v_pool)):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
