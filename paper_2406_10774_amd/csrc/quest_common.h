@@ -73,6 +73,7 @@ int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, 
 // launch gives every (sequence, head) to one work-group, which needs none.
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages);
 size_t dense_workspace_bytes(const quest_cache& c);
+size_t row_workspace_bytes(const quest_cache& c);
 // A caller's workspace: the attention's part, then the candidates'.  Both sizes are those of
 // the cache shape, enough for every call on it (a size that followed k_pages would have to
 // follow every border of the split and chunk rules, up and down).
@@ -88,6 +89,9 @@ struct Workspace {
 };
 int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
                         float* lse, void* workspace, size_t workspace_bytes, hipStream_t s);
+// Attention over every page in splits of the page-table row.
+int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
+                      float* lse, void* workspace, size_t workspace_bytes, hipStream_t s);
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
                          size_t workspace_bytes, hipStream_t s);

@@ -1,7 +1,7 @@
 // Sparse paged decode attention (Figure 5 stage 2 / Section 3.4 of arXiv
 // 2406.10774): ordinary softmax attention of one query per (sequence, head)
 // over the tokens of the selected pages only.  Attention over every page is
-// quest_dense.hip.
+// quest_dense.hip, with rows of few tokens and little work done here: their list is the row.
 //
 // Split-K flash-decoding.  One work-group per (sequence, head, split); each work-group of
 // four waves owns a contiguous slice of the head's page list, its waves take
@@ -45,7 +45,7 @@ constexpr int kSelWaves = 8;
 constexpr int kSelListCap = 2048;
 
 struct DecodeArgs : AttnArgs {
-  const int32_t* topk_idx;  // the page list [B][kv heads][k_pages] (nullptr: selected inside the launch)
+  const int32_t* topk_idx;  // the page list [B][kv heads][k_pages] (nullptr: selected inside the launch, or every page)
   const float* scores;      // selection inside the launch: scores [B][kv heads][max_pages] ...
   int32_t* topk_out;        // ... the list is also written here [B][kv heads][k_pages] ...
   int32_t* k_eff;           // ... and K_b here (nullable)
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
           if (kCand && l >= 0) p = pt[l];
         }
       } else {
-        if (pos < end) l = a.topk_idx[((size_t)b * a.kv_heads + hk) * a.k_pages + pos];
+        if (pos < end) l = a.topk_idx ? a.topk_idx[((size_t)b * a.kv_heads + hk) * a.k_pages + pos] : pos;
         if (l >= 0 && l < a.max_pages) p = pt[l];
       }
       if (l >= num_pages) l = -1;
@@ -302,13 +302,29 @@ long most_splits(const quest_cache& c, int list_len) {
   const long items = (long)c.batch * kv_heads(c) * attention_subs(c);  // work-groups per split
   return std::min(list_splits(items, (long)list_len * c.page_size), std::min<long>(list_len, kMaxTeamSize));
 }
-SplitPlan plan_splits(const quest_cache& c, int k_pages) {
+SplitPlan split_list(int list_len, long splits) {
   SplitPlan p;
-  p.list_len = std::min(k_pages, c.max_pages_per_seq);
-  const long splits = most_splits(c, p.list_len);
+  p.list_len = list_len;
   p.per_split = (int)((p.list_len + splits - 1) / splits);
   p.splits = (p.list_len + p.per_split - 1) / p.per_split;  // no empty split
   return p;
+}
+SplitPlan plan_splits(const quest_cache& c, int k_pages) {
+  const int list_len = std::min(k_pages, c.max_pages_per_seq);
+  return split_list(list_len, most_splits(c, list_len));
+}
+// Every page of a row: the same rule, with two work-groups per compute unit where a head's pages
+// of 8 tokens leave a wave half the bytes in flight (3 sequences of 400 to 1200 tokens, 32 heads:
+// 14.4 us with 2 splits, 12.3 with 5; 4 of 3000 to 6000 tokens 53.0 with 2, 50.1 with 4), and past
+// eight splits as many eights of them as fit, which is how they are merged, up to 24 (12 heads of
+// 6000 tokens: 11.1 us with 16 splits, 12.7 with 24; 32 query / 8 KV heads of 32000: 26.7 with 24, 27.5
+// with 32).
+SplitPlan plan_rows(const quest_cache& c) {
+  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);
+  const int per_unit = c.page_size == 8 && group_size(c) == 1 ? 2 : 1;
+  long splits = list_splits((items + per_unit - 1) / per_unit, (long)c.max_pages_per_seq * c.page_size);
+  if (splits > 8) splits = std::min(splits - splits % 8, 24l);
+  return split_list(c.max_pages_per_seq, std::min<long>(splits, c.max_pages_per_seq));
 }
 // One arrival counter per (sequence, head), each in a 256-byte slot of its own.
 size_t counter_bytes(const quest_cache& c) {
@@ -329,6 +345,11 @@ size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
   return split_bytes(c, plan_splits(c, k_pages).splits);
 }
 
+// One split needs none, but every dense call of a cache shape asks for the counters.
+size_t row_workspace_bytes(const quest_cache& c) {
+  return std::max(split_bytes(c, plan_rows(c).splits), counter_bytes(c));
+}
+
 // most_splits of the longest list there is: no shorter one has more.
 size_t attention_workspace_bytes(const quest_cache& c) {
   return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, c.max_pages_per_seq)));
@@ -338,8 +359,8 @@ namespace {
 // scores != nullptr: select inside the launch (topk_out, k_eff receive the list and K_b), or
 // among the candidates if there are some; the caller has checked that it can.
 int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, const float* scores,
-                  const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale, void* out,
-                  int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
+                  const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, SplitPlan p, float sm_scale,
+                  void* out, int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
                   hipStream_t s) {
   const bool select = scores != nullptr || cand != nullptr;
   DecodeArgs a;
@@ -353,8 +374,7 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.k_eff = k_eff;
   a.policy = c.flags;
   a.k_pages = k_pages;
-  SplitPlan p = plan_splits(c, k_pages);
-  if (p.splits > 1 && workspace_bytes < decode_workspace_bytes(c, k_pages)) p.splits = 1, p.per_split = p.list_len;
+  if (workspace_bytes < split_bytes(c, p.splits)) p = split_list(p.list_len, 1);
   a.splits = p.splits;
   a.list_len = p.list_len;
   a.per_split = p.per_split;
@@ -363,9 +383,10 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.part_acc = workspace ? (float*)((char*)workspace + counter_bytes(c)) : nullptr;
   a.part_ml = a.part_acc ? a.part_acc + n_part * kHeadDim : nullptr;
   const bool group = a.group > 1;
-  const long items8 = ((long)c.batch * a.kv_heads * a.subs + 7) / 8;
+  const long items = (long)c.batch * a.kv_heads * a.subs, items8 = (items + 7) / 8;
   const long heads8 = ((long)c.batch * c.num_heads + 7) / 8;
-  if (heads8 > 65535) {  // items8 <= heads8
+  const bool rows = !select && topk_idx == nullptr;  // (launch_dense_decode has a limit of its own)
+  if (heads8 > 65535 && !rows) {                     // items8 <= heads8
     set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", heads8 * 8);
     return QUEST_ERR_SHAPE;
   }
@@ -396,7 +417,14 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     set_error("quest_select_decode: internal: no selecting kernel for rows of %d scores", a.row_len);
     return QUEST_ERR_SHAPE;
   }
-  QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0, false);
+  // Whole rows of a group, one work-group per compute unit: eight waves (32 query / 8 KV heads of
+  // 8000 tokens 13.2 us, 15.1 with four; several per unit: 128 sequences of 64 tokens 18.6 and 12.9).
+  if (rows && group && items <= kComputeUnits) {
+    if (c.page_size == 8) QUEST_LAUNCH(2, true, 8, 0, false);
+    else QUEST_LAUNCH(4, true, 8, 0, false);
+  } else {
+    QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0, false);
+  }
 #undef QUEST_LAUNCH_FOR_CACHE
 #undef QUEST_LAUNCH
   return check_launch("quest_sparse_decode");
@@ -406,7 +434,13 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
                          size_t workspace_bytes, hipStream_t s) {
-  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, nullptr, k_pages, sm_scale, out, out_is_fp16,
+  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, nullptr, k_pages, plan_splits(c, k_pages), sm_scale,
+                       out, out_is_fp16, lse, workspace, workspace_bytes, s);
+}
+
+int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
+                      float* lse, void* workspace, size_t workspace_bytes, hipStream_t s) {
+  return launch_decode(c, q, nullptr, nullptr, nullptr, nullptr, nullptr, 0, plan_rows(c), sm_scale, out, out_is_fp16,
                        lse, workspace, workspace_bytes, s);
 }
 
@@ -451,15 +485,15 @@ int launch_select_decode(const quest_cache& c, const void* q, const float* score
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, const Workspace& w, hipStream_t s) {
   if (select_decode_supported(c, k_pages))
-    return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, sm_scale, out,
-                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
+    return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, plan_splits(c, k_pages), sm_scale,
+                         out, out_is_fp16, lse, w.attention, w.attention_bytes, s);
   int r;
   if (const int chunk = chunk_to_select_from(c, k_pages, w.selection_bytes)) {
     Candidates cand;
     r = launch_topk_chunks(c, scores, k_pages, chunk, w.selection, &cand, s);
     if (r != QUEST_OK) return r;
-    return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, sm_scale, out,
-                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
+    return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, plan_splits(c, k_pages), sm_scale,
+                         out, out_is_fp16, lse, w.attention, w.attention_bytes, s);
   }
   const size_t two_stages = topk_scratch_bytes(c, k_pages);
   r = two_stages > 0 && two_stages <= w.selection_bytes

@@ -2,11 +2,12 @@
 // against (Section 3.1 of arXiv 2406.10774), and what a model runs in the layers it does
 // not sparsify.
 //
-// The pages of all sequences and heads are one line of work, cut into equal shares, one
+// Rows of few tokens and little work: splits of each row (quest_decode.hip; equal_shares below).
+// Else the pages of all sequences and heads are one line of work, cut into equal shares, one
 // per work-group and at most one work-group per compute unit: sequences of any lengths keep
-// every unit busy to the end.  (Splits of a fixed number of pages per head left the shorter
-// sequences' units idle: 4 ragged sequences of 5k to 32k tokens, 32 query / 8 KV heads, 70
-// us against 55 us.)  Items along the line are (sequence, block of heads); a share that covers an
+// every unit busy to the end.  (Splits of a fixed number of pages per head leave the shorter
+// sequences' units idle: 8 sequences of 1000 to 20000 tokens, 32 heads, 245 us against 208; 5 of
+// 300 to 24000 190 against 157.)  Items along the line are (sequence, block of heads); a share that covers an
 // item in part leaves a partial result, and the last of the item's shares to finish merges
 // them (quest_team.h).
 //
@@ -31,16 +32,16 @@ namespace {
 
 constexpr int waves_of(bool group) { return group ? 8 : 4; }
 // Work-groups at most, of the 256 compute units: the memory system moves more with fewer
-// streams as long as they can carry it (2 layers of 32 heads, 32k tokens: 187 us with 128
-// work-groups, 172.7 with 192, 174.5 with 224, 175.7 with 256, 189 with 512; 32 query / 8 KV
-// heads, 4 ragged sequences: 133, 114.0, 113.3, 115.1, 127).
-// Pages of 8 tokens leave a wave half the bytes in flight (one sequence of 42k tokens, 32 heads:
-// 113.7 us with 192, 104.9 with 256, 115.9 with 384).
+// streams as long as they can carry it (one sequence of 64k tokens, 32 heads: 162 us with 192
+// work-groups, 168 with 224, 167 with 256; 8 of 1000 to 20000 tokens 208, 210, 214; one of 32k 85.6,
+// 88.5, 88.5).  Groups have more to do per page: 32 sequences of 500 to 8000 tokens, 32 query / 8 KV
+// heads, 108, 99 and 101; 8 of 1000 to 30000, 64 / 8 heads, 101, 94 and 95.
+// Pages of 8 tokens leave a wave half the bytes in flight: 2 sequences of 30000 tokens, 32 heads,
+// 162, 152 and 150; 6 of 1000 to 12000 113, 105 and 104.
 int most_shares(const quest_cache& c) { return group_size(c) > 1 ? 224 : c.page_size == 8 ? 256 : 192; }
 
 struct DenseArgs : AttnArgs {
   int shares;  // work-groups; partial results of share w are slots 2w and 2w + 1
-  int cuts;    // parts that every item is cut into, a work-group each; 0: equal shares of the line
 };
 
 // Query heads of one item and of one slot.
@@ -72,43 +73,30 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
 
   // ---- this work-group's share [off, end) of the line, and the sequence it begins in
   const int64_t w = blockIdx.x;
-  int64_t total = 0, shares = 1, off, end;
+  int64_t total = 0;
+  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+    const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
+    total += __builtin_amdgcn_readlane(wave_incl_scan(p, lane), kWave - 1);
+  }
+  total *= blocks;
+  const int64_t shares = total < a.shares ? total : a.shares;  // none is empty
+  if (w >= shares) return;
+  const int64_t begin = w * total / shares, end = (w + 1) * total / shares;
+  int64_t off = begin;
   int64_t base = 0;  // where sequence b begins
   int b = 0;
-  int parts_each = 0;
-  if (a.cuts) {
-    const int item = (int)w / a.cuts, part = (int)w - item * a.cuts;
-    b = item / blocks;
-    const int pages = pages_of(a.seq_lens[b]);
-    parts_each = min(a.cuts, pages);  // none is empty
-    if (part >= parts_each) return;
-    off = end = (int64_t)(item - b * blocks) * pages;
-    off += (int)((int64_t)part * pages / parts_each);
-    end += (int)((int64_t)(part + 1) * pages / parts_each);
-  } else {
-    for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-      const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-      total += __builtin_amdgcn_readlane(wave_incl_scan(p, lane), kWave - 1);
+  for (int b0 = 0; b0 < a.batch; b0 += kWave) {
+    const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
+    const int upto = wave_incl_scan(p, lane);
+    const int64_t after = base + (int64_t)__builtin_amdgcn_readlane(upto, kWave - 1) * blocks;
+    if (off < after) {
+      const int k = __popcll(__ballot(b0 + lane < a.batch && base + (int64_t)upto * blocks <= off));
+      b = b0 + k;
+      base += k > 0 ? (int64_t)__builtin_amdgcn_readlane(upto, k > 0 ? k - 1 : 0) * blocks : 0;
+      break;
     }
-    total *= blocks;
-    shares = total < a.shares ? total : a.shares;  // none is empty
-    if (w >= shares) return;
-    off = w * total / shares;
-    end = (w + 1) * total / shares;
-    for (int b0 = 0; b0 < a.batch; b0 += kWave) {
-      const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-      const int upto = wave_incl_scan(p, lane);
-      const int64_t after = base + (int64_t)__builtin_amdgcn_readlane(upto, kWave - 1) * blocks;
-      if (off < after) {
-        const int k = __popcll(__ballot(b0 + lane < a.batch && base + (int64_t)upto * blocks <= off));
-        b = b0 + k;
-        base += k > 0 ? (int64_t)__builtin_amdgcn_readlane(upto, k > 0 ? k - 1 : 0) * blocks : 0;
-        break;
-      }
-      base = after;
-    }
+    base = after;
   }
-  const int64_t begin = off;
   auto share_of = [&](int64_t at) { return (int)(((at + 1) * shares - 1) / total); };
 
   while (off < end) {
@@ -190,8 +178,8 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
       }
     }
     if (!whole) {
-      const int from = a.cuts ? (int)w / a.cuts * a.cuts : share_of(item_at);
-      const int parts = a.cuts ? parts_each : share_of(item_at + pages - 1) - from + 1;
+      const int from = share_of(item_at);
+      const int parts = share_of(item_at + pages - 1) - from + 1;
       uint32_t* arrivals = reinterpret_cast<uint32_t*>(
           a.counters + ((size_t)b * blocks + block) * kTeamWordStride);
       wait_stores();
@@ -264,34 +252,37 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
 }
 
 // Four adjacent heads per work-group where that leaves an item at most about 32 parts to
-// merge (256 shares over batch * heads / 4 items); fewer heads share a work-group's waves.
+// merge (256 shares over batch * heads / 4 items); fewer heads share a work-group's waves (one
+// sequence of 30000 tokens, 8 heads: 30.1 us by fours, 24.5 one by one).
 bool four_heads(const quest_cache& c) {
   return group_size(c) == 1 && kv_heads(c) % 4 == 0 && (long)c.batch * kv_heads(c) >= 32;
 }
 
-long dense_items(const quest_cache& c) {
-  return (long)c.batch * kv_heads(c) * attention_subs(c) / (four_heads(c) ? 4 : 1);
+// Units of 16 tokens of all heads, of the longest sequences the page table has room for.
+double dense_units(const quest_cache& c) {
+  return (double)c.batch * kv_heads(c) * attention_subs(c) * c.max_pages_per_seq * c.page_size / 16;
 }
 
-// Little work: every item in as many parts, because a share that ends one item and begins the
-// next hands over twice, one after the other (launches of 6 sequences of 900 tokens, 8 heads: 13.0
-// us in equal shares, 10.9 in parts; 8 heads of 3000 tokens 8.9 and 7.7; 4 sequences of 900, 32
-// query / 8 KV heads 16.2 and 11.5).  At
-// most eight units per wave, so that ragged sequences cannot make one part long; two at least.
-int dense_cuts(const quest_cache& c) {
-  const long units = (long)c.max_pages_per_seq * c.page_size / 16 / (four_heads(c) ? 1 : waves_of(group_size(c) > 1));
-  const long cuts = std::max(1l, std::min(256 / dense_items(c), units / 2));
-  return dense_items(c) <= 256 && units <= 8 * cuts ? (int)cuts : 0;
+// Long rows and much work are cut into equal shares; rows of few tokens, or little work, into
+// splits (launch_row_decode): a share finds its place on the line only when it has the
+// lengths, hands over twice if it ends one item and begins the next, and takes item after item
+// where there are many short ones.  us a launch, splits / equal shares: 32 heads of 700 tokens
+// 6.6 / 9.6, of 8000 tokens 24.1 / 26.7, of 16000 tokens (32k units) 43.7 / 45.8, of 32768 tokens (66k)
+// 87.1 / 85.6; 64 sequences of 128 tokens 24.1 / 31.0, 128 of 100 to 1000 tokens, 32 query / 8 KV
+// heads, 53.3 / 83.7, 16 of 1000 to 4000, 32 heads, 109.7 / 105.7, 8 of 1000 to 20000 251 / 209.
+// A few heads of long rows need more parts than the splits of a row are good for: 4 heads of 8000
+// tokens 10.1 / 9.3, 2 of 60000 29.8 / 16.4, 8 query / 2 KV heads of 30000 20.3 / 16.0 (but 2 sequences
+// of 9000 11.9 / 17.1), 8 heads of 8000 10.8 / 11.4.
+bool equal_shares(const quest_cache& c) {
+  const long tokens = (long)c.max_pages_per_seq * c.page_size;
+  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);
+  return (dense_units(c) > 48 * 1024 && tokens > 3072) || (items < 8 && tokens > (group_size(c) > 1 ? 16384 : 6400));
 }
 
 // Work-groups: four units of 16 tokens per wave at least (a part costs about 2 us to hand
-// over and merge), of the longest work the page table has room for.
+// over and merge).
 int dense_shares(const quest_cache& c) {
-  if (const int cuts = dense_cuts(c)) return (int)dense_items(c) * cuts;
-  const bool group = group_size(c) > 1;
-  const double heads = (double)c.batch * kv_heads(c) * attention_subs(c);
-  const double units = heads * c.max_pages_per_seq * c.page_size / 16;
-  const double shares = std::min<double>(units / (4 * waves_of(group)), most_shares(c));
+  const double shares = std::min<double>(dense_units(c) / (4 * waves_of(group_size(c) > 1)), most_shares(c));
   return std::max(16, (int)((shares + 15) / 16) * 16);
 }
 
@@ -304,25 +295,28 @@ size_t counter_bytes(const quest_cache& c) {
 }  // namespace
 
 size_t dense_workspace_bytes(const quest_cache& c) {
+  if (!equal_shares(c)) return row_workspace_bytes(c);
   return counter_bytes(c) + (size_t)dense_shares(c) * 2 * heads_per_slot(c) * (kHeadDim + 2) * sizeof(float);
 }
 
 int launch_dense_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
                         float* lse, void* workspace, size_t workspace_bytes, hipStream_t s) {
+  // The grid of heads one by one, by twos or by fours, whichever form runs.
+  const int group = group_size(c), by = group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
+  const long heads8 = ((long)c.batch * c.num_heads / by + 7) / 8;
+  if (heads8 > 65535) {
+    set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", heads8 * 8 * by);
+    return QUEST_ERR_SHAPE;
+  }
+  if (!equal_shares(c) || workspace_bytes < dense_workspace_bytes(c))
+    return launch_row_decode(c, q, sm_scale, out, out_is_fp16, lse, workspace, workspace_bytes, s);
   DenseArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   const int block = four_heads(c) ? 4 : 1;
-  const long items = dense_items(c);
-  if (items > 8 * 65535l) {
-    set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", items * block);
-    return QUEST_ERR_SHAPE;
-  }
-  const bool whole = workspace_bytes < dense_workspace_bytes(c);  // no workspace: every work-group takes one item
-  a.cuts = whole ? 1 : dense_cuts(c);
-  a.shares = whole ? (int)items : dense_shares(c);
+  a.shares = dense_shares(c);
   a.counters = (uint64_t*)workspace;
-  a.part_acc = whole ? nullptr : (float*)((char*)workspace + counter_bytes(c));
-  a.part_ml = whole ? nullptr : a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
+  a.part_acc = (float*)((char*)workspace + counter_bytes(c));
+  a.part_ml = a.part_acc + (size_t)a.shares * 2 * heads_per_slot(c) * kHeadDim;
   const dim3 grid((unsigned)a.shares);
 #define QUEST_DENSE_LAUNCH(L, G, B)                                                              \
   hipLaunchKernelGGL((dense_kernel<L, G, B, waves_of(G)>), grid, dim3(waves_of(G) * kWave), \

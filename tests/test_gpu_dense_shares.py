@@ -1,8 +1,11 @@
-"""Attention over every page: the line of pages of all sequences and heads that the launch cuts
-into equal shares, where the cutting can go wrong: fewer pages than shares, shares that hold
-many whole items, items over many shares, more than 64 sequences (one lane each while the
-line is measured), little work in parts of each item, heads by fours and one by one, groups that need two work-groups.  Against
-the oracle; a second call on the same workspace gives the same bits."""
+"""Attention over every page in both of its forms, where the cutting can go wrong.  Splits of the
+page-table row (rows of few tokens, or little work): fewer pages than splits, sequences that
+end in front of a split, groups that need two work-groups, more sequences than compute units.
+Equal shares of the line of all pages (long rows and much work; what counts is the room in the
+page table, so the sequences here are short): fewer pages than shares, shares that hold many
+whole items, items over many shares, more than 64 sequences (one lane each while the line is
+measured), heads by fours and one by one, groups, pages of 8 tokens.  Against the oracle; a
+second call on the same workspace gives the same bits."""
 import math
 
 import numpy as np
@@ -22,8 +25,35 @@ RAGGED70 = tuple(1 + (i * 37) % 90 for i in range(70))
     (4, 1, 16, RAGGED70), (3, 1, 16, (5003, 1, 17)), (1, 1, 16, (9001,)), (1, 1, 32, RAGGED70 * 2),
     (32, 1, 16, (700, 5)), (8, 1, 32, (903, 1, 32, 738)), (8, 4, 16, (900, 17, 500)),
     (8, 1, 8, (260, 3, 4100, 900)), (2, 9, 16, (2100, 5, 333)), (1, 4, 8, RAGGED70), (2, 4, 64, (6007,)),
+    (12, 1, 16, (5999,)), (4, 3, 8, RAGGED70 * 2), (2, 1, 64, (4097, 1)),
 ])
 def test_dense_shares(kv_heads, group, S, lens):
+    check(kv_heads, group, S, lens, 0)
+
+
+def equal_shares(batch, kv_heads, group, S, pages):
+    """The rule that decides: more than 48k units of 16 tokens, of rows of more than 3072 tokens; fewer
+    than 8 heads (or groups) of long rows."""
+    items = batch * kv_heads * -(-group // 8)
+    return (items * pages * S / 16 > 48 * 1024 and pages * S > 3072) or \
+        (items < 8 and pages * S > (16384 if group > 1 else 6400))
+
+
+@pytest.mark.parametrize("kv_heads,group,S,lens,room", [
+    (32, 1, 16, (1,), 2000), (32, 1, 16, (3001,), 2000), (32, 1, 8, (1999, 16), 2000), (36, 1, 64, (700,), 400),
+    (4, 1, 16, RAGGED70, 300), (3, 1, 16, (5003, 1, 17), 6000), (1, 1, 16, (9001,), 50000),
+    (1, 1, 32, RAGGED70 * 2, 250), (33, 1, 8, (700, 5), 3000), (8, 1, 32, (903, 1, 32, 738), 1000),
+    (8, 4, 16, (900, 17, 500), 3000), (8, 1, 8, (260, 3, 4100, 900), 4000), (2, 9, 16, (2100, 5, 333), 6000),
+    (1, 4, 8, RAGGED70, 1700), (2, 4, 64, (6007,), 7000), (8, 8, 8, (1, 2000, 9, 700), 4000),
+    (12, 2, 32, tuple(1 + i * 13 for i in range(66)), 130), (8, 4, 16, (7000, 9000), 3500),
+    (1, 1, 8, (7001, 3), 900), (2, 1, 64, (6500, 64), 110), (1, 5, 16, (17000, 20), 1100),
+])
+def test_equal_shares(kv_heads, group, S, lens, room):
+    assert equal_shares(len(lens), kv_heads, group, S, room)
+    check(kv_heads, group, S, lens, room)
+
+
+def check(kv_heads, group, S, lens, room):
     import torch
     from gpu_util import Layer
     from paper_2406_10774_amd import binding as Q
@@ -31,6 +61,7 @@ def test_dense_shares(kv_heads, group, S, lens):
                        page_size=S, decode_steps=0)
     table, N = synth.make_page_table(w, permute=True)
     k_pool, v_pool, _ = synth.fill_pools(w, table, N)
+    table = np.pad(table, ((0, 0), (0, max(0, room - table.shape[1]))))
     k_pool *= np.float16(0.25)
     rng = np.random.default_rng(len(lens))
     q = rng.standard_normal((w.batch, kv_heads * group, 128)).astype(np.float16)

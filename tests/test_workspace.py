@@ -88,3 +88,24 @@ def test_calls_without_a_workspace(kind, batch, kv_heads, group, page_size, page
     c = make_cache(batch, kv_heads, group, page_size, pages)
     for nbytes in (0, 64):
         assert call(kind, c, k_pages, nbytes) == (HIP if accepted else WORKSPACE)
+
+
+@pytest.mark.parametrize("batch,kv_heads,group,page_size,pages,counters,heads,candidates", [
+    # (heads: partial results of one query head, of max, denominator and 128 channels each)
+    (1, 32, 1, 16, 2048, 32, 192 * 2 * 4, 0),           # equal shares, two slots of four heads each
+    (1, 36, 1, 64, 800, 36, 192 * 2 * 4, 0),
+    (1, 33, 1, 16, 2048, 33, 192 * 2, 0),               # heads one by one
+    (4, 8, 4, 16, 2048, 128, 224 * 2 * 8, 0),           # groups, slots of eight heads
+    (2, 4, 12, 16, 6144, 96, 224 * 2 * 8, 2 * 4 * 3072),
+    (1, 32, 1, 8, 4096, 32, 256 * 2 * 4, 0),            # pages of 8 tokens
+    (1, 32, 1, 16, 100, 32, 32 * 8, 0),                 # little work: eight splits of a row
+    (64, 32, 1, 16, 8, 2048, 0, 0),                     # one split
+    (3, 32, 1, 8, 150, 96, 96 * 5, 0),                  # pages of 8 tokens: two work-groups per unit
+    (1, 1, 1, 16, 16, 1, 0, 0), (1, 8, 4, 16, 500, 32, 32 * 31, 0),
+    (1, 32, 1, 16, 16384, 32, 192 * 2 * 4, 32 * 8192),  # very long rows: candidates behind
+])
+def test_size_is_that_of_the_layout(batch, kv_heads, group, page_size, pages, counters, heads, candidates):
+    """Counters, then partial results of dense attention or of the most splits of a list, then
+    candidates, as the kernels lay them out."""
+    c = make_cache(batch, kv_heads, group, page_size, pages)
+    assert size_of(c, 0) == counters * 256 + heads * 130 * 4 + candidates * 8
