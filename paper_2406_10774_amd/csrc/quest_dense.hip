@@ -272,11 +272,12 @@ double dense_units(const quest_cache& c) {
 // heads, 53.3 / 83.7, 16 of 1000 to 4000, 32 heads, 109.7 / 105.7, 8 of 1000 to 20000 251 / 209.
 // A few heads of long rows need more parts than the splits of a row are good for: 4 heads of 8000
 // tokens 10.1 / 9.3, 2 of 60000 29.8 / 16.4, 8 query / 2 KV heads of 30000 20.3 / 16.0 (but 2 sequences
-// of 9000 11.9 / 17.1), 8 heads of 8000 10.8 / 11.4.
+// of 9000 11.9 / 17.1), 8 heads of 8000 10.8 / 11.4.  More than 128 items have one split each: 4 sequences
+// of 1242 to 4314 tokens, 40 heads, 51.4 / 42.9, but 5 of 2000, 32 heads, 27.7 / 31.5.
 bool equal_shares(const quest_cache& c) {
   const long tokens = (long)c.max_pages_per_seq * c.page_size;
   const long items = (long)c.batch * kv_heads(c) * attention_subs(c);
-  return (dense_units(c) > 48 * 1024 && tokens > 3072) || (items < 8 && tokens > (group_size(c) > 1 ? 16384 : 6400));
+  return (tokens > 3072 && (dense_units(c) > 48 * 1024 || items > 128)) || (items < 8 && tokens > (group_size(c) > 1 ? 16384 : 6400));
 }
 
 // Work-groups: four units of 16 tokens per wave at least (a part costs about 2 us to hand
