@@ -23,7 +23,8 @@
 // key and value; a work-group serves them all from one load on the matrix cores
 // (GroupState in quest_decode_core.h).  32 query / 8 KV heads, 4 sequences of up to 32k
 // tokens: a step takes 23 us instead of 40 us (2048-token budget; every query head loaded
-// its pages and selected its list alone).
+// its pages and selected its list alone).  Short lists of few heads are the exception: see
+// heads_apart.
 #include "quest_common.h"
 #include "quest_decode_core.h"
 #include "quest_team.h"
@@ -65,6 +66,7 @@ struct DecodeArgs : AttnArgs {
 // the splits run; the split that finishes last merges them, without a second launch.
 // kLoads, kGroup: see HeadState; a work-group serves one query head, or up to kGroupHeads
 // of a KV head, so that a page is loaded (and a list selected) once for all of them.
+// a.subs: work-groups per KV head and split that this takes.
 //
 // kSelItems > 0: the page list does not exist yet.  Every work-group first selects the
 // pages of its head itself from the scores (the same selection as quest_topk, kSelItems
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   const int slot = blockIdx.x & 7;
   const int split = blockIdx.x >> 3;
   const int item = blockIdx.y * 8 + slot;  // (sequence, KV head, query heads of its group)
-  const int subs = kGroup ? a.subs : 1;    // work-groups per KV head and split
+  const int subs = a.subs;
   const int per_seq = a.kv_heads * subs;
   if (item >= a.batch * per_seq) return;
   const int b = a.batch == 1 ? 0 : item / per_seq;
@@ -298,8 +300,8 @@ long list_splits(long items, long tokens) {
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
   return std::min(kComputeUnits / items, useful);
 }
-long most_splits(const quest_cache& c, int list_len) {
-  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);  // work-groups per split
+// items: work-groups per split.
+long most_splits(const quest_cache& c, long items, int list_len) {
   return std::min(list_splits(items, (long)list_len * c.page_size), std::min<long>(list_len, kMaxTeamSize));
 }
 SplitPlan split_list(int list_len, long splits) {
@@ -309,9 +311,31 @@ SplitPlan split_list(int list_len, long splits) {
   p.splits = (p.list_len + p.per_split - 1) / p.per_split;  // no empty split
   return p;
 }
+long group_items(const quest_cache& c) { return (long)c.batch * kv_heads(c) * attention_subs(c); }
 SplitPlan plan_splits(const quest_cache& c, int k_pages) {
   const int list_len = std::min(k_pages, c.max_pages_per_seq);
-  return split_list(list_len, most_splits(c, list_len));
+  return split_list(list_len, most_splits(c, group_items(c), list_len));
+}
+// Query heads of a group in work-groups of their own, on the vector unit: their pages then come
+// from memory once and from the caches for the others, and a launch takes about 1 us less to
+// get going and to finish (no keys through LDS, one head's outputs to merge), as long as that
+// is little to load.  us a launch over a given list, apart / together, query heads / KV heads: 32/8 of
+// 512 tokens 6.3 / 7.6, 1024 7.4 / 8.3, 2048 10.6 / 9.7; 16/8 of 2048 8.0 / 8.1, 4096 10.3 / 9.5; 4
+// sequences of 32/8, 256 6.9 / 7.1, 512 10.6 / 8.4; 8/1 of 4096 9.5 / 14.0; 32/4 of 2048 11.3 / 13.0.
+// Where the launch selects its list, the selection is repeated for more work-groups: 16/8 of 1024
+// tokens 11.3 / 11.8 (a step), 32/8 of 512 11.2 / 11.8, 1024 12.5 / 12.4, 64/8 of 256 12.4 / 11.9, 32/4 of
+// 1024 13.5 / 13.9, 8/1 of 4096 15.9 / 17.4.
+bool heads_apart(const quest_cache& c, int k_pages, bool select) {
+  if (group_size(c) == 1) return false;
+  const int64_t tokens = (int64_t)std::min(k_pages, c.max_pages_per_seq) * c.page_size;
+  const int64_t heads = (int64_t)c.batch * c.num_heads, kv = (int64_t)c.batch * kv_heads(c);
+  const bool few = group_items(c) <= 4;
+  return select ? (heads - kv) * tokens <= (few ? 32 : 12) * 1024 : heads * tokens <= (few ? 72 : 44) * 1024;
+}
+// No more splits than plan_splits has: less work-groups are left for each item.
+SplitPlan plan_apart(const quest_cache& c, int k_pages) {
+  const int list_len = std::min(k_pages, c.max_pages_per_seq);
+  return split_list(list_len, most_splits(c, (long)c.batch * c.num_heads, list_len));
 }
 // Every page of a row: the same rule, with two work-groups per compute unit where a head's pages
 // of 8 tokens leave a wave half the bytes in flight (3 sequences of 400 to 1200 tokens, 32 heads:
@@ -320,7 +344,7 @@ SplitPlan plan_splits(const quest_cache& c, int k_pages) {
 // 6000 tokens: 11.1 us with 16 splits, 12.7 with 24; 32 query / 8 KV heads of 32000: 26.7 with 24, 27.5
 // with 32).
 SplitPlan plan_rows(const quest_cache& c) {
-  const long items = (long)c.batch * kv_heads(c) * attention_subs(c);
+  const long items = group_items(c);
   const int per_unit = c.page_size == 8 && group_size(c) == 1 ? 2 : 1;
   long splits = list_splits((items + per_unit - 1) / per_unit, (long)c.max_pages_per_seq * c.page_size);
   if (splits > 8) splits = std::min(splits - splits % 8, 24l);
@@ -352,17 +376,20 @@ size_t row_workspace_bytes(const quest_cache& c) {
 
 // most_splits of the longest list there is: no shorter one has more.
 size_t attention_workspace_bytes(const quest_cache& c) {
-  return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, c.max_pages_per_seq)));
+  return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, group_items(c), c.max_pages_per_seq)));
 }
 
 namespace {
 // scores != nullptr: select inside the launch (topk_out, k_eff receive the list and K_b), or
 // among the candidates if there are some; the caller has checked that it can.
 int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, const float* scores,
-                  const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, SplitPlan p, float sm_scale,
+                  const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale,
                   void* out, int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
                   hipStream_t s) {
   const bool select = scores != nullptr || cand != nullptr;
+  const bool rows = !select && topk_idx == nullptr;  // every page of a row
+  const bool apart = !rows && heads_apart(c, k_pages, select);
+  SplitPlan p = rows ? plan_rows(c) : apart ? plan_apart(c, k_pages) : plan_splits(c, k_pages);
   DecodeArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   a.topk_idx = topk_idx;
@@ -382,11 +409,11 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.counters = (uint64_t*)workspace;
   a.part_acc = workspace ? (float*)((char*)workspace + counter_bytes(c)) : nullptr;
   a.part_ml = a.part_acc ? a.part_acc + n_part * kHeadDim : nullptr;
-  const bool group = a.group > 1;
+  const bool group = a.group > 1 && !apart;
+  if (apart) a.subs = a.group;
   const long items = (long)c.batch * a.kv_heads * a.subs, items8 = (items + 7) / 8;
   const long heads8 = ((long)c.batch * c.num_heads + 7) / 8;
-  const bool rows = !select && topk_idx == nullptr;  // (launch_dense_decode has a limit of its own)
-  if (heads8 > 65535 && !rows) {                     // items8 <= heads8
+  if (heads8 > 65535 && !rows) {  // items8 <= heads8 (launch_dense_decode has a limit of its own)
     set_error("quest_sparse_decode: batch * heads = %ld exceeds the launch limit", heads8 * 8);
     return QUEST_ERR_SHAPE;
   }
@@ -434,14 +461,14 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
 int launch_sparse_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, int k_pages,
                          float sm_scale, void* out, int out_is_fp16, float* lse, void* workspace,
                          size_t workspace_bytes, hipStream_t s) {
-  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, nullptr, k_pages, plan_splits(c, k_pages), sm_scale,
-                       out, out_is_fp16, lse, workspace, workspace_bytes, s);
+  return launch_decode(c, q, topk_idx, nullptr, nullptr, nullptr, nullptr, k_pages, sm_scale, out, out_is_fp16,
+                       lse, workspace, workspace_bytes, s);
 }
 
 int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void* out, int out_is_fp16,
                       float* lse, void* workspace, size_t workspace_bytes, hipStream_t s) {
-  return launch_decode(c, q, nullptr, nullptr, nullptr, nullptr, nullptr, 0, plan_rows(c), sm_scale, out, out_is_fp16,
-                       lse, workspace, workspace_bytes, s);
+  return launch_decode(c, q, nullptr, nullptr, nullptr, nullptr, nullptr, 0, sm_scale, out, out_is_fp16, lse,
+                       workspace, workspace_bytes, s);
 }
 
 // Selection and attention in one launch: while a row of scores fits the in-register
@@ -485,15 +512,15 @@ int launch_select_decode(const quest_cache& c, const void* q, const float* score
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, const Workspace& w, hipStream_t s) {
   if (select_decode_supported(c, k_pages))
-    return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, plan_splits(c, k_pages), sm_scale,
-                         out, out_is_fp16, lse, w.attention, w.attention_bytes, s);
+    return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, sm_scale, out,
+                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
   int r;
   if (const int chunk = chunk_to_select_from(c, k_pages, w.selection_bytes)) {
     Candidates cand;
     r = launch_topk_chunks(c, scores, k_pages, chunk, w.selection, &cand, s);
     if (r != QUEST_OK) return r;
-    return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, plan_splits(c, k_pages), sm_scale,
-                         out, out_is_fp16, lse, w.attention, w.attention_bytes, s);
+    return launch_decode(c, q, nullptr, nullptr, &cand, topk_idx, k_eff, k_pages, sm_scale, out,
+                         out_is_fp16, lse, w.attention, w.attention_bytes, s);
   }
   const size_t two_stages = topk_scratch_bytes(c, k_pages);
   r = two_stages > 0 && two_stages <= w.selection_bytes

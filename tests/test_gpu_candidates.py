@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("max_pages,S,group,k_pages,policy", [
     (5120, 16, 1, 64, 0), (5121, 16, 1, 64, 12), (6144, 8, 4, 300, 4), (8193, 16, 1, 256, 12), (8193, 16, 1, 1, 8),
     (8200, 8, 1, 512, 0), (16384, 16, 4, 256, 12), (32769, 16, 1, 256, 0), (32769, 8, 1, 500, 4), (12289, 64, 9, 17, 12),
+    (6144, 16, 4, 10, 12), (8193, 8, 9, 16, 0),           # groups whose heads attend one by one
 ])
 def test_candidates(max_pages, S, group, k_pages, policy):
     import torch

@@ -28,9 +28,25 @@ def bound(k_pool, v_pool, q, table, lens, idx, scale):
 @pytest.mark.parametrize("kv_heads,group", [(1, 2), (3, 3), (2, 5), (2, 8), (1, 9), (2, 16)])
 @pytest.mark.parametrize("S", [8, 16, 64])
 def test_unit_edges(kv_heads, group, S):
+    check_edges(kv_heads, group, S, edge_lengths(S), 7, (1, 7, 64))
+
+
+def edge_lengths(S):
+    return (1, 3, 7, 8, 9, 15, 16, 17, 31, 33, 64, 65, S * 37 + 5, S * 40)
+
+
+@pytest.mark.parametrize("kv_heads,group", [(1, 2), (3, 3), (2, 5), (2, 8), (1, 9), (2, 16)])
+@pytest.mark.parametrize("S", [8, 16, 64])
+def test_unit_edges_of_longer_lists(kv_heads, group, S):
+    """The same for lists that the heads of a group attend over together: short lists of few heads
+    are attended over head by head (at most 72k tokens of all heads)."""
+    repeat = 1 + 72 * 1024 // (14 * kv_heads * group * 40 * S)
+    check_edges(kv_heads, group, S, edge_lengths(S) * repeat, 40, (39, 64))
+
+
+def check_edges(kv_heads, group, S, lens, pages, select):
     from gpu_util import Layer
-    lens = (1, 3, 7, 8, 9, 15, 16, 17, 31, 33, 64, 65, S * 37 + 5, S * 40)
-    w = synth.Workload(700 + group, f"group-S{S}", len(lens), kv_heads, lens, token_budget=S * 7,
+    w = synth.Workload(700 + group, f"group-S{S}", len(lens), kv_heads, lens, token_budget=S * pages,
                        planted_per_head=2, page_size=S, decode_steps=0)
     table, N = synth.make_page_table(w, permute=True)
     k_pool, v_pool, _ = synth.fill_pools(w, table, N)          # stale slots hold NaN
@@ -66,17 +82,17 @@ def test_unit_edges(kv_heads, group, S):
         clean[b][clean[b] >= w.pages_of(b)] = -1
     got, lse = layer.decode(q, holes, K)
     check(got, lse, clean, "list")
-    for k_pages in (1, K, 64):
+    for k_pages in select:
         idx, keff, got, lse = layer.select_decode(q, k_pages, scores=sc.astype(np.float32))
         check(got, lse, idx, f"select {k_pages}")
 
 
-@pytest.mark.parametrize("group,S", [(1, 16), (4, 16), (4, 8), (9, 64)])
-def test_infinite_and_nan_values(group, S):
+@pytest.mark.parametrize("group,S,repeat", [(1, 16, 1), (4, 16, 1), (4, 8, 1), (9, 64, 1), (4, 16, 16), (4, 8, 16), (9, 64, 2)])
+def test_infinite_and_nan_values(group, S, repeat):
     """An infinite value is infinite in the output wherever its weight is not zero, a NaN is NaN;
     every other channel and head comes out as without them."""
     from gpu_util import Layer
-    lens = (S * 9 + 3, S * 3, 200)
+    lens = (S * 9 + 3, S * 3, 200) * repeat                    # repeated: the heads of a group together
     kv_heads = 2
     w = synth.Workload(760 + group, "non-finite", len(lens), kv_heads, lens, token_budget=S * 64, planted_per_head=0,
                        page_size=S, decode_steps=0)

@@ -56,7 +56,7 @@ def test_as_close_as_heads_of_their_own():
             (4, 8, 16, (20000,)), (8, 2, 64, (1053, 700, 900, 300)), (2, 4, 8, (4000, 9000)), (3, 9, 32, (16000, 5)),
             (8, 4, 16, (6000, 2500)), (8, 8, 16, (300,)), (2, 16, 16, (5000,)), (8, 4, 8, (1000, 400, 70)),
             (5, 3, 16, (9000,)), (4, 4, 32, (3000, 2000, 1000))):
-        w = synth.Workload(790 + group, "precision", len(lens), kv_heads, lens, token_budget=S * 32, planted_per_head=16,
+        w = synth.Workload(790 + group, "precision", len(lens), kv_heads, lens, token_budget=S * 256, planted_per_head=16,
                            page_size=S, decode_steps=0)
         table, N = synth.make_page_table(w, permute=True)
         k_pool, v_pool, _ = synth.fill_pools(w, table, N)
