@@ -38,7 +38,7 @@ namespace quest {
 
 namespace {
 
-constexpr long kComputeUnits = 256;  // MI355X; only used to decide how finely to split
+constexpr long kComputeUnits = 256, kDies = 8;  // MI355X; only used to decide how finely to split
 constexpr int kDecWaves = 4;
 // With the selection done in the same launch (see decode_split_kernel): 8 waves, the size
 // the selection is fastest at, and room in LDS for a page list of this many entries.
@@ -289,6 +289,10 @@ struct SplitPlan {
 // themselves leave a second round that is nearly empty are three splits of each better: 9
 // sequences of 32 heads 64.5 us with 1, 57.7 with 3 (10 sequences: 65.7 and 60.3; 12: 69.4
 // and 72.5; at 512 tokens 1 is better everywhere).
+// All splits of an item run on one die (see decode_split_kernel), so that is counted per die: its
+// 32 units for the items that fall to it.  15 heads of one KV head, a list of 6024 tokens: 12.6 us
+// with 16 splits, 15.3 with 17; attention over whole rows of 20000 tokens, 10 heads, 21.5 us with
+// 16, 26.8 with 24; 5 sequences of 5000 to 9000, 10 heads, 32.5 with 4, 45.5 with 5.
 // Short lists: a split merges in about 2.3 us, so 256 tokens stay whole (7.5 us against
 // 7.9 us), 512 and 1024 tokens are worth 8 splits (8.4 us against 10.1 us), more tokens
 // 16 (8 heads, 4096 tokens: 10.4 us, 12.1 with 8 splits, 11.0 with 32), very long lists a
@@ -298,11 +302,16 @@ long list_splits(long items, long tokens) {
     return items < kComputeUnits * 11 / 8 && tokens >= 1024 ? 3 : 1;
   if (tokens <= 256) return 1;
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
-  return std::min(kComputeUnits / items, useful);
+  return std::min(kComputeUnits / kDies / ((items + kDies - 1) / kDies), useful);
 }
-// items: work-groups per split.
+// items: work-groups per split.  One head's pages of 8 tokens leave a wave half the bytes in flight:
+// splits of half the tokens (2 sequences, 8 heads, 1464 tokens: 7.2 us with 16 splits, 7.6 with 11; 32
+// heads, 256 tokens 5.6 with 8, 6.6 with 1; but 160 tokens 5.4 and 5.2; 4 sequences of 32 heads, 256
+// tokens 7.5 with 2, 7.2 with 1).
 long most_splits(const quest_cache& c, long items, int list_len) {
-  return std::min(list_splits(items, (long)list_len * c.page_size), std::min<long>(list_len, kMaxTeamSize));
+  long tokens = (long)list_len * c.page_size;
+  if (c.page_size == 8 && group_size(c) == 1 && items <= 64 && tokens > 192) tokens *= 2;
+  return std::min(list_splits(items, tokens), std::min<long>(list_len, kMaxTeamSize));
 }
 SplitPlan split_list(int list_len, long splits) {
   SplitPlan p;
@@ -339,15 +348,14 @@ SplitPlan plan_apart(const quest_cache& c, int k_pages) {
 }
 // Every page of a row: the same rule, with two work-groups per compute unit where a head's pages
 // of 8 tokens leave a wave half the bytes in flight (3 sequences of 400 to 1200 tokens, 32 heads:
-// 14.4 us with 2 splits, 12.3 with 5; 4 of 3000 to 6000 tokens 53.0 with 2, 50.1 with 4), and past
-// eight splits as many eights of them as fit, which is how they are merged, up to 24 (12 heads of
-// 6000 tokens: 11.1 us with 16 splits, 12.7 with 24; 32 query / 8 KV heads of 32000: 26.7 with 24, 27.5
-// with 32).
+// 14.4 us with 2 splits, 12.3 with 5; 4 of 3000 to 6000 tokens 53.0 with 2, 50.1 with 4), and 16 or
+// 24 splits past 16, which are merged eight at a time (32 query / 8 KV heads of 32000 tokens: 26.7 us
+// with 24, 27.5 with 32; 8 heads of 8000 10.8 and 11.0).
 SplitPlan plan_rows(const quest_cache& c) {
   const long items = group_items(c);
   const int per_unit = c.page_size == 8 && group_size(c) == 1 ? 2 : 1;
   long splits = list_splits((items + per_unit - 1) / per_unit, (long)c.max_pages_per_seq * c.page_size);
-  if (splits > 8) splits = std::min(splits - splits % 8, 24l);
+  if (splits > 16) splits = splits < 24 ? 16 : 24;
   return split_list(c.max_pages_per_seq, std::min<long>(splits, c.max_pages_per_seq));
 }
 // One arrival counter per (sequence, head), each in a 256-byte slot of its own.
