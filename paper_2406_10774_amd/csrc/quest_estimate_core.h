@@ -166,11 +166,13 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   // (one query head per KV head in the paper's models: no further round).
   float keep = score_pages(qv[0]);
 #pragma unroll
-  for (int i = 1; i < kQ; ++i) keep = fmaxf(keep, score_pages(qv[i]));  // past the group: its last head again
+  for (int i = 1; i < kQ; ++i)
+    if (i < group) keep = fmaxf(keep, score_pages(qv[i]));
   for (int g0 = kQ; g0 < group; g0 += kQ) {
     load_queries(g0);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) keep = fmaxf(keep, score_pages(qv[i]));
+    for (int i = 0; i < kQ; ++i)
+      if (g0 + i < group) keep = fmaxf(keep, score_pages(qv[i]));
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
   const int p = base + kIters * grp + c;
