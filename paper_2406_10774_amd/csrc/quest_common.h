@@ -69,8 +69,9 @@ int launch_topk_chunks(const quest_cache& c, const float* scores, int k_pages, i
 size_t topk_scratch_bytes(const quest_cache& c, int k_pages);
 int launch_topk_chunked(const quest_cache& c, const float* scores, int k_pages, int32_t* topk_idx,
                         int32_t* k_eff, void* scratch, hipStream_t s);
-// What a launch over a list of k_pages, or over all pages, uses.  With less an attention
-// launch gives every (sequence, head) to one work-group, which needs none.
+// What a launch over a list of k_pages, or over all pages, has to be given (a given list may use more,
+// of attention_workspace_bytes).  With less than it uses an attention launch gives every
+// (sequence, head) to one work-group, which needs none.
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages);
 size_t dense_workspace_bytes(const quest_cache& c);
 size_t row_workspace_bytes(const quest_cache& c);

@@ -297,21 +297,30 @@ struct SplitPlan {
 // 7.9 us), 512 and 1024 tokens are worth 8 splits (8.4 us against 10.1 us), more tokens
 // 16 (8 heads, 4096 tokens: 10.4 us, 12.1 with 8 splits, 11.0 with 32), very long lists a
 // split per 256 tokens.
-long list_splits(long items, long tokens) {
+// per_unit: work-groups per compute unit.
+long list_splits(long items, long tokens, int per_unit = 1) {
   if (items > kComputeUnits)
     return items < kComputeUnits * 11 / 8 && tokens >= 1024 ? 3 : 1;
   if (tokens <= 256) return 1;
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
-  return std::min(kComputeUnits / kDies / ((items + kDies - 1) / kDies), useful);
+  return std::max(1l, std::min(per_unit * kComputeUnits / kDies / ((items + kDies - 1) / kDies), useful));
 }
-// items: work-groups per split.  One head's pages of 8 tokens leave a wave half the bytes in flight:
-// splits of half the tokens (2 sequences, 8 heads, 1464 tokens: 7.2 us with 16 splits, 7.6 with 11; 32
-// heads, 256 tokens 5.6 with 8, 6.6 with 1; but 160 tokens 5.4 and 5.2; 4 sequences of 32 heads, 256
-// tokens 7.5 with 2, 7.2 with 1).
-long most_splits(const quest_cache& c, long items, int list_len) {
+// One head's pages of 8 tokens leave a wave half the bytes in flight.  Few heads: splits of half the
+// tokens (2 sequences, 8 heads, 1464 tokens: 7.2 us with 16 splits, 7.6 with 11; 32 heads, 256 tokens
+// 5.6 with 8, 6.6 with 1; but 160 tokens 5.4 and 5.2, and of 616 tokens nine, merged in two rounds,
+// cost more than eight).  More heads over a given list: two work-groups per unit (5 sequences
+// of 32 heads, 3168 tokens: 43.0 us with 3 splits, 49.8 with 1; 11 of 8 heads, 736 tokens 8.8 with 5,
+// 10.4 with 2; 6 of 32, 2048 tokens 35.9 with 2, 34.9 with 1); selecting launches are as fast
+// either way.
+// items: work-groups per split.
+long most_splits(const quest_cache& c, long items, int list_len, bool select) {
   long tokens = (long)list_len * c.page_size;
-  if (c.page_size == 8 && group_size(c) == 1 && items <= 64 && tokens > 192) tokens *= 2;
-  return std::min(list_splits(items, tokens), std::min<long>(list_len, kMaxTeamSize));
+  int per_unit = 1;
+  if (c.page_size == 8 && group_size(c) == 1) {
+    if (!select && items > 64 && items <= 170 && tokens >= 512) per_unit = 2;
+    if (items <= 64 && (tokens >= 1024 || (tokens > 192 && tokens <= 256))) tokens *= 2;
+  }
+  return std::min(list_splits(items, tokens, per_unit), std::min<long>(list_len, kMaxTeamSize));
 }
 SplitPlan split_list(int list_len, long splits) {
   SplitPlan p;
@@ -321,9 +330,9 @@ SplitPlan split_list(int list_len, long splits) {
   return p;
 }
 long group_items(const quest_cache& c) { return (long)c.batch * kv_heads(c) * attention_subs(c); }
-SplitPlan plan_splits(const quest_cache& c, int k_pages) {
+SplitPlan plan_splits(const quest_cache& c, int k_pages, bool select) {
   const int list_len = std::min(k_pages, c.max_pages_per_seq);
-  return split_list(list_len, most_splits(c, group_items(c), list_len));
+  return split_list(list_len, most_splits(c, group_items(c), list_len, select));
 }
 // Query heads of a group in work-groups of their own, on the vector unit: their pages then come
 // from memory once and from the caches for the others, and a launch takes about 1 us less to
@@ -333,28 +342,29 @@ SplitPlan plan_splits(const quest_cache& c, int k_pages) {
 // sequences of 32/8, 256 6.9 / 7.1, 512 10.6 / 8.4; 8/1 of 4096 9.5 / 14.0; 32/4 of 2048 11.3 / 13.0.
 // Where the launch selects its list, the selection is repeated for more work-groups: 16/8 of 1024
 // tokens 11.3 / 11.8 (a step), 32/8 of 512 11.2 / 11.8, 1024 12.5 / 12.4, 64/8 of 256 12.4 / 11.9, 32/4 of
-// 1024 13.5 / 13.9, 8/1 of 4096 15.9 / 17.4.
+// 1024 13.5 / 13.9, 8/1 of 4096 15.9 / 17.4; groups of two gain little from each other: 16/8 of 1952
+// (every page) 11.1 / 11.6.
 bool heads_apart(const quest_cache& c, int k_pages, bool select) {
   if (group_size(c) == 1) return false;
   const int64_t tokens = (int64_t)std::min(k_pages, c.max_pages_per_seq) * c.page_size;
   const int64_t heads = (int64_t)c.batch * c.num_heads, kv = (int64_t)c.batch * kv_heads(c);
   const bool few = group_items(c) <= 4;
-  return select ? (heads - kv) * tokens <= (few ? 32 : 12) * 1024 : heads * tokens <= (few ? 72 : 44) * 1024;
+  return select ? (heads - kv) * tokens <= (few ? 32 : group_size(c) == 2 ? 16 : 12) * 1024 : heads * tokens <= (few ? 72 : 44) * 1024;
 }
 // No more splits than plan_splits has: less work-groups are left for each item.
 SplitPlan plan_apart(const quest_cache& c, int k_pages) {
   const int list_len = std::min(k_pages, c.max_pages_per_seq);
-  return split_list(list_len, most_splits(c, (long)c.batch * c.num_heads, list_len));
+  return split_list(list_len, most_splits(c, (long)c.batch * c.num_heads, list_len, true));
 }
-// Every page of a row: the same rule, with two work-groups per compute unit where a head's pages
-// of 8 tokens leave a wave half the bytes in flight (3 sequences of 400 to 1200 tokens, 32 heads:
+// Every page of a row: the same rule, with two work-groups per compute unit for more than 48 heads of
+// 8-token pages (3 sequences of 400 to 1200 tokens, 32 heads:
 // 14.4 us with 2 splits, 12.3 with 5; 4 of 3000 to 6000 tokens 53.0 with 2, 50.1 with 4), and 16 or
 // 24 splits past 16, which are merged eight at a time (32 query / 8 KV heads of 32000 tokens: 26.7 us
 // with 24, 27.5 with 32; 8 heads of 8000 10.8 and 11.0).
 SplitPlan plan_rows(const quest_cache& c) {
   const long items = group_items(c);
-  const int per_unit = c.page_size == 8 && group_size(c) == 1 ? 2 : 1;
-  long splits = list_splits((items + per_unit - 1) / per_unit, (long)c.max_pages_per_seq * c.page_size);
+  const int half = c.page_size == 8 && group_size(c) == 1 && items > 48 ? 2 : 1;
+  long splits = list_splits((items + half - 1) / half, (long)c.max_pages_per_seq * c.page_size);
   if (splits > 16) splits = splits < 24 ? 16 : 24;
   return split_list(c.max_pages_per_seq, std::min<long>(splits, c.max_pages_per_seq));
 }
@@ -374,7 +384,7 @@ size_t split_bytes(const quest_cache& c, size_t splits) {
 }  // namespace
 
 size_t decode_workspace_bytes(const quest_cache& c, int k_pages) {
-  return split_bytes(c, plan_splits(c, k_pages).splits);
+  return split_bytes(c, plan_splits(c, k_pages, true).splits);
 }
 
 // One split needs none, but every dense call of a cache shape asks for the counters.
@@ -384,7 +394,7 @@ size_t row_workspace_bytes(const quest_cache& c) {
 
 // most_splits of the longest list there is: no shorter one has more.
 size_t attention_workspace_bytes(const quest_cache& c) {
-  return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, group_items(c), c.max_pages_per_seq)));
+  return std::max(dense_workspace_bytes(c), split_bytes(c, most_splits(c, group_items(c), c.max_pages_per_seq, false)));
 }
 
 namespace {
@@ -397,7 +407,7 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   const bool select = scores != nullptr || cand != nullptr;
   const bool rows = !select && topk_idx == nullptr;  // every page of a row
   const bool apart = !rows && heads_apart(c, k_pages, select);
-  SplitPlan p = rows ? plan_rows(c) : apart ? plan_apart(c, k_pages) : plan_splits(c, k_pages);
+  SplitPlan p = rows ? plan_rows(c) : apart ? plan_apart(c, k_pages) : plan_splits(c, k_pages, select);
   DecodeArgs a;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   a.topk_idx = topk_idx;
@@ -409,6 +419,7 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   a.k_eff = k_eff;
   a.policy = c.flags;
   a.k_pages = k_pages;
+  if (workspace_bytes < split_bytes(c, p.splits) && !rows && !apart) p = plan_splits(c, k_pages, true);
   if (workspace_bytes < split_bytes(c, p.splits)) p = split_list(p.list_len, 1);
   a.splits = p.splits;
   a.list_len = p.list_len;
