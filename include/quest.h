@@ -140,8 +140,7 @@ typedef struct quest_cache {
  *   - any call over at most 64 tokens per head, of more than 256 (sequence, query
  *     head) pairs, or of 256 pairs over at most 256 tokens;
  *   - calls with a list of one page or of at most 256 tokens, and with longer lists
- *     those of 129 or more (sequence, group) pairs (but not of 257 to 351 pairs
- *     over 1024 tokens or more).
+ *     those of 129 or more (sequence, group) pairs.
  * Tokens are min(k_pages, max_pages_per_seq) * page_size.  Other calls refuse it, and
  * so do quest_select_decode and quest_decode_step where
  * quest_topk_workspace_bytes(cache, k_pages) is not 0.

@@ -286,9 +286,12 @@ struct SplitPlan {
 // launch: 36.0 us with 1 split, 39.6 with 2, 42.5 with 4; 8 sequences 46.8 / 49.2 / 49.8;
 // 40 heads of one sequence 13.4 us with 6 splits, 14.7 with 8; 16 sequences of 8 KV heads
 // with 4 query heads each 29.2 us with 2 splits, 35.0 with 4.  Only when the items
-// themselves leave a second round that is nearly empty are three splits of each better: 9
-// sequences of 32 heads 64.5 us with 1, 57.7 with 3 (10 sequences: 65.7 and 60.3; 12: 69.4
-// and 72.5; at 512 tokens 1 is better everywhere).
+// themselves leave a second round that is nearly empty are three splits of each better, as
+// long as those make four rounds: 9 sequences of 32 heads 64.5 us with 1, 57.7 with 3 (10
+// sequences: 65.7 and 60.3; 12: 69.4 and 72.5; 43 of 8 heads 78.4 and 79.9; at 512 tokens 1 is better
+// everywhere).  Up to 2048 tokens only in rows of twice the list: in short rows the shorter
+// sequences leave splits empty (10 sequences of 151 to 1317 tokens, 32 heads, a list of 1040: 26.5 us
+// with 1, 31.0 with 3).
 // All splits of an item run on one die (see decode_split_kernel), so that is counted per die: its
 // 32 units for the items that fall to it.  15 heads of one KV head, a list of 6024 tokens: 12.6 us
 // with 16 splits, 15.3 with 17; attention over whole rows of 20000 tokens, 10 heads, 21.5 us with
@@ -299,8 +302,7 @@ struct SplitPlan {
 // split per 256 tokens.
 // per_unit: work-groups per compute unit.
 long list_splits(long items, long tokens, int per_unit = 1) {
-  if (items > kComputeUnits)
-    return items < kComputeUnits * 11 / 8 && tokens >= 1024 ? 3 : 1;
+  if (items > kComputeUnits) return 3 * items <= 4 * kComputeUnits && tokens >= 1024 ? 3 : 1;
   if (tokens <= 256) return 1;
   const long useful = std::max(8l, std::min(tokens / 128, std::max(16l, tokens / 256)));
   return std::max(1l, std::min(per_unit * kComputeUnits / kDies / ((items + kDies - 1) / kDies), useful));
@@ -316,6 +318,7 @@ long list_splits(long items, long tokens, int per_unit = 1) {
 long most_splits(const quest_cache& c, long items, int list_len, bool select) {
   long tokens = (long)list_len * c.page_size;
   int per_unit = 1;
+  if (items > kComputeUnits && tokens < 2048 && c.max_pages_per_seq < 2 * (long)list_len) return 1;
   if (c.page_size == 8 && group_size(c) == 1) {
     if (!select && items > 64 && items <= 170 && tokens >= 512) per_unit = 2;
     if (items <= 64 && (tokens >= 1024 || (tokens > 192 && tokens <= 256))) tokens *= 2;

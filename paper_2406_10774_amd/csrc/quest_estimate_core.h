@@ -165,14 +165,21 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   // The page's score for the KV head: the largest of its query heads' scores
   // (one query head per KV head in the paper's models: no further round).
   float keep = score_pages(qv[0]);
+  auto score_rest = [&](int from, int heads) {  // of the queries loaded: no branch between four of them
+    if (heads >= kQ) {
 #pragma unroll
-  for (int i = 1; i < kQ; ++i)
-    if (i < group) keep = fmaxf(keep, score_pages(qv[i]));
+      for (int i = 0; i < kQ; ++i)
+        if (i >= from) keep = fmaxf(keep, score_pages(qv[i]));
+    } else {
+#pragma unroll
+      for (int i = 0; i < kQ - 1; ++i)
+        if (i >= from && i < heads) keep = fmaxf(keep, score_pages(qv[i]));
+    }
+  };
+  if (kGroup) score_rest(1, group);
   for (int g0 = kQ; g0 < group; g0 += kQ) {
     load_queries(g0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i)
-      if (g0 + i < group) keep = fmaxf(keep, score_pages(qv[i]));
+    score_rest(0, group - g0);
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
   const int p = base + kIters * grp + c;

@@ -13,7 +13,7 @@ namespace {
 
 // Every GPU the library runs on holds its own copy of this array until the process
 // ends.  Counters and split-K partial results take up to about 1.3 MiB (the launch keeps
-// items * splits near one work-group per compute unit), 4.9 MiB for 257 to 351 groups of eight
+// items * splits near one work-group per compute unit), 4.8 MiB for 257 to 341 groups of eight
 // query heads, which get three splits each; the rest is for the candidates of the
 // selection of rows from 5121 pages on (batch * KV heads * chunks * k_pages * 8 bytes: 1.1
 // MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens, in chunks of

@@ -88,7 +88,7 @@ def test_static_scratch_refuses_shapes_beyond_its_size():
     # candidates of 2048-page chunks do not fit behind the splits' partial results: chunks of 4096
     (9, 29, 1, 32768, 250, (32768 * 16, 3, 2048 * 16, 4096 * 16 + 1, 30000 * 16, 249 * 16, 16, 9000, 100000)),
     # nor does the attention's part beside the two-stage selection: no splits, separate launches
-    (39, 9, 8, 16384, 360, tuple(1 + i * 16384 * 16 // 39 for i in range(39))),
+    (37, 9, 8, 16384, 360, tuple(1 + i * 16384 * 16 // 37 for i in range(37))),
     # eight sequences of 32 heads, which leave the whole array to the candidates
     (8, 32, 1, 32768, 256, tuple(32768 * 16 - i * 70001 for i in range(8))),
 ])
