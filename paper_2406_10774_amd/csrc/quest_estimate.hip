@@ -30,12 +30,12 @@ constexpr unsigned kLdsPerUnit = 160 * 1024;  // of a gfx950 compute unit
 // early (16 sequences of 8k to 64k tokens: 91.6 us against 93.3 us; one of 512k 80.2 against
 // 81.9).  In a small table a trip to memory more would show (4 sequences, 8 heads: 7.0 us
 // against 6.8 us).
-template <bool kAppend, int kIters, bool kGroup>
+template <bool kAppend, int kIters, int kQ, bool kWhole>
 __global__ __launch_bounds__(kEstWaves* kWave) void estimate_kernel(const EstimateArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int base = (blockIdx.x * kEstWaves + wave) * (4 * kIters);
   if (kIters == kEstIters && (long)base << a.page_shift >= a.seq_lens[blockIdx.y]) return;
-  estimate_wave<kAppend, kIters, kGroup>(a, blockIdx.y, blockIdx.z, base);
+  estimate_wave<kAppend, kIters, kQ, kWhole>(a, blockIdx.y, blockIdx.z, base);
 }
 
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
@@ -56,10 +56,17 @@ void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
   // streams better that way than with more (512k tokens in order 80.2 us, 83.3 with six; two
   // sequences of 400k 123.5 and 128.9; 16 ragged ones 91.6 and 94.7); small ones do not care.
   const unsigned lds = kIters == kEstIters ? kLdsPerUnit / 5 : 0;
-  if (a.group > 1)
-    hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, true>), grid, block, lds, s, a);
-  else
-    hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, false>), grid, block, lds, s, a);
+  // The heads of a group by fours, with no branch between them if there are no others (3 sequences of
+  // 64 query / 8 KV heads 3.5 us, 3.7 with branches), else only those there are (4 sequences of up to
+  // 33k tokens, 40 / 8 heads, 7.4 us, 10.0 with the last one scored again up to a multiple of four,
+  // 8.8 by twos); pairs as they are (2 of 265k tokens, 16 / 8 heads 18.3 us, 20.4 by fours).
+#define QUEST_ESTIMATE(Q, W) \
+  hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q, W>), grid, block, lds, s, a)
+  if (a.group == 1) QUEST_ESTIMATE(1, true);
+  else if (a.group == 2) QUEST_ESTIMATE(2, true);
+  else if (a.group % 4 == 0) QUEST_ESTIMATE(4, true);
+  else QUEST_ESTIMATE(4, false);
+#undef QUEST_ESTIMATE
 }
 
 template <bool kAppend>

@@ -34,8 +34,9 @@ struct EstimateArgs {
 // One wave scores the 4 * kIters logical pages starting at `base` of (sequence b,
 // head h): DPP row g takes pages base + kIters*g .. + kIters - 1, one per
 // wave-wide load pair.
-// kGroup: several query heads per KV head.
-template <bool kAppend, int kIters, bool kGroup>
+// kQ: query heads of a KV head that are loaded and scored at a time: 1 where there is one.
+// kWhole: their number is a multiple of kQ.
+template <bool kAppend, int kIters, int kQ, bool kWhole>
 __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int h, int base) {
   char* __restrict__ meta = a.meta;
   const char* __restrict__ q = a.q;
@@ -67,11 +68,10 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   static_assert(kIters == 2 || kIters == 4, "entries of a quad");
   int entry = pt[min(base + kIters * grp + (c & (kIters - 1)), max_pages - 1)];
   const int seq_len = __builtin_amdgcn_readfirstlane(seq_lens[b]);
-  // The group's query vectors, four at a time, the first four in front of the metadata
+  // The group's query vectors, kQ at a time, the first of them in front of the metadata
   // (fetched one by one between the heads they cost a trip to L2 each: 8.2 us against 7.9 us
   // at 4 heads per KV head, 4 sequences of up to 32k tokens).
-  constexpr int kQ = kGroup ? 4 : 1;
-  const int group = kGroup ? a.group : 1;
+  const int group = kQ > 1 ? a.group : 1;
   uint4 qv[kQ];
   auto load_queries = [&](int g0) {
 #pragma unroll
@@ -165,21 +165,14 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   // The page's score for the KV head: the largest of its query heads' scores
   // (one query head per KV head in the paper's models: no further round).
   float keep = score_pages(qv[0]);
-  auto score_rest = [&](int from, int heads) {  // of the queries loaded: no branch between four of them
-    if (heads >= kQ) {
 #pragma unroll
-      for (int i = 0; i < kQ; ++i)
-        if (i >= from) keep = fmaxf(keep, score_pages(qv[i]));
-    } else {
-#pragma unroll
-      for (int i = 0; i < kQ - 1; ++i)
-        if (i >= from && i < heads) keep = fmaxf(keep, score_pages(qv[i]));
-    }
-  };
-  if (kGroup) score_rest(1, group);
+  for (int i = 1; i < kQ; ++i)
+    if (kWhole || i < group) keep = fmaxf(keep, score_pages(qv[i]));
   for (int g0 = kQ; g0 < group; g0 += kQ) {
     load_queries(g0);
-    score_rest(0, group - g0);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i)
+      if (kWhole || g0 + i < group) keep = fmaxf(keep, score_pages(qv[i]));
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
   const int p = base + kIters * grp + c;
