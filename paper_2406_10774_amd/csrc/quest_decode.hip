@@ -289,9 +289,9 @@ struct SplitPlan {
 // themselves leave a second round that is nearly empty are three splits of each better, as
 // long as those make four rounds: 9 sequences of 32 heads 64.5 us with 1, 57.7 with 3 (10
 // sequences: 65.7 and 60.3; 12: 69.4 and 72.5; 43 of 8 heads 78.4 and 79.9; at 512 tokens 1 is better
-// everywhere).  Up to 2048 tokens only in rows of twice the list: in short rows the shorter
-// sequences leave splits empty (10 sequences of 151 to 1317 tokens, 32 heads, a list of 1040: 26.5 us
-// with 1, 31.0 with 3).
+// everywhere).  More than 300 up to 2048 tokens only in rows of twice the list: in short rows the
+// shorter sequences leave splits empty (10 sequences of 151 to 1317 tokens, 32 heads, a list of 1040:
+// 26.5 us with 1, 31.0 with 3; but 7 of 1017 to 1887, 40 heads, 52.1 and 47.6).
 // All splits of an item run on one die (see decode_split_kernel), so that is counted per die: its
 // 32 units for the items that fall to it.  15 heads of one KV head, a list of 6024 tokens: 12.6 us
 // with 16 splits, 15.3 with 17; attention over whole rows of 20000 tokens, 10 heads, 21.5 us with
@@ -308,20 +308,27 @@ long list_splits(long items, long tokens, int per_unit = 1) {
   return std::max(1l, std::min(per_unit * kComputeUnits / kDies / ((items + kDies - 1) / kDies), useful));
 }
 // One head's pages of 8 tokens leave a wave half the bytes in flight.  Few heads: splits of half the
-// tokens (2 sequences, 8 heads, 1464 tokens: 7.2 us with 16 splits, 7.6 with 11; 32 heads, 256 tokens
-// 5.6 with 8, 6.6 with 1; but 160 tokens 5.4 and 5.2, and of 616 tokens nine, merged in two rounds,
-// cost more than eight).  More heads over a given list: two work-groups per unit (5 sequences
-// of 32 heads, 3168 tokens: 43.0 us with 3 splits, 49.8 with 1; 11 of 8 heads, 736 tokens 8.8 with 5,
-// 10.4 with 2; 6 of 32, 2048 tokens 35.9 with 2, 34.9 with 1); selecting launches are as fast
-// either way.
+// tokens, up to the 16 that long lists have (2 sequences, 8 heads, 1464 tokens: 7.2 us with 16 splits,
+// 7.6 with 11; 32 heads, 256 tokens 5.6 with 8, 6.6 with 1; but 160 tokens 5.4 and 5.2, and of 616 tokens
+// nine, merged in two rounds, cost more than eight).  More heads over a given list: two
+// work-groups per unit (11 sequences of 8 heads, 736 tokens 8.8 us with 5 splits, 10.4 with 2; 3 of 32,
+// 6680 tokens 51.9 and 56.7; 6 of 32, 2048 tokens 35.9 with 2, 34.9 with 1); selecting launches are as
+// fast either way.
+// 129 to 170 heads, lists of 3072 tokens or more: three splits, as fast as one where all sequences
+// are longer than the list, faster where they are not (a step of 4 sequences of 2621 to 3960 tokens,
+// 40 heads, all attended: 49.2 us, 52.7; groups, which have more to merge, lose: 20 of 32 query / 8 KV
+// heads 56.7 and 52.9).
 // items: work-groups per split.
 long most_splits(const quest_cache& c, long items, int list_len, bool select) {
   long tokens = (long)list_len * c.page_size;
   int per_unit = 1;
-  if (items > kComputeUnits && tokens < 2048 && c.max_pages_per_seq < 2 * (long)list_len) return 1;
-  if (c.page_size == 8 && group_size(c) == 1) {
-    if (!select && items > 64 && items <= 170 && tokens >= 512) per_unit = 2;
-    if (items <= 64 && (tokens >= 1024 || (tokens > 192 && tokens <= 256))) tokens *= 2;
+  if (items > 300 && tokens < 2048 && c.max_pages_per_seq < 2 * (long)list_len) return 1;
+  if (group_size(c) == 1) {
+    const bool small = c.page_size == 8;
+    if (items > 128 && items <= 170 && tokens >= 3072) per_unit = 2;
+    if (small && !select && items > 64 && items <= 170 && tokens >= 512) per_unit = 2;
+    if (small && items <= 64 && (tokens >= 1024 || (tokens > 192 && tokens <= 256)))
+      tokens = std::max(tokens, std::min(2 * tokens, 4096l));
   }
   return std::min(list_splits(items, tokens, per_unit), std::min<long>(list_len, kMaxTeamSize));
 }
@@ -352,16 +359,16 @@ bool heads_apart(const quest_cache& c, int k_pages, bool select) {
   const int64_t tokens = (int64_t)std::min(k_pages, c.max_pages_per_seq) * c.page_size;
   const int64_t heads = (int64_t)c.batch * c.num_heads, kv = (int64_t)c.batch * kv_heads(c);
   const bool few = group_items(c) <= 4;
-  return select ? (heads - kv) * tokens <= (few ? 32 : group_size(c) == 2 ? 16 : 12) * 1024 : heads * tokens <= (few ? 72 : group_size(c) >= 8 ? 52 : 44) * 1024;
+  return select ? (heads - kv) * tokens <= (few ? 32 : group_size(c) == 2 ? 16 : group_size(c) <= 4 ? 14 : 12) * 1024 : heads * tokens <= (few ? 72 : group_size(c) >= 8 ? 52 : 44) * 1024;
 }
 // No more splits than plan_splits has: less work-groups are left for each item.
 SplitPlan plan_apart(const quest_cache& c, int k_pages) {
   const int list_len = std::min(k_pages, c.max_pages_per_seq);
   return split_list(list_len, most_splits(c, (long)c.batch * c.num_heads, list_len, true));
 }
-// Every page of a row: the same rule, with two work-groups per compute unit for 65 to 144 heads,
+// Every page of a row: the same rule, with two work-groups per compute unit for 64 to 170 heads,
 // which even out ragged sequences (7 sequences of 500 to 2500 tokens, 20 heads, 26.1 us with 3 splits, 29.2
-// with 1; but 5 of 1000, 32 heads, 17.3 and 15.9), and for all above 48 of 8-token pages, which
+// with 1; 4 of 751 to 2221, 40 heads, 26.0 and 28.7; but 5 of 1000, 32 heads, 17.3 and 15.9), and for all above 48 of 8-token pages, which
 // leave a wave half the bytes in flight (3 of 400 to 1200, 32 heads: 12.3 us with 5 splits, 14.4 with 2;
 // 4 of 3000 to 6000 50.1 with 4, 53.0 with 2).  16 or 24 splits past 16, which are merged eight at a
 // time (32 query / 8 KV heads of 32000 tokens: 26.7 us with 24, 27.5 with 32; 8 heads of 8000 10.8 and
@@ -374,7 +381,8 @@ SplitPlan plan_rows(const quest_cache& c) {
   if (group_size(c) > 1) {
     splits = items > 64 && tokens <= 512 ? 1 : list_splits(items, tokens);
   } else {
-    const bool two = c.page_size == 8 ? items > 48 : items > 64 && items <= 144;
+    const bool two = c.page_size == 8 ? items > 48
+                                      : items >= (tokens <= 3072 ? 64 : 65) && items <= 170 && tokens >= 1024;
     splits = items > kComputeUnits && tokens < 2048 ? 1 : list_splits(items, tokens, two ? 2 : 1);
   }
   if (splits > 16) splits = splits < 24 ? 16 : 24;
