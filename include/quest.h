@@ -236,9 +236,11 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
  * fp32 rounding: the list is split differently).  One launch, in which every
  * work-group first selects the pages of its (sequence, KV head) from the scores
  * and keeps the list in on-chip memory, when k_pages <= 2048 and
- * max_pages_per_seq <= 4096 and QUEST_FLAG_SEPARATE_LAUNCHES is not set; else
- * the selection and the attention as launches of their own (the selection in
- * two stages for very long rows, see quest_workspace_bytes).
+ * max_pages_per_seq <= 4096 and QUEST_FLAG_SEPARATE_LAUNCHES is not set.  Rows of
+ * more than 5120 pages: a launch picks candidates from chunks of the rows, and
+ * the attention launch selects among those, while they are at most 4096 per row
+ * and the workspace has room for them.  Else the selection and the attention as
+ * launches of their own (the selection in two stages for very long rows).
  * workspace: quest_workspace_bytes(cache, k_pages) bytes. */
 int quest_select_decode(const quest_cache* cache, const void* q, const float* scores,
                         int32_t k_pages, float sm_scale, int32_t* topk_idx, int32_t* k_eff,
@@ -259,8 +261,8 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * calls); calls sharing a workspace must not overlap in time.
  * The call enqueues the estimate, then what quest_select_decode enqueues: two
  * launches in all when k_pages <= 2048 and max_pages_per_seq <= 4096 and
- * QUEST_FLAG_SEPARATE_LAUNCHES is not set, else three (four with the two-stage
- * selection of very long rows). */
+ * QUEST_FLAG_SEPARATE_LAUNCHES is not set, else three (four where very long rows
+ * are selected in two stages). */
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes);
 int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v_new,
                       int32_t k_pool_write, const void* q, int32_t k_pages, float sm_scale,

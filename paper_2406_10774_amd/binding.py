@@ -84,7 +84,8 @@ def load():
 # A step of a short context lasts about 9 us on the GPU, so what happens here in front of the
 # launches counts: torch is looked up once, pointers and the stream go to ctypes as plain
 # integers, and the stream is read without building a torch.cuda.Stream (0.1 us, not
-# 2.7 us).  quest_decode_step at one head, call after call: 12.4 -> 8.9 us, the GPU's own time.
+# 2.7 us).  quest_decode_step at one head, call after call: 12.2 -> 9.6 us, of which the two
+# launches themselves take 8.8.
 _half = None
 _current_device = None
 _raw_stream = None

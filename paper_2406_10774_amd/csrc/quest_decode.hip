@@ -359,7 +359,9 @@ bool heads_apart(const quest_cache& c, int k_pages, bool select) {
   const int64_t tokens = (int64_t)std::min(k_pages, c.max_pages_per_seq) * c.page_size;
   const int64_t heads = (int64_t)c.batch * c.num_heads, kv = (int64_t)c.batch * kv_heads(c);
   const bool few = group_items(c) <= 4;
-  return select ? (heads - kv) * tokens <= (few ? 32 : group_size(c) == 2 ? 16 : group_size(c) <= 4 ? 14 : 12) * 1024 : heads * tokens <= (few ? 72 : group_size(c) >= 8 ? 52 : 44) * 1024;
+  const int group = group_size(c);
+  if (select) return (heads - kv) * tokens <= (few ? 32 : group == 2 ? 16 : group <= 4 ? 14 : 12) * 1024;
+  return heads * tokens <= (few ? 72 : group >= 8 ? 52 : 44) * 1024;
 }
 // No more splits than plan_splits has: less work-groups are left for each item.
 SplitPlan plan_apart(const quest_cache& c, int k_pages) {
@@ -367,13 +369,14 @@ SplitPlan plan_apart(const quest_cache& c, int k_pages) {
   return split_list(list_len, most_splits(c, (long)c.batch * c.num_heads, list_len, true));
 }
 // Every page of a row: the same rule, with two work-groups per compute unit for 64 to 170 heads,
-// which even out ragged sequences (7 sequences of 500 to 2500 tokens, 20 heads, 26.1 us with 3 splits, 29.2
-// with 1; 4 of 751 to 2221, 40 heads, 26.0 and 28.7; but 5 of 1000, 32 heads, 17.3 and 15.9), and for all above 48 of 8-token pages, which
-// leave a wave half the bytes in flight (3 of 400 to 1200, 32 heads: 12.3 us with 5 splits, 14.4 with 2;
-// 4 of 3000 to 6000 50.1 with 4, 53.0 with 2).  16 or 24 splits past 16, which are merged eight at a
-// time (32 query / 8 KV heads of 32000 tokens: 26.7 us with 24, 27.5 with 32; 8 heads of 8000 10.8 and
-// 11.0).  Of few tokens one: 13 sequences of 64 / 8 heads, 300 tokens, 9.4 and 11.3 with 2; 10 of 151 to
-// 1317 tokens, 32 heads, 24.4, 25.6 with 3.
+// which even out ragged sequences (7 sequences of 500 to 2500 tokens, 20 heads, 26.1 us with 3
+// splits, 29.2 with 1; 4 of 751 to 2221, 40 heads, 26.0 and 28.7; but 5 of 1000, 32 heads, 17.3 and
+// 15.9), and for all above 48 of 8-token pages, which leave a wave half the bytes in flight (3 of
+// 400 to 1200, 32 heads: 12.3 us with 5 splits, 14.4 with 2; 4 of 3000 to 6000 50.1 with 4, 53.0 with
+// 2).  16 or 24 splits past 16, which are merged eight at a time (32 query / 8 KV heads of 32000
+// tokens: 26.7 us with 24, 27.5 with 32; 8 heads of 8000 10.8 and 11.0).  Of few tokens one: 13
+// sequences of 64 / 8 heads, 300 tokens, 9.4 and 11.3 with 2; 10 of 151 to 1317 tokens, 32 heads, 24.4,
+// 25.6 with 3.
 SplitPlan plan_rows(const quest_cache& c) {
   const long items = group_items(c);
   const long tokens = (long)c.max_pages_per_seq * c.page_size;

@@ -32,10 +32,10 @@ def test_dense_shares(kv_heads, group, S, lens):
 
 
 def equal_shares(batch, kv_heads, group, S, pages):
-    """The rule that decides: more than 48k units of 16 tokens, of rows of more than 3072 tokens; fewer
-    than 8 heads (or groups) of long rows."""
+    """The rule that decides: rows of more than 3072 tokens with more than 48k units of 16 tokens or more
+    than 128 heads (or groups); fewer than 8 of them with long rows."""
     items = batch * kv_heads * -(-group // 8)
-    return (items * pages * S / 16 > 48 * 1024 and pages * S > 3072) or \
+    return (pages * S > 3072 and (items * pages * S / 16 > 48 * 1024 or items > 128)) or \
         (items < 8 and pages * S > (16384 if group > 1 else 6400))
 
 
@@ -47,6 +47,7 @@ def equal_shares(batch, kv_heads, group, S, pages):
     (1, 4, 8, RAGGED70, 1700), (2, 4, 64, (6007,), 7000), (8, 8, 8, (1, 2000, 9, 700), 4000),
     (12, 2, 32, tuple(1 + i * 13 for i in range(66)), 130), (8, 4, 16, (7000, 9000), 3500),
     (1, 1, 8, (7001, 3), 900), (2, 1, 64, (6500, 64), 110), (1, 5, 16, (17000, 20), 1100),
+    (2, 1, 16, RAGGED70, 200), (1, 9, 32, RAGGED70, 100),                    # more than 128 heads or groups
 ])
 def test_equal_shares(kv_heads, group, S, lens, room):
     assert equal_shares(len(lens), kv_heads, group, S, room)
