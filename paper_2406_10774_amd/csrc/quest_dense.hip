@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
   int64_t total = 0;
   for (int b0 = 0; b0 < a.batch; b0 += kWave) {
     const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-    total += __builtin_amdgcn_readlane(wave_incl_scan(p, lane), kWave - 1);
+    total += __builtin_amdgcn_readlane(wave_incl_scan(p), kWave - 1);
   }
   total *= blocks;
   const int64_t shares = total < a.shares ? total : a.shares;  // none is empty
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
   int b = 0;
   for (int b0 = 0; b0 < a.batch; b0 += kWave) {
     const int p = b0 + lane < a.batch ? pages_of(a.seq_lens[b0 + lane]) : 0;
-    const int upto = wave_incl_scan(p, lane);
+    const int upto = wave_incl_scan(p);
     const int64_t after = base + (int64_t)__builtin_amdgcn_readlane(upto, kWave - 1) * blocks;
     if (off < after) {
       const int k = __popcll(__ballot(b0 + lane < a.batch && base + (int64_t)upto * blocks <= off));

@@ -2,27 +2,21 @@
 // largest criticality score are the ones attended).  One work-group per
 // (sequence, head).
 //
-// Scores are mapped to unsigned 32-bit keys whose integer order equals the
-// order of the float values (-0 folded onto +0), taken relative to the row's
-// smallest key and shifted left so that the leading bit of the row's range is
-// bit 31.  An MSB-first radix select (8-bit digits, LDS histogram per digit)
-// narrows down the key of the K-th largest score; it stops as soon as every key
-// left in the threshold bin belongs to the selection, or the range's bits are
-// used up.  A final pass in page order emits every page above
-// the threshold bin plus the first `need` pages inside it, each at the position
-// given by a block-wide prefix count, so the output is ascending and the lowest
-// page index wins among equal scores.
+// Scores are mapped to unsigned 32-bit keys whose integer order equals the order of the float
+// values (-0 folded onto +0).  A lower bound of the K-th largest, from the largest keys of K or
+// more sets of pages, leaves a fraction of the row; 256 bins of equal width between it and
+// the largest score tell in which bin the K-th lies (LDS histogram); the few keys of that bin are
+// ranked one by one, or, where they are many, narrowed down by a radix select first.
+// Every page in front is emitted, and of the bin those that are left to take, each at the position given
+// by a work-group-wide prefix count, so the output is ascending and the lowest page index wins
+// among equal scores.  (quest_topk_core.h)
 //
-// The kernel is latency-bound (a few thousand keys per head), so the work is
-// organised to shorten the dependent chain: keys live in registers (thread t
-// owns pages [t*ITEMS, (t+1)*ITEMS)), the score loads are issued before
-// seq_lens is known, the range normalisation makes the first digit spread the
-// row over the whole histogram (scores of one head share sign and most of the
-// exponent: on raw keys the first one or two digits would decide nothing, and
-// their LDS atomics would all hit the same few bins), every wave searches the
-// histogram for the threshold bin itself so a pass needs a single barrier, and
-// lanes that carry the first lane's digit share one LDS atomic in the first
-// pass (a row with outliers still puts most keys into one bin there).
+// The kernel is bound by instructions and latency (a few thousand keys per head): keys
+// live in registers, the score loads are issued before seq_lens is known, every wave
+// searches the histogram and ranks the bin's keys itself so that there are four barriers in
+// all, atomics and stores to LDS go to spare entries instead of being branched around, and
+// what is counted once per wave is kept in scalar registers.  32 rows of 2053 scores, K = 128: 3.9 us
+// a launch, 5.4 with 8-bit digits of the keys from the first on; 8193, K = 256: 6.7 and 10.8 us.
 #include "quest_common.h"
 #include "quest_topk_core.h"
 
@@ -35,7 +29,7 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ seq_lens,
     int32_t* __restrict__ topk_idx, int32_t* __restrict__ k_eff, int num_heads, int max_pages,
     int k_pages, int page_shift, int policy) {
-  __shared__ TopkShared<kThreads> sm;
+  __shared__ __align__(16) TopkShared<kThreads, kItems> sm;
   const int h = blockIdx.x;
   const int b = blockIdx.y;
   const size_t bh = (size_t)b * num_heads + h;
@@ -53,7 +47,7 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
     int32_t* __restrict__ topk_idx, int32_t* __restrict__ k_eff, int num_heads, int max_pages,
     int k_pages, int page_shift, int policy) {
   constexpr int kWaves = kBigThreads / kWave;
-  __shared__ uint32_t hist[256];
+  __shared__ __align__(16) uint32_t hist[256];
   __shared__ int wave_gt[kWaves], wave_eq[kWaves];
   const int h = blockIdx.x;
   const int b = blockIdx.y;
@@ -87,12 +81,12 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
     __syncthreads();
     for (int i = tid; i < num_pages; i += kBigThreads) {
       const uint32_t key = key_of(i);
-      if ((key & high_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+      if ((key & high_mask) == prefix) atomicAdd(&hist[255u - ((key >> shift) & 255u)], 1u);
     }
     __syncthreads();
     const BinHit hit = find_bin(hist, need, lane);
-    prefix |= (uint32_t)hit.bin << shift;
-    need -= hit.above;
+    prefix |= (uint32_t)(255 - hit.bin) << shift;
+    need -= hit.before;
     __syncthreads();
   }
   const uint32_t T = prefix;
@@ -105,8 +99,8 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
     n_gt += key > T;
     n_eq += key == T;
   }
-  const int gt_incl = wave_incl_scan(n_gt, lane);
-  const int eq_incl = wave_incl_scan(n_eq, lane);
+  const int gt_incl = wave_incl_scan(n_gt);
+  const int eq_incl = wave_incl_scan(n_eq);
   if (lane == kWave - 1) {
     wave_gt[wave] = gt_incl;
     wave_eq[wave] = eq_incl;
@@ -161,7 +155,7 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(
     float* __restrict__ cand_score, int32_t* __restrict__ cand_page, int num_heads, int max_pages,
     int k_pages, int num_chunks, int page_shift, int policy) {
   constexpr int kPages = kThreads * kChunkItems;
-  __shared__ TopkShared<kThreads> sm;
+  __shared__ __align__(16) TopkShared<kThreads, kChunkItems> sm;
   // chunk-major launch order: the last chunk of a row, often a short one, must not take
   // the place of a full one on a compute unit that is still free
   const int h = blockIdx.x;
@@ -174,8 +168,8 @@ __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(
   int32_t* out_page = cand_page + at;
   topk_block_put<kThreads, kChunkItems>(
       sm, row, seq_lens + b, min(kPages, max_pages - chunk * kPages), k_pages,
-      [=](int pos, int page, int j, float score) {
-        if (page >= 0) {
+      [=](bool sel, int pos, int page, int j, float score) {
+        if (sel && page >= 0) {
           out_page[pos] = page + chunk * kPages;
           out_score[pos] = j >= 0 ? score : row[page];
         }
@@ -189,7 +183,7 @@ __global__ __launch_bounds__(kThreads) void topk_candidates_kernel(
     const int32_t* __restrict__ seq_lens, int32_t* __restrict__ topk_idx,
     int32_t* __restrict__ k_eff, int num_heads, int row_len, int k_pages, int page_shift,
     int policy) {
-  __shared__ TopkShared<kThreads> sm;
+  __shared__ __align__(16) TopkShared<kThreads, kItems> sm;
   const int h = blockIdx.x;
   const int b = blockIdx.y;
   const size_t bh = (size_t)b * num_heads + h;
@@ -200,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void topk_candidates_kernel(
   int32_t my_page[kItems];
   topk_block_put<kThreads, kItems>(
       sm, cand_score + bh * row_len, seq_lens + b, row_len, k_pages,
-      [&](int pos, int cand, int j, float) {
+      [&](bool sel, int pos, int cand, int j, float) {
         int32_t page = -1;
         if (j >= 0) {
 #pragma unroll
@@ -209,13 +203,13 @@ __global__ __launch_bounds__(kThreads) void topk_candidates_kernel(
         } else if (cand >= 0) {
           page = pages[cand];
         }
-        out[pos] = page;
+        if (sel) out[pos] = page;
       },
       (h == 0 && k_eff != nullptr) ? k_eff + b : nullptr, CandidateRow{page_shift, policy, k_pages, kLargeChunk},
       [&] {
 #pragma unroll
         for (int jj = 0; jj < kItems; ++jj)
-          my_page[jj] = pages[min((int)threadIdx.x * kItems + jj, row_len - 1)];
+          my_page[jj] = pages[min((int)threadIdx.x + jj * kThreads, row_len - 1)];
       });
 }
 

@@ -3,76 +3,66 @@
 // selects its pages itself.  See quest_topk.hip for the algorithm.
 #pragma once
 
+#include <type_traits>
+
 #include "quest_common.h"
 
 namespace quest {
 
 #if defined(__HIPCC__)
 
+// An unsigned key in the order of the scores, -0 equal to +0 (the negation of its bits is +0's
+// key), and never 0.
 __device__ __forceinline__ uint32_t score_key(float s) {
-  uint32_t u = __builtin_bit_cast(uint32_t, s);
-  if (u == 0x80000000u) u = 0;  // -0 ranks equal to +0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __builtin_bit_cast(uint32_t, s);
+  return (int32_t)u < 0 ? 0u - u : u | 0x80000000u;
+}
+__device__ __forceinline__ float score_of(uint32_t key) {
+  return __builtin_bit_cast(float, (int32_t)key < 0 ? key ^ 0x80000000u : 0u - key);
 }
 
-// Inclusive prefix sum over the 64 lanes: DPP row shifts inside each 16-lane
-// row, then the totals of the preceding rows.
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);  // row_shr:8
-  const int r0 = __builtin_amdgcn_readlane(v, 15);
-  const int r1 = __builtin_amdgcn_readlane(v, 31);
-  const int r2 = __builtin_amdgcn_readlane(v, 47);
-  const int row = lane >> 4;
-  return v + (row >= 1 ? r0 : 0) + (row >= 2 ? r1 : 0) + (row >= 3 ? r2 : 0);
+// Inclusive prefix sum over the 64 lanes: DPP row shifts inside each 16-lane row, then the
+// last lane of a row to the next row, and of the second row to the two behind it.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
+  return v;
 }
 
-// Minimum / maximum over the 64 lanes, returned in every lane (wave-uniform): DPP
-// row shifts gather each 16-lane row's result in its last lane (a lane without a
-// source keeps its own value), the four rows are combined on the scalar side.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));
-  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));
-  return min(min((uint32_t)__builtin_amdgcn_readlane((int)v, 15), (uint32_t)__builtin_amdgcn_readlane((int)v, 31)),
-             min((uint32_t)__builtin_amdgcn_readlane((int)v, 47), (uint32_t)__builtin_amdgcn_readlane((int)v, 63)));
+// The same way: lane 63 ends up with the largest value of the 64 lanes.
+__device__ __forceinline__ uint32_t wave_max_in_last(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+  return v;
 }
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
 
-// Scan the 256-bin histogram from the top bin down for the bin that holds the
-// need-th largest key.  Lane l owns bins 255-4l .. 252-4l.  Every lane returns
-// the same (bin, keys above the bin, keys in the bin).
+// The bin of a 256-bin histogram in which the need-th entry lies, counting from bin 0.  Lane
+// l owns bins 4l .. 4l + 3.  Every lane returns the same (bin, entries before the bin,
+// entries in the bin).  No branches: one costs as much as ten instructions here.
 struct BinHit {
-  int bin, above, count;
+  int bin, before, count;
 };
-template <int kCopies = 1>  // the histogram is the sum of kCopies arrays of 256 bins
 __device__ __forceinline__ BinHit find_bin(const uint32_t* hist, int need, int lane) {
-  const int top = 255 - 4 * lane;
-  int c0 = hist[top], c1 = hist[top - 1], c2 = hist[top - 2], c3 = hist[top - 3];
-#pragma unroll
-  for (int r = 1; r < kCopies; ++r) {
-    c0 += hist[r * 256 + top], c1 += hist[r * 256 + top - 1];
-    c2 += hist[r * 256 + top - 2], c3 += hist[r * 256 + top - 3];
-  }
-  const int tot = c0 + c1 + c2 + c3;
-  const int incl = wave_incl_scan(tot, lane);
-  int above = incl - tot;
-  const bool mine = above < need && need <= incl;
-  int bin = top, count = c0;
-  if (need > above + c0) {
-    above += c0, bin = top - 1, count = c1;
-    if (need > above + c1) {
-      above += c1, bin = top - 2, count = c2;
-      if (need > above + c2) above += c2, bin = top - 3, count = c3;
-    }
-  }
-  const int src = __ffsll((long long)__ballot(mine)) - 1;  // exactly one lane
+  const int4 c = reinterpret_cast<const int4*>(hist)[lane];
+  const int tot = c.x + c.y + c.z + c.w;
+  const int incl = wave_incl_scan(tot);
+  const int b0 = incl - tot, b1 = b0 + c.x, b2 = b1 + c.y, b3 = b2 + c.z;
+  const bool p1 = b1 < need, p2 = b2 < need, p3 = b3 < need;  // the entry is past the lane's bin 0, 1, 2
+  const int bin = 4 * lane + p1 + p2 + p3;
+  const int before = p3 ? b3 : p2 ? b2 : p1 ? b1 : b0;
+  const int count = p3 ? c.w : p2 ? c.z : p1 ? c.y : c.x;
+  const int src = __popcll(__ballot(incl < need));  // the first lane that reaches it
   BinHit r;
   r.bin = __builtin_amdgcn_readlane(bin, src);
-  r.above = __builtin_amdgcn_readlane(above, src);
+  r.before = __builtin_amdgcn_readlane(before, src);
   r.count = __builtin_amdgcn_readlane(count, src);
   return r;
 }
@@ -95,18 +85,22 @@ __device__ __forceinline__ ForcedPages forced_pages(int policy, int num_pages) {
   return f;
 }
 
-// The first digit is counted for every key of the row, and lanes with the same digit
-// serialise on one LDS address: with many keys per thread it gets several copies of its
-// histogram, chosen by lane (with few keys the extra clearing and summing cost more than
-// the conflicts: 23.0 us vs 22.7 us per step at 2049 pages, 25 us vs 30 us at 32769).
-constexpr int kMaxHistCopies0 = 4;
-constexpr int hist_copies0(int items) { return items >= 10 ? kMaxHistCopies0 : 1; }
+// Keys left in the threshold bin that are ranked directly, one per lane.
+constexpr int kFewKeys = 64;
 
-template <int kThreads>
+template <int kThreads, int kItems>
 struct TopkShared {
-  uint32_t hist[kMaxHistCopies0 + 3][256];  // copies for the first digit, then one per later digit
-  int wave_tot[kThreads / kWave];
-  uint32_t range[kThreads / kWave][2];  // smallest and largest key seen by each wave
+  static constexpr int kWaves = kThreads / kWave;
+  static constexpr int kRuns = kItems * kWaves;  // runs of 64 consecutive pages, one per wave and item
+  static constexpr int kRunsPerLane = kRuns <= 64 ? 1 : kRuns <= 128 ? 2 : kRuns <= 256 ? 4 : kRuns <= 512 ? 8 : 16;
+  static_assert(kItems <= kWave, "a lane per item");
+  static_assert(kRuns <= kWave * kRunsPerLane && kWaves % kRunsPerLane == 0, "a wave's runs at one place of the lanes'");
+  // Entries for lanes that have nothing to write stand behind the others: a store or an atomic
+  // without a condition is cheaper than a branch around it.
+  uint32_t hist[256 + kWave];
+  uint32_t few_key[kFewKeys + kWave], few_page[kFewKeys + kWave];  // the threshold bin's, in any order
+  uint2 range[kWaves];                       // lower bound of the threshold (inverted) and largest key, by wave
+  uint32_t count[kWave * kRunsPerLane];      // of each run: keys in front of the threshold bin (see topk_block_put)
 };
 
 // What a row of scores is, given the sequence length: its number of valid entries and
@@ -132,172 +126,357 @@ struct CandidateRow {
   }
 };
 
+// Inside a lane group of kGroup (2, 4, 8 or 16) lanes, one step towards the group's maximum: the
+// value of a lane kGroup / 2 away, whose half of the group has its own maximum already.
+template <int kGroup>
+__device__ __forceinline__ uint32_t group_max_step(uint32_t v) {
+  constexpr int kCtrl = kGroup == 2 ? 0xb1 : kGroup == 4 ? 0x4e : kGroup == 8 ? 0x141 : 0x140;
+  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, true));
+}
+
+typedef unsigned long long LaneMask;
+// `start` plus the lanes of the mask in front of this one.
+__device__ __forceinline__ int lanes_before(LaneMask mask, int start) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, start));
+}
+// 1 if a < b, else 0: a compare would leave it in a lane mask, which the next instruction waits for.
+__device__ __forceinline__ uint32_t is_less(uint32_t a, uint32_t b) {
+  uint32_t d;
+  asm("v_sub_u32 %0, %1, %2 clamp" : "=v"(d) : "v"(b), "v"(a));  // 0 if b < a
+  return min(d, 1u);
+}
+// v of one lane (a constant) becomes the wave-uniform value.
+__device__ __forceinline__ void set_lane(uint32_t& v, int lane, uint32_t value) {
+  asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(value), "n"(lane));
+}
+__device__ __forceinline__ bool in_mask(LaneMask mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // Selection for one row of scores by one work-group of kThreads threads (all of
 // them must call).  shape(seq_len) describes the row (it has room for max_pages
-// entries); put(position, page, j, score) receives the list: positions 0 .. k_pages-1,
+// entries); put(selected, position, page, j, score) receives the list from the threads that pass
+// selected (the others' arguments mean nothing, but position is at least 0): positions 0 .. k_pages-1,
 // pages ascending, -1 past the K_b selected ones; j >= 0 says that the page is the calling
-// thread's j-th one (page == threadIdx.x * kItems + j) and `score` its score as loaded,
+// thread's j-th one (page == threadIdx.x + j * kThreads) and `score` its score as loaded,
 // j < 0 that it is not (then `score` carries nothing).  A put that needs per-page data
 // takes it from what the thread already holds whenever j >= 0: a load issued from inside
 // put is waited for before the next page's put starts.
 // after_loads() is called once, right after the loads of the scores have been issued:
 // the place for loads the caller wants in flight behind them.
 template <int kThreads, int kItems, class Put, class Shape, class AfterLoads>
-__device__ __forceinline__ void topk_block_put(TopkShared<kThreads>& sm,
+__device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
                                                const float* __restrict__ row,
                                                const int32_t* __restrict__ seq_len_ptr,
                                                int max_pages, int k_pages, Put put,
                                                int32_t* __restrict__ k_eff_slot, Shape shape,
                                                AfterLoads after_loads) {
+  using Shared = TopkShared<kThreads, kItems>;
   constexpr int kWaves = kThreads / kWave;
-  constexpr int kCopies0 = hist_copies0(kItems);
-  uint32_t(&hist)[kMaxHistCopies0 + 3][256] = sm.hist;
-  int(&wave_tot)[kWaves] = sm.wave_tot;
-  uint32_t(&range)[kWaves][2] = sm.range;
   const int tid = threadIdx.x;
   const int lane = lane_id();
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // issue every load first: this thread's scores (entries past the valid pages
   // are inside the row, so reading them is safe; they are masked below) and the
   // sequence length
-  const int base = tid * kItems;
   float raw[kItems];
+  const uint32_t last_offset = ((uint32_t)max_pages - 1u) * (uint32_t)sizeof(float);
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
     // clamped, not predicated: the loads stay independent and all in flight at once
-    const int i = min(base + j, max_pages - 1);
-    raw[j] = row[i];
+    const uint32_t at = min((uint32_t)(tid + j * kThreads) * (uint32_t)sizeof(float), last_offset);
+    raw[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + at);
   }
-  const int seq_len = *seq_len_ptr;
+  const int seq_len = __builtin_amdgcn_readfirstlane(*seq_len_ptr);
   after_loads();
 
-  for (int i = tid; i < (kCopies0 + 3) * 256; i += kThreads) (&hist[0][0])[i] = 0;
+  if (tid < 256) sm.hist[tid] = 0;
+  if (wave == 0) sm.few_key[lane] = 0xffffffffu;
 
   const RowShape row_shape = shape(seq_len);
   const int num_pages = min(row_shape.num_pages, max_pages);  // whatever the length says: no entry past the row
   const int K = min(k_pages, num_pages);
   if (tid == 0 && k_eff_slot != nullptr) *k_eff_slot = K;
   if (K == num_pages) {  // everything is selected: identity list, padded with -1
-    for (int i = tid; i < k_pages; i += kThreads) put(i, i < K ? i : -1, -1, 0.f);
+    for (int i = tid; i < k_pages; i += kThreads) put(true, i, i < K ? i : -1, -1, 0.f);
     return;
   }
 
   // Pages that are kept whatever their score rank above every score and, like
-  // equal scores, by page index: they stay out of the histograms, take their
-  // places off the count, and are emitted with the keys above the threshold.
+  // equal scores, by page index: they are no keys, take their places off the count,
+  // and are the first and the last entry of the list.
   const ForcedPages forced = forced_pages(row_shape.policy, num_pages);
   if (forced.count >= K) {  // K is 1 or 2 here: the list is the forced pages, lowest first
     if (tid == 0) {
-      put(0, forced.first ? 0 : num_pages - 1, -1, 0.f);
-      if (K == 2) put(1, num_pages - 1, -1, 0.f);
+      put(true, 0, forced.first ? 0 : num_pages - 1, -1, 0.f);
+      if (K == 2) put(true, 1, num_pages - 1, -1, 0.f);
     }
     return;
   }
+  const int first = forced.first, end = num_pages - (int)forced.newest;  // the keys: pages first .. end - 1
+  int need = K - forced.count;  // how many of them the list takes, at least one
 
-  // Keys of the valid, not forced pages; their range over the row.
-  uint32_t key[kItems];
-  bool valid[kItems], kept[kItems];
-  uint32_t lo = 0xffffffffu, hi = 0u;
+  // ---- A lower bound of the need-th largest key: the smallest of the largest keys of any
+  // `need` or more disjoint sets of pages.  The sets are the pages of a thread, or of 2, 4,
+  // .. 16 adjacent ones, or 2, 4, .. 16 equal parts of a thread's, whichever leave just enough of
+  // them; a thread's pages lie kThreads apart, so every set samples the whole context.  Few
+  // keys pass the bound (650 to 1500 of 8193 for 256).
+  constexpr int kClasses = kItems >= 16 ? 16 : kItems >= 8 ? 8 : kItems >= 4 ? 4 : kItems >= 2 ? 2 : 1;
+  uint32_t key[kItems], best[kClasses];  // (key 0: none)
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    key[j] = score_key(raw[j]);
-    kept[j] = forced.is(base + j);
-    valid[j] = base + j < num_pages && !kept[j];
-    if (valid[j]) lo = min(lo, key[j]), hi = max(hi, key[j]);
+    const bool is_key = tid < end - j * kThreads && (j > 0 || tid >= first);
+    key[j] = is_key ? score_key(raw[j]) : 0u;
+    best[j % kClasses] = j < kClasses ? key[j] : max(best[j % kClasses], key[j]);
   }
-  lo = wave_min(lo);
-  hi = wave_max(hi);
-  if (lane == 0) range[wave][0] = lo, range[wave][1] = hi;
-  __syncthreads();
+  uint32_t lo = 0xffffffffu, hi = best[0];
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) lo = min(lo, range[w][0]), hi = max(hi, range[w][1]);
-  lo = __builtin_amdgcn_readfirstlane(lo);
+  for (int c = 1; c < kClasses; ++c) hi = max(hi, best[c]);
+  // (with page 0 kept, thread 0's sets may be empty: they stay out of the bound and of the count)
+  const int spread = min(end, kThreads);
+  if (spread - first >= need) {
+    int group = 1;
+    uint32_t v = hi;
+    const auto widen = [&](int to, uint32_t wider) {
+      const bool enough = (int)((unsigned)spread / to) - first >= need;
+      v = enough ? wider : v;
+      group = enough ? to : group;
+    };
+    widen(2, group_max_step<2>(v));
+    widen(4, group_max_step<4>(v));
+    widen(8, group_max_step<8>(v));
+    widen(16, group_max_step<16>(v));
+    const int leader = tid & -group;
+    lo = leader >= first && leader < end ? v : lo;
+  } else if (min(end, kClasses * kThreads) - kClasses * first >= need) {
+    bool done = false;
+    const auto parts = [&](auto parts_of_thread) {
+      constexpr int kParts = decltype(parts_of_thread)::value;
+      if constexpr (kParts <= kClasses) {
+        if (done || min(end, kParts * kThreads) - kParts * first < need) return;
+        done = true;
+#pragma unroll
+        for (int c = 0; c < kParts; ++c) {
+          uint32_t v = best[c];
+#pragma unroll
+          for (int i = c + kParts; i < kClasses; i += kParts) v = max(v, best[i]);
+          if (tid >= first && tid + c * kThreads < end) lo = min(lo, v);
+        }
+      }
+    };
+    parts(std::integral_constant<int, 2>{});
+    parts(std::integral_constant<int, 4>{});
+    parts(std::integral_constant<int, 8>{});
+    parts(std::integral_constant<int, 16>{});
+  } else {  // as many pages as that: the smallest key
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+      if (key[j] > 0u) lo = min(lo, key[j]);
+  }
+  const uint2 reach = make_uint2(wave_max_in_last(~lo), wave_max_in_last(hi));
+  if (lane == kWave - 1) sm.range[wave] = reach;
+  __syncthreads();
+  uint32_t not_lo = 0u;
+  hi = 0u;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) not_lo = max(not_lo, sm.range[w].x), hi = max(hi, sm.range[w].y);
+  lo = ~__builtin_amdgcn_readfirstlane(not_lo);
   hi = __builtin_amdgcn_readfirstlane(hi);
 
-  // ---- radix select on (key - lo), shifted left so that the range's leading bit is
-  // bit 31: the first digit already spreads the row over the histogram, and only
-  // ceil(bits / 8) digits exist.  Monotone and one-to-one on the row's keys, so order
-  // and ties are those of the scores.  Invariant: the selection is every key greater
-  // than `prefix` on the bits decided so far, plus `need` of the keys that match it.
-  const int bits = hi > lo ? 32 - __builtin_clz(hi - lo) : 0;
-  const int align = 32 - bits;  // 32 when all keys are equal: nothing to decide
+  // ---- Count the keys from lo on in 256 bins of equal width between the scores hi and lo: the bin never
+  // decreases as scores fall, whatever the rounding, and equal keys share one (if the width is no
+  // number or no finite one, all share bin 0).  Scores rather than their bits: those of a range that
+  // spans zero are nearly all exponents.  The list takes every key in front of the bin in which the
+  // need-th lies, and then `need` of the keys in it: 5 to 50 with the bound above, few enough to
+  // rank directly.
+  const uint32_t range = hi - lo;
+  const float hi_score = score_of(hi), bins = 256.f * __builtin_amdgcn_rcpf(hi_score - score_of(lo));
+  const float hi_bins = hi_score * bins;
+  uint32_t digit[kItems];  // the bin; behind all bins for what does not count
+  uint32_t slot[kItems];   // a key's place among those of its bin, in any order
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) key[j] = bits ? (key[j] - lo) << align : 0u;
-  const int n_pass = (bits + 7) >> 3;
-  uint32_t prefix = 0u;
-  int need = K - forced.count;  // the forced pages are in the list for certain
-  int decided_shift = 32;       // bits [decided_shift, 32) of the threshold are known
+  for (int j = 0; j < kItems; ++j) {
+    key[j] = hi - key[j];  // 0: the best; what is no key ranks behind every key
+    const float x = __builtin_fmaf(raw[j], -bins, hi_bins);
+    uint32_t bin;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(x));  // below 0 and NaN: 0; too large: the largest
+    digit[j] = key[j] <= range ? min(bin, 255u) : 256u + lane;
+    slot[j] = atomicAdd(&sm.hist[digit[j]], 1u);
+  }
+  __syncthreads();
+  BinHit hit = find_bin(sm.hist, need, lane);
+  need -= hit.before;
+  if (need != hit.count && hit.count > kFewKeys) {
+    // Radix select among the bin's keys, 8-bit digits from the leading bit of the range, until the
+    // keys left are few or equal.  Then keys in front, in the last bin and behind are told apart.
+    const uint32_t bin0 = hit.bin;
+    uint32_t base = 0u;
+    int shift = range ? 32 - __builtin_clz(range) : 0;
+#pragma unroll 1
+    do {
+      const uint32_t last = shift > 0 ? 0xffffffffu >> (32 - shift) : 0u;  // of the keys left, relative to base
+      shift = max(shift - 8, 0);
+      __syncthreads();
+      if (tid < 256) sm.hist[tid] = 0;
+      __syncthreads();
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    if (pass >= n_pass) break;
-    const int shift = 24 - 8 * pass;
-    const uint32_t high_mask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
-    uint32_t* hp = pass == 0 ? hist[lane & (kCopies0 - 1)] : hist[kCopies0 - 1 + pass];
+      for (int j = 0; j < kItems; ++j) {
+        const uint32_t rest = key[j] - base;
+        slot[j] = atomicAdd(&sm.hist[digit[j] == bin0 && rest <= last ? rest >> shift : 256u + lane], 1u);
+      }
+      __syncthreads();
+      hit = find_bin(sm.hist, need, lane);
+      base += (uint32_t)hit.bin << shift;
+      need -= hit.before;
+    } while (need != hit.count && hit.count > kFewKeys && shift > 0);
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const bool act = valid[j] && (key[j] & high_mask) == prefix;
-      const uint32_t digit = (key[j] >> shift) & 255u;
-      if (pass == 0) {
-        // a row with outliers puts nearly all keys into one bin here: the lanes that
-        // carry lane 0's digit are counted by lane 0 alone (one atomic per lane at most,
-        // all lanes are active)
-        const uint32_t dd = act ? digit : 0xffffffffu;
-        const uint32_t d0 = __builtin_amdgcn_readfirstlane(dd);
-        const uint32_t n_same = (uint32_t)__popcll(__ballot(dd == d0));
-        const bool go = lane == 0 ? act : (act && dd != d0);
-        if (go) atomicAdd(&hp[digit], lane == 0 ? n_same : 1u);
-      } else if (act) {
-        atomicAdd(&hp[digit], 1u);
+      const bool front = digit[j] < bin0 || (digit[j] == bin0 && key[j] < base);
+      const bool inside = digit[j] == bin0 && !front && (key[j] - base) >> shift == 0u;
+      digit[j] = front ? 0u : inside ? 1u : 2u;
+    }
+    hit.bin = 1;
+  }
+  const bool whole = need == hit.count;                    // the list takes all of the bin
+  const int n_few = !whole && hit.count <= kFewKeys ? hit.count : 0;
+  const bool ties = !whole && n_few == 0;                  // more equal keys than places: the lowest pages
+
+  // ---- List positions in page order.  A wave's j-th pages are a run of 64 consecutive ones,
+  // runs follow each other by (j, wave); the runs' counts go through LDS, and so do, in
+  // any order, the few keys of the bin with their pages.
+  const uint32_t front_end = whole ? hit.bin + 1 : hit.bin;
+  uint32_t my_count = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j)
+    set_lane(my_count, j, __popcll(__ballot(digit[j] < front_end)));
+  if (n_few > 0) {
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const uint32_t to = digit[j] == (uint32_t)hit.bin ? slot[j] : kFewKeys + lane;
+      sm.few_key[to] = key[j];
+      sm.few_page[to] = tid + j * kThreads;
+    }
+  } else if (ties) {  // rows have fewer than 2^16 pages
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const uint32_t n = __popcll(__ballot(digit[j] == (uint32_t)hit.bin));
+      my_count += lane == j ? n << 16 : 0u;
+    }
+  }
+  if (lane < kItems) sm.count[lane * kWaves + wave] = my_count;
+  __syncthreads();
+  constexpr int kPerLane = Shared::kRunsPerLane;
+  uint32_t part[kPerLane];
+  int sum = 0;
+#pragma unroll
+  for (int i = 0; i < kPerLane; ++i) {
+    part[i] = sm.count[lane * kPerLane + i];  // (lanes past the runs get what is there, and nobody looks at them)
+    sum += (int)part[i];
+  }
+  // The few keys, one per lane: those with fewer than `need` better ones are taken, unless
+  // equal keys stand at the threshold: then the lowest of their pages.  Every wave does it.
+  uint32_t threshold = 0u;           // the last key that the list takes
+  uint32_t few_page = 0xffffffffu;   // of a key that is taken
+  LaneMask taken = 0;
+  bool split_ties = false;
+  if (n_few > 0) {
+    const uint32_t mine = sm.few_key[lane];
+    few_page = sm.few_page[lane];
+    uint32_t better = 0;
+#pragma unroll 1
+    for (int i = 0; i < n_few; i += 16) {
+      const uint4* them = reinterpret_cast<const uint4*>(sm.few_key + i);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint4 t = them[k];
+        better += is_less(t.x, mine) + is_less(t.y, mine);
+        better += is_less(t.z, mine) + is_less(t.w, mine);
       }
     }
-    __syncthreads();
-    const BinHit hit = pass == 0 ? find_bin<kCopies0>(hist[0], need, lane)
-                                 : find_bin(hp, need, lane);
-    prefix |= (uint32_t)hit.bin << shift;
-    need -= hit.above;
-    decided_shift = shift;
-    if (need == hit.count) break;  // the whole bin is selected: no need to split it further
+    const LaneMask filled = ~0ull >> (kWave - n_few);
+    const LaneMask at_threshold = filled & __ballot(better == (uint32_t)need - 1u);
+    if (__popcll(at_threshold) == 1) {
+      threshold = __builtin_amdgcn_readlane((int)mine, __ffsll((long long)at_threshold) - 1);
+      taken = filled & __ballot(mine <= threshold);
+    } else {
+      taken = filled & __ballot(better < (uint32_t)need);
+      split_ties = true;
+      const uint32_t most = wave_max_in_last(in_mask(taken) ? better : 0u);
+      int places = __builtin_amdgcn_readlane((int)most, kWave - 1);
+      LaneMask left = taken & __ballot(better == (uint32_t)places);
+      taken &= ~left;
+      places = need - places;
+#pragma unroll 1
+      for (int bit = 15; bit >= 0; --bit) {
+        const LaneMask zeros = left & ~__ballot((few_page >> bit) & 1u);
+        const int c = __popcll(zeros);
+        if (c >= places) {
+          left = zeros;
+        } else {
+          taken |= zeros;
+          left &= ~zeros;
+          places -= c;
+        }
+      }
+      taken |= left;
+    }
+    few_page = in_mask(taken) ? few_page : 0xffffffffu;
   }
-
-  // ---- emit in page order.  key > bin: selected; key in bin: the first `need`.
-  const uint32_t T = decided_shift < 32 ? prefix >> decided_shift : 0u;
-  int n_gt = 0, n_eq = 0;
-  bool gt[kItems], eq[kItems];
+  int before = wave_incl_scan(sum) - sum;
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    const uint32_t kd = decided_shift < 32 ? key[j] >> decided_shift : 0u;
-    gt[j] = (valid[j] && kd > T) || kept[j];
-    eq[j] = valid[j] && kd == T;
-    n_gt += gt[j];
-    n_eq += eq[j];
+  for (int i = 0; i + 1 < kPerLane; ++i)
+    if (i < (wave & (kPerLane - 1))) before += (int)part[i];
+  const auto front_before = [&](int j) {
+    return (uint32_t)__builtin_amdgcn_readlane(before, (j * kWaves + wave) / kPerLane);
+  };
+  const auto few_before = [&](int j) {
+    return __popcll(__ballot(few_page < (uint32_t)(j * kThreads + wave * kWave)));
+  };
+  if (!split_ties && !ties) {
+    const uint32_t upto = whole ? (uint32_t)hit.bin : threshold;
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const LaneMask sel = __ballot((whole ? digit[j] : key[j]) <= upto);
+      const int at = (int)front_before(j) + few_before(j) + first;
+      put(in_mask(sel), lanes_before(sel, at), tid + j * kThreads, j, raw[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const LaneMask equal = __ballot(digit[j] == (uint32_t)hit.bin);
+      LaneMask sel = __ballot(digit[j] < front_end);
+      const uint32_t b = front_before(j);  // with ties: and the equal keys before, in the upper half
+      int at = (int)(b & 0xffffu) + few_before(j) + first;
+      if (split_ties) {
+        sel |= equal & __ballot((taken >> (slot[j] & 63u)) & 1u);
+      } else {
+        const int ties_before = (int)(b >> 16);
+        sel |= equal & __ballot(lanes_before(equal, ties_before) < need);
+        at += min(ties_before, need);
+      }
+      put(in_mask(sel), lanes_before(sel, at), tid + j * kThreads, j, raw[j]);
+    }
   }
-  const int packed = n_gt | (n_eq << 16);  // rows handled here have fewer than 2^16 pages
-  const int incl = wave_incl_scan(packed, lane);
-  if (lane == kWave - 1) wave_tot[wave] = incl;
-  __syncthreads();
-  int before = incl - packed;
-  for (int w = 0; w < kWaves; ++w)
-    if (w < wave) before += wave_tot[w];
-  int gt_before = (uint32_t)before & 0xffffu, eq_before = (uint32_t)before >> 16;
+  if (forced.count > 0) {
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    const bool sel = gt[j] || (eq[j] && eq_before < need);
-    if (sel) put(gt_before + min(eq_before, need), base + j, j, raw[j]);
-    gt_before += gt[j];
-    eq_before += eq[j];
+    for (int j = 0; j < kItems; ++j) {
+      const int page = tid + j * kThreads;
+      put(forced.first && page == 0, 0, page, j, raw[j]);
+      put(forced.newest && page == num_pages - 1, K - 1, page, j, raw[j]);
+    }
   }
 }
 
 // The list goes to memory.
 template <int kThreads, int kItems>
-__device__ __forceinline__ void topk_block(TopkShared<kThreads>& sm, const float* __restrict__ row,
+__device__ __forceinline__ void topk_block(TopkShared<kThreads, kItems>& sm, const float* __restrict__ row,
                                            const int32_t* __restrict__ seq_len_ptr, int max_pages,
                                            int k_pages, int32_t* __restrict__ out,
                                            int32_t* __restrict__ k_eff_slot, int page_shift,
                                            int policy) {
   topk_block_put<kThreads, kItems>(
-      sm, row, seq_len_ptr, max_pages, k_pages, [out](int pos, int page, int, float) { out[pos] = page; },
+      sm, row, seq_len_ptr, max_pages, k_pages, [out](bool sel, int pos, int page, int, float) {
+        if (sel) out[pos] = page;
+      },
       k_eff_slot, WholeRow{page_shift, policy}, [] {});
 }
 
