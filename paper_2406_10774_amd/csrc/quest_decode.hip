@@ -40,10 +40,12 @@ namespace {
 
 constexpr long kComputeUnits = 256, kDies = 8;  // MI355X; only used to decide how finely to split
 constexpr int kDecWaves = 4;
-// With the selection done in the same launch (see decode_split_kernel): 8 waves, the size
-// the selection is fastest at, and room in LDS for a page list of this many entries.
-constexpr int kSelWaves = 8;
+// With the selection done in the same launch (see decode_split_kernel): room in LDS for a page list
+// of this many entries, scores per thread up to which their page-table entries are fetched with
+// them, and the longest row.
 constexpr int kSelListCap = 2048;
+constexpr int kLookAhead = 8;
+constexpr int kMostSelected = 256 * 34, kMostSelectedOfGroup = 256 * 20;
 
 struct DecodeArgs : AttnArgs {
   const int32_t* topk_idx;  // the page list [B][kv heads][k_pages] (nullptr: selected inside the launch, or every page)
@@ -135,11 +137,12 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     // which travel with their scores so that the list needs no look-up afterwards, and
     // what the attention needs besides the pages.
     // (of candidates: their logical pages)
+    constexpr bool kLate = !kCand && kSelItems > kLookAhead;
     int mine[kSelItems];
     const int32_t* per_score = kCand ? a.cand_page + row * a.row_len : pt;
     auto more_loads = [&] {
 #pragma unroll
-      for (int j = 0; j < kSelItems; ++j)
+      for (int j = 0; j < (kLate ? 0 : kSelItems); ++j)
         mine[j] = per_score[min((int)threadIdx.x + j * kThreads, a.row_len - 1)];
       seq_len = a.seq_lens[b];
       st.init(sm_acc[wave], q, n_heads, lane);
@@ -147,7 +150,8 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
     // Lanes without a page write to entries of their own behind the list.
     auto put = [&](bool selected, int pos, int entry, int j, float) {
       int of = kCand ? -1 : 0;
-      if (j >= 0) {
+      if (kLate) {
+      } else if (j >= 0) {
 #pragma unroll
         for (int jj = 0; jj < kSelItems; ++jj)
           if (jj == j) of = mine[jj];
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
         if (pos < end) {
           const int2 entry = sm_list[pos];
           l = entry.x, p = entry.y;
-          if (kCand && l >= 0) p = pt[l];
+          if ((kCand || kSelItems > kLookAhead) && l >= 0) p = pt[l];
         }
       } else {
         if (pos < end) l = a.topk_idx ? a.topk_idx[((size_t)b * a.kv_heads + hk) * a.k_pages + pos] : pos;
@@ -470,39 +474,54 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   const dim3 grid((unsigned)(8 * a.splits), (unsigned)items8);
 #define QUEST_LAUNCH(L, G, W, I, C) \
   hipLaunchKernelGGL((decode_split_kernel<L, G, W, I, C>), grid, dim3((W) * kWave), 0, s, a)
-#define QUEST_LAUNCH_FOR_CACHE(W, I, C)                \
-  do {                                                 \
-    if (c.page_size == 8) {                            \
-      if (group) QUEST_LAUNCH(2, true, W, I, C);       \
-      else QUEST_LAUNCH(2, false, W, I, C);            \
-    } else {                                           \
-      if (group) QUEST_LAUNCH(4, true, W, I, C);       \
-      else QUEST_LAUNCH(4, false, W, I, C);            \
-    }                                                  \
+#define QUEST_LAUNCH_FOR_PAGE(G, W, I, C)           \
+  do {                                              \
+    if (c.page_size == 8) QUEST_LAUNCH(2, G, W, I, C); \
+    else QUEST_LAUNCH(4, G, W, I, C);               \
   } while (0)
   if (select) {
-#define QUEST_SELECT_CASE(I)                                      \
-  if (a.row_len <= kSelWaves * kWave * (I)) {                     \
-    if (cand) QUEST_LAUNCH_FOR_CACHE(kSelWaves, I, true);         \
-    else QUEST_LAUNCH_FOR_CACHE(kSelWaves, I, false);             \
-    return check_launch("quest_select_decode");                   \
+#define QUEST_SELECT_CASE(G, C, W, I)                                                      \
+  if (group == G && (cand != nullptr) == C && a.row_len <= (W) * kWave * (I)) {            \
+    QUEST_LAUNCH_FOR_PAGE(G, W, I, C);                                                     \
+    return check_launch("quest_select_decode");                                            \
   }
-    QUEST_SELECT_CASE(2)
-    QUEST_SELECT_CASE(5)
-    QUEST_SELECT_CASE(8)
+    // Waves and scores per thread.  Four waves select short rows as fast as eight and have less to
+    // merge (32 heads, 438 pages: 12.3 us a step, 12.9 with eight); a group's matrix products are better off
+    // on eight (4 sequences of up to 2050 pages, 32 query / 8 KV heads: 21.4 us, 22.6 with four), and so
+    // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: four
+    // waves, so that the sums are those of attention over a given list, which the same call makes
+    // with QUEST_FLAG_SEPARATE_LAUNCHES.
+#define QUEST_SELECT_CASES(C)     \
+  QUEST_SELECT_CASE(false, C, 4, 2) \
+  QUEST_SELECT_CASE(false, C, 4, 4) \
+  QUEST_SELECT_CASE(false, C, 8, 3) \
+  QUEST_SELECT_CASE(false, C, 8, 5) \
+  QUEST_SELECT_CASE(false, C, 8, 8) \
+  QUEST_SELECT_CASE(true, C, 8, 1)  \
+  QUEST_SELECT_CASE(true, C, 8, 2)  \
+  QUEST_SELECT_CASE(true, C, 8, 3)  \
+  QUEST_SELECT_CASE(true, C, 8, 5)  \
+  QUEST_SELECT_CASE(true, C, 8, 8)
+    QUEST_SELECT_CASES(false)
+    QUEST_SELECT_CASES(true)
+    QUEST_SELECT_CASE(false, false, 4, 20)
+    QUEST_SELECT_CASE(false, false, 4, 27)
+    QUEST_SELECT_CASE(false, false, 4, 34)
+    QUEST_SELECT_CASE(true, false, 4, 20)
+#undef QUEST_SELECT_CASES
 #undef QUEST_SELECT_CASE
     set_error("quest_select_decode: internal: no selecting kernel for rows of %d scores", a.row_len);
     return QUEST_ERR_SHAPE;
   }
   // Whole rows of a group, one work-group per compute unit: eight waves (32 query / 8 KV heads of
   // 8000 tokens 13.2 us, 15.1 with four; several per unit: 128 sequences of 64 tokens 18.6 and 12.9).
-  if (rows && group && items <= kComputeUnits) {
-    if (c.page_size == 8) QUEST_LAUNCH(2, true, 8, 0, false);
-    else QUEST_LAUNCH(4, true, 8, 0, false);
-  } else {
-    QUEST_LAUNCH_FOR_CACHE(kDecWaves, 0, false);
-  }
-#undef QUEST_LAUNCH_FOR_CACHE
+  if (rows && group && items <= kComputeUnits)
+    QUEST_LAUNCH_FOR_PAGE(true, 8, 0, false);
+  else if (group)
+    QUEST_LAUNCH_FOR_PAGE(true, kDecWaves, 0, false);
+  else
+    QUEST_LAUNCH_FOR_PAGE(false, kDecWaves, 0, false);
+#undef QUEST_LAUNCH_FOR_PAGE
 #undef QUEST_LAUNCH
   return check_launch("quest_sparse_decode");
 }
@@ -521,30 +540,31 @@ int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void*
                        workspace, workspace_bytes, s);
 }
 
-// Selection and attention in one launch: while a row of scores fits the in-register
-// selection of 512 threads with at most 8 keys each and the list fits in LDS.  Every
-// split of a head repeats the selection, so for longer rows (measured at 4097 pages:
-// 34.9 us against 34.2 us) the separate Top-K launch is the faster form.
+// Selection and attention in one launch: while a row of scores fits the in-register selection
+// and the list fits in LDS.  Every split of a head repeats the selection, which costs less than the
+// launches it saves up to here (32 heads, 8193 pages: 44.4 us a step, 46.3 with candidates picked by a
+// launch of their own, 47.8 with a Top-K launch; 16 sequences of up to 4096 pages 188 us, 193 with the
+// Top-K launch).  Groups of query heads have less to stream that hides it: 3 sequences of 6799 pages, 32
+// query / 8 KV heads, 26.7 us a step, 25.9 with candidates, 6 of 8210 pages, 64 / 8 heads, 64.5 and 63.1;
+// 2 of 4627 pages 26.4, 28.1 with a Top-K launch.
 bool select_decode_supported(const quest_cache& c, int k_pages) {
-  return !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) &&
-         c.max_pages_per_seq <= kSelWaves * kWave * 8 && k_pages <= kSelListCap;
+  return !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) && k_pages <= kSelListCap &&
+         c.max_pages_per_seq <= (group_size(c) == 1 ? kMostSelected : kMostSelectedOfGroup);
 }
 
 namespace {
 // Longer rows: a launch picks candidates from the chunks of the rows, and the attention launch
-// selects among those, as long as they are as few as the scores of a short row.  A step of
-// 32 heads: 49.6 us instead of 55.6 us at 12500 pages (Top-K of whole rows and attention over
-// its list), 45.5 instead of 48.0 us at 8193, 106.3 instead of 108.2 us at 32769 (Top-K in two
-// stages); 8 KV heads of 8 query heads 27.0 instead of 29.8 us at 6125.  At 5000 pages the Top-K
-// of whole rows is 0.4 us faster.  Chunks of 4096 pages where 2048 leave too many candidates
-// (8193 pages 46.6 us).
+// selects among those, as long as they are as few as the scores of a short row: a step of
+// 32 heads 49.6 us instead of 55.6 us at 12500 pages (Top-K of whole rows and attention over
+// its list), 106.3 instead of 108.2 us at 32769 (Top-K in two stages).  Chunks of 4096 pages where
+// 2048 leave too many candidates.
 constexpr int kCandFromPages = 5121;
-constexpr int kMostSelected = kSelWaves * kWave * 8;  // candidates of a row that a launch can select among
+constexpr int kMostCandidatesOfRow = 4096;  // that a launch selects among
 int chunk_to_select_from(const quest_cache& c, int k_pages, size_t room) {
   if ((c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) || c.max_pages_per_seq < kCandFromPages || k_pages > kSelListCap)
     return 0;
   for (const int chunk : {kSmallChunk, kLargeChunk})
-    if (candidates_per_row(c, k_pages, chunk) <= kMostSelected && candidate_bytes(c, k_pages, chunk) > 0 &&
+    if (candidates_per_row(c, k_pages, chunk) <= kMostCandidatesOfRow && candidate_bytes(c, k_pages, chunk) > 0 &&
         candidate_bytes(c, k_pages, chunk) <= room)
       return chunk;
   return 0;
@@ -554,7 +574,7 @@ int chunk_to_select_from(const quest_cache& c, int k_pages, size_t room) {
 // The most candidates that a row can have (candidate_bytes): at most half of its pages.
 size_t selection_workspace_bytes(const quest_cache& c) {
   const bool select = c.max_pages_per_seq >= kCandFromPages && !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES);
-  const size_t most = c.max_pages_per_seq >= kChunkedFromPages ? kMaxCandidates : select ? kMostSelected : 0;
+  const size_t most = c.max_pages_per_seq >= kChunkedFromPages ? kMaxCandidates : select ? kMostCandidatesOfRow : 0;
   return (size_t)c.batch * kv_heads(c) * std::min<size_t>(most, c.max_pages_per_seq / 2) * (sizeof(float) + sizeof(int32_t));
 }
 
