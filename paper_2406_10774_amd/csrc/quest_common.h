@@ -149,6 +149,16 @@ __device__ __forceinline__ float row16_sum(float x) {
   return x;
 }
 
+// Largest value of the 16 lanes of a DPP row, in every lane of the row.
+template <int N>
+__device__ __forceinline__ float row_ror_max(float x) {
+  const int v = __builtin_bit_cast(int, x);
+  return fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, v, 0x120 + N, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ float row16_max(float x) {
+  return row_ror_max<1>(row_ror_max<2>(row_ror_max<4>(row_ror_max<8>(x))));
+}
+
 // fp16 pair dot product accumulated in fp32 (v_dot2_f32_f16).
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float acc) {
   return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, a), __builtin_bit_cast(half2_t, b), acc,

@@ -211,27 +211,48 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   const int n_out = n_heads * kHeadDim;
   // ---- this split's result per query head: written out if it is the only split, else
   // published as a partial; the split that arrives last merges
-  for (int x = t; x < n_out; x += kThreads) {
-    const int g = kGroup ? x / kHeadDim : 0, ch = x & (kHeadDim - 1);
-    float m_tot = sm_m[0][g];
+  if constexpr (kGroup) {  // 64 outputs of one head per wave
+    for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
+      const int g = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
+      const int part = lane & (kWaves - 1);
+      const Merged all = merge_parts(sm_m[part][g], sm_l[part][g], kWaves, lane);
+      float acc = 0.f;
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) m_tot = fmaxf(m_tot, sm_m[w][g]);
-    float l_tot = 0.f, acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-      const float f = __builtin_amdgcn_exp2f(sm_m[w][g] - m_tot);
-      l_tot += sm_l[w][g] * f;
-      acc += sm_acc[w][g * kStride + ch] * f;
+      for (int w = 0; w < kWaves; ++w) acc += sm_acc[w][g * kStride + ch] * from_lane(all.weight, w);
+      if (a.splits == 1) {
+        store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + ch, acc / all.l);
+        if (ch == 0 && a.lse) a.lse[bh + g] = (all.m + __builtin_amdgcn_logf(all.l)) * kLn2;
+      } else {
+        const size_t ps = (bh + g) * a.splits + split;
+        dev_st(a.part_acc + ps * kHeadDim + ch, acc);
+        if (ch == 0) {
+          dev_st(a.part_ml + ps * 2 + 0, all.m);
+          dev_st(a.part_ml + ps * 2 + 1, all.l);
+        }
+      }
     }
-    if (a.splits == 1) {
-      store_out(a.out, a.out_is_fp16, bh * kHeadDim + x, acc / l_tot);
-      if (ch == 0 && a.lse) a.lse[bh + g] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
-    } else {
-      const size_t ps = (bh + g) * a.splits + split;
-      dev_st(a.part_acc + ps * kHeadDim + ch, acc);
-      if (ch == 0) {
-        dev_st(a.part_ml + ps * 2 + 0, m_tot);
-        dev_st(a.part_ml + ps * 2 + 1, l_tot);
+  } else {
+    for (int ch = t; ch < kHeadDim; ch += kThreads) {
+      float m_tot = sm_m[0][0];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) m_tot = fmaxf(m_tot, sm_m[w][0]);
+      float l_tot = 0.f, acc = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float f = __builtin_amdgcn_exp2f(sm_m[w][0] - m_tot);
+        l_tot += sm_l[w][0] * f;
+        acc += sm_acc[w][ch] * f;
+      }
+      if (a.splits == 1) {
+        store_out(a.out, a.out_is_fp16, bh * kHeadDim + ch, acc / l_tot);
+        if (ch == 0 && a.lse) a.lse[bh] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
+      } else {
+        const size_t ps = bh * a.splits + split;
+        dev_st(a.part_acc + ps * kHeadDim + ch, acc);
+        if (ch == 0) {
+          dev_st(a.part_ml + ps * 2 + 0, m_tot);
+          dev_st(a.part_ml + ps * 2 + 1, l_tot);
+        }
       }
     }
   }
@@ -244,41 +265,88 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   team_acquire(a.device_fences);
   if (t == 0) team_reset(arrivals);
 
-  // one pass over the splits in chunks of 8, all loads of a chunk in flight at once, with
-  // a running maximum (the same rescaling as between pages); always in split order, so the
-  // result does not depend on which split arrived last
+  // one pass over the splits in chunks of 8 (a group's of 16), all loads of a chunk in flight at
+  // once, with a running maximum (the same rescaling as between pages); always in split order, so
+  // the result does not depend on which split arrived last
+  if constexpr (kGroup) {
 #pragma unroll 1
-  for (int x = t; x < n_out; x += kThreads) {
-    const int g = kGroup ? x / kHeadDim : 0, ch = x & (kHeadDim - 1);
-    const float* ml = a.part_ml + (bh + g) * a.splits * 2;
-    const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + ch;
-    float mx = kNegBig, l_all = 0.f, o = 0.f;
-    for (int s0 = 0; s0 < a.splits; s0 += 8) {
-      float2 pml[8];
-      float pa[8];
+    for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
+      const int g = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
+      const float* ml = a.part_ml + (bh + g) * a.splits * 2;
+      const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + ch;
+      float mx = kNegBig, l_all = 0.f, o = 0.f;
+      for (int s0 = 0; s0 < a.splits; s0 += 16) {
+        const int n = min(16, a.splits - s0);
+        const float2 pml = dev_ld2(ml + 2 * (s0 + min(lane & 15, n - 1)));
+        float pa[16];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int sidx = min(s0 + i, a.splits - 1);
-        pml[i] = dev_ld2(ml + 2 * sidx);
-        pa[i] = dev_ld(pacc + (size_t)sidx * kHeadDim);
+        for (int i = 0; i < 8; ++i) pa[i] = dev_ld(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
+        if (n > 8) {
+#pragma unroll
+          for (int i = 8; i < 16; ++i) pa[i] = dev_ld(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
+        }
+        const Merged part = merge_parts(pml.x, pml.y, n, lane);
+        const float cm = fmaxf(mx, part.m);
+        const float rescale = __builtin_amdgcn_exp2f(mx - cm), scale = __builtin_amdgcn_exp2f(part.m - cm);
+        l_all = l_all * rescale + part.l * scale;
+        o *= rescale;
+        const float weight = part.weight * scale;
+        // (what is not there is left out, not taken times zero: the values may be infinite)
+        if (n >= 8) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) o += pa[i] * from_lane(weight, i);
+#pragma unroll
+          for (int i = 8; i < 16; ++i)
+            if (i < n) o += pa[i] * from_lane(weight, i);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 7; ++i)
+            if (i < n) o += pa[i] * from_lane(weight, i);
+        }
+        mx = cm;
       }
-      float cm = mx;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) cm = fmaxf(cm, pml[i].x);
-      const float rescale = __builtin_amdgcn_exp2f(mx - cm);
-      l_all *= rescale;
-      o *= rescale;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (s0 + i >= a.splits) continue;  // not a factor of zero: the values may be infinite
-        const float f = __builtin_amdgcn_exp2f(pml[i].x - cm);
-        l_all += pml[i].y * f;
-        o += pa[i] * f;
-      }
-      mx = cm;
+      store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + ch, o / l_all);
+      if (ch == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
     }
-    store_out(a.out, a.out_is_fp16, bh * kHeadDim + x, o / l_all);
-    if (ch == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
+  } else {
+#pragma unroll 1
+    for (int ch = t; ch < kHeadDim; ch += kThreads) {
+      const float* ml = a.part_ml + bh * a.splits * 2;
+      const float* pacc = a.part_acc + bh * a.splits * kHeadDim + ch;
+      float mx = kNegBig, l_all = 0.f, o = 0.f;
+      for (int s0 = 0; s0 < a.splits; s0 += 8) {
+        float2 pml[8];
+        float pa[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int sidx = min(s0 + i, a.splits - 1);
+          pml[i] = dev_ld2(ml + 2 * sidx);
+          pa[i] = dev_ld(pacc + (size_t)sidx * kHeadDim);
+        }
+        float cm = mx;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cm = fmaxf(cm, pml[i].x);
+        const float rescale = __builtin_amdgcn_exp2f(mx - cm);
+        l_all *= rescale;
+        o *= rescale;
+        const auto add = [&](int i) {
+          const float f = __builtin_amdgcn_exp2f(pml[i].x - cm);
+          l_all += pml[i].y * f;
+          o += pa[i] * f;
+        };
+        if (s0 + 8 <= a.splits) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) add(i);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (s0 + i < a.splits) add(i);  // not a factor of zero: the values may be infinite
+        }
+        mx = cm;
+      }
+      store_out(a.out, a.out_is_fp16, bh * kHeadDim + ch, o / l_all);
+      if (ch == 0 && a.lse) a.lse[bh] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
+    }
   }
 }
 
