@@ -54,6 +54,17 @@ def test_equal_shares(kv_heads, group, S, lens, room):
     check(kv_heads, group, S, lens, room)
 
 
+@pytest.mark.parametrize("kv_heads,group,S,lens,room", [
+    # items shorter than, as long as and longer than the 128 KiB that stand in front of each on the line
+    (32, 1, 16, (16, 63, 64, 65, 1, 2000, 1), 1000), (1, 1, 16, (255, 256, 257, 1) * 35, 200),
+    (8, 4, 16, (255, 256, 257, 3000, 1, 16) * 2, 600), (8, 2, 8, (127, 128, 129, 1) * 4, 1200),
+    (32, 1, 64, (64, 65, 1, 900), 400), (2, 1, 16, (1,), 30000), (4, 1, 32, (20000,), 700),
+])
+def test_borders_between_items(kv_heads, group, S, lens, room):
+    assert equal_shares(len(lens), kv_heads, group, S, room)
+    check(kv_heads, group, S, lens, room)
+
+
 def check(kv_heads, group, S, lens, room):
     import torch
     from gpu_util import Layer
