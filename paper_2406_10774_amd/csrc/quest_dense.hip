@@ -54,13 +54,10 @@ template <int kLoads, bool kGroup, int kBlock, int kWaves>
 __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a) {
   using Head = HeadState<kLoads, kGroup>;
   constexpr int kThreads = kWaves * kWave;
-  constexpr int kTeams = kThreads / 32;  // groups of threads that merge partial results
   constexpr int kSlots = Head::kSlots, kStride = Head::kStride;
   constexpr int kHeads = slot_heads<kGroup, kBlock>();
-  constexpr int kAccFloats = kWaves * kSlots * kStride > kTeams * kHeadDim ? kWaves * kSlots * kStride : kTeams * kHeadDim;
-  __shared__ __align__(16) float sm_acc[kAccFloats];
-  __shared__ float sm_m[kWaves * kSlots > kTeams ? kWaves * kSlots : kTeams];
-  __shared__ float sm_l[kWaves * kSlots > kTeams ? kWaves * kSlots : kTeams];
+  __shared__ __align__(16) float sm_acc[kWaves * kSlots * kStride];
+  __shared__ float sm_m[kWaves * kSlots], sm_l[kWaves * kSlots];
   __shared__ uint32_t sm_before;
   const int t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -158,25 +155,21 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
     const int n_out = (kGroup ? n_heads : kBlock) * kHeadDim;
     const bool whole = n_pages == pages;
     const size_t slot = 2 * (size_t)w + (item_at >= begin ? 1 : 0);  // items begun before: slot 0
-    for (int x = t; x < n_out; x += kThreads) {
-      const int g = x / kHeadDim, ch = x & (kHeadDim - 1);
+    // (64 outputs of one head per wave)
+    for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
+      const int g = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
       float m_tot, l_tot, acc;
       if constexpr (kBlock > 1) {
         m_tot = sm_m[g], l_tot = sm_l[g], acc = sm_acc[g * kStride + ch];
       } else {
-        m_tot = sm_m[g];
+        const int part = (lane & (kWaves - 1)) * kSlots + g;
+        const Merged all = merge_parts(sm_m[part], sm_l[part], kWaves, lane);
+        m_tot = all.m, l_tot = all.l, acc = 0.f;
 #pragma unroll
-        for (int i = 1; i < kWaves; ++i) m_tot = fmaxf(m_tot, sm_m[i * kSlots + g]);
-        l_tot = 0.f, acc = 0.f;
-#pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
-          const float f = __builtin_amdgcn_exp2f(sm_m[i * kSlots + g] - m_tot);
-          l_tot += sm_l[i * kSlots + g] * f;
-          acc += sm_acc[(i * kSlots + g) * kStride + ch] * f;
-        }
+        for (int i = 0; i < kWaves; ++i) acc += sm_acc[(i * kSlots + g) * kStride + ch] * from_lane(all.weight, i);
       }
       if (whole) {
-        store_out(a.out, a.out_is_fp16, bh0 * kHeadDim + x, acc / l_tot);
+        store_out(a.out, a.out_is_fp16, (bh0 + g) * kHeadDim + ch, acc / l_tot);
         if (ch == 0 && a.lse) a.lse[bh0 + g] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
       } else {
         const size_t ps = slot * kHeads + g;
@@ -199,59 +192,54 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
       if (__builtin_amdgcn_readfirstlane(sm_before) == (uint32_t)parts - 1) {
         team_acquire(a.device_fences);
         if (t == 0) team_reset(arrivals);
-        // Teams of 32 threads, four channels a thread: a head's parts are dealt to as
-        // many teams as there are for it, eight at a time in flight per team, and the teams'
-        // sums added through LDS.  Fixed order: the result does not depend on who was last.
-        const int heads = n_out / kHeadDim;
-        const int ways = kTeams / (heads <= 1 ? 1 : heads <= 2 ? 2 : heads <= 4 ? 4 : 8);  // teams per head
-        const int team = t >> 5, quad = (t & 31) * 4;
-        const int g = team / ways, way = team - g * ways;
-        float mx = kNegBig, l_all = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
-        if (g < heads) {
-          for (int k0 = way; k0 < parts; k0 += 8 * ways) {
-            float2 ml[8], pa[8], pb[8];
+        // A head's parts are dealt to as many waves as there are for it, two channels a lane, 16 parts
+        // at a time in flight per wave, and the waves' sums added through LDS.  Fixed order: the
+        // result does not depend on who was last.
+        const int heads = n_out / kHeadDim;  // at most kWaves
+        const int ways_log2 = (kWaves == 8 ? 3 : 2) - (heads <= 1 ? 0 : heads <= 2 ? 1 : heads <= 4 ? 2 : 3);
+        const int g = wave >> ways_log2, way = wave & ((1 << ways_log2) - 1);
+        const float* head_ml = a.part_ml + ((size_t)2 * from * kHeads + g) * 2;  // part k: 2 k kHeads further,
+        const float* head_acc = a.part_acc + ((size_t)2 * from * kHeads + g) * kHeadDim;  // the first in slot 1
+        const auto place = [&](int k) { return (uint32_t)((2 * k + (k == 0 ? 1 : 0)) * kHeads); };
+        const int mine = g < heads ? (parts - way + (1 << ways_log2) - 1) >> ways_log2 : 0;
+        float mx = kNegBig, l_all = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll 1
+        for (int i0 = 0; i0 < mine; i0 += 16) {
+          const int n = min(16, mine - i0);
+          const auto part_of = [&](int i) { return way + ((i0 + min(i, n - 1)) << ways_log2); };
+          const float2 ml = dev_ld2(head_ml + place(part_of(lane & 15)) * 2);
+          float2 pa[16];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              const int k = min(k0 + i * ways, parts - 1);
-              const size_t ps = (2 * (size_t)(from + k) + (k == 0 ? 1 : 0)) * kHeads + g;
-              ml[i] = dev_ld2(a.part_ml + ps * 2);
-              pa[i] = dev_ld2(a.part_acc + ps * kHeadDim + quad);
-              pb[i] = dev_ld2(a.part_acc + ps * kHeadDim + quad + 2);
+          for (int i = 0; i < 16; ++i) pa[i] = dev_ld2(head_acc + place(part_of(i)) * kHeadDim + 2 * lane);
+          const Merged sum = merge_parts(ml.x, ml.y, n, lane);
+          const float cm = fmaxf(mx, sum.m);
+          const float rescale = __builtin_amdgcn_exp2f(mx - cm), scale = __builtin_amdgcn_exp2f(sum.m - cm);
+          l_all = l_all * rescale + sum.l * scale;
+          o0 *= rescale, o1 *= rescale;
+          const float weight = sum.weight * scale;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            if (i < n) {  // not a factor of zero: the values may be infinite
+              const float f = from_lane(weight, i);
+              o0 += pa[i].x * f, o1 += pa[i].y * f;
             }
-            float cm = mx;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) cm = fmaxf(cm, ml[i].x);
-            const float rescale = __builtin_amdgcn_exp2f(mx - cm);
-            l_all *= rescale;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] *= rescale;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              if (k0 + i * ways >= parts) continue;  // not a factor of zero: the values may be infinite
-              const float f = __builtin_amdgcn_exp2f(ml[i].x - cm);
-              l_all += ml[i].y * f;
-              o[0] += pa[i].x * f;
-              o[1] += pa[i].y * f;
-              o[2] += pb[i].x * f;
-              o[3] += pb[i].y * f;
-            }
-            mx = cm;
           }
+          mx = cm;
         }
-        *reinterpret_cast<float4*>(sm_acc + team * kHeadDim + quad) = make_float4(o[0], o[1], o[2], o[3]);
-        if ((t & 31) == 0) sm_m[team] = mx, sm_l[team] = l_all;
+        *reinterpret_cast<float2*>(sm_acc + wave * kHeadDim + 2 * lane) = make_float2(o0, o1);
+        if (lane == 0) sm_m[wave] = mx, sm_l[wave] = l_all;
         __syncthreads();
-        for (int x = t; x < n_out; x += kThreads) {
-          const int hh = x / kHeadDim, ch = x & (kHeadDim - 1);
-          float m_tot = kNegBig, l_tot = 0.f, acc = 0.f;
-          for (int i = 0; i < ways; ++i) m_tot = fmaxf(m_tot, sm_m[hh * ways + i]);
-          for (int i = 0; i < ways; ++i) {
-            const float f = __builtin_amdgcn_exp2f(sm_m[hh * ways + i] - m_tot);
-            l_tot += sm_l[hh * ways + i] * f;
-            acc += sm_acc[(hh * ways + i) * kHeadDim + ch] * f;
-          }
-          store_out(a.out, a.out_is_fp16, bh0 * kHeadDim + x, acc / l_tot);
-          if (ch == 0 && a.lse) a.lse[bh0 + hh] = (m_tot + __builtin_amdgcn_logf(l_tot)) * kLn2;
+        for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
+          const int hh = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
+          const int first_way = hh << ways_log2, ways = 1 << ways_log2;
+          const int part = first_way + (lane & (ways - 1));
+          const Merged all = merge_parts(sm_m[part], sm_l[part], ways, lane);
+          float acc = 0.f;
+#pragma unroll
+          for (int i = 0; i < kWaves; ++i)
+            if (i < ways) acc += sm_acc[(first_way + i) * kHeadDim + ch] * from_lane(all.weight, i);
+          store_out(a.out, a.out_is_fp16, (bh0 + hh) * kHeadDim + ch, acc / all.l);
+          if (ch == 0 && a.lse) a.lse[bh0 + hh] = (all.m + __builtin_amdgcn_logf(all.l)) * kLn2;
         }
       }
     }
