@@ -225,8 +225,9 @@ def main():
     three_us = us_step
     calls = "quest_append_estimate, quest_topk, quest_sparse_decode (three launches)"
     # the library's own rule (quest.h): the attention launch selects its pages itself for
-    # rows of at most 4096 pages and lists of at most 2048; else the call is three launches
-    selects_inside = table.shape[1] <= 4096 and K <= 2048
+    # rows of at most 8704 pages (of one query head per KV head) and lists of at most 2048; else
+    # the call is three launches
+    selects_inside = table.shape[1] <= 8704 and K <= 2048
     one_call = two_us < us_step
     two_launches = one_call and selects_inside
     if one_call:

@@ -127,8 +127,8 @@ typedef struct quest_cache {
  * k_pages.  Pure host function.
  * The workspace holds one arrival counter per (sequence, head) and the split-K
  * partial results (running max, denominator and un-normalised accumulator of
- * each split); for rows of more than 5120 pages also the candidates that
- * quest_select_decode and quest_decode_step select from there (the best k_pages
+ * each split); for rows of more than 5120 pages also room for the candidates that
+ * quest_select_decode and quest_decode_step select from in long rows (the best k_pages
  * of every chunk of 2048 or 4096 pages of a row: up to 4096 of them, from 16384
  * pages on 8192, and never more than half of the row).  With
  * QUEST_FLAG_SEPARATE_LAUNCHES rows of fewer than 16384 pages keep none; a
@@ -236,8 +236,9 @@ int quest_sparse_decode(const quest_cache* cache, const void* q, const int32_t* 
  * fp32 rounding: the list is split differently).  One launch, in which every
  * work-group first selects the pages of its (sequence, KV head) from the scores
  * and keeps the list in on-chip memory, when k_pages <= 2048 and
- * max_pages_per_seq <= 4096 and QUEST_FLAG_SEPARATE_LAUNCHES is not set.  Rows of
- * more than 5120 pages: a launch picks candidates from chunks of the rows, and
+ * max_pages_per_seq <= 8704 (5120 with several query heads per KV head) and
+ * QUEST_FLAG_SEPARATE_LAUNCHES is not set.  Longer
+ * rows: a launch picks candidates from chunks of the rows, and
  * the attention launch selects among those, while they are at most 4096 per row
  * and the workspace has room for them.  Else the selection and the attention as
  * launches of their own (the selection in two stages for very long rows).
@@ -260,9 +261,9 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * allocation (same rule as for quest_sparse_decode; one buffer may serve both
  * calls); calls sharing a workspace must not overlap in time.
  * The call enqueues the estimate, then what quest_select_decode enqueues: two
- * launches in all when k_pages <= 2048 and max_pages_per_seq <= 4096 and
- * QUEST_FLAG_SEPARATE_LAUNCHES is not set, else three (four where very long rows
- * are selected in two stages). */
+ * launches in all when k_pages <= 2048 and max_pages_per_seq <= 8704 (5120 with
+ * several query heads per KV head) and QUEST_FLAG_SEPARATE_LAUNCHES is not set,
+ * else three (four where very long rows are selected in two stages). */
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes);
 int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v_new,
                       int32_t k_pool_write, const void* q, int32_t k_pages, float sm_scale,
