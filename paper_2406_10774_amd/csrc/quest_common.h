@@ -235,6 +235,16 @@ __device__ __forceinline__ uint4 rows_key_max8(uint4 v) {
   return make_uint4(rows_key_max2(v.x), rows_key_max2(v.y), rows_key_max2(v.z), rows_key_max2(v.w));
 }
 
+// Operands and result of a 16x16x32 matrix product.
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// LDS serves a wave in order; this keeps the compiler to it (no instruction).
+__device__ __forceinline__ void lds_in_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Byte offset of the metadata entry of (physical page, head).

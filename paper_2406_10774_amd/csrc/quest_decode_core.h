@@ -173,8 +173,6 @@ constexpr int kGroupHeads = 8;
 constexpr float kWeightScale = 16384.f, kRestScale = 4096.f;  // 2^14, 2^12: a rest is at most 2^3
 constexpr int kGroupStride = kHeadDim + 4;  // floats per head in LDS: lanes spread over the banks
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // Tokens of a unit that hold data: tokens [0, first) of the first eight and, of the others,
 // [8, 8 + second); anything from below zero to above eight.
@@ -214,12 +212,6 @@ __device__ __forceinline__ void group_load(GroupRegs& r, const char* __restrict_
   for (int i = 0; i < 4; ++i) r.k[i] = ld16_stream(k_pool + (i < 2 ? base_a : base_b) + i * 1024 + lane * 16);
 #pragma unroll
   for (int i = 0; i < 4; ++i) r.v[i] = ld16_stream(v_pool + (i < 2 ? base_a : base_b) + i * 1024 + lane * 16);
-}
-
-// LDS serves a wave in order; this keeps the compiler to it (no instruction).
-__device__ __forceinline__ void lds_in_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 __device__ __forceinline__ void group_fold(GroupState& st, GroupRegs& r, float scale_log2, int lane) {

@@ -3,7 +3,8 @@
 //
 // Since m <= M per channel, max(q m, q M) is q * (q >= 0 ? M : m) exactly: the
 // sign of q picks the row, done once per wave as a bit mask, and the products
-// go through v_dot2_f32_f16 (fp16 products are exact in fp32, fp32 sum).
+// go through v_dot2_f32_f16 (fp16 products are exact in fp32, fp32 sum), or, of three and
+// more query heads per KV head, through matrix products with q split by its sign.
 //
 // One wavefront owns (head, block of 8 or 16 consecutive logical pages).  A 16-lane
 // DPP row reads one metadata entry: 16 B per lane of the min row, then 16 B per
@@ -30,12 +31,13 @@ constexpr unsigned kLdsPerUnit = 160 * 1024;  // of a gfx950 compute unit
 // early (16 sequences of 8k to 64k tokens: 91.6 us against 93.3 us; one of 512k 80.2 against
 // 81.9).  In a small table a trip to memory more would show (4 sequences, 8 heads: 7.0 us
 // against 6.8 us).
-template <bool kAppend, int kIters, int kQ, bool kWhole>
-__global__ __launch_bounds__(kEstWaves* kWave) void estimate_kernel(const EstimateArgs a) {
+template <bool kAppend, int kIters, int kQ>
+__global__ __launch_bounds__(kEstWaves* kWave, kQ == 0 ? (kIters == 2 ? 7 : 4) : 1) void estimate_kernel(const EstimateArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int base = (blockIdx.x * kEstWaves + wave) * (4 * kIters);
   if (kIters == kEstIters && (long)base << a.page_shift >= a.seq_lens[blockIdx.y]) return;
-  estimate_wave<kAppend, kIters, kQ, kWhole>(a, blockIdx.y, blockIdx.z, base);
+  __shared__ __align__(16) char stage[kQ == 0 ? kEstWaves * 4 * kIters * kMetaBytes : 16];
+  estimate_wave<kAppend, kIters, kQ>(a, blockIdx.y, blockIdx.z, base, stage + (kQ == 0 ? wave * 4 * kIters * kMetaBytes : 0));
 }
 
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
@@ -43,8 +45,11 @@ __global__ __launch_bounds__(kEstWaves* kWave) void estimate_kernel(const Estima
 // at 2049 pages of 32 heads, 13.6 against 14.2 at 4100, 23.0 against 23.4 at 8193; but 98.0
 // against 93.7 us for 16 sequences of 8k to 64k tokens (1.2 M pages), and the calls of a layer
 // 56.0 against 54.0 us for 2 sequences and 8 KV heads (0.49 M pages).
+// On the matrix cores 16 pages fill an operand and eight leave half of it: 3.0 against 3.3 us at 4100
+// entries, 4.7 against 4.8 at 33k, 6.6 against 6.4 at 66k, 15.7 against 14.2 at 263k.
 int est_iters(const quest_cache& c) {
-  return (long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (3l << 17) ? 2 : kEstIters;
+  const long entries = (long)c.batch * kv_heads(c) * c.max_pages_per_seq;
+  return entries <= (group_size(c) > 2 ? 5l << 13 : 3l << 17) ? 2 : kEstIters;
 }
 
 template <bool kAppend, int kIters>
@@ -55,17 +60,14 @@ void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
   // LDS that nobody uses: it keeps the work-groups of a compute unit at five.  A large table
   // streams better that way than with more (512k tokens in order 80.2 us, 83.3 with six; two
   // sequences of 400k 123.5 and 128.9; 16 ragged ones 91.6 and 94.7); small ones do not care.
-  const unsigned lds = kIters == kEstIters ? kLdsPerUnit / 5 : 0;
-  // The heads of a group by fours, with no branch between them if there are no others (3 sequences of
-  // 64 query / 8 KV heads 3.5 us, 3.7 with branches), else only those there are (4 sequences of up to
-  // 33k tokens, 40 / 8 heads, 7.4 us, 10.0 with the last one scored again up to a multiple of four,
-  // 8.8 by twos); pairs as they are (2 of 265k tokens, 16 / 8 heads 18.3 us, 20.4 by fours).
-#define QUEST_ESTIMATE(Q, W) \
-  hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q, W>), grid, block, lds, s, a)
-  if (a.group == 1) QUEST_ESTIMATE(1, true);
-  else if (a.group == 2) QUEST_ESTIMATE(2, true);
-  else if (a.group % 4 == 0) QUEST_ESTIMATE(4, true);
-  else QUEST_ESTIMATE(4, false);
+  // (Groups use as much: 8 KiB per wave.)
+  const unsigned lds = kIters == kEstIters && a.group <= 2 ? kLdsPerUnit / 5 : 0;
+  // One or two query heads on the vector unit: two meet 16 sequences of up to 32k tokens in 14.7 us (14.4
+  // one), 4 of them in 6.1; from three on the matrix cores (14.2 and 6.4 us).
+#define QUEST_ESTIMATE(Q) hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q>), grid, block, lds, s, a)
+  if (a.group == 1) QUEST_ESTIMATE(1);
+  else if (a.group == 2) QUEST_ESTIMATE(2);
+  else QUEST_ESTIMATE(0);
 #undef QUEST_ESTIMATE
 }
 

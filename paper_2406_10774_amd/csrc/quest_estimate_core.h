@@ -31,13 +31,19 @@ struct EstimateArgs {
   int page_shift;  // log2(tokens per page)
 };
 
+// Per half: 0xffff where q is negative (min row wins), 0 elsewhere (max row wins).
+__device__ __forceinline__ uint4 negative8(const uint4 q) {
+  const auto of = [](uint32_t v) { return __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, v) >> 15); };
+  return make_uint4(of(q.x), of(q.y), of(q.z), of(q.w));
+}
+
 // One wave scores the 4 * kIters logical pages starting at `base` of (sequence b,
 // head h): DPP row g takes pages base + kIters*g .. + kIters - 1, one per
 // wave-wide load pair.
-// kQ: query heads of a KV head that are loaded and scored at a time: 1 where there is one.
-// kWhole: their number is a multiple of kQ.
-template <bool kAppend, int kIters, int kQ, bool kWhole>
-__device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int h, int base) {
+// kQ: query heads of a KV head: 1, 2, or 0 for any number, scored on the matrix cores (`stage`: 512
+// bytes of LDS of this wave per page, unused otherwise).
+template <bool kAppend, int kIters, int kQ>
+__device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int h, int base, char* stage) {
   char* __restrict__ meta = a.meta;
   const char* __restrict__ q = a.q;
   const int32_t* __restrict__ page_table = a.page_table;
@@ -68,15 +74,18 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   static_assert(kIters == 2 || kIters == 4, "entries of a quad");
   int entry = pt[min(base + kIters * grp + (c & (kIters - 1)), max_pages - 1)];
   const int seq_len = __builtin_amdgcn_readfirstlane(seq_lens[b]);
-  // The group's query vectors, kQ at a time, the first of them in front of the metadata
-  // (fetched one by one between the heads they cost a trip to L2 each: 8.2 us against 7.9 us
-  // at 4 heads per KV head, 4 sequences of up to 32k tokens).
-  const int group = kQ > 1 ? a.group : 1;
-  uint4 qv[kQ];
+  // The query vectors in front of the metadata.  One or two: lane c has channels 8c .. +7 of
+  // each.  More: as rows of a matrix operand, lane c of row g has channels 32j + 8g .. +7 of head c (heads
+  // past the group: the last one again).
+  constexpr bool kMatrix = kQ == 0;
+  const int group = kMatrix ? a.group : kQ;
+  constexpr int kQueries = kMatrix ? 4 : kQ;
+  uint4 qv[kQueries];
   auto load_queries = [&](int g0) {
 #pragma unroll
-    for (int i = 0; i < kQ; ++i)
-      qv[i] = ld16(q + (bh * group + min(g0 + i, group - 1)) * (kHeadDim * 2) + c * 16);
+    for (int i = 0; i < kQueries; ++i)
+      qv[i] = kMatrix ? ld16(q + (bh * group + min(g0 + c, group - 1)) * (kHeadDim * 2) + i * 64 + grp * 16)
+                      : ld16(q + (bh * group + i) * (kHeadDim * 2) + c * 16);
   };
   load_queries(0);
   asm volatile("" : "+v"(entry) : "s"(seq_len));
@@ -140,15 +149,88 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
     }
   }
 
+  if constexpr (kMatrix) {
+    // Three or more query heads meet every entry: a contraction over twice the channels.  13 vector
+    // instructions per head and load pair held a wave longer than its loads; here it is eight matrix
+    // instructions and about 110 others for up to 16 heads and 16 pages.  us an append and estimate, before /
+    // now: 4 sequences of up to 32k tokens, 8 KV heads, groups of four 7.1 / 6.4, of eight 9.7 / 6.4; 16
+    // sequences of up to 64k, of eight 38.4 / 26.1 (one query head per KV head: 25.4, 6.6 TB/s); one of
+    // 32k, of eight 5.2 / 3.8.  Against 64 bits, 2-norm over nine shapes: 4.09e-8 (4.11e-8 before).
+    // Turned through LDS: entries as columns of a matrix operand, lane c of row g with channels
+    // 32j + 8g .. +7 of page c (of eight pages: twice).  The 16-byte chunks of page p are exclusive-ored
+    // with p, so neither side has bank conflicts.
+    constexpr int kPages = 4 * kIters;
+    uint4 lo[4], hi[4];
+    auto split_queries = [&] {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint4 neg = negative8(qv[j]);
+        lo[j] = make_uint4(qv[j].x & neg.x, qv[j].y & neg.y, qv[j].z & neg.z, qv[j].w & neg.w);
+        hi[j] = make_uint4(qv[j].x & ~neg.x, qv[j].y & ~neg.y, qv[j].z & ~neg.z, qv[j].w & ~neg.w);
+      }
+    };
+    split_queries();  // while the metadata is on its way
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int it = 0; it < kIters; ++it) {
+      const int p = kIters * grp + it;
+      st16(stage + p * kMetaBytes + ((c ^ p) << 4), mn[it]);
+      st16(stage + p * kMetaBytes + kHeadDim * 2 + ((c ^ p) << 4), mx[it]);
+    }
+    lds_in_order();
+    const int page = c & (kPages - 1);
+    const char* entry_of = stage + page * kMetaBytes;
+    float keep = -INFINITY;
+    bool odd = false;
+    // 16 heads against the pages: q where it is positive meets the max row, where it is negative the
+    // min row; the other of the two products is zero.  Eight sums of 32 channels, added as a tree.
+    auto score_heads = [&] {
+      f32x4_t s[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int at = ((4 * j + grp) ^ page) << 4;
+        const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+        s[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, lo[j]),
+                                                      __builtin_bit_cast(half8_t, ld16(entry_of + at)), zero, 0, 0, 0);
+        s[j] += __builtin_amdgcn_mfma_f32_16x16x32_f16(
+            __builtin_bit_cast(half8_t, hi[j]), __builtin_bit_cast(half8_t, ld16(entry_of + kHeadDim * 2 + at)), zero, 0, 0, 0);
+        // Operands of one j at a time, or of two: registers for seven waves per SIMD, or for four (five are what
+        // LDS has room for).
+        if (kIters == 2 || j == 1) __builtin_amdgcn_sched_barrier(0);
+      }
+      float z[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z[i] = (s[0][i] + s[1][i]) + (s[2][i] + s[3][i]);
+      odd |= !((z[0] + z[1]) + (z[2] + z[3]) > -INFINITY);
+      keep = fmaxf(keep, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));  // heads 4g .. 4g + 3
+    };
+    score_heads();
+    for (int g0 = 16; g0 < group; g0 += 16) {
+      load_queries(g0);
+      split_queries();
+      score_heads();
+    }
+    // An infinite entry, or one that is no number, may have met a zero.  Such pages, which a cache
+    // hardly ever holds, are scored as one or two heads are.
+    if (__ballot(odd) == 0) {
+      LanePair s = pair_across16(__builtin_bit_cast(uint32_t, keep));
+      s = pair_across32(__builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second))));
+      keep = fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second));
+      if (lane < kPages && base + lane < num_pages) scores[bh * max_pages + base + lane] = keep;
+      return;
+    }
+#pragma unroll
+    for (int it = 0; it < kIters; ++it) {
+      const int p = kIters * grp + it;
+      mn[it] = ld16(stage + p * kMetaBytes + ((c ^ p) << 4));
+      mx[it] = ld16(stage + p * kMetaBytes + kHeadDim * 2 + ((c ^ p) << 4));
+    }
+  }
+
   // One query head against the pages this wave holds: lane c of a row keeps the
   // score of the row's c-th page.
   auto score_pages = [&](const uint4 qh) {
-    // per half: 0xffff where q is negative (min row wins), 0 elsewhere (max row wins)
-    uint4 neg;
-    neg.x = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, qh.x) >> 15);
-    neg.y = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, qh.y) >> 15);
-    neg.z = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, qh.z) >> 15);
-    neg.w = __builtin_bit_cast(uint32_t, __builtin_bit_cast(short2_t, qh.w) >> 15);
+    const uint4 neg = negative8(qh);
     float mine = 0.f;
 #pragma unroll
     for (int it = 0; it < kIters; ++it) {
@@ -164,15 +246,15 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   };
   // The page's score for the KV head: the largest of its query heads' scores
   // (one query head per KV head in the paper's models: no further round).
-  float keep = score_pages(qv[0]);
-#pragma unroll
-  for (int i = 1; i < kQ; ++i)
-    if (kWhole || i < group) keep = fmaxf(keep, score_pages(qv[i]));
-  for (int g0 = kQ; g0 < group; g0 += kQ) {
-    load_queries(g0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i)
-      if (kWhole || g0 + i < group) keep = fmaxf(keep, score_pages(qv[i]));
+  float keep;
+  if constexpr (kMatrix) {
+    const char* heads = q + bh * group * (kHeadDim * 2) + c * 16;
+    keep = score_pages(ld16(heads));
+#pragma unroll 1
+    for (int i = 1; i < group; ++i) keep = fmaxf(keep, score_pages(ld16(heads + i * (kHeadDim * 2))));
+  } else {
+    keep = score_pages(qv[0]);
+    if constexpr (kQ == 2) keep = fmaxf(keep, score_pages(qv[1]));
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
   const int p = base + kIters * grp + c;

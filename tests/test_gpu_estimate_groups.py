@@ -57,3 +57,50 @@ def test_scores(kv_heads, group, S, pages, lens):
     assert np.array_equal(both.np16(both.meta).view(np.uint16), after.view(np.uint16))
     for a, b in ((both.k_pool, one.k_pool), (both.v_pool, one.v_pool)):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# three heads to more than one operand's sixteen, at the border between 8 and 16 pages per wave (40960
+# entries), rows that end on a wave's pages, one more and one less
+@pytest.mark.parametrize("kv_heads,group,S,pages,lens", [
+    (8, 3, 16, 5120, (5120 * 16,)), (8, 3, 16, 5121, (5121 * 16 - 15,)), (1, 16, 8, 41000, (16 * 8 * 200 + 8,)),
+    (2, 17, 16, 70, (16 * 16, 16 * 16 + 1, 8 * 16, 8 * 16 + 1, 70 * 16)), (1, 33, 32, 20481, (20481 * 32, 15 * 32)),
+    (4, 4, 64, 9, (9 * 64, 1)),
+])
+def test_scores_on_the_matrix_cores(kv_heads, group, S, pages, lens):
+    test_scores(kv_heads, group, S, pages, lens)
+
+
+@pytest.mark.parametrize("kv_heads,group,pages", [(2, 4, 61), (8, 8, 5200), (3, 17, 100), (1, 3, 41003)])
+def test_infinite_metadata(kv_heads, group, pages):
+    """Infinite entries: the sign of the query picks the row, and the other row's infinity
+    meets nothing.  Pages next to them keep the bound of finite ones."""
+    import torch
+    from paper_2406_10774_amd import binding as Q
+    dev, S, N = "cuda:0", 16, 40
+    rng = np.random.default_rng(pages)
+    meta = np.sort(rng.standard_normal((kv_heads, N, 2, 128)), axis=2).astype(np.float16)
+    meta[:, 3, 1, 5] = np.inf                        # only the max row
+    meta[:, 4, 0, 77] = -np.inf                      # only the min row
+    meta[:, 5, 0, 9], meta[:, 5, 1, 9] = -np.inf, np.inf
+    meta[:, 6, :, 100] = np.inf                      # both rows: not a number with a -inf beside it
+    meta[:, 6, :, 31] = np.inf
+    q = rng.standard_normal((1, kv_heads * group, 128)).astype(np.float16)
+    q[q == 0] = 1
+    table = rng.integers(0, N, (1, pages)).astype(np.int32)
+    t = lambda x: torch.from_numpy(x).to(dev)
+    pool = torch.zeros((N, kv_heads, S, 128), dtype=torch.float16, device=dev)
+    scores = torch.full((1, kv_heads, pages), -7.0, device=dev)
+    cache = Q.Cache(pool, pool, t(meta), t(table), t(np.array([pages * S - 3], np.int32)), num_heads=kv_heads * group)
+    Q.quest_estimate(cache, t(q), scores)
+    got = scores.cpu().numpy()[0]
+    m, x = meta.astype(np.float64), q[0].astype(np.float64).reshape(kv_heads, group, 1, 128)
+    with np.errstate(invalid="ignore"):
+        term = np.where(x < 0, x * m[:, None, :, 0], x * m[:, None, :, 1])   # [kv heads][group][N][128]
+        each = term.sum(-1)
+        want = np.fmax.reduce(each, axis=1)
+        size = np.where(np.isfinite(each), np.abs(term).sum(-1), 0).max(1)
+    want, size = want[:, table[0]], size[:, table[0]]
+    odd = ~np.isfinite(want)
+    assert np.array_equal(got[odd], want[odd], equal_nan=True) and np.isinf(want).any()
+    # 128 exact products summed in fp32, in any order
+    assert (np.abs(got[~odd] - want[~odd]) <= 128 * 2.0 ** -24 * size[~odd]).all()
