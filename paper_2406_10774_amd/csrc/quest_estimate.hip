@@ -3,8 +3,8 @@
 //
 // Since m <= M per channel, max(q m, q M) is q * (q >= 0 ? M : m) exactly: the
 // sign of q picks the row, done once per wave as a bit mask, and the products
-// go through v_dot2_f32_f16 (fp16 products are exact in fp32, fp32 sum), or, of three and
-// more query heads per KV head, through matrix products with q split by its sign.
+// go through v_dot2_f32_f16 (fp16 products are exact in fp32, fp32 sum), or, where several
+// query heads share a KV head, through matrix products with q split by its sign.
 //
 // One wavefront owns (head, block of 8 or 16 consecutive logical pages).  A 16-lane
 // DPP row reads one metadata entry: 16 B per lane of the min row, then 16 B per
@@ -40,6 +40,14 @@ __global__ __launch_bounds__(kEstWaves* kWave, kQ == 0 ? (kIters == 2 ? 7 : 4) :
   estimate_wave<kAppend, kIters, kQ>(a, blockIdx.y, blockIdx.z, base, stage + (kQ == 0 ? wave * 4 * kIters * kMetaBytes : 0));
 }
 
+// The matrix cores score groups.  Two query heads meet the metadata of 16 sequences of up to 32k tokens
+// in 14.7 us on the vector unit (one in 14.4), of 4 sequences in 6.1: no longer than four on the matrix
+// cores (14.2 and 6.4).  Nor do three or four over small tables, where the turn through LDS shows: 2.85
+// against 2.98 us at 8100 entries, but 4.08 against 3.75 at 16400.
+bool on_matrix_cores(const quest_cache& c) {
+  return group_size(c) > ((long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (3l << 12) ? 4 : 2);
+}
+
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
 // table is scanned faster by twice as many waves of half the size: 8.3 us against 8.75 us
 // at 2049 pages of 32 heads, 13.6 against 14.2 at 4100, 23.0 against 23.4 at 8193; but 98.0
@@ -60,14 +68,19 @@ void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
   // LDS that nobody uses: it keeps the work-groups of a compute unit at five.  A large table
   // streams better that way than with more (512k tokens in order 80.2 us, 83.3 with six; two
   // sequences of 400k 123.5 and 128.9; 16 ragged ones 91.6 and 94.7); small ones do not care.
-  // (Groups use as much: 8 KiB per wave.)
+  // (On the matrix cores they use as much: 8 KiB per wave.)
   const unsigned lds = kIters == kEstIters && a.group <= 2 ? kLdsPerUnit / 5 : 0;
-  // One or two query heads on the vector unit: two meet 16 sequences of up to 32k tokens in 14.7 us (14.4
-  // one), 4 of them in 6.1; from three on the matrix cores (14.2 and 6.4 us).
 #define QUEST_ESTIMATE(Q) hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q>), grid, block, lds, s, a)
   if (a.group == 1) QUEST_ESTIMATE(1);
   else if (a.group == 2) QUEST_ESTIMATE(2);
-  else QUEST_ESTIMATE(0);
+  else if (kIters == 2 && !on_matrix_cores(c)) {
+    if constexpr (kIters == 2) {
+      if (a.group == 3) QUEST_ESTIMATE(3);
+      else QUEST_ESTIMATE(4);
+    }
+  } else {
+    QUEST_ESTIMATE(0);
+  }
 #undef QUEST_ESTIMATE
 }
 

@@ -40,7 +40,7 @@ __device__ __forceinline__ uint4 negative8(const uint4 q) {
 // One wave scores the 4 * kIters logical pages starting at `base` of (sequence b,
 // head h): DPP row g takes pages base + kIters*g .. + kIters - 1, one per
 // wave-wide load pair.
-// kQ: query heads of a KV head: 1, 2, or 0 for any number, scored on the matrix cores (`stage`: 512
+// kQ: query heads of a KV head: 1 to 4, or 0 for any number, scored on the matrix cores (`stage`: 512
 // bytes of LDS of this wave per page, unused otherwise).
 template <bool kAppend, int kIters, int kQ>
 __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int h, int base, char* stage) {
@@ -74,8 +74,8 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   static_assert(kIters == 2 || kIters == 4, "entries of a quad");
   int entry = pt[min(base + kIters * grp + (c & (kIters - 1)), max_pages - 1)];
   const int seq_len = __builtin_amdgcn_readfirstlane(seq_lens[b]);
-  // The query vectors in front of the metadata.  One or two: lane c has channels 8c .. +7 of
-  // each.  More: as rows of a matrix operand, lane c of row g has channels 32j + 8g .. +7 of head c (heads
+  // The query vectors in front of the metadata.  Up to four: lane c has channels 8c .. +7 of
+  // each.  Any number: as rows of a matrix operand, lane c of row g has channels 32j + 8g .. +7 of head c (heads
   // past the group: the last one again).
   constexpr bool kMatrix = kQ == 0;
   const int group = kMatrix ? a.group : kQ;
@@ -150,7 +150,7 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   }
 
   if constexpr (kMatrix) {
-    // Three or more query heads meet every entry: a contraction over twice the channels.  13 vector
+    // Several query heads meet every entry: a contraction over twice the channels.  13 vector
     // instructions per head and load pair held a wave longer than its loads; here it is eight matrix
     // instructions and about 110 others for up to 16 heads and 16 pages.  us an append and estimate, before /
     // now: 4 sequences of up to 32k tokens, 8 KV heads, groups of four 7.1 / 6.4, of eight 9.7 / 6.4; 16
@@ -211,7 +211,7 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
       score_heads();
     }
     // An infinite entry, or one that is no number, may have met a zero.  Such pages, which a cache
-    // hardly ever holds, are scored as one or two heads are.
+    // hardly ever holds, are scored head by head.
     if (__ballot(odd) == 0) {
       LanePair s = pair_across16(__builtin_bit_cast(uint32_t, keep));
       s = pair_across32(__builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second))));
@@ -254,7 +254,8 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
     for (int i = 1; i < group; ++i) keep = fmaxf(keep, score_pages(ld16(heads + i * (kHeadDim * 2))));
   } else {
     keep = score_pages(qv[0]);
-    if constexpr (kQ == 2) keep = fmaxf(keep, score_pages(qv[1]));
+#pragma unroll
+    for (int i = 1; i < kQ; ++i) keep = fmaxf(keep, score_pages(qv[i]));
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
   const int p = base + kIters * grp + c;

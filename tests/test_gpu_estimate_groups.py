@@ -59,18 +59,19 @@ def test_scores(kv_heads, group, S, pages, lens):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-# three heads to more than one operand's sixteen, at the border between 8 and 16 pages per wave (40960
-# entries), rows that end on a wave's pages, one more and one less
+# three heads to more than one operand's sixteen, at the border to the vector unit (12288 entries) and
+# between 8 and 16 pages per wave (40960), rows that end on a wave's pages, one more and one less
 @pytest.mark.parametrize("kv_heads,group,S,pages,lens", [
     (8, 3, 16, 5120, (5120 * 16,)), (8, 3, 16, 5121, (5121 * 16 - 15,)), (1, 16, 8, 41000, (16 * 8 * 200 + 8,)),
     (2, 17, 16, 70, (16 * 16, 16 * 16 + 1, 8 * 16, 8 * 16 + 1, 70 * 16)), (1, 33, 32, 20481, (20481 * 32, 15 * 32)),
-    (4, 4, 64, 9, (9 * 64, 1)),
+    (4, 4, 64, 9, (9 * 64, 1)), (8, 3, 16, 1536, (1536 * 16 - 9,)), (8, 3, 16, 1537, (1537 * 16,)),
+    (8, 4, 16, 384, (384 * 16, 5, 100 * 16, 129)), (8, 4, 16, 385, (385 * 16, 5, 100 * 16, 129)),
 ])
 def test_scores_on_the_matrix_cores(kv_heads, group, S, pages, lens):
     test_scores(kv_heads, group, S, pages, lens)
 
 
-@pytest.mark.parametrize("kv_heads,group,pages", [(2, 4, 61), (8, 8, 5200), (3, 17, 100), (1, 3, 41003)])
+@pytest.mark.parametrize("kv_heads,group,pages", [(2, 4, 61), (8, 8, 5200), (3, 17, 100), (1, 3, 41003), (8, 4, 1600)])
 def test_infinite_metadata(kv_heads, group, pages):
     """Infinite entries: the sign of the query picks the row, and the other row's infinity
     meets nothing.  Pages next to them keep the bound of finite ones."""
