@@ -135,7 +135,10 @@ __global__ __launch_bounds__(kBigThreads) void topk_big_kernel(
 // positions in the candidate row order like pages do: equal scores still go to the
 // lower page, page 0 is candidate 0 and the newest page is the last candidate whenever
 // the policy flags keep them in their chunks.
-constexpr int kChunkItems = 4;  // keys per thread: 16 waves x 4 keys are 0.3 us faster than 8 waves x 8 keys
+// Threads: 4 keys each of a chunk of 2048 pages (512 threads; a step of 8 heads, 500k tokens, 31.2 us, 31.5
+// with 8 keys each), 8 each of 4096 (512 threads: 32 heads, 512k tokens, 103.5 us a step, 104.5 with 1024
+// threads, of which two work-groups fill a compute unit).
+constexpr int kChunkThreads = 512;
 
 struct ChunkOfRow {
   int page_shift, policy, chunk, chunk_pages;
@@ -149,7 +152,7 @@ struct ChunkOfRow {
   }
 };
 
-template <int kThreads>
+template <int kThreads, int kChunkItems>
 __global__ __launch_bounds__(kThreads) void topk_chunk_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ seq_lens,
     float* __restrict__ cand_score, int32_t* __restrict__ cand_page, int num_heads, int max_pages,
@@ -276,13 +279,13 @@ int launch_topk_chunks(const quest_cache& c, const float* scores, int k_pages, i
   out->page = cand_page;
   const dim3 grid(kv_heads(c), chunks, c.batch);
 #define QUEST_CHUNKS(T)                                                                           \
-  hipLaunchKernelGGL((topk_chunk_kernel<T>), grid, dim3(T), 0, s, scores, c.seq_lens, cand_score, \
-                     cand_page, kv_heads(c), c.max_pages_per_seq, k_pages, chunks,                \
-                     page_shift_of(c.page_size), c.flags)
+  hipLaunchKernelGGL((topk_chunk_kernel<kChunkThreads, (T) / kChunkThreads>), grid,               \
+                     dim3(kChunkThreads), 0, s, scores, c.seq_lens, cand_score, cand_page,        \
+                     kv_heads(c), c.max_pages_per_seq, k_pages, chunks, page_shift_of(c.page_size), c.flags)
   if (chunk_pages == kSmallChunk)
-    QUEST_CHUNKS(kSmallChunk / kChunkItems);
+    QUEST_CHUNKS(kSmallChunk);
   else
-    QUEST_CHUNKS(kLargeChunk / kChunkItems);
+    QUEST_CHUNKS(kLargeChunk);
 #undef QUEST_CHUNKS
   return check_launch("quest_select_decode");
 }
