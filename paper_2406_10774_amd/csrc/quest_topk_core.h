@@ -50,8 +50,14 @@ __device__ __forceinline__ uint32_t wave_max_in_last(uint32_t v) {
 struct BinHit {
   int bin, before, count;
 };
+template <int kCopies = 1>  // the histogram is the sum of that many
 __device__ __forceinline__ BinHit find_bin(const uint32_t* hist, int need, int lane) {
-  const int4 c = reinterpret_cast<const int4*>(hist)[lane];
+  int4 c = reinterpret_cast<const int4*>(hist)[lane];
+#pragma unroll
+  for (int i = 1; i < kCopies; ++i) {
+    const int4 more = reinterpret_cast<const int4*>(hist)[i * kWave + lane];
+    c.x += more.x, c.y += more.y, c.z += more.z, c.w += more.w;
+  }
   const int tot = c.x + c.y + c.z + c.w;
   const int incl = wave_incl_scan(tot);
   const int b0 = incl - tot, b1 = b0 + c.x, b2 = b1 + c.y, b3 = b2 + c.z;
@@ -88,6 +94,13 @@ __device__ __forceinline__ ForcedPages forced_pages(int policy, int num_pages) {
 // Keys left in the threshold bin that are ranked directly, one per lane.
 constexpr int kFewKeys = 64;
 
+// Digits and places beside the keys are three registers a key.  Where those would spill, the keys
+// alone tell all: radix digits of the key from the first pass on, and a place is handed out when a
+// key turns out to be of the last bin.  32 rows of 65535 scores, K = 64: 20.7 us, 42.3 with digits and
+// places partly in scratch memory; 512 rows 53 and 230; 49152 scores 16.5 and 28.0, 512 rows 39 and 129.
+// 33 keys per thread fit (12.6 us; 12.7 to 15.8 from the keys alone).
+constexpr bool keys_only(int threads, int items) { return 3 * items > 128 * 1024 / threads - 24; }
+
 template <int kThreads, int kItems>
 struct TopkShared {
   static constexpr int kWaves = kThreads / kWave;
@@ -95,12 +108,19 @@ struct TopkShared {
   static constexpr int kRunsPerLane = kRuns <= 64 ? 1 : kRuns <= 128 ? 2 : kRuns <= 256 ? 4 : kRuns <= 512 ? 8 : 16;
   static_assert(kItems <= kWave, "a lane per item");
   static_assert(kRuns <= kWave * kRunsPerLane && kWaves % kRunsPerLane == 0, "a wave's runs at one place of the lanes'");
+  // Leading bits put many keys into the same few bins, and lanes with the same bin wait for each
+  // other: a histogram for each quarter of the lanes (32 rows of 65535 scores on both sides of zero,
+  // K = 32767: 61 us, 96 with one histogram).
+  static constexpr int kCopies = keys_only(kThreads, kItems) ? 4 : 1;
+  static constexpr int kSpare = 256 * kCopies;
+  static_assert(kSpare <= kThreads, "cleared by one store a thread");
   // Entries for lanes that have nothing to write stand behind the others: a store or an atomic
   // without a condition is cheaper than a branch around it.
-  uint32_t hist[256 + kWave];
+  uint32_t hist[kSpare + kWave];
   uint32_t few_key[kFewKeys + kWave], few_page[kFewKeys + kWave];  // the threshold bin's, in any order
   uint2 range[kWaves];                       // lower bound of the threshold (inverted) and largest key, by wave
   uint32_t count[kWave * kRunsPerLane];      // of each run: keys in front of the threshold bin (see topk_block_put)
+  uint32_t few_count;                        // keys of the bin that have their place (if there are keys only)
 };
 
 // What a row of scores is, given the sequence length: its number of valid entries and
@@ -151,69 +171,18 @@ __device__ __forceinline__ void set_lane(uint32_t& v, int lane, uint32_t value) 
 }
 __device__ __forceinline__ bool in_mask(LaneMask mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-// Selection for one row of scores by one work-group of kThreads threads (all of
-// them must call).  shape(seq_len) describes the row (it has room for max_pages
-// entries); put(selected, position, page, j, score) receives the list from the threads that pass
-// selected (the others' arguments mean nothing, but position is at least 0): positions 0 .. k_pages-1,
-// pages ascending, -1 past the K_b selected ones; j >= 0 says that the page is the calling
-// thread's j-th one (page == threadIdx.x + j * kThreads) and `score` its score as loaded,
-// j < 0 that it is not (then `score` carries nothing).  A put that needs per-page data
-// takes it from what the thread already holds whenever j >= 0: a load issued from inside
-// put is waited for before the next page's put starts.
-// after_loads() is called once, right after the loads of the scores have been issued:
-// the place for loads the caller wants in flight behind them.
-template <int kThreads, int kItems, class Put, class Shape, class AfterLoads>
-__device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
-                                               const float* __restrict__ row,
-                                               const int32_t* __restrict__ seq_len_ptr,
-                                               int max_pages, int k_pages, Put put,
-                                               int32_t* __restrict__ k_eff_slot, Shape shape,
-                                               AfterLoads after_loads) {
-  using Shared = TopkShared<kThreads, kItems>;
+// The part of topk_block_put that ranks: of the keys of pages first .. end - 1 the `need`
+// best go to put at positions from `first` on.
+template <int kThreads, int kItems, class Put>
+__device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, const float (&raw)[kItems],
+                                          int first, int end, int need, Put put) {
   constexpr int kWaves = kThreads / kWave;
+  using Shared = TopkShared<kThreads, kItems>;
+  constexpr bool kKeysOnly = keys_only(kThreads, kItems);
+  constexpr int kCopies = kKeysOnly ? Shared::kCopies : 1;
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // issue every load first: this thread's scores (entries past the valid pages
-  // are inside the row, so reading them is safe; they are masked below) and the
-  // sequence length
-  float raw[kItems];
-  const uint32_t last_offset = ((uint32_t)max_pages - 1u) * (uint32_t)sizeof(float);
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    // clamped, not predicated: the loads stay independent and all in flight at once
-    const uint32_t at = min((uint32_t)(tid + j * kThreads) * (uint32_t)sizeof(float), last_offset);
-    raw[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + at);
-  }
-  const int seq_len = __builtin_amdgcn_readfirstlane(*seq_len_ptr);
-  after_loads();
-
-  if (tid < 256) sm.hist[tid] = 0;
-  if (wave == 0) sm.few_key[lane] = 0xffffffffu;
-
-  const RowShape row_shape = shape(seq_len);
-  const int num_pages = min(row_shape.num_pages, max_pages);  // whatever the length says: no entry past the row
-  const int K = min(k_pages, num_pages);
-  if (tid == 0 && k_eff_slot != nullptr) *k_eff_slot = K;
-  if (K == num_pages) {  // everything is selected: identity list, padded with -1
-    for (int i = tid; i < k_pages; i += kThreads) put(true, i, i < K ? i : -1, -1, 0.f);
-    return;
-  }
-
-  // Pages that are kept whatever their score rank above every score and, like
-  // equal scores, by page index: they are no keys, take their places off the count,
-  // and are the first and the last entry of the list.
-  const ForcedPages forced = forced_pages(row_shape.policy, num_pages);
-  if (forced.count >= K) {  // K is 1 or 2 here: the list is the forced pages, lowest first
-    if (tid == 0) {
-      put(true, 0, forced.first ? 0 : num_pages - 1, -1, 0.f);
-      if (K == 2) put(true, 1, num_pages - 1, -1, 0.f);
-    }
-    return;
-  }
-  const int first = forced.first, end = num_pages - (int)forced.newest;  // the keys: pages first .. end - 1
-  int need = K - forced.count;  // how many of them the list takes, at least one
 
   // ---- A lower bound of the need-th largest key: the smallest of the largest keys of any
   // `need` or more disjoint sets of pages.  The sets are the pages of a thread, or of 2, 4,
@@ -289,52 +258,66 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
   // need-th lies, and then `need` of the keys in it: 5 to 50 with the bound above, few enough to
   // rank directly.
   const uint32_t range = hi - lo;
-  const float hi_score = score_of(hi), bins = 256.f * __builtin_amdgcn_rcpf(hi_score - score_of(lo));
-  const float hi_bins = hi_score * bins;
   uint32_t digit[kItems];  // the bin; behind all bins for what does not count
   uint32_t slot[kItems];   // a key's place among those of its bin, in any order
+  BinHit hit = {0, 0, 0};
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    key[j] = hi - key[j];  // 0: the best; what is no key ranks behind every key
-    const float x = __builtin_fmaf(raw[j], -bins, hi_bins);
-    uint32_t bin;
-    asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(x));  // below 0 and NaN: 0; too large: the largest
-    digit[j] = key[j] <= range ? min(bin, 255u) : 256u + lane;
-    slot[j] = atomicAdd(&sm.hist[digit[j]], 1u);
+  for (int j = 0; j < kItems; ++j) key[j] = hi - key[j];  // 0: the best; what is no key ranks behind every key
+  if constexpr (!kKeysOnly) {
+    const float hi_score = score_of(hi), bins = 256.f * __builtin_amdgcn_rcpf(hi_score - score_of(lo));
+    const float hi_bins = hi_score * bins;
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      const float x = __builtin_fmaf(raw[j], -bins, hi_bins);
+      uint32_t bin;
+      asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(x));  // below 0 and NaN: 0; too large: the largest
+      digit[j] = key[j] <= range ? min(bin, 255u) : Shared::kSpare + lane;
+      slot[j] = atomicAdd(&sm.hist[digit[j]], 1u);
+    }
+    __syncthreads();
+    hit = find_bin(sm.hist, need, lane);
+    need -= hit.before;
   }
-  __syncthreads();
-  BinHit hit = find_bin(sm.hist, need, lane);
-  need -= hit.before;
-  if (need != hit.count && hit.count > kFewKeys) {
+  // The bin's keys: those from `base` to `base + last` (with digits, of those in the bin).
+  uint32_t base = 0u, last = range;
+  if (kKeysOnly || (need != hit.count && hit.count > kFewKeys)) {
     // Radix select among the bin's keys, 8-bit digits from the leading bit of the range, until the
     // keys left are few or equal.  Then keys in front, in the last bin and behind are told apart.
     const uint32_t bin0 = hit.bin;
-    uint32_t base = 0u;
     int shift = range ? 32 - __builtin_clz(range) : 0;
+    bool clear = !kKeysOnly;
 #pragma unroll 1
     do {
-      const uint32_t last = shift > 0 ? 0xffffffffu >> (32 - shift) : 0u;  // of the keys left, relative to base
       shift = max(shift - 8, 0);
-      __syncthreads();
-      if (tid < 256) sm.hist[tid] = 0;
-      __syncthreads();
+      if (clear) {
+        __syncthreads();
+        if (tid < 256 * kCopies) sm.hist[tid] = 0;
+        __syncthreads();
+      }
+      clear = true;
 #pragma unroll
       for (int j = 0; j < kItems; ++j) {
         const uint32_t rest = key[j] - base;
-        slot[j] = atomicAdd(&sm.hist[digit[j] == bin0 && rest <= last ? rest >> shift : 256u + lane], 1u);
+        const bool counts = (kKeysOnly || digit[j] == bin0) && rest <= last;
+        const uint32_t bin = (rest >> shift) + (lane & (kCopies - 1)) * 256;
+        const uint32_t at = atomicAdd(&sm.hist[counts ? bin : Shared::kSpare + lane], 1u);
+        if constexpr (!kKeysOnly) slot[j] = at;
       }
       __syncthreads();
-      hit = find_bin(sm.hist, need, lane);
+      hit = find_bin<kCopies>(sm.hist, need, lane);
       base += (uint32_t)hit.bin << shift;
+      last = min(last - ((uint32_t)hit.bin << shift), (1u << shift) - 1u);
       need -= hit.before;
     } while (need != hit.count && hit.count > kFewKeys && shift > 0);
+    if constexpr (!kKeysOnly) {
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      const bool front = digit[j] < bin0 || (digit[j] == bin0 && key[j] < base);
-      const bool inside = digit[j] == bin0 && !front && (key[j] - base) >> shift == 0u;
-      digit[j] = front ? 0u : inside ? 1u : 2u;
+      for (int j = 0; j < kItems; ++j) {
+        const bool front = digit[j] < bin0 || (digit[j] == bin0 && key[j] < base);
+        const bool inside = digit[j] == bin0 && !front && key[j] - base <= last;
+        digit[j] = front ? 0u : inside ? 1u : 2u;
+      }
+      hit.bin = 1;
     }
-    hit.bin = 1;
   }
   const bool whole = need == hit.count;                    // the list takes all of the bin
   const int n_few = !whole && hit.count <= kFewKeys ? hit.count : 0;
@@ -343,22 +326,33 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
   // ---- List positions in page order.  A wave's j-th pages are a run of 64 consecutive ones,
   // runs follow each other by (j, wave); the runs' counts go through LDS, and so do, in
   // any order, the few keys of the bin with their pages.
-  const uint32_t front_end = whole ? hit.bin + 1 : hit.bin;
+  const uint32_t bin_at = kKeysOnly ? base : hit.bin, bin_end = kKeysOnly ? base + last + 1u : hit.bin + 1;
+  const uint32_t front_end = whole ? bin_end : bin_at;
+  const auto in_front = [&](int j) { return (kKeysOnly ? key[j] : digit[j]) < front_end; };
+  const auto in_bin = [&](int j) { return kKeysOnly ? key[j] - base <= last : digit[j] == bin_at; };
   uint32_t my_count = 0;
 #pragma unroll
   for (int j = 0; j < kItems; ++j)
-    set_lane(my_count, j, __popcll(__ballot(digit[j] < front_end)));
+    set_lane(my_count, j, __popcll(__ballot(in_front(j))));
   if (n_few > 0) {
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const uint32_t to = digit[j] == (uint32_t)hit.bin ? slot[j] : kFewKeys + lane;
-      sm.few_key[to] = key[j];
-      sm.few_page[to] = tid + j * kThreads;
+      if constexpr (kKeysOnly) {
+        if (in_bin(j)) {
+          const uint32_t to = atomicAdd(&sm.few_count, 1u);
+          sm.few_key[to] = key[j];
+          sm.few_page[to] = tid + j * kThreads;
+        }
+      } else {
+        const uint32_t to = in_bin(j) ? slot[j] : kFewKeys + lane;
+        sm.few_key[to] = key[j];
+        sm.few_page[to] = tid + j * kThreads;
+      }
     }
   } else if (ties) {  // rows have fewer than 2^16 pages
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const uint32_t n = __popcll(__ballot(digit[j] == (uint32_t)hit.bin));
+      const uint32_t n = __popcll(__ballot(in_bin(j)));
       my_count += lane == j ? n << 16 : 0u;
     }
   }
@@ -376,7 +370,7 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
   // equal keys stand at the threshold: then the lowest of their pages.  Every wave does it.
   uint32_t threshold = 0u;           // the last key that the list takes
   uint32_t few_page = 0xffffffffu;   // of a key that is taken
-  LaneMask taken = 0;
+  uint32_t last_page = 0u;           // the last page that it takes of keys equal to that one
   bool split_ties = false;
   if (n_few > 0) {
     const uint32_t mine = sm.few_key[lane];
@@ -394,6 +388,7 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
     }
     const LaneMask filled = ~0ull >> (kWave - n_few);
     const LaneMask at_threshold = filled & __ballot(better == (uint32_t)need - 1u);
+    LaneMask taken;
     if (__popcll(at_threshold) == 1) {
       threshold = __builtin_amdgcn_readlane((int)mine, __ffsll((long long)at_threshold) - 1);
       taken = filled & __ballot(mine <= threshold);
@@ -403,6 +398,7 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
       const uint32_t most = wave_max_in_last(in_mask(taken) ? better : 0u);
       int places = __builtin_amdgcn_readlane((int)most, kWave - 1);
       LaneMask left = taken & __ballot(better == (uint32_t)places);
+      threshold = __builtin_amdgcn_readlane((int)mine, __ffsll((long long)left) - 1);
       taken &= ~left;
       places = need - places;
 #pragma unroll 1
@@ -418,6 +414,8 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
         }
       }
       taken |= left;
+      last_page = wave_max_in_last(in_mask(taken) && mine == threshold ? few_page : 0u);
+      last_page = __builtin_amdgcn_readlane((int)last_page, kWave - 1);
     }
     few_page = in_mask(taken) ? few_page : 0xffffffffu;
   }
@@ -432,30 +430,99 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
     return __popcll(__ballot(few_page < (uint32_t)(j * kThreads + wave * kWave)));
   };
   if (!split_ties && !ties) {
-    const uint32_t upto = whole ? (uint32_t)hit.bin : threshold;
+    const uint32_t upto = whole ? bin_end - 1u : threshold;
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const LaneMask sel = __ballot((whole ? digit[j] : key[j]) <= upto);
+      const LaneMask sel = __ballot((whole && !kKeysOnly ? digit[j] : key[j]) <= upto);
       const int at = (int)front_before(j) + few_before(j) + first;
       put(in_mask(sel), lanes_before(sel, at), tid + j * kThreads, j, raw[j]);
     }
   } else {
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const LaneMask equal = __ballot(digit[j] == (uint32_t)hit.bin);
-      LaneMask sel = __ballot(digit[j] < front_end);
+      LaneMask sel;
       const uint32_t b = front_before(j);  // with ties: and the equal keys before, in the upper half
       int at = (int)(b & 0xffffu) + few_before(j) + first;
       if (split_ties) {
-        sel |= equal & __ballot((taken >> (slot[j] & 63u)) & 1u);
+        const uint32_t page = tid + j * kThreads;
+        sel = __ballot(key[j] < threshold || (key[j] == threshold && page <= last_page));
       } else {
+        const LaneMask equal = __ballot(in_bin(j));
         const int ties_before = (int)(b >> 16);
-        sel |= equal & __ballot(lanes_before(equal, ties_before) < need);
+        sel = __ballot(in_front(j)) | (equal & __ballot(lanes_before(equal, ties_before) < need));
         at += min(ties_before, need);
       }
       put(in_mask(sel), lanes_before(sel, at), tid + j * kThreads, j, raw[j]);
     }
   }
+}
+
+// Selection for one row of scores by one work-group of kThreads threads (all of
+// them must call).  shape(seq_len) describes the row (it has room for max_pages
+// entries); put(selected, position, page, j, score) receives the list from the threads that pass
+// selected (the others' arguments mean nothing, but position is at least 0): positions 0 .. k_pages-1,
+// pages ascending, -1 past the K_b selected ones; j >= 0 says that the page is the calling
+// thread's j-th one (page == threadIdx.x + j * kThreads) and `score` its score as loaded,
+// j < 0 that it is not (then `score` carries nothing).  A put that needs per-page data
+// takes it from what the thread already holds whenever j >= 0: a load issued from inside
+// put is waited for before the next page's put starts.
+// after_loads() is called once, right after the loads of the scores have been issued:
+// the place for loads the caller wants in flight behind them.
+template <int kThreads, int kItems, class Put, class Shape, class AfterLoads>
+__device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
+                                               const float* __restrict__ row,
+                                               const int32_t* __restrict__ seq_len_ptr,
+                                               int max_pages, int k_pages, Put put,
+                                               int32_t* __restrict__ k_eff_slot, Shape shape,
+                                               AfterLoads after_loads) {
+  using Shared = TopkShared<kThreads, kItems>;
+  const int tid = threadIdx.x;
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // issue every load first: this thread's scores (entries past the valid pages
+  // are inside the row, so reading them is safe; they are masked below) and the
+  // sequence length
+  float raw[kItems];
+  const uint32_t last_offset = ((uint32_t)max_pages - 1u) * (uint32_t)sizeof(float);
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    // clamped, not predicated: the loads stay independent and all in flight at once
+    const uint32_t at = min((uint32_t)(tid + j * kThreads) * (uint32_t)sizeof(float), last_offset);
+    raw[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + at);
+  }
+  const int seq_len = __builtin_amdgcn_readfirstlane(*seq_len_ptr);
+  after_loads();
+
+  if (tid < Shared::kSpare) sm.hist[tid] = 0;
+  if (wave == 0) sm.few_key[lane] = 0xffffffffu;
+  if constexpr (Shared::kCopies > 1)
+    if (tid == 0) sm.few_count = 0;
+
+  const RowShape row_shape = shape(seq_len);
+  const int num_pages = min(row_shape.num_pages, max_pages);  // whatever the length says: no entry past the row
+  const int K = min(k_pages, num_pages);
+  if (tid == 0 && k_eff_slot != nullptr) *k_eff_slot = K;
+  if (K == num_pages) {  // everything is selected: identity list, padded with -1
+    for (int i = tid; i < k_pages; i += kThreads) put(true, i, i < K ? i : -1, -1, 0.f);
+    return;
+  }
+
+  // Pages that are kept whatever their score rank above every score and, like
+  // equal scores, by page index: they are no keys, take their places off the count,
+  // and are the first and the last entry of the list.
+  const ForcedPages forced = forced_pages(row_shape.policy, num_pages);
+  if (forced.count >= K) {  // K is 1 or 2 here: the list is the forced pages, lowest first
+    if (tid == 0) {
+      put(true, 0, forced.first ? 0 : num_pages - 1, -1, 0.f);
+      if (K == 2) put(true, 1, num_pages - 1, -1, 0.f);
+    }
+    return;
+  }
+  const int first = forced.first, end = num_pages - (int)forced.newest;  // the keys: pages first .. end - 1
+  const int need = K - forced.count;  // how many of them the list takes, at least one
+
+  topk_rank<kThreads, kItems>(sm, raw, first, end, need, put);
   if (forced.count > 0) {
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
