@@ -171,14 +171,14 @@ __device__ __forceinline__ void set_lane(uint32_t& v, int lane, uint32_t value) 
 }
 __device__ __forceinline__ bool in_mask(LaneMask mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-// The part of topk_block_put that ranks: of the keys of pages first .. end - 1 the `need`
-// best go to put at positions from `first` on.
-template <int kThreads, int kItems, class Put>
+// The part of topk_block_put that ranks: of the keys of pages first .. end - 1, all among the first
+// kUsed pages of each thread, the `need` best go to put at positions from `first` on.
+template <int kThreads, int kItems, int kUsed, class Put>
 __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, const float (&raw)[kItems],
                                           int first, int end, int need, Put put) {
   constexpr int kWaves = kThreads / kWave;
   using Shared = TopkShared<kThreads, kItems>;
-  constexpr bool kKeysOnly = keys_only(kThreads, kItems);
+  constexpr bool kKeysOnly = keys_only(kThreads, kUsed);
   constexpr int kCopies = kKeysOnly ? Shared::kCopies : 1;
   const int tid = threadIdx.x;
   const int lane = lane_id();
@@ -189,10 +189,10 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
   // .. 16 adjacent ones, or 2, 4, .. 16 equal parts of a thread's, whichever leave just enough of
   // them; a thread's pages lie kThreads apart, so every set samples the whole context.  Few
   // keys pass the bound (650 to 1500 of 8193 for 256).
-  constexpr int kClasses = kItems >= 16 ? 16 : kItems >= 8 ? 8 : kItems >= 4 ? 4 : kItems >= 2 ? 2 : 1;
-  uint32_t key[kItems], best[kClasses];  // (key 0: none)
+  constexpr int kClasses = kUsed >= 16 ? 16 : kUsed >= 8 ? 8 : kUsed >= 4 ? 4 : kUsed >= 2 ? 2 : 1;
+  uint32_t key[kUsed], best[kClasses];  // (key 0: none)
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) {
+  for (int j = 0; j < kUsed; ++j) {
     const bool is_key = tid < end - j * kThreads && (j > 0 || tid >= first);
     key[j] = is_key ? score_key(raw[j]) : 0u;
     best[j % kClasses] = j < kClasses ? key[j] : max(best[j % kClasses], key[j]);
@@ -238,7 +238,7 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
     parts(std::integral_constant<int, 16>{});
   } else {  // as many pages as that: the smallest key
 #pragma unroll
-    for (int j = 0; j < kItems; ++j)
+    for (int j = 0; j < kUsed; ++j)
       if (key[j] > 0u) lo = min(lo, key[j]);
   }
   const uint2 reach = make_uint2(wave_max_in_last(~lo), wave_max_in_last(hi));
@@ -258,16 +258,16 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
   // need-th lies, and then `need` of the keys in it: 5 to 50 with the bound above, few enough to
   // rank directly.
   const uint32_t range = hi - lo;
-  uint32_t digit[kItems];  // the bin; behind all bins for what does not count
-  uint32_t slot[kItems];   // a key's place among those of its bin, in any order
+  uint32_t digit[kUsed];  // the bin; behind all bins for what does not count
+  uint32_t slot[kUsed];   // a key's place among those of its bin, in any order
   BinHit hit = {0, 0, 0};
 #pragma unroll
-  for (int j = 0; j < kItems; ++j) key[j] = hi - key[j];  // 0: the best; what is no key ranks behind every key
+  for (int j = 0; j < kUsed; ++j) key[j] = hi - key[j];  // 0: the best; what is no key ranks behind every key
   if constexpr (!kKeysOnly) {
     const float hi_score = score_of(hi), bins = 256.f * __builtin_amdgcn_rcpf(hi_score - score_of(lo));
     const float hi_bins = hi_score * bins;
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < kUsed; ++j) {
       const float x = __builtin_fmaf(raw[j], -bins, hi_bins);
       uint32_t bin;
       asm("v_cvt_u32_f32 %0, %1" : "=v"(bin) : "v"(x));  // below 0 and NaN: 0; too large: the largest
@@ -296,7 +296,7 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
       }
       clear = true;
 #pragma unroll
-      for (int j = 0; j < kItems; ++j) {
+      for (int j = 0; j < kUsed; ++j) {
         const uint32_t rest = key[j] - base;
         const bool counts = (kKeysOnly || digit[j] == bin0) && rest <= last;
         const uint32_t bin = (rest >> shift) + (lane & (kCopies - 1)) * 256;
@@ -311,7 +311,7 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
     } while (need != hit.count && hit.count > kFewKeys && shift > 0);
     if constexpr (!kKeysOnly) {
 #pragma unroll
-      for (int j = 0; j < kItems; ++j) {
+      for (int j = 0; j < kUsed; ++j) {
         const bool front = digit[j] < bin0 || (digit[j] == bin0 && key[j] < base);
         const bool inside = digit[j] == bin0 && !front && key[j] - base <= last;
         digit[j] = front ? 0u : inside ? 1u : 2u;
@@ -332,11 +332,11 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
   const auto in_bin = [&](int j) { return kKeysOnly ? key[j] - base <= last : digit[j] == bin_at; };
   uint32_t my_count = 0;
 #pragma unroll
-  for (int j = 0; j < kItems; ++j)
+  for (int j = 0; j < kUsed; ++j)
     set_lane(my_count, j, __popcll(__ballot(in_front(j))));
   if (n_few > 0) {
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < kUsed; ++j) {
       if constexpr (kKeysOnly) {
         if (in_bin(j)) {
           const uint32_t to = atomicAdd(&sm.few_count, 1u);
@@ -351,12 +351,12 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
     }
   } else if (ties) {  // rows have fewer than 2^16 pages
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < kUsed; ++j) {
       const uint32_t n = __popcll(__ballot(in_bin(j)));
       my_count += lane == j ? n << 16 : 0u;
     }
   }
-  if (lane < kItems) sm.count[lane * kWaves + wave] = my_count;
+  if (lane < kUsed) sm.count[lane * kWaves + wave] = my_count;
   __syncthreads();
   constexpr int kPerLane = Shared::kRunsPerLane;
   uint32_t part[kPerLane];
@@ -432,14 +432,14 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
   if (!split_ties && !ties) {
     const uint32_t upto = whole ? bin_end - 1u : threshold;
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < kUsed; ++j) {
       const LaneMask sel = __ballot((whole && !kKeysOnly ? digit[j] : key[j]) <= upto);
       const int at = (int)front_before(j) + few_before(j) + first;
       put(in_mask(sel), lanes_before(sel, at), tid + j * kThreads, j, raw[j]);
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
+    for (int j = 0; j < kUsed; ++j) {
       LaneMask sel;
       const uint32_t b = front_before(j);  // with ties: and the equal keys before, in the upper half
       int at = (int)(b & 0xffffu) + few_before(j) + first;
@@ -520,9 +520,19 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
     return;
   }
   const int first = forced.first, end = num_pages - (int)forced.newest;  // the keys: pages first .. end - 1
-  const int need = K - forced.count;  // how many of them the list takes, at least one
+  int need = K - forced.count;  // how many of them the list takes, at least one
 
-  topk_rank<kThreads, kItems>(sm, raw, first, end, need, put);
+  // A sequence that ends far in front of a long row's end leaves most of a thread's pages empty: the
+  // work is then done for the first of them only (rows of 8704 pages of which 435 hold tokens, K = 32, a launch
+  // that selects and attends: 7.9 us, 10.4 for all of them; 32 heads 9.2 and 11.9).
+  constexpr int kPart = kItems >= 20 ? kItems * 3 / 8 : kItems;
+  const auto rank = [&](auto items) {
+    topk_rank<kThreads, kItems, decltype(items)::value>(sm, raw, first, end, need, put);
+  };
+  if (kPart < kItems && end <= kPart * kThreads)
+    rank(std::integral_constant<int, kPart>{});
+  else
+    rank(std::integral_constant<int, kItems>{});
   if (forced.count > 0) {
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
