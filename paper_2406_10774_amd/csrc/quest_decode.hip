@@ -208,27 +208,26 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
 
   __syncthreads();
   const int t = threadIdx.x;
-  const int n_out = n_heads * kHeadDim;
   // ---- this split's result per query head: written out if it is the only split, else
   // published as a partial; the split that arrives last merges
-  if constexpr (kGroup) {  // 64 outputs of one head per wave
-    for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
-      const int g = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
+  if constexpr (kGroup) {  // a head per wave, two channels a lane: its weights once
+    for (int g = wave; g < n_heads; g += kWaves) {
       const int part = lane & (kWaves - 1);
       const Merged all = merge_parts(sm_m[part][g], sm_l[part][g], kWaves, lane);
-      float acc = 0.f;
+      float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) acc += sm_acc[w][g * kStride + ch] * from_lane(all.weight, w);
+      for (int w = 0; w < kWaves; ++w) {
+        const float2 x = *reinterpret_cast<const float2*>(&sm_acc[w][g * kStride + 2 * lane]);
+        const float f = from_lane(all.weight, w);
+        acc.x += x.x * f, acc.y += x.y * f;
+      }
       if (a.splits == 1) {
-        store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + ch, acc / all.l);
-        if (ch == 0 && a.lse) a.lse[bh + g] = (all.m + __builtin_amdgcn_logf(all.l)) * kLn2;
+        store_out2(a.out, a.out_is_fp16, (bh + g) * kHeadDim + 2 * lane, acc.x / all.l, acc.y / all.l);
+        if (lane == 0 && a.lse) a.lse[bh + g] = (all.m + __builtin_amdgcn_logf(all.l)) * kLn2;
       } else {
         const size_t ps = (bh + g) * a.splits + split;
-        dev_st(a.part_acc + ps * kHeadDim + ch, acc);
-        if (ch == 0) {
-          dev_st(a.part_ml + ps * 2 + 0, all.m);
-          dev_st(a.part_ml + ps * 2 + 1, all.l);
-        }
+        dev_st2(a.part_acc + ps * kHeadDim + 2 * lane, acc);
+        if (lane == 0) dev_st2(a.part_ml + ps * 2, make_float2(all.m, all.l));
       }
     }
   } else {
@@ -270,43 +269,47 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   // the result does not depend on which split arrived last
   if constexpr (kGroup) {
 #pragma unroll 1
-    for (int x0 = wave * kWave; x0 < n_out; x0 += kThreads) {
-      const int g = x0 / kHeadDim, ch = (x0 & (kHeadDim - 1)) + lane;
+    for (int g = wave; g < n_heads; g += kWaves) {
       const float* ml = a.part_ml + (bh + g) * a.splits * 2;
-      const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + ch;
-      float mx = kNegBig, l_all = 0.f, o = 0.f;
+      const float* pacc = a.part_acc + (bh + g) * a.splits * kHeadDim + 2 * lane;
+      float mx = kNegBig, l_all = 0.f;
+      float2 o = make_float2(0.f, 0.f);
       for (int s0 = 0; s0 < a.splits; s0 += 16) {
         const int n = min(16, a.splits - s0);
         const float2 pml = dev_ld2(ml + 2 * (s0 + min(lane & 15, n - 1)));
-        float pa[16];
+        float2 pa[16];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) pa[i] = dev_ld(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
+        for (int i = 0; i < 8; ++i) pa[i] = dev_ld2(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
         if (n > 8) {
 #pragma unroll
-          for (int i = 8; i < 16; ++i) pa[i] = dev_ld(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
+          for (int i = 8; i < 16; ++i) pa[i] = dev_ld2(pacc + (size_t)(s0 + min(i, n - 1)) * kHeadDim);
         }
         const Merged part = merge_parts(pml.x, pml.y, n, lane);
         const float cm = fmaxf(mx, part.m);
         const float rescale = __builtin_amdgcn_exp2f(mx - cm), scale = __builtin_amdgcn_exp2f(part.m - cm);
         l_all = l_all * rescale + part.l * scale;
-        o *= rescale;
+        o.x *= rescale, o.y *= rescale;
         const float weight = part.weight * scale;
+        const auto add = [&](int i) {
+          const float f = from_lane(weight, i);
+          o.x += pa[i].x * f, o.y += pa[i].y * f;
+        };
         // (what is not there is left out, not taken times zero: the values may be infinite)
         if (n >= 8) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) o += pa[i] * from_lane(weight, i);
+          for (int i = 0; i < 8; ++i) add(i);
 #pragma unroll
           for (int i = 8; i < 16; ++i)
-            if (i < n) o += pa[i] * from_lane(weight, i);
+            if (i < n) add(i);
         } else {
 #pragma unroll
           for (int i = 0; i < 7; ++i)
-            if (i < n) o += pa[i] * from_lane(weight, i);
+            if (i < n) add(i);
         }
         mx = cm;
       }
-      store_out(a.out, a.out_is_fp16, (bh + g) * kHeadDim + ch, o / l_all);
-      if (ch == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
+      store_out2(a.out, a.out_is_fp16, (bh + g) * kHeadDim + 2 * lane, o.x / l_all, o.y / l_all);
+      if (lane == 0 && a.lse) a.lse[bh + g] = (mx + __builtin_amdgcn_logf(l_all)) * kLn2;
     }
   } else {
 #pragma unroll 1

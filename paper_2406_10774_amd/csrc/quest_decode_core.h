@@ -120,10 +120,12 @@ __device__ __forceinline__ void merge_rows(Softmax& st) {
 
 // Partial results of the same outputs, one in each of the first n <= 16 lanes of every DPP row:
 // their maximum, the sum of their denominators relative to it, and the lane's weight.  The weights
-// are worked out once per wave, side by side, not once per output one after the other: with the
-// outputs of a group on every wave of a work-group that is fewer instructions (4 sequences, 32
-// query / 8 KV heads: 21.0 us a step, 21.4 with every output its own); with one head's
-// on two waves the chain over the lanes is longer (32 heads 19.9 us, 19.8).
+// are worked out once per wave, side by side, not once per output one after the other.  A wave has
+// all of a group's head, two channels a lane, so that a head's weights are worked out once, and a wave that
+// has two heads waits twice for the chain over its lanes, not four times (lists of 512 tokens,
+// 2 sequences of 64 query / 8 KV heads, 8 splits: 8.2 us, 10.5 with one channel a lane, 10.1 with every output's
+// weights its own; 2048 tokens, 16 splits: 10.7, 12.9 and 14.6).  With one head's outputs on two
+// waves the chain is longer than their own weights (32 heads 19.9 us a step, 19.8).
 struct Merged {
   float m, l, weight;
 };
@@ -554,6 +556,11 @@ __device__ __forceinline__ void store_out(void* out, int out_is_fp16, size_t idx
     reinterpret_cast<_Float16*>(out)[idx] = (_Float16)v;
   else
     reinterpret_cast<float*>(out)[idx] = v;
+}
+// Two neighbours.
+__device__ __forceinline__ void store_out2(void* out, int out_is_fp16, size_t idx, float v0, float v1) {
+  store_out(out, out_is_fp16, idx, v0);
+  store_out(out, out_is_fp16, idx + 1, v1);
 }
 
 #endif  // __HIPCC__

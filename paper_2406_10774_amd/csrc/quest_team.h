@@ -49,6 +49,11 @@ __device__ __forceinline__ float2 dev_ld2(const float* p) {
   return make_float2(__builtin_bit_cast(float, (uint32_t)bits), __builtin_bit_cast(float, (uint32_t)(bits >> 32)));
 }
 
+__device__ __forceinline__ void dev_st2(float* p, float2 v) {
+  const uint64_t bits = (uint64_t)__builtin_bit_cast(uint32_t, v.y) << 32 | __builtin_bit_cast(uint32_t, v.x);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Wait until this wave's global stores have completed.
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

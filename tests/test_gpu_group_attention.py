@@ -121,3 +121,31 @@ def test_infinite_and_nan_values(group, S, repeat):
         assert np.array_equal(got[odd], want[odd], equal_nan=True)
         assert (np.abs(got - want)[~odd] <= limit[~odd]).all()
         assert np.abs(lse - want_lse).max() <= 1e-4
+
+
+@pytest.mark.parametrize("batch,kv_heads,group,k_pages", [
+    (32, 8, 8, 20), (16, 8, 5, 20), (4, 8, 8, 40), (3, 8, 8, 80), (2, 8, 9, 128), (2, 8, 3, 130), (1, 2, 16, 600)])
+def test_splits_of_a_list(batch, kv_heads, group, k_pages):
+    """1, 2, 8, 10, 8, 15 and 32 splits of a list, whose partial results a wave per query head merges 16
+    at a time; given lists and selected ones, fp32 and fp16 outputs."""
+    from gpu_util import Layer
+    S, N, P = 16, 40, k_pages + 30
+    rng = np.random.default_rng([batch, group])
+    k_pool, v_pool = (rng.standard_normal((N, kv_heads, S, 128)).astype(np.float16) for _ in range(2))
+    k_pool *= np.float16(0.25)
+    table = rng.integers(0, N, (batch, P)).astype(np.int32)
+    lens = np.array([S * P - 7 * b % (S * 40) for b in range(batch)], np.int32)
+    q = rng.standard_normal((batch, kv_heads * group, 128)).astype(np.float16)
+    sc = rng.standard_normal((batch, kv_heads, P)).astype(np.float32)
+    idx, _ = O.topk(sc, lens, S, k_pages)
+    layer = Layer(k_pool, v_pool, table, lens, num_q_heads=kv_heads * group)
+    scale = 1 / math.sqrt(128)
+    want, want_lse = O.sparse_decode(k_pool, v_pool, q, table, lens, idx, scale)
+    limit = bound(k_pool, v_pool, q, table, lens, idx, scale)
+    got, lse = layer.decode(q, idx, k_pages)
+    assert (np.abs(got - want) <= limit).all() and np.abs(lse - want_lse).max() <= 1e-4
+    half, lse16 = layer.decode(q, idx, k_pages, fp16_out=True)
+    assert np.array_equal(half, got.astype(np.float16)) and np.array_equal(lse16, lse)
+    list_, _, got, lse = layer.select_decode(q, k_pages, scores=sc)
+    assert np.array_equal(list_, idx)
+    assert (np.abs(got - want) <= limit).all() and np.abs(lse - want_lse).max() <= 1e-4
