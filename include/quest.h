@@ -127,10 +127,10 @@ typedef struct quest_cache {
  * k_pages.  Pure host function.
  * The workspace holds one arrival counter per (sequence, head) and the split-K
  * partial results (running max, denominator and un-normalised accumulator of
- * each split); for rows of more than 5120 pages also room for the candidates that
- * quest_select_decode and quest_decode_step select from in long rows (the best k_pages
- * of every chunk of 2048 or 4096 pages of a row: up to 4096 of them, from 16384
- * pages on 8192, and never more than half of the row).  With
+ * each split); for rows of more than 8704 pages (5120 with several query heads per
+ * KV head) also the candidates that quest_select_decode and quest_decode_step select
+ * from there (the best k_pages of every chunk of 2048 or 4096 pages of a row: up to
+ * 4096 of them, from 16384 pages on 8192, and never more than half of the row).  With
  * QUEST_FLAG_SEPARATE_LAUNCHES rows of fewer than 16384 pages keep none; a
  * workspace of that size serves calls without the flag too, which then select
  * without candidates.

@@ -611,6 +611,13 @@ int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void*
                        workspace, workspace_bytes, s);
 }
 
+namespace {
+// Rows short enough for a launch that selects from the whole row.
+bool selected_whole(const quest_cache& c) {
+  return c.max_pages_per_seq <= (group_size(c) == 1 ? kMostSelected : kMostSelectedOfGroup);
+}
+}  // namespace
+
 // Selection and attention in one launch: while a row of scores fits the in-register selection
 // and the list fits in LDS.  Every split of a head repeats the selection, which costs less than the
 // launches it saves up to here (32 heads, 8193 pages: 44.4 us a step, 46.3 with candidates picked by a
@@ -619,8 +626,7 @@ int launch_row_decode(const quest_cache& c, const void* q, float sm_scale, void*
 // query / 8 KV heads, 26.7 us a step, 25.9 with candidates, 6 of 8210 pages, 64 / 8 heads, 64.5 and 63.1;
 // 2 of 4627 pages 26.4, 28.1 with a Top-K launch.
 bool select_decode_supported(const quest_cache& c, int k_pages) {
-  return !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) && k_pages <= kSelListCap &&
-         c.max_pages_per_seq <= (group_size(c) == 1 ? kMostSelected : kMostSelectedOfGroup);
+  return !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) && k_pages <= kSelListCap && selected_whole(c);
 }
 
 namespace {
@@ -629,11 +635,9 @@ namespace {
 // 32 heads 49.6 us instead of 55.6 us at 12500 pages (Top-K of whole rows and attention over
 // its list), 106.3 instead of 108.2 us at 32769 (Top-K in two stages).  Chunks of 4096 pages where
 // 2048 leave too many candidates.
-constexpr int kCandFromPages = 5121;
 constexpr int kMostCandidatesOfRow = 4096;  // that a launch selects among
 int chunk_to_select_from(const quest_cache& c, int k_pages, size_t room) {
-  if ((c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) || c.max_pages_per_seq < kCandFromPages || k_pages > kSelListCap)
-    return 0;
+  if ((c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) || selected_whole(c) || k_pages > kSelListCap) return 0;
   for (const int chunk : {kSmallChunk, kLargeChunk})
     if (candidates_per_row(c, k_pages, chunk) <= kMostCandidatesOfRow && candidate_bytes(c, k_pages, chunk) > 0 &&
         candidate_bytes(c, k_pages, chunk) <= room)
@@ -644,7 +648,7 @@ int chunk_to_select_from(const quest_cache& c, int k_pages, size_t room) {
 
 // The most candidates that a row can have (candidate_bytes): at most half of its pages.
 size_t selection_workspace_bytes(const quest_cache& c) {
-  const bool select = c.max_pages_per_seq >= kCandFromPages && !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES);
+  const bool select = !selected_whole(c) && !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES);
   const size_t most = c.max_pages_per_seq >= kChunkedFromPages ? kMaxCandidates : select ? kMostCandidatesOfRow : 0;
   return (size_t)c.batch * kv_heads(c) * std::min<size_t>(most, c.max_pages_per_seq / 2) * (sizeof(float) + sizeof(int32_t));
 }

@@ -15,10 +15,11 @@ namespace {
 // ends.  Counters and split-K partial results take up to about 1.3 MiB (the launch keeps
 // items * splits near one work-group per compute unit), 4.8 MiB for 257 to 341 groups of eight
 // query heads, which get three splits each; the rest is for the candidates of the
-// selection of rows from 5121 pages on (batch * KV heads * chunks * k_pages * 8 bytes: 1.1
-// MiB for one sequence of 32 heads at 512k tokens with a budget of 4096 tokens, in chunks of
-// 2048 pages).  Candidates of such chunks that do not fit are picked from chunks of 4096, and
-// where those of a two-stage selection do not fit either, the attention runs without splits.
+// selection of rows from 8705 pages on, 5121 with groups of query heads (batch * KV heads *
+// chunks * k_pages * 8 bytes: 0.6 MiB for one sequence of 32 heads at 512k tokens with a budget of
+// 4096 tokens, in chunks of 4096 pages).  Candidates of 2048-page chunks that do not fit are picked
+// from chunks of 4096, and where those of a two-stage selection do not fit either, the attention
+// runs without splits.
 constexpr size_t kScratchBytes = 8u << 20;
 constexpr size_t kMostCandidates = 4u << 20;  // of the two-stage selection
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

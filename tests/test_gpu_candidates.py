@@ -1,5 +1,5 @@
-"""Selection among candidates inside the attention launch (rows of more than 5120 pages): the
-page list, K_b, outputs and lse are those of the separate launches, for rows that end on and
+"""Selection among candidates inside the attention launch (rows of more than 8704 pages, 5120 with
+groups of query heads), and of whole rows up to there: the page list, K_b, outputs and lse are those of the separate launches, for rows that end on and
 inside chunks, with ties, forced pages, infinite scores, groups of query heads and pages of 8
 tokens, with a workspace that has no room for candidates, and on the static entry point."""
 import math
@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (5120, 16, 1, 64, 0), (5121, 16, 1, 64, 12), (6144, 8, 4, 300, 4), (8193, 16, 1, 256, 12), (8193, 16, 1, 1, 8),
     (8200, 8, 1, 512, 0), (16384, 16, 4, 256, 12), (32769, 16, 1, 256, 0), (32769, 8, 1, 500, 4), (12289, 64, 9, 17, 12),
     (6144, 16, 4, 10, 12), (8193, 8, 9, 16, 0),           # groups whose heads attend one by one
+    (8704, 16, 1, 65, 8), (8705, 16, 1, 64, 12), (10001, 8, 1, 512, 0), (12289, 16, 1, 256, 4), (16383, 64, 1, 100, 8),
+    (16383, 16, 1, 2048, 12),                             # one query head per KV head, candidates
 ])
 def test_candidates(max_pages, S, group, k_pages, policy):
     import torch
@@ -58,7 +60,8 @@ def test_candidates(max_pages, S, group, k_pages, policy):
 
     plain, ref, ref_lse = run(Q.QUEST_FLAG_SEPARATE_LAUNCHES, lambda n, c: n)
     nbytes, out, lse = run(0, lambda n, c: n)
-    assert (nbytes > plain) == (5120 < max_pages < 16384) or max_pages >= 16384
+    whole_rows = 8704 if group == 1 else 5120
+    assert (nbytes > plain) == (whole_rows < max_pages < 16384) or max_pages >= 16384
     # the same pages in the same splits, on eight waves instead of four: fp32 sums in another
     # order, n 2^-24 of sum p |v| each, |v| < 6
     n = k_pages * S

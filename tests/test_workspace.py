@@ -103,6 +103,8 @@ def test_calls_without_a_workspace(kind, batch, kv_heads, group, page_size, page
     (3, 32, 1, 8, 150, 96, 96 * 5, 0),                  # pages of 8 tokens: two work-groups per unit
     (1, 1, 1, 16, 16, 1, 0, 0), (1, 8, 4, 16, 500, 32, 32 * 31, 0),
     (1, 32, 1, 16, 16384, 32, 192 * 2 * 4, 32 * 8192),  # very long rows: candidates behind
+    (1, 32, 1, 16, 8704, 32, 192 * 2 * 4, 0), (1, 32, 1, 16, 8705, 32, 192 * 2 * 4, 32 * 4096),  # whole rows, candidates
+    (1, 8, 4, 16, 5120, 32, 32 * 32, 0), (1, 8, 4, 16, 5121, 32, 32 * 32, 8 * 2560),  # (32 splits of a list)
 ])
 def test_size_is_that_of_the_layout(batch, kv_heads, group, page_size, pages, counters, heads, candidates):
     """Counters, then partial results of dense attention or of the most splits of a list, then
