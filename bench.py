@@ -35,6 +35,12 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 
 
+def selects_inside(max_pages, k_pages, groups):
+    """The library's own rule (quest.h): the attention launch selects its pages itself from rows of at
+    most 8704 pages, 5120 with groups of query heads, and for lists of at most 2048 pages."""
+    return max_pages <= (5120 if groups else 8704) and k_pages <= 2048
+
+
 def parse():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -224,15 +230,12 @@ def main():
     # headline: the faster of the ways the library offers to run the complete step
     three_us = us_step
     calls = "quest_append_estimate, quest_topk, quest_sparse_decode (three launches)"
-    # the library's own rule (quest.h): the attention launch selects its pages itself for
-    # rows of at most 8704 pages (of one query head per KV head) and lists of at most 2048; else
-    # the call is three launches
-    selects_inside = table.shape[1] <= 8704 and K <= 2048
+    inside = selects_inside(table.shape[1], K, Hq != H)  # else the call is three launches
     one_call = two_us < us_step
-    two_launches = one_call and selects_inside
+    two_launches = one_call and inside
     if one_call:
         us_step, us_step_events = two_us, two_us_events
-        calls = ("quest_decode_step (two launches: estimate; selection + attention)" if selects_inside
+        calls = ("quest_decode_step (two launches: estimate; selection + attention)" if inside
                  else "quest_decode_step (one call; estimate, selection and attention as launches of their own)")
 
     g_dense = capture(dense_step, timed)

@@ -72,6 +72,16 @@ def test_one_workspace_on_drawn_shapes():
         assert call(kind, make_cache(*shape, flags[1]), used, nbytes) == HIP, (shape, asked, used, flags, kind)
 
 
+@pytest.mark.parametrize("group", [1, 2, 8])
+def test_the_benchmark_knows_which_rows_are_selected_whole(group):
+    """Where a step is two launches: the library keeps no candidates there."""
+    import bench
+    for pages in (4096, 4097, 5120, 5121, 8192, 8704, 8705, 12500):
+        candidates = size_of(make_cache(1, 32, group, 16, pages), 0) - size_of(make_cache(1, 32, group, 16, pages, 1), 0)
+        assert bench.selects_inside(pages, 2048, group > 1) == (candidates == 0)
+        assert not bench.selects_inside(pages, 2049, group > 1)
+
+
 @pytest.mark.parametrize("kind,batch,kv_heads,group,page_size,pages,k_pages,accepted", [
     ("dense", 1, 32, 1, 16, 4, 0, True), ("dense", 1, 32, 1, 16, 5, 0, False), ("dense", 8, 32, 1, 16, 16, 0, True),
     ("dense", 8, 32, 1, 16, 17, 0, False), ("dense", 9, 29, 1, 16, 2048, 0, True), ("dense", 9, 8, 4, 16, 2048, 0, True),
