@@ -286,7 +286,7 @@ def main():
     # the attention launch that selects its own pages (the second launch of the one-call step)
     k_seldec = kernel_us(lambda i: Q.quest_select_decode(caches[i], q_all[i], scores, K, scale, idx,
                                                          out, workspace=ws_step)) \
-        if selects_inside else float("nan")
+        if inside else float("nan")
     score_bytes = float(np.mean([H * p * 4 for p in pages_steps]))
     kernels = {
         "append_meta_us": round(k_app, 3),
@@ -296,8 +296,8 @@ def main():
         "topk_us": round(k_topk, 3),
         "topk_two_stage_us": None if k_topk2 is None else round(k_topk2, 3),
         "sparse_decode_us": round(k_dec, 3), "sparse_decode_gbps": round(kv_bytes / k_dec / 1e3, 1),
-        "select_decode_us": round(k_seldec, 3) if selects_inside else None,
-        "select_decode_gbps": round((kv_bytes + score_bytes) / k_seldec / 1e3, 1) if selects_inside else None,
+        "select_decode_us": round(k_seldec, 3) if inside else None,
+        "select_decode_gbps": round((kv_bytes + score_bytes) / k_seldec / 1e3, 1) if inside else None,
         "dense_decode_us": round(k_dense, 3), "dense_decode_gbps": round(dense_bytes / k_dense / 1e3, 1),
     }
     if k_appest >= k_dec:
