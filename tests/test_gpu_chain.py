@@ -208,8 +208,8 @@ def test_decode_step_long_rows():
 
 @pytest.mark.parametrize("k_pages", [2048, 2049])
 def test_decode_step_at_the_limits_of_the_selecting_launch(k_pages):
-    """Rows of 4096 pages and a list of 2048 pages are the largest the attention launch
-    selects for itself; one page more in the list and the call is three launches."""
+    """A list of 2048 pages is the longest that the attention launch selects for itself; one page more
+    and the call is three launches.  Rows of 4096 pages are the longest that eight waves select."""
     w = synth.Workload(96, "limits-step", 1, 2, (16 * 4095 + 9,), token_budget=16 * k_pages,
                        planted_per_head=8, decode_steps=4)
     run_decode_steps(w, steps=3, permute=True, flags=0)
