@@ -620,9 +620,12 @@ bool selected_whole(const quest_cache& c) {
 
 // Selection and attention in one launch: while a row of scores fits the in-register selection
 // and the list fits in LDS.  Every split of a head repeats the selection, which costs less than the
-// launches it saves up to here (32 heads, 8193 pages: 44.4 us a step, 46.3 with candidates picked by a
-// launch of their own, 47.8 with a Top-K launch; 16 sequences of up to 4096 pages 188 us, 193 with the
-// Top-K launch).  Groups of query heads have less to stream that hides it: 3 sequences of 6799 pages, 32
+// launches it saves.  Where the longest tiling ends, us a call over rows of 8704 pages this way / with candidates
+// picked by a launch of their own: 32 heads, lists of 64 pages 12.7 / 12.5, 256 20.8 / 20.9, 1024 52.5 /
+// 54.1; 16 sequences of them, 64 pages 53.2 / 61.0, 256 180 / 188; with 2611 pages of the row in use 10.6 /
+// 12.3 and 18.6 / 20.9, with 435 10.5 / 11.0 and 18.3 / 19.2.  Full rows of 6913 pages on in one sequence of
+// few heads with short lists are the worst of it (8 heads, 64 pages 11.4 / 10.9); the host does not know
+// how full they are.  (Rows of 8193 pages with a Top-K launch 47.8 us a step, 44.4 this way.)  Groups of query heads have less to stream that hides it: 3 sequences of 6799 pages, 32
 // query / 8 KV heads, 26.7 us a step, 25.9 with candidates, 6 of 8210 pages, 64 / 8 heads, 64.5 and 63.1;
 // 2 of 4627 pages 26.4, 28.1 with a Top-K launch.
 bool select_decode_supported(const quest_cache& c, int k_pages) {

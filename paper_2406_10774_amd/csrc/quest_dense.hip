@@ -84,7 +84,8 @@ __global__ __launch_bounds__(kWaves* kWave) void dense_kernel(const DenseArgs a)
     total += __builtin_amdgcn_readlane(wave_incl_scan(p), kWave - 1);
   }
   total *= blocks;
-  const int64_t shares = total < a.shares ? total : a.shares;  // none is empty
+  // none is empty, but one may have no page: all of it in front of an item's
+  const int64_t shares = total < a.shares ? total : a.shares;
   if (w >= shares) return;
   const int64_t begin = w * total / shares, end = (w + 1) * total / shares;
   int64_t off = begin;
