@@ -122,6 +122,11 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
     mn[it] = ld16_stream(e);
     mx[it] = ld16_stream(e + kHeadDim * 2);
   }
+  // Where the scores go is worked out while the metadata is on its way, and the last sums in front of the
+  // branch around the store: the compiler would put both behind it, at the wave's end (8100 entries or less:
+  // 1.5 % of the launch).
+  float* row = scores + bh * max_pages;
+  asm volatile("" : "+s"(row));
 
   if (appends) {
     const int slot = pos - (last << page_shift);
@@ -216,7 +221,7 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
       LanePair s = pair_across16(__builtin_bit_cast(uint32_t, keep));
       s = pair_across32(__builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second))));
       keep = fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second));
-      if (lane < kPages && base + lane < num_pages) scores[bh * max_pages + base + lane] = keep;
+      if (lane < kPages && base + lane < num_pages) row[base + lane] = keep;
       return;
     }
 #pragma unroll
@@ -258,8 +263,9 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
     for (int i = 1; i < kQ; ++i) keep = fmaxf(keep, score_pages(qv[i]));
   }
   // lanes c < 4 of each row hold 4 consecutive pages: 16 consecutive floats per wave
+  asm volatile("" : "+v"(keep));
   const int p = base + kIters * grp + c;
-  if (c < kIters && p < num_pages) scores[bh * max_pages + p] = keep;
+  if (c < kIters && p < num_pages) row[p] = keep;
 }
 
 #endif  // __HIPCC__
