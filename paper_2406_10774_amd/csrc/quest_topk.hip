@@ -15,8 +15,8 @@
 // live in registers, the score loads are issued before seq_lens is known, every wave
 // searches the histogram and ranks the bin's keys itself so that there are three barriers in
 // all (more only where the radix select runs), atomics and stores to LDS go to spare entries instead of being branched around, and
-// what is counted once per wave is kept in scalar registers.  32 rows of 2053 scores, K = 128: 3.9 us
-// a launch, 5.4 with 8-bit digits of the keys from the first on; 8193, K = 256: 6.7 and 10.8 us.
+// what is counted once per wave is kept in scalar registers.  32 rows of 2053 scores, K = 128: 3.8 us
+// a launch, 5.4 with 8-bit digits of the keys from the first on; 8193, K = 256: 6.3 and 11.0 us.
 #include "quest_common.h"
 #include "quest_topk_core.h"
 

@@ -96,8 +96,9 @@ constexpr int kFewKeys = 64;
 
 // Digits and places beside the keys are three registers a key.  Where those would spill, the keys
 // alone tell all: radix digits of the key from the first pass on, and a place is handed out when a
-// key turns out to be of the last bin.  32 rows of 65535 scores, K = 64: 20.7 us, 42.3 with digits and
-// places partly in scratch memory; 512 rows 53 and 230; 49152 scores 16.5 and 28.0, 512 rows 39 and 129.
+// key turns out to be of the last bin.  32 rows of 65535 scores, K = 64: 19.6 us, 42.3 with digits and
+// places partly in scratch memory; 512 rows 50 and 229; 49152 scores 15.7 and 28.0, 512 rows 37 and 128.
+// (All but five of 49152: 36.1 us, 32.2: their leading bits need a pass more than bins of equal width.)
 // 33 keys per thread fit (12.6 us; 12.7 to 15.8 from the keys alone).
 constexpr bool keys_only(int threads, int items) { return 3 * items > 128 * 1024 / threads - 24; }
 
