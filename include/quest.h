@@ -263,7 +263,10 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * The call enqueues the estimate, then what quest_select_decode enqueues: two
  * launches in all when k_pages <= 2048 and max_pages_per_seq <= 8704 (5120 with
  * several query heads per KV head) and QUEST_FLAG_SEPARATE_LAUNCHES is not set,
- * else three (four where very long rows are selected in two stages). */
+ * else three (four where very long rows are selected in two stages).  Where the two
+ * launches would be, short rows take one, in which every work-group also scores its
+ * (sequence, KV head): up to 256 pages, up to 1024 with many (sequence, head) pairs,
+ * up to 128 with several query heads per KV head. */
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes);
 int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v_new,
                       int32_t k_pool_write, const void* q, int32_t k_pages, float sm_scale,

@@ -102,6 +102,12 @@ int launch_select_decode(const quest_cache& c, const void* q, const float* score
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, const Workspace& workspace, hipStream_t s);
 
+// The whole step as one launch.
+bool step_in_one_launch(const quest_cache& c, int k_pages);
+int launch_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write, const void* q, int k_pages,
+                float sm_scale, float* scores, int32_t* topk_idx, int32_t* k_eff, void* out, int out_is_fp16, float* lse,
+                const Workspace& workspace, hipStream_t s);
+
 // Leading part of a decode workspace: the arrival counters (must be zero before a launch).
 size_t decode_counter_bytes(const quest_cache& c);
 int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write,

@@ -27,6 +27,7 @@
 // heads_apart.
 #include "quest_common.h"
 #include "quest_decode_core.h"
+#include "quest_estimate_core.h"
 #include "quest_team.h"
 #include "quest_topk_core.h"
 
@@ -62,6 +63,10 @@ struct DecodeArgs : AttnArgs {
   uint32_t seq_inverse;     // ceil(2^32 / items per sequence), if that is exact for every item; else 0
 };
 
+struct StepArgs : DecodeArgs {
+  EstimateArgs est;
+};
+
 // All splits of one (sequence, head) get work-group ids that are equal modulo 8
 // (grid.x is a multiple of 8), so under the usual round-robin placement they run on
 // one die and their traffic stays in one L2.  Nothing depends on that: partial results
@@ -80,8 +85,12 @@ struct DecodeArgs : AttnArgs {
 //
 // kCand: the scores are those of candidates that a launch before has picked from the chunks
 // of a longer row, each with its page.
-template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand>
-__global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const DecodeArgs a) {
+//
+// kEstPasses > 0: the scores do not exist either: the whole step is this launch.  Every work-group scores
+// its row itself (estimate_row, with kEstPasses and kEstQ), then selects; step_in_one_launch says when.
+template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand, int kEstPasses = 0, int kEstQ = 0>
+__global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(
+    const typename std::conditional<(kEstPasses > 0), StepArgs, DecodeArgs>::type a) {
   using Head = HeadState<kLoads, kGroup>;
   constexpr int kThreads = kWaves * kWave;
   constexpr int kSlots = Head::kSlots, kStride = Head::kStride;
@@ -92,12 +101,24 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
   // physical page) pairs
   __shared__ __align__(16) typename std::conditional<(kSelItems > 0), TopkShared<kThreads, kSelItems>, char>::type sm_topk;
   __shared__ int2 sm_list[kSelItems > 0 ? kSelListCap + kWave : 1];
+  // of a row that is scored here: scores and physical pages, and where groups turn the metadata (a group's
+  // attention has room for that)
+  constexpr int kIters = kEstQ == 0 ? 2 : 4;  // pages per wave and pass: four times that
+  constexpr int kRow = kEstPasses > 0 ? kWaves * kEstPasses * 4 * kIters : 1;
+  constexpr int kStage = 4 * kIters * kMetaBytes;
+  __shared__ float sm_score[kRow];
+  __shared__ int sm_phys[kRow];
+  __shared__ __align__(16) char sm_stage[kEstPasses > 0 && kEstQ == 0 && !kGroup ? kWaves * kStage : 16];
+  static_assert(kEstQ != 0 || !kGroup || kEstPasses == 0 || sizeof(sm_acc[0]) >= kStage, "metadata of a wave");
 
   // Every argument in one trip to memory, not one per use: 0.2 us less until the first score.
   asm volatile("" ::"s"(a.batch), "s"(a.kv_heads), "s"(a.subs), "s"(a.group), "s"(a.num_heads), "s"(a.max_pages), "s"(a.seq_inverse),
                "s"(a.page_table), "s"(a.seq_lens), "s"(a.q), "s"(a.scores), "s"(a.row_len), "s"(a.k_pages));
   asm volatile("" ::"s"(a.k_pool), "s"(a.v_pool), "s"(a.counters), "s"(a.per_split), "s"(a.list_len), "s"(a.splits),
                "s"(a.page_shift), "s"(a.unit_shift), "s"(a.scale_log2), "s"(a.policy), "s"(a.topk_out), "s"(a.k_eff));
+  if constexpr (kEstPasses > 0)
+    asm volatile("" ::"s"(a.est.meta), "s"(a.est.q), "s"(a.est.scores), "s"(a.est.k_new), "s"(a.est.v_new), "s"(a.est.k_pool),
+                 "s"(a.est.v_pool), "s"(a.est.k_pool_write), "s"(a.est.num_phys_pages));
   // blockIdx.x = slot + 8 * split, blockIdx.y = group of 8 items: the linear work-group
   // id is slot + 8 * (split + splits * blockIdx.y).  The usual shapes are taken apart without
   // integer divisions: they sit in front of the first load of every work-group.
@@ -156,13 +177,29 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(const Decod
         for (int jj = 0; jj < kSelItems; ++jj)
           if (jj == j) of = mine[jj];
       } else if (entry >= 0) {
-        of = per_score[entry];
+        of = kEstPasses > 0 ? sm_phys[entry] : per_score[entry];
       }
       sm_list[selected ? pos : kSelListCap + lane] = make_int2(kCand ? of : entry, of);
     };
     int32_t* k_eff = (writer && hk == 0 && a.k_eff != nullptr) ? a.k_eff + b : nullptr;
     const float* scores = a.scores + row * a.row_len;
-    if constexpr (kCand)
+    if constexpr (kEstPasses > 0) {
+      st.init(sm_acc[wave], q, n_heads, lane);
+      char* stage = kGroup ? reinterpret_cast<char*>(sm_acc[wave]) : sm_stage + (sizeof(sm_stage) > 16 ? wave * kStage : 0);
+      const RowOfPages r = estimate_row<kWaves, kEstPasses, kIters, kEstQ>(a.est, b, hk, wave, stage, sm_score, sm_phys);
+      seq_len = r.seq_len;
+      __syncthreads();
+      if (writer) store_row<kThreads>(a.est, b, hk, sm_score, r);
+      float raw[kSelItems];
+#pragma unroll
+      for (int j = 0; j < kSelItems; ++j) {
+        const int at = min((int)threadIdx.x + j * kThreads, kRow - 1);
+        raw[j] = sm_score[at];
+        mine[j] = sm_phys[at];
+      }
+      topk_select<kThreads, kSelItems>(sm_topk, raw, WholeRow{a.page_shift, a.policy}(seq_len), a.row_len, a.k_pages, put,
+                                       k_eff);
+    } else if constexpr (kCand)
       topk_block_put<kThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
                                           CandidateRow{a.page_shift, a.policy, a.k_pages, a.chunk_pages}, more_loads);
     else
@@ -506,12 +543,13 @@ namespace {
 int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, const float* scores,
                   const Candidates* cand, int32_t* topk_out, int32_t* k_eff, int k_pages, float sm_scale,
                   void* out, int out_is_fp16, float* lse, void* workspace, size_t workspace_bytes,
-                  hipStream_t s) {
+                  hipStream_t s, const EstimateArgs* est = nullptr) {
   const bool select = scores != nullptr || cand != nullptr;
   const bool rows = !select && topk_idx == nullptr;  // every page of a row
   const bool apart = !rows && heads_apart(c, k_pages, select);
   SplitPlan p = rows ? plan_rows(c) : apart ? plan_apart(c, k_pages) : plan_splits(c, k_pages, select);
-  DecodeArgs a;
+  StepArgs a;
+  if (est) a.est = *est;
   fill_attn_args(a, c, q, sm_scale, out, out_is_fp16, lse);
   a.topk_idx = topk_idx;
   a.scores = cand ? cand->score : scores;
@@ -550,6 +588,37 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     if (c.page_size == 8) QUEST_LAUNCH(2, G, W, I, C); \
     else QUEST_LAUNCH(4, G, W, I, C);               \
   } while (0)
+  if (est) {
+#define QUEST_STEP(L, G, W, I, P, Q) \
+  hipLaunchKernelGGL((decode_split_kernel<L, G, W, I, false, P, Q>), grid, dim3((W) * kWave), 0, s, a)
+#define QUEST_STEP_CASE(G, W, I, P, Q)                                                     \
+  if (group == G && (Q) == queries && a.max_pages <= (W) * (P) * ((Q) ? 16 : 8)) {         \
+    if (c.page_size == 8) QUEST_STEP(2, G, W, I, P, Q); else QUEST_STEP(4, G, W, I, P, Q); \
+    return check_launch("quest_decode_step");                                              \
+  }
+    const int queries = a.group == 1 ? 1 : estimate_on_matrix_cores(c) ? 0 : 4;
+    // Waves, scores per thread, passes (estimate_row).  Four waves up to 256 pages; more pages are streamed faster by
+    // eight (192 rows of 313 pages, 64 tokens each, 22.9 us a step, 23.6 with four), but those take a compute unit each
+    // (384 rows of 434 pages 47.3 us with four, 52.6 with eight).
+    QUEST_STEP_CASE(false, 4, 1, 2, 1)
+    QUEST_STEP_CASE(false, 4, 1, 4, 1)
+    if (items <= kComputeUnits) {
+      QUEST_STEP_CASE(false, 8, 1, 4, 1)
+      QUEST_STEP_CASE(false, 8, 2, 8, 1)
+    } else {
+      QUEST_STEP_CASE(false, 4, 2, 8, 1)
+    }
+    QUEST_STEP_CASE(true, 8, 1, 1, 4)
+    QUEST_STEP_CASE(false, 8, 1, 1, 4)
+    QUEST_STEP_CASE(true, 8, 1, 1, 0)
+    QUEST_STEP_CASE(false, 8, 1, 1, 0)
+    QUEST_STEP_CASE(true, 8, 1, 2, 0)
+    QUEST_STEP_CASE(false, 8, 1, 2, 0)
+#undef QUEST_STEP_CASE
+#undef QUEST_STEP
+    set_error("quest_decode_step: internal: no one-launch step for rows of %d pages", a.max_pages);
+    return QUEST_ERR_SHAPE;
+  }
   if (select) {
 #define QUEST_SELECT_CASE(G, C, W, I)                                                      \
   if (group == G && (cand != nullptr) == C && a.row_len <= (W) * kWave * (I)) {            \
@@ -654,6 +723,39 @@ size_t selection_workspace_bytes(const quest_cache& c) {
   const bool select = !selected_whole(c) && !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES);
   const size_t most = c.max_pages_per_seq >= kChunkedFromPages ? kMaxCandidates : select ? kMostCandidatesOfRow : 0;
   return (size_t)c.batch * kv_heads(c) * std::min<size_t>(most, c.max_pages_per_seq / 2) * (sizeof(float) + sizeof(int32_t));
+}
+
+// The whole step as one launch (decode_split_kernel with kEstPasses): the estimate's launch, the gap between
+// two launches and the trip of the scores through memory go, about 3.4 us of 11 to 12. Against that every split of a
+// row scores all of it, which its compute unit's path to L2 (64 bytes a clock) and its vector unit have to
+// carry, and a row that comes from memory reaches one unit at 25 to 30 KiB per us.  us a step, two
+// launches / one:
+//   one head, 61 pages 8.0 / 6.8, 124 8.5 / 7.4, 252 9.3 / 9.2; 32 heads, 61 9.7 / 8.1, 124 11.0 / 9.5, 252 11.2 / 10.9,
+//   but 434 11.9 / 12.7: a row in several splits up to 256 pages;
+//   two splits, 4 sequences of 32 heads, 996 pages 38.7 / 37.3, shorter ones among them 35.5 / 34.1, but 3
+//   sequences (96 rows) of 700 to 1300 pages 1 to 15 % slower: from 113 rows on up to 1024;
+//   one split, 6 sequences of 32 heads, 434 pages 27.8 / 26.6, 996 36.5 / 34.3, a list of 256 tokens 25.3 / 23.4; but
+//   5 to 8 of 1500 to 2000 pages, 2 to 10 % slower; three splits as a row in several;
+//   more rows than units, 12 sequences of 32 heads, 252 pages 46.1 / 42.6, 434 49.5 / 47.3; of 996, or 640 rows
+//   of 500, up to 8 % slower; thousands of rows of a few pages 3 %, of 120 pages 4 % faster.
+// Groups of query heads have each page scored for all of them: 32 query / 8 KV heads, 120 pages 9.9 / 9.8; 10 sequences
+// of 64 / 8 heads, 56 pages 13.4 / 12.5, one of 120 10.5 / 10.7; with 16 and more heads in a group, or more rows
+// than units, 2 to 13 % slower.
+bool step_in_one_launch(const quest_cache& c, int k_pages) {
+  if (!select_decode_supported(c, k_pages) || c.num_phys_pages >= (1l << 22)) return false;  // (32-bit offsets)
+  const long items = group_items(c), pages = c.max_pages_per_seq;
+  if (group_size(c) > 1) return group_size(c) <= 8 && items <= kComputeUnits && pages <= (group_size(c) <= 4 ? 128 : 64);
+  const int splits = plan_splits(c, k_pages, true).splits;
+  if (items > 2 * kComputeUnits || splits > 2) return pages <= 256 && (items <= 4 * kComputeUnits || pages >= 64);
+  if (items > kComputeUnits) return pages <= 512;
+  return pages <= (items > 112 ? 1024 : 256);
+}
+int launch_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write, const void* q, int k_pages,
+                float sm_scale, float* scores, int32_t* topk_idx, int32_t* k_eff, void* out, int out_is_fp16, float* lse,
+                const Workspace& w, hipStream_t s) {
+  const EstimateArgs est = estimate_args(c, k_new, v_new, k_pool_write, q, scores);
+  return launch_decode(c, q, nullptr, scores, nullptr, topk_idx, k_eff, k_pages, sm_scale, out, out_is_fp16, lse,
+                       w.attention, w.attention_bytes, s, &est);
 }
 
 int launch_select_decode(const quest_cache& c, const void* q, const float* scores, int k_pages,

@@ -45,9 +45,11 @@ __global__ __launch_bounds__(kEstWaves* kWave, kQ == 0 ? (kIters == 2 ? 7 : 4) :
 // cores (14.2 and 6.4).  Nor do three or four over small tables, where the turn through LDS shows: 2.85
 // against 2.98 us at 8100 entries, but 4.08 against 3.75 at 16400.  Five and more are faster there in every
 // table: five 3.00 and 2.83 at 256 entries, 4.03 and 3.73 at 9600; eight 3.17 and 2.93, 4.64 and 3.86.
-bool on_matrix_cores(const quest_cache& c) {
+}  // namespace
+bool estimate_on_matrix_cores(const quest_cache& c) {
   return group_size(c) > ((long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (3l << 12) ? 4 : 2);
 }
+namespace {
 
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller
 // table is scanned faster by twice as many waves of half the size: 8.3 us against 8.75 us
@@ -74,7 +76,7 @@ void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
 #define QUEST_ESTIMATE(Q) hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q>), grid, block, lds, s, a)
   if (a.group == 1) QUEST_ESTIMATE(1);
   else if (a.group == 2) QUEST_ESTIMATE(2);
-  else if (kIters == 2 && !on_matrix_cores(c)) {
+  else if (kIters == 2 && !estimate_on_matrix_cores(c)) {
     if constexpr (kIters == 2) {
       if (a.group == 3) QUEST_ESTIMATE(3);
       else QUEST_ESTIMATE(4);
@@ -95,8 +97,8 @@ void launch(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
 
 }  // namespace
 
-namespace {
-EstimateArgs make_args(const quest_cache& c, const void* q, float* scores) {
+EstimateArgs estimate_args(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write, const void* q,
+                           float* scores) {
   EstimateArgs a;
   a.meta = (char*)c.meta;
   a.q = (const char*)q;
@@ -108,27 +110,22 @@ EstimateArgs make_args(const quest_cache& c, const void* q, float* scores) {
   a.max_pages = c.max_pages_per_seq;
   a.num_phys_pages = c.num_phys_pages;
   a.page_shift = page_shift_of(c.page_size);
-  a.k_new = a.v_new = nullptr;
-  a.k_pool = a.v_pool = nullptr;
-  a.k_pool_write = 0;
-  return a;
-}
-}  // namespace
-
-int launch_estimate(const quest_cache& c, const void* q, float* scores, hipStream_t s) {
-  launch<false>(c, make_args(c, q, scores), s);
-  return check_launch("quest_estimate");
-}
-
-int launch_append_estimate(const quest_cache& c, const void* k_new, const void* v_new,
-                           int k_pool_write, const void* q, float* scores, hipStream_t s) {
-  EstimateArgs a = make_args(c, q, scores);
   a.k_new = (const char*)k_new;
   a.v_new = (const char*)v_new;
   a.k_pool = (char*)c.k_pool;
   a.v_pool = (char*)c.v_pool;
   a.k_pool_write = k_pool_write;
-  launch<true>(c, a, s);
+  return a;
+}
+
+int launch_estimate(const quest_cache& c, const void* q, float* scores, hipStream_t s) {
+  launch<false>(c, estimate_args(c, nullptr, nullptr, 0, q, scores), s);
+  return check_launch("quest_estimate");
+}
+
+int launch_append_estimate(const quest_cache& c, const void* k_new, const void* v_new,
+                           int k_pool_write, const void* q, float* scores, hipStream_t s) {
+  launch<true>(c, estimate_args(c, k_new, v_new, k_pool_write, q, scores), s);
   return check_launch("quest_append_estimate");
 }
 

@@ -459,7 +459,8 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
 }
 
 // Selection for one row of scores by one work-group of kThreads threads (all of
-// them must call).  shape(seq_len) describes the row (it has room for max_pages
+// them must call): thread t has the scores of entries t + j * kThreads (whatever stands past the
+// valid ones).  row_shape describes the row (it has room for max_pages
 // entries); put(selected, position, page, j, score) receives the list from the threads that pass
 // selected (the others' arguments mean nothing, but position is at least 0): positions 0 .. k_pages-1,
 // pages ascending, -1 past the K_b selected ones; j >= 0 says that the page is the calling
@@ -467,40 +468,20 @@ __device__ __forceinline__ void topk_rank(TopkShared<kThreads, kItems>& sm, cons
 // j < 0 that it is not (then `score` carries nothing).  A put that needs per-page data
 // takes it from what the thread already holds whenever j >= 0: a load issued from inside
 // put is waited for before the next page's put starts.
-// after_loads() is called once, right after the loads of the scores have been issued:
-// the place for loads the caller wants in flight behind them.
-template <int kThreads, int kItems, class Put, class Shape, class AfterLoads>
-__device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
-                                               const float* __restrict__ row,
-                                               const int32_t* __restrict__ seq_len_ptr,
-                                               int max_pages, int k_pages, Put put,
-                                               int32_t* __restrict__ k_eff_slot, Shape shape,
-                                               AfterLoads after_loads) {
+template <int kThreads, int kItems, class Put>
+__device__ __forceinline__ void topk_select(TopkShared<kThreads, kItems>& sm, const float (&raw)[kItems],
+                                            const RowShape row_shape, int max_pages, int k_pages, Put put,
+                                            int32_t* __restrict__ k_eff_slot) {
   using Shared = TopkShared<kThreads, kItems>;
   const int tid = threadIdx.x;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // issue every load first: this thread's scores (entries past the valid pages
-  // are inside the row, so reading them is safe; they are masked below) and the
-  // sequence length
-  float raw[kItems];
-  const uint32_t last_offset = ((uint32_t)max_pages - 1u) * (uint32_t)sizeof(float);
-#pragma unroll
-  for (int j = 0; j < kItems; ++j) {
-    // clamped, not predicated: the loads stay independent and all in flight at once
-    const uint32_t at = min((uint32_t)(tid + j * kThreads) * (uint32_t)sizeof(float), last_offset);
-    raw[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + at);
-  }
-  const int seq_len = __builtin_amdgcn_readfirstlane(*seq_len_ptr);
-  after_loads();
 
   if (tid < Shared::kSpare) sm.hist[tid] = 0;
   if (wave == 0) sm.few_key[lane] = 0xffffffffu;
   if constexpr (Shared::kCopies > 1)
     if (tid == 0) sm.few_count = 0;
 
-  const RowShape row_shape = shape(seq_len);
   const int num_pages = min(row_shape.num_pages, max_pages);  // whatever the length says: no entry past the row
   const int K = min(k_pages, num_pages);
   if (tid == 0 && k_eff_slot != nullptr) *k_eff_slot = K;
@@ -542,6 +523,34 @@ __device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
       put(forced.newest && page == num_pages - 1, K - 1, page, j, raw[j]);
     }
   }
+}
+
+// The same for a row of scores in memory.  shape(seq_len) describes the row.
+// after_loads() is called once, right after the loads of the scores have been issued:
+// the place for loads the caller wants in flight behind them.
+template <int kThreads, int kItems, class Put, class Shape, class AfterLoads>
+__device__ __forceinline__ void topk_block_put(TopkShared<kThreads, kItems>& sm,
+                                               const float* __restrict__ row,
+                                               const int32_t* __restrict__ seq_len_ptr,
+                                               int max_pages, int k_pages, Put put,
+                                               int32_t* __restrict__ k_eff_slot, Shape shape,
+                                               AfterLoads after_loads) {
+  const int tid = threadIdx.x;
+
+  // issue every load first: this thread's scores (entries past the valid pages
+  // are inside the row, so reading them is safe; they are masked later) and the
+  // sequence length
+  float raw[kItems];
+  const uint32_t last_offset = ((uint32_t)max_pages - 1u) * (uint32_t)sizeof(float);
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    // clamped, not predicated: the loads stay independent and all in flight at once
+    const uint32_t at = min((uint32_t)(tid + j * kThreads) * (uint32_t)sizeof(float), last_offset);
+    raw[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + at);
+  }
+  const int seq_len = __builtin_amdgcn_readfirstlane(*seq_len_ptr);
+  after_loads();
+  topk_select<kThreads, kItems>(sm, raw, shape(seq_len), max_pages, k_pages, put, k_eff_slot);
 }
 
 // The list goes to memory.

@@ -1,0 +1,106 @@
+"""quest_decode_step as one launch (short rows) against the same call in separate launches: rows that end around a
+tile's and a pass's last page, sequences of one page and one token, the newest token first and last in its page,
+groups of query heads on both units, few and many rows.  Scores, lists, metadata and pools bit for bit, and nothing
+written past a sequence's pages; attention within the rounding of its fp32 sums."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2406_10774_amd import binding as Q
+
+pytestmark = pytest.mark.gpu
+
+# (sequences, query heads, KV heads, page size, pages of the row, pages of the list)
+SHAPES = [
+    (3, 2, 2, 16, 1, 1), (3, 2, 2, 16, 17, 4), (2, 32, 32, 16, 64, 16), (3, 3, 3, 8, 65, 300), (2, 1, 1, 32, 127, 40),
+    (2, 2, 2, 64, 128, 9), (2, 32, 32, 16, 129, 64), (3, 1, 1, 8, 255, 2000), (2, 2, 2, 16, 256, 32),
+    (15, 8, 8, 8, 257, 20), (24, 8, 8, 8, 512, 64), (13, 40, 40, 8, 250, 8), (33, 8, 8, 8, 511, 16), (16, 8, 8, 8, 513, 40),
+    (17, 8, 8, 8, 1024, 17), (25, 8, 8, 8, 1024, 33), (25, 8, 8, 8, 1025, 30), (130, 8, 8, 8, 65, 3),
+    (2, 4, 2, 16, 31, 4), (2, 12, 4, 8, 128, 500), (3, 32, 8, 16, 127, 64), (8, 32, 8, 64, 100, 32), (2, 10, 2, 16, 33, 8),
+    (3, 64, 8, 16, 64, 16), (24, 64, 8, 8, 9, 60), (30, 16, 8, 16, 128, 100),
+]
+
+
+def edge_lengths(n, pages, S, rng):
+    """The longest row, and sequences that end just before, at and behind page and pass borders."""
+    some = [pages * S, 1, (pages - 1) * S + 1, S, S + 1, 16 * S, 16 * S + 1, 64 * S, 128 * S - 1, 128 * S + 1]
+    some += [int(x) for x in rng.integers(1, pages * S + 1, n)]
+    return np.array([min(max(x, 1), pages * S) for x in some[:n]], np.int32)
+
+
+def run(shape, flags, write, with_new, seed):
+    import torch
+    B, H, Hkv, S, pages, K = shape
+    rng = np.random.default_rng([seed, *shape])
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    half = dict(dtype=torch.float16, device="cuda")
+    shared, D = 96, 128                                   # full pages may be anybody's; the newest page is one's own
+    N = shared + B
+    lens = edge_lengths(B, pages, S, rng)
+    table = rng.integers(0, shared, (B, pages)).astype(np.int32)
+    for b, n in enumerate(lens):
+        table[b, (n - 1) // S] = shared + b
+        table[b, (n - 1) // S + 1:] = 2 ** 30             # nobody may look up what lies past the sequence
+    k_pool = torch.empty((N, Hkv, S, D), **half).normal_(generator=gen)
+    v_pool = torch.empty((N, Hkv, S, D), **half).normal_(generator=gen)
+    for b, n in enumerate(lens):                          # stale slots
+        k_pool[shared + b, :, (n - 1) % S:] = float("nan")
+        v_pool[shared + b, :, (n - 1) % S:] = float("nan")
+    new = [torch.empty((B, Hkv, D), **half).normal_(generator=gen) for _ in range(2)]
+    q = torch.empty((B, H, D), **half).normal_(generator=gen)
+    table = torch.from_numpy(table).cuda()
+    lens_t = torch.from_numpy(lens).cuda()
+    meta = torch.full((Hkv, N, 2, D), float("nan"), **half)
+    safe = torch.arange(N, dtype=torch.int32, device="cuda").view(N, 1)   # metadata of every page by itself
+    tokens = torch.full((N,), S, dtype=torch.int32, device="cuda")
+    tokens[shared:] = (lens_t - 1) % S
+    Q.quest_build_meta(Q.Cache(k_pool, v_pool, meta, safe, tokens))
+    if not (with_new and write):                          # the token is in the pools already
+        for b, n in enumerate(lens):
+            k_pool[shared + b, :, (n - 1) % S] = new[0][b]
+            v_pool[shared + b, :, (n - 1) % S] = new[1][b]
+    if not with_new:
+        tokens[shared:] += 1
+        Q.quest_build_meta(Q.Cache(k_pool, v_pool, meta, safe, tokens))
+    results = []
+    for separate in (False, True):
+        kp, vp, mt = k_pool.clone(), v_pool.clone(), meta.clone()
+        c = Q.Cache(kp, vp, mt, table, lens_t, num_heads=H, flags=flags | (Q.QUEST_FLAG_SEPARATE_LAUNCHES if separate else 0))
+        scores = torch.full((B, Hkv, pages), float("nan"), device="cuda")
+        idx = torch.full((B, Hkv, K), -7, dtype=torch.int32, device="cuda")
+        keff = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+        out = torch.full((B, H, D), float("nan"), device="cuda")
+        lse = torch.full((B, H), float("nan"), device="cuda")
+        ws = torch.zeros(max(Q.quest_step_workspace_bytes(c, K), 16), dtype=torch.uint8, device="cuda")
+        Q.quest_decode_step(c, new[0] if with_new else None, new[1] if with_new and write else None, write, q, K,
+                            1 / math.sqrt(D), scores, idx, out, ws, k_eff=keff, lse=lse)
+        torch.cuda.synchronize()
+        assert int(ws[:256 * B * H].max()) == 0 if ws.numel() >= 256 * B * H else True
+        results.append((scores, idx, keff, mt, kp, vp, out, lse))
+    got, want = results
+    for name, g, w in zip(("scores", "list", "k_eff", "metadata", "keys", "values"), got, want):
+        bits = torch.int32 if g.element_size() == 4 else torch.int16
+        assert torch.equal(g.view(bits), w.view(bits)), name
+    # logits are sums of 128 exact products, off by at most 128 * 2^-24 * sum |q_i k_i|; twice that for a weight against
+    # the sum of weights, exp2 and the division 2^-21, and fp32 sums over n tokens 2 n 2^-24; both sides
+    finite_k = torch.nan_to_num(got[4].float()).abs().sum(-1).max()
+    logit = float(finite_k * q.abs().max()) / math.sqrt(D)
+    n = min(int(lens.max()), K * S)
+    limit = 2 * (256 * 2.0 ** -24 * logit + 2.0 ** -21 + 2 * n * 2.0 ** -24)
+    v_max = float(torch.nan_to_num(got[5].float()).abs().max())
+    assert float((got[6] - want[6]).abs().max()) <= limit * v_max
+    assert float((got[7] - want[7]).abs().max()) <= limit * max(1.0, float(want[7].abs().max()))
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(str(x) for x in s))
+def test_equals_separate_launches(shape):
+    run(shape, 0, True, True, 1)
+
+
+@pytest.mark.parametrize("flags,write,with_new", [
+    (Q.QUEST_FLAG_KEEP_FIRST_PAGE | Q.QUEST_FLAG_KEEP_NEWEST_PAGE, True, True), (Q.QUEST_FLAG_DEVICE_FENCES, True, True),
+    (0, False, True), (0, False, False)])
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[6], SHAPES[10], SHAPES[20]], ids=lambda s: "x".join(str(x) for x in s))
+def test_options(shape, flags, write, with_new):
+    run(shape, flags, write, with_new, 2)
