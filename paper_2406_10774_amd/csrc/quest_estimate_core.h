@@ -343,7 +343,7 @@ struct RowOfPages {
 
 // One work-group scores a whole row, (sequence b, head h): the scores (those of estimate_wave) and the physical
 // pages go to LDS.  A row has at most kWaves * kPasses * 4 kIters pages;
-// wave w takes blocks w, w + kWaves, .. of 4 kIters pages, with the entries of up to four blocks in flight, and
+// wave w takes blocks w, w + kWaves, .. of 4 kIters pages, with the entries of up to five blocks in flight, and
 // folds them in the order they come.  What bounds it: the launch's start and two trips to memory, 1.5 us, then
 // 64 bytes a clock from L2 or, where few compute units share a row, about 27 KiB per us from memory.
 // Nobody has inserted the newest token yet: every work-group of the row stores its key and value (the
@@ -355,7 +355,7 @@ struct RowOfPages {
 template <int kWaves, int kPasses, int kIters, int kQ>
 __device__ __forceinline__ RowOfPages estimate_row(const EstimateArgs& a, int b, int h, int wave, char* stage,
                                                    float* sm_score, int* sm_phys) {
-  constexpr int kBlock = 4 * kIters, kDepth = kPasses < 4 ? kPasses : 4;
+  constexpr int kBlock = 4 * kIters, kDepth = kPasses < 6 ? kPasses : 4;
   const int lane = lane_id();
   const int grp = lane >> 4, c = lane & 15;
   const size_t bh = (size_t)b * a.num_heads + h;
