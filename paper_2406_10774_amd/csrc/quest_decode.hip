@@ -88,18 +88,23 @@ struct StepArgs : DecodeArgs {
 //
 // kEstPasses > 0: the scores do not exist either: the whole step is this launch.  Every work-group scores
 // its row itself (estimate_row, with kEstPasses and kEstQ), then selects; step_in_one_launch says when.
-template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand, int kEstPasses = 0, int kEstQ = 0>
-__global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(
+//
+// kSelWaves: waves that select; those past kWaves end when the list is there (a barrier counts the waves that
+// are left).
+template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand, int kEstPasses = 0, int kEstQ = 0,
+          int kSelWaves = kWaves>
+__global__ __launch_bounds__(kSelWaves* kWave) void decode_split_kernel(
     const typename std::conditional<(kEstPasses > 0), StepArgs, DecodeArgs>::type a) {
   using Head = HeadState<kLoads, kGroup>;
-  constexpr int kThreads = kWaves * kWave;
+  static_assert(kSelWaves == kWaves || (!kGroup && kEstPasses == 0), "the others have nothing but the list to do");
+  constexpr int kThreads = kWaves * kWave, kSelThreads = kSelWaves * kWave;
   constexpr int kSlots = Head::kSlots, kStride = Head::kStride;
   __shared__ __align__(16) float sm_acc[kWaves][kSlots * kStride];
   __shared__ float sm_m[kWaves][kSlots], sm_l[kWaves][kSlots];
   __shared__ uint32_t sm_before;
   // the selection's LDS only where there is a selection; the list as (logical page,
   // physical page) pairs
-  __shared__ __align__(16) typename std::conditional<(kSelItems > 0), TopkShared<kThreads, kSelItems>, char>::type sm_topk;
+  __shared__ __align__(16) typename std::conditional<(kSelItems > 0), TopkShared<kSelThreads, kSelItems>, char>::type sm_topk;
   __shared__ int2 sm_list[kSelItems > 0 ? kSelListCap + kWave : 1];
   // of a row that is scored here: scores and physical pages, and where groups turn the metadata (a group's
   // attention has room for that)
@@ -164,9 +169,9 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(
     auto more_loads = [&] {
 #pragma unroll
       for (int j = 0; j < (kLate ? 0 : kSelItems); ++j)
-        mine[j] = per_score[min((int)threadIdx.x + j * kThreads, a.row_len - 1)];
+        mine[j] = per_score[min((int)threadIdx.x + j * kSelThreads, a.row_len - 1)];
       seq_len = a.seq_lens[b];
-      st.init(sm_acc[wave], q, n_heads, lane);
+      st.init(sm_acc[kSelWaves > kWaves ? 0 : wave], q, n_heads, lane);
     };
     // Lanes without a page write to entries of their own behind the list.
     auto put = [&](bool selected, int pos, int entry, int j, float) {
@@ -200,14 +205,15 @@ __global__ __launch_bounds__(kWaves* kWave) void decode_split_kernel(
       topk_select<kThreads, kSelItems>(sm_topk, raw, WholeRow{a.page_shift, a.policy}(seq_len), a.row_len, a.k_pages, put,
                                        k_eff);
     } else if constexpr (kCand)
-      topk_block_put<kThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
+      topk_block_put<kSelThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
                                           CandidateRow{a.page_shift, a.policy, a.k_pages, a.chunk_pages}, more_loads);
     else
-      topk_block_put<kThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
+      topk_block_put<kSelThreads, kSelItems>(sm_topk, scores, a.seq_lens + b, a.row_len, a.k_pages, put, k_eff,
                                           WholeRow{a.page_shift, a.policy}, more_loads);
     __syncthreads();
     if (writer)
-      for (int i = threadIdx.x; i < a.k_pages; i += kThreads) a.topk_out[row * a.k_pages + i] = sm_list[i].x;
+      for (int i = threadIdx.x; i < a.k_pages; i += kSelThreads) a.topk_out[row * a.k_pages + i] = sm_list[i].x;
+    if (kSelWaves > kWaves && wave >= kWaves) return;
   } else {
     seq_len = a.seq_lens[b];
     st.init(sm_acc[wave], q, n_heads, lane);
@@ -626,11 +632,21 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     QUEST_LAUNCH_FOR_PAGE(G, W, I, C);                                                     \
     return check_launch("quest_select_decode");                                            \
   }
+#define QUEST_LONG_CASE(I)                                                                                \
+  if (!group && cand == nullptr && a.row_len <= 8 * kWave * (I)) {                                       \
+    if (c.page_size == 8)                                                                                \
+      hipLaunchKernelGGL((decode_split_kernel<2, false, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
+    else                                                                                                 \
+      hipLaunchKernelGGL((decode_split_kernel<4, false, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
+    return check_launch("quest_select_decode");                                                          \
+  }
     // Waves and scores per thread.  Four waves select short rows as fast as eight and have less to
     // merge (32 heads, 438 pages: 12.3 us a step, 12.9 with eight); a group's matrix products are better off
     // on eight (4 sequences of up to 2050 pages, 32 query / 8 KV heads: 21.4 us, 22.6 with four), and so
-    // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: four
-    // waves, so that the sums are those of attention over a given list, which the same call makes
+    // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: eight waves
+    // select (half the scores per thread each, two waves to hide each other's waits on a SIMD: 8193 pages of 32 heads, 256 in the
+    // list, 19.8 us a launch with four, 18.8 with eight, 19.3 with sixteen; 64 in the list 12.2, 11.0 and 11.0), and four
+    // attend, so that the sums are those of attention over a given list, which the same call makes
     // with QUEST_FLAG_SEPARATE_LAUNCHES.
 #define QUEST_SELECT_CASES(C)     \
   QUEST_SELECT_CASE(false, C, 4, 2) \
@@ -645,10 +661,11 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   QUEST_SELECT_CASE(true, C, 8, 8)
     QUEST_SELECT_CASES(false)
     QUEST_SELECT_CASES(true)
-    QUEST_SELECT_CASE(false, false, 4, 20)
-    QUEST_SELECT_CASE(false, false, 4, 27)
-    QUEST_SELECT_CASE(false, false, 4, 34)
+    QUEST_LONG_CASE(10)
+    QUEST_LONG_CASE(14)
+    QUEST_LONG_CASE(17)
     QUEST_SELECT_CASE(true, false, 4, 20)
+#undef QUEST_LONG_CASE
 #undef QUEST_SELECT_CASES
 #undef QUEST_SELECT_CASE
     set_error("quest_select_decode: internal: no selecting kernel for rows of %d scores", a.row_len);

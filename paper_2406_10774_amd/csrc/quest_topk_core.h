@@ -506,8 +506,9 @@ __device__ __forceinline__ void topk_select(TopkShared<kThreads, kItems>& sm, co
 
   // A sequence that ends far in front of a long row's end leaves most of a thread's pages empty: the
   // work is then done for the first of them only (rows of 8704 pages of which 435 hold tokens, K = 32, a launch
-  // that selects and attends: 7.9 us, 10.4 for all of them; 32 heads 9.2 and 11.9).
-  constexpr int kPart = kItems >= 20 ? kItems * 3 / 8 : kItems;
+  // that selects and attends: 7.9 us, 9.2 for all of them; quest_topk of rows of 6100 pages, a tenth of them in use,
+  // 32 rows 4.1 and 5.0 us).
+  constexpr int kPart = kItems >= 10 ? kItems * 3 / 8 : kItems;
   const auto rank = [&](auto items) {
     topk_rank<kThreads, kItems, decltype(items)::value>(sm, raw, first, end, need, put);
   };

@@ -1,0 +1,32 @@
+"""Where a kernel's split of a row ends: the part of a thread's pages that is enough for a short sequence in a long row
+(quest_topk, and the launch that selects and attends, for which eight waves select and four attend)."""
+import numpy as np
+import pytest
+
+from oracle import quest_oracle as O
+from test_gpu_long_rows import test_short_sequences_selected_in_the_attention_launch as check_selected
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("family", ["spread", "ties"])
+@pytest.mark.parametrize("n,part", [(5120, 3 * 512), (5121, 5 * 512), (7168, 5 * 512), (7169, 6 * 512)])
+def test_selected_in_the_attention_launch(n, part, family):
+    check_selected(n, part, 1, family)
+
+
+@pytest.mark.parametrize("n,part", [(4097, 3 * 512), (6144, 4 * 512), (8192, 6 * 512), (10241, 4 * 1024), (17408, 6 * 1024)])
+def test_topk(n, part):
+    import torch
+    from gpu_util import Layer
+    rng = np.random.default_rng(n)
+    S, heads = 8, 2
+    lens = np.array([S * part, S * (part - 1) + 1, S * part + 1, S * (part + 3) - 5, S * 70, S * n], np.int32)
+    pool = np.zeros((1, heads, S, 128), np.float16)
+    layer = Layer(pool, pool, np.zeros((len(lens), n), np.int32), lens)
+    for scores in (rng.standard_normal((len(lens), heads, n)), rng.integers(0, 9, (len(lens), heads, n))):
+        scores = scores.astype(np.float32)
+        for k in (1, 65, 800):
+            idx, keff = layer.topk(k, scores)
+            want, want_keff = O.topk(scores, lens, S, k)
+            assert np.array_equal(idx, want) and np.array_equal(keff, want_keff), k
