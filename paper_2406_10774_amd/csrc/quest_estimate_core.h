@@ -253,7 +253,7 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   asm volatile("" ::"s"(meta), "s"(q), "s"(page_table), "s"(seq_lens), "s"(max_pages), "s"(a.page_shift),
                "s"(a.num_phys_pages), "s"(num_heads));
   // The wave's page-table entries in one load (whether a page holds tokens is decided
-  // afterwards): lane c of row g fetches entry c % kIters of the row's, and the quad hands
+  // afterwards): lane c of row g fetches entry c % 4 of the row's kIters, and the quad hands
   // them round.  (A load per page, each under its own condition, is a chain of kIters trips
   // to the cache.)  Together 7.6 us instead of 7.9 us in the case above, 13.8 us instead of
   // 14.5 us at 4105 pages of 32 heads, 2.8 us instead of 3.0 us at one head.

@@ -1,9 +1,11 @@
 """Where a kernel's split of a row ends: the part of a thread's pages that is enough for a short sequence in a long row
-(quest_topk, and the launch that selects and attends, for which eight waves select and four attend)."""
+(quest_topk, and the launch that selects and attends, for which eight waves select and four attend), and the estimate's
+blocks of 12 pages (one query head per KV head, tables of 40961 to 114688 entries)."""
 import numpy as np
 import pytest
 
 from oracle import quest_oracle as O
+from test_gpu_estimate_groups import test_scores as check_scores
 from test_gpu_long_rows import test_short_sequences_selected_in_the_attention_launch as check_selected
 
 pytestmark = pytest.mark.gpu
@@ -30,3 +32,12 @@ def test_topk(n, part):
             idx, keff = layer.topk(k, scores)
             want, want_keff = O.topk(scores, lens, S, k)
             assert np.array_equal(idx, want) and np.array_equal(keff, want_keff), k
+
+
+@pytest.mark.parametrize("kv_heads,S,pages,lens", [
+    (8, 16, 1000, (1000 * 16, 12 * 16, 12 * 16 + 1, 48 * 16, 47 * 16 + 3, 997 * 16)),
+    (8, 8, 2003, (2003 * 8 - 1, 3 * 8, 1, 4 * 8 + 1, 1000 * 8, 48 * 8 + 1)),
+    (1, 64, 7001, (7001 * 64, 35 * 64, 36 * 64 + 1, 37 * 64, 7000 * 64 - 63, 12 * 64)),
+])
+def test_blocks_of_twelve_pages(kv_heads, S, pages, lens):
+    check_scores(kv_heads, 1, S, pages, lens)
