@@ -96,7 +96,7 @@ template <int kLoads, bool kGroup, int kWaves, int kSelItems, bool kCand, int kE
 __global__ __launch_bounds__(kSelWaves* kWave) void decode_split_kernel(
     const typename std::conditional<(kEstPasses > 0), StepArgs, DecodeArgs>::type a) {
   using Head = HeadState<kLoads, kGroup>;
-  static_assert(kSelWaves == kWaves || (!kGroup && kEstPasses == 0), "the others have nothing but the list to do");
+  static_assert(kSelWaves == kWaves || kEstPasses == 0, "the others have nothing but the list to do");
   constexpr int kThreads = kWaves * kWave, kSelThreads = kSelWaves * kWave;
   constexpr int kSlots = Head::kSlots, kStride = Head::kStride;
   __shared__ __align__(16) float sm_acc[kWaves][kSlots * kStride];
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kSelWaves* kWave) void decode_split_kernel(
       for (int j = 0; j < (kLate ? 0 : kSelItems); ++j)
         mine[j] = per_score[min((int)threadIdx.x + j * kSelThreads, a.row_len - 1)];
       seq_len = a.seq_lens[b];
-      st.init(sm_acc[kSelWaves > kWaves ? 0 : wave], q, n_heads, lane);
+      st.init(sm_acc[kSelWaves > kWaves ? min(wave, kWaves - 1) : wave], q, n_heads, lane);
     };
     // Lanes without a page write to entries of their own behind the list.
     auto put = [&](bool selected, int pos, int entry, int j, float) {
@@ -632,20 +632,20 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     QUEST_LAUNCH_FOR_PAGE(G, W, I, C);                                                     \
     return check_launch("quest_select_decode");                                            \
   }
-#define QUEST_LONG_CASE(I)                                                                                \
-  if (!group && cand == nullptr && a.row_len <= 8 * kWave * (I)) {                                       \
-    if (c.page_size == 8)                                                                                \
-      hipLaunchKernelGGL((decode_split_kernel<2, false, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
-    else                                                                                                 \
-      hipLaunchKernelGGL((decode_split_kernel<4, false, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
-    return check_launch("quest_select_decode");                                                          \
+#define QUEST_LONG_CASE(G, I)                                                                             \
+  if (group == G && cand == nullptr && a.row_len <= 8 * kWave * (I)) {                                    \
+    if (c.page_size == 8)                                                                                 \
+      hipLaunchKernelGGL((decode_split_kernel<2, G, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
+    else                                                                                                  \
+      hipLaunchKernelGGL((decode_split_kernel<4, G, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
+    return check_launch("quest_select_decode");                                                           \
   }
     // Waves and scores per thread.  Four waves select short rows as fast as eight and have less to
     // merge (32 heads, 438 pages: 12.3 us a step, 12.9 with eight); a group's matrix products are better off
     // on eight (4 sequences of up to 2050 pages, 32 query / 8 KV heads: 21.4 us, 22.6 with four), and so
     // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: eight waves
     // select (half the scores per thread each, two waves to hide each other's waits on a SIMD: 8193 pages of 32 heads, 256 in the
-    // list, 19.8 us a launch with four, 18.8 with eight, 19.3 with sixteen; 64 in the list 12.2, 11.0 and 11.0), and four
+    // list, 19.8 us a launch with four, 18.8 with eight, 19.3 with sixteen; 64 in the list 12.2, 11.0 and 11.0; 32 query / 8 KV heads of 4600 pages 9.7, 9.1), and four
     // attend, so that the sums are those of attention over a given list, which the same call makes
     // with QUEST_FLAG_SEPARATE_LAUNCHES.
 #define QUEST_SELECT_CASES(C)     \
@@ -661,10 +661,10 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   QUEST_SELECT_CASE(true, C, 8, 8)
     QUEST_SELECT_CASES(false)
     QUEST_SELECT_CASES(true)
-    QUEST_LONG_CASE(10)
-    QUEST_LONG_CASE(14)
-    QUEST_LONG_CASE(17)
-    QUEST_SELECT_CASE(true, false, 4, 20)
+    QUEST_LONG_CASE(false, 10)
+    QUEST_LONG_CASE(false, 14)
+    QUEST_LONG_CASE(false, 17)
+    QUEST_LONG_CASE(true, 10)
 #undef QUEST_LONG_CASE
 #undef QUEST_SELECT_CASES
 #undef QUEST_SELECT_CASE

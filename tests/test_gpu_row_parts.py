@@ -12,9 +12,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("family", ["spread", "ties"])
-@pytest.mark.parametrize("n,part", [(5120, 3 * 512), (5121, 5 * 512), (7168, 5 * 512), (7169, 6 * 512)])
-def test_selected_in_the_attention_launch(n, part, family):
-    check_selected(n, part, 1, family)
+@pytest.mark.parametrize("n,part,group", [(5120, 3 * 512, 1), (5121, 5 * 512, 1), (7168, 5 * 512, 1), (7169, 6 * 512, 1),
+                                          (5119, 3 * 512, 4), (4098, 3 * 512, 9)])
+def test_selected_in_the_attention_launch(n, part, group, family):
+    check_selected(n, part, group, family)
 
 
 @pytest.mark.parametrize("n,part", [(4097, 3 * 512), (6144, 4 * 512), (8192, 6 * 512), (10241, 4 * 1024), (17408, 6 * 1024)])
