@@ -235,7 +235,7 @@ def main():
     two_launches = one_call and inside
     if one_call:
         us_step, us_step_events = two_us, two_us_events
-        calls = ("quest_decode_step (two launches: estimate; selection + attention)" if inside
+        calls = ("quest_decode_step (two launches: estimate; selection + attention; short rows: one)" if inside
                  else "quest_decode_step (one call; estimate, selection and attention as launches of their own)")
 
     g_dense = capture(dense_step, timed)
