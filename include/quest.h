@@ -265,7 +265,7 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * several query heads per KV head) and QUEST_FLAG_SEPARATE_LAUNCHES is not set,
  * else three (four where very long rows are selected in two stages).  Where the two
  * launches would be, short rows take one, in which every work-group also scores its
- * (sequence, KV head): up to 320 pages, up to 1024 with many (sequence, head) pairs,
+ * (sequence, KV head): up to 256 pages, 320 from 32 and 1024 with many (sequence, head) pairs,
  * up to 128 with several query heads per KV head. */
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes);
 int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v_new,

@@ -748,9 +748,9 @@ size_t selection_workspace_bytes(const quest_cache& c) {
 // row scores all of it, which its compute unit's path to L2 (64 bytes a clock) and its vector unit have to
 // carry, and a row that comes from memory reaches one unit at 25 to 30 KiB per us.  us a step, two
 // launches / one:
-//   one head, 61 pages 8.0 / 6.8, 124 8.5 / 7.4, 252 9.3 / 9.2, 314 9.2 / 9.6, but called one after the other, not
-//   replayed, 256 pages 9.5 / 8.3: a call has one launch to enqueue; 32 heads, 61 9.7 / 8.1, 124 11.0 / 9.5, 314
-//   11.5 / 11.4, but 434 11.9 / 12.7: a row in several splits up to 320 pages;
+//   one head, 61 pages 8.0 / 6.8, 124 8.5 / 7.4, 252 9.3 / 9.2, but 314 9.2 / 9.6, and replayed in a
+//   graph of 16 layers, 257 pages 8.7 / 9.7 (called one after the other, 260 pages 9.5 / 8.3): up to 256; 32 heads, 61 9.7 / 8.1, 124 11.0 / 9.5, 314
+//   11.5 / 11.4, but 434 11.9 / 12.7: from 32 rows in several splits on up to 320 pages;
 //   two splits, 4 sequences of 32 heads, 996 pages 38.7 / 37.3, shorter ones among them 35.5 / 34.1, but 3
 //   sequences (96 rows) of 700 to 1300 pages 1 to 15 % slower: from 113 rows on up to 1024;
 //   one split, 6 sequences of 32 heads, 434 pages 27.8 / 26.6, 996 36.5 / 34.3, a list of 256 tokens 25.3 / 23.4; but
@@ -765,7 +765,7 @@ bool step_in_one_launch(const quest_cache& c, int k_pages) {
   const long items = group_items(c), pages = c.max_pages_per_seq;
   if (group_size(c) > 1) return group_size(c) <= 8 && items <= kComputeUnits && pages <= (group_size(c) <= 4 ? 128 : 64);
   const int splits = plan_splits(c, k_pages, true).splits;
-  if (items <= 112) return pages <= 320;
+  if (items <= 112) return pages <= (items >= 32 ? 320 : 256);
   if (items > 2 * kComputeUnits || splits > 2) return pages <= 256 && (items <= 4 * kComputeUnits || pages >= 64);
   if (items > kComputeUnits) return pages <= 512;
   return pages <= 1024;

@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (3, 2, 2, 16, 1, 1), (3, 2, 2, 16, 17, 4), (2, 32, 32, 16, 64, 16), (3, 3, 3, 8, 65, 300), (2, 1, 1, 32, 127, 40),
     (2, 2, 2, 64, 128, 9), (2, 32, 32, 16, 129, 64), (3, 1, 1, 8, 255, 2000), (2, 2, 2, 16, 256, 32), (2, 2, 2, 16, 257, 32), (3, 1, 1, 8, 320, 33), (2, 2, 2, 16, 321, 64),
+    (1, 32, 32, 16, 257, 32), (4, 8, 8, 8, 320, 33), (3, 32, 32, 8, 321, 20), (31, 1, 1, 8, 257, 9),
     (15, 8, 8, 8, 257, 20), (24, 8, 8, 8, 512, 64), (13, 40, 40, 8, 250, 8), (33, 8, 8, 8, 511, 16), (16, 8, 8, 8, 513, 40),
     (17, 8, 8, 8, 1024, 17), (25, 8, 8, 8, 1024, 33), (25, 8, 8, 8, 1025, 30), (130, 8, 8, 8, 65, 3),
     (2, 4, 2, 16, 31, 4), (2, 12, 4, 8, 128, 500), (3, 32, 8, 16, 127, 64), (8, 32, 8, 64, 100, 32), (2, 10, 2, 16, 33, 8),
