@@ -266,7 +266,10 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * else three (four where very long rows are selected in two stages).  Where the two
  * launches would be, short rows take one, in which every work-group also scores its
  * (sequence, KV head): up to 256 pages, 320 from 32 and 1024 with many (sequence, head) pairs,
- * up to 128 with several query heads per KV head. */
+ * up to 128 with several query heads per KV head.
+ * Results must not overlap what the call reads, with two exceptions: out, lse, topk_idx and k_eff may
+ * lie on k_new and v_new, and an fp16 out may be q itself (out == q).  (Such a step takes two launches where
+ * one would write a result before all of the launch has read what lies there.) */
 int quest_step_workspace_bytes(const quest_cache* cache, int32_t k_pages, size_t* out_bytes);
 int quest_decode_step(const quest_cache* cache, const void* k_new, const void* v_new,
                       int32_t k_pool_write, const void* q, int32_t k_pages, float sm_scale,

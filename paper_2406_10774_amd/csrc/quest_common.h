@@ -102,8 +102,11 @@ int launch_select_decode(const quest_cache& c, const void* q, const float* score
                          float sm_scale, int32_t* topk_idx, int32_t* k_eff, void* out,
                          int out_is_fp16, float* lse, const Workspace& workspace, hipStream_t s);
 
-// The whole step as one launch.
+// The whole step as one launch: the shapes, and the buffers, for which it may take the place of two.
 bool step_in_one_launch(const quest_cache& c, int k_pages);
+bool step_reads_before_it_writes(const quest_cache& c, const void* k_new, const void* v_new, const void* q, int k_pages,
+                                 const int32_t* topk_idx, const int32_t* k_eff, const void* out, int out_is_fp16,
+                                 const float* lse, const Workspace& workspace);
 int launch_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write, const void* q, int k_pages,
                 float sm_scale, float* scores, int32_t* topk_idx, int32_t* k_eff, void* out, int out_is_fp16, float* lse,
                 const Workspace& workspace, hipStream_t s);

@@ -770,6 +770,30 @@ bool step_in_one_launch(const quest_cache& c, int k_pages) {
   if (items > kComputeUnits) return pages <= 512;
   return pages <= 1024;
 }
+
+// In two launches every wave has read the new token when the second one writes its results, and a
+// work-group of the second reads no query vectors but those of the heads whose outputs it writes: a caller may have its
+// results written over k_new and v_new, and fp16 outputs over q, head by head.  In one launch a
+// work-group may end before another one of its launch has begun, so results must not lie on the new token; and where a
+// group's query heads have a work-group each, every one of them scores with all the queries of the group.
+bool step_reads_before_it_writes(const quest_cache& c, const void* k_new, const void* v_new, const void* q, int k_pages,
+                                 const int32_t* topk_idx, const int32_t* k_eff, const void* out, int out_is_fp16,
+                                 const float* lse, const Workspace& w) {
+  const size_t heads = (size_t)c.batch * c.num_heads, kv = (size_t)c.batch * kv_heads(c);
+  const size_t q_bytes = heads * kRowBytes, new_bytes = kv * kRowBytes, out_bytes = heads * kHeadDim * (out_is_fp16 ? 2 : 4);
+  const auto meet = [](const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return a != nullptr && b != nullptr && x < y + nb && y < x + na;
+  };
+  const auto on = [&](const void* result, size_t bytes) {
+    return meet(result, bytes, k_new, new_bytes) || meet(result, bytes, v_new, new_bytes);
+  };
+  const bool in_place = out == q && out_is_fp16 && !heads_apart(c, k_pages, true);
+  if (meet(out, out_bytes, q, q_bytes) && !in_place) return false;
+  return !on(out, out_bytes) && !on(lse, heads * sizeof(float)) && !on(topk_idx, kv * k_pages * sizeof(int32_t)) &&
+         !on(k_eff, c.batch * sizeof(int32_t)) && !on(w.attention, w.attention_bytes);
+}
+
 int launch_step(const quest_cache& c, const void* k_new, const void* v_new, int k_pool_write, const void* q, int k_pages,
                 float sm_scale, float* scores, int32_t* topk_idx, int32_t* k_eff, void* out, int out_is_fp16, float* lse,
                 const Workspace& w, hipStream_t s) {

@@ -29,7 +29,8 @@ int launch_decode_step(const quest_cache& c, const void* k_new, const void* v_ne
                        const void* q, int k_pages, float sm_scale, float* scores, int32_t* topk_idx,
                        int32_t* k_eff, void* out, int out_is_fp16, float* lse, const Workspace& workspace,
                        hipStream_t s) {
-  if (step_in_one_launch(c, k_pages))
+  if (step_in_one_launch(c, k_pages) &&
+      step_reads_before_it_writes(c, k_new, v_new, q, k_pages, topk_idx, k_eff, out, out_is_fp16, lse, workspace))
     return launch_step(c, k_new, v_new, k_pool_write, q, k_pages, sm_scale, scores, topk_idx, k_eff, out, out_is_fp16,
                        lse, workspace, s);
   int r = k_new ? launch_append_estimate(c, k_new, v_new, k_pool_write, q, scores, s)

@@ -7,6 +7,20 @@ import numpy as np
 from paper_2406_10774_amd import binding as Q
 
 
+def kernel_launches(call):
+    """How many launches `call` enqueues: the nodes of a graph that it is captured in (and that is not run)."""
+    import ctypes
+    import torch
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:            # the runtime that torch has loaded
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    count = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
 class Layer:
     """Device copy of one layer's paged KV cache plus the buffers of a decode step."""
 
