@@ -633,7 +633,7 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     return check_launch("quest_select_decode");                                            \
   }
 #define QUEST_LONG_CASE(G, I)                                                                             \
-  if (group == G && cand == nullptr && a.row_len <= 8 * kWave * (I)) {                                    \
+  if (group == G && cand == nullptr && eight_select && a.row_len <= 8 * kWave * (I)) {                                  \
     if (c.page_size == 8)                                                                                 \
       hipLaunchKernelGGL((decode_split_kernel<2, G, 4, I, false, 0, 0, 8>), grid, dim3(8 * kWave), 0, s, a); \
     else                                                                                                  \
@@ -643,11 +643,16 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     // Waves and scores per thread.  Four waves select short rows as fast as eight and have less to
     // merge (32 heads, 438 pages: 12.3 us a step, 12.9 with eight); a group's matrix products are better off
     // on eight (4 sequences of up to 2050 pages, 32 query / 8 KV heads: 21.4 us, 22.6 with four), and so
-    // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: eight waves
-    // select (half the scores per thread each, two waves to hide each other's waits on a SIMD: 8193 pages of 32 heads, 256 in the
-    // list, 19.8 us a launch with four, 18.8 with eight, 19.3 with sixteen; 64 in the list 12.2, 11.0 and 11.0; 32 query / 8 KV heads of 4600 pages 9.7, 9.1), and four
+    // is the selection in the middle (32 heads, 2053 pages: 19.8 and 20.1 us).  Rows of more than 4096 pages: four waves
     // attend, so that the sums are those of attention over a given list, which the same call makes
-    // with QUEST_FLAG_SEPARATE_LAUNCHES.
+    // with QUEST_FLAG_SEPARATE_LAUNCHES, and up to a number of work-groups eight select (half the scores per thread each, two
+    // waves to hide each other's waits on a SIMD: 8193 pages of 32 heads, 256 in the list, 19.8 us a launch with four, 18.8
+    // with eight, 19.3 with sixteen; 64 in the list 12.2, 11.0 and 11.0; 32 query / 8 KV heads of 4600 pages 9.7, 9.1).  More
+    // give a compute unit several work-groups, which hide each other's waits themselves as far as they fit on it.  A
+    // group's: a list of 16 pages of 8 tokens, 256 of them 8.1 us with four, 7.5 with eight, but 264 10.7 and 14.7, 384
+    // 11.7 and 15.9; 64 pages of 16 tokens, 264 35.1 and 45.3, 512 48.3 and 53.8.  One query head's: 16 pages
+    // of 8 tokens, 512 11.8 and 11.2, but 640 15.1 and 17.6, 1024 18.5 and 21.5 (other row lengths 0 to 3 % less);
+    // 64 pages of 16 tokens, 320 items of three splits 32.5 and 35.1.
 #define QUEST_SELECT_CASES(C)     \
   QUEST_SELECT_CASE(false, C, 4, 2) \
   QUEST_SELECT_CASE(false, C, 4, 4) \
@@ -661,10 +666,15 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
   QUEST_SELECT_CASE(true, C, 8, 8)
     QUEST_SELECT_CASES(false)
     QUEST_SELECT_CASES(true)
+    const bool eight_select = items * a.splits <= (group ? kComputeUnits : 2 * kComputeUnits);
     QUEST_LONG_CASE(false, 10)
     QUEST_LONG_CASE(false, 14)
     QUEST_LONG_CASE(false, 17)
     QUEST_LONG_CASE(true, 10)
+    QUEST_SELECT_CASE(false, false, 4, 20)
+    QUEST_SELECT_CASE(false, false, 4, 27)
+    QUEST_SELECT_CASE(false, false, 4, 34)
+    QUEST_SELECT_CASE(true, false, 4, 20)
 #undef QUEST_LONG_CASE
 #undef QUEST_SELECT_CASES
 #undef QUEST_SELECT_CASE

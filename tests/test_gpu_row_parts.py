@@ -42,3 +42,38 @@ def test_topk(n, part):
 ])
 def test_blocks_of_twelve_pages(kv_heads, S, pages, lens):
     check_scores(kv_heads, 1, S, pages, lens)
+
+
+@pytest.mark.parametrize("B,heads,group,n", [
+    (32, 16, 1, 4200), (33, 16, 1, 4097), (33, 16, 1, 5120), (33, 16, 1, 5121), (33, 16, 1, 6912), (33, 16, 1, 8704),
+    (32, 8, 4, 5120), (33, 8, 4, 4097), (33, 8, 4, 5120), (17, 8, 9, 4600),
+])
+def test_many_rows_selected_in_the_attention_launch(B, heads, group, n):
+    """Eight waves select in up to 512 work-groups (256 of groups), four in more: lists of the separate launches, and as
+    four attend either way, their out and lse, bit for bit."""
+    import math
+    import torch
+    from paper_2406_10774_amd import binding as Q
+    S, N, gen = 8, 200, torch.Generator(device="cuda").manual_seed(n)
+    half = dict(dtype=torch.float16, device="cuda", generator=gen)
+    pools = [torch.randn((N, heads, S, 128), **half) for _ in range(2)]
+    q = torch.randn((B, heads * group, 128), **half)
+    meta = torch.zeros((heads, N, 2, 128), dtype=torch.float16, device="cuda")
+    table = torch.randint(0, N, (B, n), dtype=torch.int32, device="cuda", generator=gen)
+    lens = torch.randint(1, S * n + 1, (B,), dtype=torch.int32, device="cuda", generator=gen)
+    lens[:3] = torch.tensor([S * n, S * n * 3 // 8, 1])
+    scores = torch.randn((B, heads, n), device="cuda", generator=gen)
+    scores[1::2] = torch.round(4 * scores[1::2])                   # thousands of equal scores
+    for k in (16, 300):
+        got = []
+        for flags in (0, Q.QUEST_FLAG_SEPARATE_LAUNCHES):
+            cache = Q.Cache(*pools, meta, table, lens, flags=flags, num_heads=heads * group)
+            ws = torch.zeros(max(8, Q.quest_workspace_bytes(cache, k)), dtype=torch.uint8, device="cuda")
+            idx = torch.full((B, heads, k), -7, dtype=torch.int32, device="cuda")
+            keff = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+            out = torch.full(q.shape, float("nan"), device="cuda")
+            lse = torch.full(q.shape[:2], float("nan"), device="cuda")
+            Q.quest_select_decode(cache, q, scores, k, 1 / math.sqrt(128), idx, out, k_eff=keff, lse=lse, workspace=ws)
+            got.append((idx, keff, out, lse))
+        for name, a, b in zip(("list", "k_eff", "out", "lse"), *got):
+            assert torch.equal(a, b), (name, k)
