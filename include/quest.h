@@ -265,8 +265,8 @@ int quest_select_decode(const quest_cache* cache, const void* q, const float* sc
  * several query heads per KV head) and QUEST_FLAG_SEPARATE_LAUNCHES is not set,
  * else three (four where very long rows are selected in two stages).  Where the two
  * launches would be, short rows take one, in which every work-group also scores its
- * (sequence, KV head): up to 256 pages, 320 from 32 and 1024 with many (sequence, head) pairs,
- * up to 128 with several query heads per KV head.
+ * (sequence, KV head): up to 128 to 256 pages, up to 512 or 1024 with 113 to 512 (sequence, head) pairs;
+ * up to 64 or 128 with two to eight query heads per KV head.
  * Results must not overlap what the call reads, with two exceptions: out, lse, topk_idx and k_eff may
  * lie on k_new and v_new, and an fp16 out may be q itself (out == q).  (Such a step takes two launches where
  * one would write a result before all of the launch has read what lies there.) */

@@ -603,12 +603,11 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     return check_launch("quest_decode_step");                                              \
   }
     const int queries = a.group == 1 ? 1 : estimate_on_matrix_cores(c) ? 0 : 4;
-    // Waves, scores per thread, passes (estimate_row).  Four waves up to 320 pages; more pages of more rows are streamed faster by
+    // Waves, scores per thread, passes (estimate_row).  Four waves up to 256 pages; more pages of more rows are streamed faster by
     // eight (192 rows of 313 pages, 64 tokens each, 22.9 us a step, 23.6 with four), but those take a compute unit each
     // (384 rows of 434 pages 47.3 us with four, 52.6 with eight).
     QUEST_STEP_CASE(false, 4, 1, 2, 1)
     QUEST_STEP_CASE(false, 4, 1, 4, 1)
-    if (items <= 112) QUEST_STEP_CASE(false, 4, 2, 5, 1)
     if (items <= kComputeUnits) {
       QUEST_STEP_CASE(false, 8, 1, 4, 1)
       QUEST_STEP_CASE(false, 8, 2, 8, 1)
@@ -620,7 +619,6 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     QUEST_STEP_CASE(true, 8, 1, 1, 0)
     QUEST_STEP_CASE(false, 8, 1, 1, 0)
     QUEST_STEP_CASE(true, 8, 1, 2, 0)
-    QUEST_STEP_CASE(false, 8, 1, 2, 0)
 #undef QUEST_STEP_CASE
 #undef QUEST_STEP
     set_error("quest_decode_step: internal: no one-launch step for rows of %d pages", a.max_pages);
@@ -754,31 +752,42 @@ size_t selection_workspace_bytes(const quest_cache& c) {
 }
 
 // The whole step as one launch (decode_split_kernel with kEstPasses): the estimate's launch, the gap between
-// two launches and the trip of the scores through memory go, about 3.4 us of 11 to 12. Against that every split of a
-// row scores all of it, which its compute unit's path to L2 (64 bytes a clock) and its vector unit have to
-// carry, and a row that comes from memory reaches one unit at 25 to 30 KiB per us.  us a step, two
-// launches / one:
-//   one head, 61 pages 8.0 / 6.8, 124 8.5 / 7.4, 252 9.3 / 9.2, but 314 9.2 / 9.6, and replayed in a
-//   graph of 16 layers, 257 pages 8.7 / 9.7 (called one after the other, 260 pages 9.5 / 8.3): up to 256; 32 heads, 61 9.7 / 8.1, 124 11.0 / 9.5, 314
-//   11.5 / 11.4, but 434 11.9 / 12.7: from 32 rows in several splits on up to 320 pages;
-//   two splits, 4 sequences of 32 heads, 996 pages 38.7 / 37.3, shorter ones among them 35.5 / 34.1, but 3
-//   sequences (96 rows) of 700 to 1300 pages 1 to 15 % slower: from 113 rows on up to 1024;
-//   one split, 6 sequences of 32 heads, 434 pages 27.8 / 26.6, 996 36.5 / 34.3, a list of 256 tokens 25.3 / 23.4; but
-//   5 to 8 of 1500 to 2000 pages, 2 to 10 % slower; three splits as a row in several;
-//   more rows than units, 12 sequences of 32 heads, 252 pages 46.1 / 42.6, 434 49.5 / 47.3; of 996, or 640 rows
-//   of 500, up to 8 % slower; thousands of rows of a few pages 3 %, of 120 pages 4 % faster.
-// Groups of query heads have each page scored for all of them: 32 query / 8 KV heads, 120 pages 9.9 / 9.8; 10 sequences
-// of 64 / 8 heads, 56 pages 13.4 / 12.5, one of 120 10.5 / 10.7; with 16 and more heads in a group, or more rows
-// than units, 2 to 13 % slower.
+// two launches and the trip of the scores through memory go, about 3.4 us of 11 to 12. Against that every
+// work-group of a row scores all of it, which its compute unit's path to L2 (64 bytes a clock) and its vector unit
+// have to carry, and a row that comes from memory reaches one unit at 25 to 30 KiB per us.  The lines lie where 5700
+// calls of random shapes (1 to 64 sequences, ragged or in wide tables, pages of 8 to 64 tokens, lists of one page to all)
+// stop being faster on either side; replayed, us a step, two launches / one:
+//   up to 8 rows, 256 pages: one head, 61 pages 8.0 / 6.8, 124 8.5 / 7.4, 252 9.3 / 9.2, but 257 8.7 / 9.7, 314 9.2 / 9.6;
+//   9 to 112 rows, 192 pages: 32 heads of 61 9.7 / 8.1, of 124 11.0 / 9.5; but 32 of 249, all attended, 12.0 / 13.0, of 257
+//   17.0 / 19.0; 38 of 288 8.9 / 9.6; with more than half of the pages in the list 128: 64 rows of 161, all
+//   attended, 13.6 / 14.4;
+//   113 to 160 rows, 512 pages: 144 of 434 16.5 / 14.3, 128 of 507 18.2 / 17.5; but 120 of 740 16.6 / 18.3, 160 of 881 19.5 / 20.7; more rows up to 256, 1024 pages: 6 sequences of 32 heads, 434 pages
+//   27.8 / 26.6, 996 36.5 / 34.3; but 5 to 8 of 1500 to 2000 pages, 2 to 10 % slower;
+//   257 to 384 rows, which leave the second round of units half empty, 256 pages: 280 of 315 15.1 / 16.9, 336 of
+//   305 18.0 / 19.8; up to 512 rows, 512 pages: 12 sequences of 32 heads, 434 49.5 / 47.3;
+//   three splits of a row, or more rows, 256 pages: 640 rows of 500 up to 8 % slower; thousands of rows of a few pages
+//   3 %, of 120 pages 4 % faster.
+// Groups of query heads have each page scored for all of them, one work-group a unit: 64 pages (10 sequences of 64 / 8
+// heads, 56 pages 13.4 / 12.5, one of 120 10.5 / 10.7), groups of up to four with half of the pages or less in the list 128
+// (31 sequences of 32 / 8 heads, 109 pages 12.5 / 10.9, 10 of 64 / 16, 95 pages 17.1 / 15.7; all attended, 10 of 32 / 8, 71
+// pages 14.6 / 15.3).  Query heads in work-groups of their own each score the row for the whole group: 64 pages (16 / 8 heads
+// of 125 pages 9.3 / 9.6, 15 / 5 of 103 9.2 / 9.7), and it is those work-groups that have to fit (18
+// sequences of 40 / 5 heads, one page, 720 of them: 8.0 / 11.1).  With 16 and more heads in a group 2 to 13 % slower.
 bool step_in_one_launch(const quest_cache& c, int k_pages) {
   if (!select_decode_supported(c, k_pages) || c.num_phys_pages >= (1l << 22)) return false;  // (32-bit offsets)
-  const long items = group_items(c), pages = c.max_pages_per_seq;
-  if (group_size(c) > 1) return group_size(c) <= 8 && items <= kComputeUnits && pages <= (group_size(c) <= 4 ? 128 : 64);
-  const int splits = plan_splits(c, k_pages, true).splits;
-  if (items <= 112) return pages <= (items >= 32 ? 320 : 256);
-  if (items > 2 * kComputeUnits || splits > 2) return pages <= 256 && (items <= 4 * kComputeUnits || pages >= 64);
-  if (items > kComputeUnits) return pages <= 512;
-  return pages <= 1024;
+  const long pages = c.max_pages_per_seq;
+  const bool few_chosen = 2l * k_pages <= pages;
+  if (const int group = group_size(c); group > 1) {
+    const bool apart = heads_apart(c, k_pages, true);
+    const long items = apart ? (long)c.batch * c.num_heads : group_items(c);
+    return group <= 8 && items <= kComputeUnits && pages <= (group <= 4 && !apart && few_chosen ? 128 : 64);
+  }
+  const long items = group_items(c);
+  if (items <= 112) return pages <= (items <= 8 ? 256 : few_chosen ? 192 : 128);
+  if (items > 2 * kComputeUnits || plan_splits(c, k_pages, true).splits > 2)
+    return pages <= 256 && (items <= 4 * kComputeUnits || pages >= 64);
+  if (items > kComputeUnits) return pages <= (2 * items > 3 * kComputeUnits ? 512 : 256);
+  return pages <= (items > 160 ? 1024 : 512);
 }
 
 // In two launches every wave has read the new token when the second one writes its results, and a

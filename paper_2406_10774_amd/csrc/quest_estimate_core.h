@@ -343,7 +343,7 @@ struct RowOfPages {
 
 // One work-group scores a whole row, (sequence b, head h): the scores (those of estimate_wave) and the physical
 // pages go to LDS.  A row has at most kWaves * kPasses * 4 kIters pages;
-// wave w takes blocks w, w + kWaves, .. of 4 kIters pages, with the entries of up to five blocks in flight, and
+// wave w takes blocks w, w + kWaves, .. of 4 kIters pages, with the entries of up to four blocks in flight, and
 // folds them in the order they come.  What bounds it: the launch's start and two trips to memory, 1.5 us, then
 // 64 bytes a clock from L2 or, where few compute units share a row, about 27 KiB per us from memory.
 // Nobody has inserted the newest token yet: every work-group of the row stores its key and value (the
@@ -351,11 +351,11 @@ struct RowOfPages {
 // one of them writes that entry back (store_row).  Another work-group may find the entry as it was or with the key folded in,
 // element by element: min and max with the same key again change nothing, and a page's first token
 // does not look at the entry.
-// kQ: 1, 0 (matrix cores), or 4 (up to four).
+// kQ: 1, 0 (matrix cores, groups of up to 16), or 4 (up to four).
 template <int kWaves, int kPasses, int kIters, int kQ>
 __device__ __forceinline__ RowOfPages estimate_row(const EstimateArgs& a, int b, int h, int wave, char* stage,
                                                    float* sm_score, int* sm_phys) {
-  constexpr int kBlock = 4 * kIters, kDepth = kPasses < 6 ? kPasses : 4;
+  constexpr int kBlock = 4 * kIters, kDepth = kPasses < 4 ? kPasses : 4;
   const int lane = lane_id();
   const int grp = lane >> 4, c = lane & 15;
   const size_t bh = (size_t)b * a.num_heads + h;
@@ -431,7 +431,6 @@ __device__ __forceinline__ RowOfPages estimate_row(const EstimateArgs& a, int b,
       }
     }
     if (base_of(p) < num_pages) {
-      if (kQ == 0 && p > 0 && a.group > 16) queries.load(0, lane);
       score_wave<kIters, kQ>(queries, low, high, num_pages - base_of(p), stage, lane, [&](bool has, int page, float score) {
         if (has) sm_score[base_of(p) + page] = score;
       });

@@ -105,3 +105,34 @@ def test_equals_separate_launches(shape):
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[6], SHAPES[10], SHAPES[20]], ids=lambda s: "x".join(str(x) for x in s))
 def test_options(shape, flags, write, with_new):
     run(shape, flags, write, with_new, 2)
+
+
+@pytest.mark.parametrize("shape,launches", [
+    ((1, 8, 8, 16, 256, 32), 1), ((1, 8, 8, 16, 257, 32), 2),                                # up to 8 rows
+    ((1, 9, 9, 16, 192, 96), 1), ((1, 9, 9, 16, 193, 20), 2), ((1, 9, 9, 16, 192, 97), 2),   # up to 112
+    ((1, 9, 9, 16, 128, 128), 1), ((1, 9, 9, 16, 129, 128), 2), ((2, 56, 56, 8, 192, 9), 1), ((1, 32, 32, 16, 257, 32), 2),
+    ((1, 113, 113, 16, 512, 9), 1), ((4, 40, 40, 16, 512, 9), 1), ((4, 40, 40, 16, 513, 9), 2),
+    ((1, 161, 161, 16, 1024, 9), 1), ((8, 32, 32, 8, 1024, 300), 1), ((8, 32, 32, 8, 1025, 300), 2),
+    ((1, 150, 150, 16, 256, 192), 1), ((1, 150, 150, 16, 257, 192), 2),                      # three splits
+    ((1, 257, 257, 16, 256, 9), 1), ((1, 257, 257, 16, 257, 9), 2), ((12, 32, 32, 8, 257, 30), 2),
+    ((1, 385, 385, 8, 512, 30), 1), ((16, 32, 32, 64, 512, 16), 1), ((16, 32, 32, 64, 513, 16), 2),
+    ((1, 513, 513, 16, 256, 9), 1), ((1, 513, 513, 16, 257, 9), 2), ((5, 205, 205, 16, 63, 9), 2), ((5, 205, 205, 16, 64, 9), 1),
+    ((1, 16, 8, 16, 64, 40), 1), ((1, 16, 8, 16, 65, 40), 2),                                # query heads apart
+    ((16, 16, 8, 16, 64, 1), 1), ((17, 16, 8, 16, 64, 1), 2), ((18, 40, 5, 16, 1, 1), 2),
+    ((8, 32, 8, 16, 128, 64), 1), ((8, 32, 8, 16, 129, 64), 2), ((8, 32, 8, 16, 128, 65), 2),  # together
+    ((32, 32, 8, 16, 64, 64), 1), ((33, 32, 8, 16, 64, 64), 2),
+    ((8, 64, 8, 16, 64, 30), 1), ((8, 64, 8, 16, 65, 30), 2), ((2, 72, 8, 16, 30, 20), 2),
+], ids=str)
+def test_where_one_launch_ends(shape, launches):
+    """Only captured: nothing runs, so the buffers hold nothing."""
+    import torch
+    from gpu_util import kernel_launches
+    B, H, Hkv, S, pages, K = shape
+    pool = torch.empty((1, Hkv, S, 128), dtype=torch.float16, device="cuda")
+    meta = torch.empty((Hkv, 1, 2, 128), dtype=torch.float16, device="cuda")
+    table, lens = (torch.zeros(n, dtype=torch.int32, device="cuda") for n in ((B, pages), (B,)))
+    c = Q.Cache(pool, pool, meta, table, lens, num_heads=H)
+    new, q, out = (torch.empty((B, n, 128), dtype=torch.float16, device="cuda") for n in (Hkv, H, H))
+    scores, idx = torch.empty((B, Hkv, pages), device="cuda"), torch.empty((B, Hkv, K), dtype=torch.int32, device="cuda")
+    ws = torch.zeros(max(Q.quest_step_workspace_bytes(c, K), 16), dtype=torch.uint8, device="cuda")
+    assert kernel_launches(lambda: Q.quest_decode_step(c, new, new, True, q, K, 0.1, scores, idx, out, ws)) == launches
