@@ -6,7 +6,7 @@
 // go through v_dot2_f32_f16 (fp16 products are exact in fp32, fp32 sum), or, where several
 // query heads share a KV head, through matrix products with q split by its sign.
 //
-// One wavefront owns (head, block of 8, 12 or 16 consecutive logical pages).  A 16-lane
+// One wavefront owns (head, block of 8 or 16 consecutive logical pages).  A 16-lane
 // DPP row reads one metadata entry: 16 B per lane of the min row, then 16 B per
 // lane of the max row (two 256 B segments, 512 B contiguous), so one wave-wide
 // load instruction covers four pages; the 128-channel sum is a reduction inside
@@ -58,15 +58,13 @@ namespace {
 // 56.0 against 54.0 us for 2 sequences and 8 KV heads (0.49 M pages).
 // On the matrix cores 16 pages fill an operand and eight leave half of it: 3.0 against 3.3 us at 4100
 // entries, 4.7 against 4.8 at 33k, 6.6 against 6.4 at 66k, 15.7 against 14.2 at 263k.
-// One query head, tables for which the waves of eight pages are about one round (8192 fit the chip) or little
-// more: 12 pages.  us of 8 / 12: 48k entries 5.7 / 5.5, 66k (the last 32 work-groups of eight would wait for a round of their
-// own) 7.1 / 7.0, 76k 8.1 / 7.8, 80k of two ragged sequences 7.0 / 6.4, 96k 9.4 / 9.1, 114k 10.9 / 10.8; but 131k 11.9 / 11.9, 24k
-// 3.8 / 3.9, and 64k, where the waves of eight just fit, 6.8 / 7.0.
-constexpr int kFullRound = 2048;  // work-groups
+// Not 12 for one query head in tables of 41k to 114k entries, where the waves of eight are about one round: full
+// tables gain 2 to 8 % (66k 7.8 and 7.5), but where the sequences are shorter than the table's rows the waves with
+// pages fall on the same units in every few rows once the work-groups of a row go into 256 a few times (2049 pages are
+// 43 of 12 pages a wave, 65 of eight): at 0.3 of 2049 pages, 32 heads, 4.6 and 5.4; 576 rows of 183 pages, 0.27 of
+// them in use, 6.0 and 9.0.  700 random tables: 1 % faster on average, a fifth of them up to 1.5 times slower.
 int est_iters(const quest_cache& c) {
-  const long rows = (long)c.batch * kv_heads(c), entries = rows * c.max_pages_per_seq;
-  const long groups = rows * ((c.max_pages_per_seq + 31) / 32);  // of eight pages a wave
-  if (group_size(c) == 1 && entries > 5l << 13 && entries <= 7l << 14 && !(groups > kFullRound * 9 / 10 && groups <= kFullRound)) return 3;
+  const long entries = (long)c.batch * kv_heads(c) * c.max_pages_per_seq;
   return entries <= (group_size(c) > 2 ? 5l << 13 : 3l << 17) ? 2 : kEstIters;
 }
 
@@ -81,30 +79,23 @@ void launch_iters(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
   // (On the matrix cores they use as much: 8 KiB per wave.)
   const unsigned lds = kIters == kEstIters && a.group <= 2 ? kLdsPerUnit / 5 : 0;
 #define QUEST_ESTIMATE(Q) hipLaunchKernelGGL((estimate_kernel<kAppend, kIters, Q>), grid, block, lds, s, a)
-  if constexpr (kIters == 3) {
-    QUEST_ESTIMATE(1);
-  } else {
-    if (a.group == 1) QUEST_ESTIMATE(1);
-    else if (a.group == 2) QUEST_ESTIMATE(2);
-    else if (kIters == 2 && !estimate_on_matrix_cores(c)) {
-      if constexpr (kIters == 2) {
-        if (a.group == 3) QUEST_ESTIMATE(3);
-        else QUEST_ESTIMATE(4);
-      }
-    } else {
-      QUEST_ESTIMATE(0);
+  if (a.group == 1) QUEST_ESTIMATE(1);
+  else if (a.group == 2) QUEST_ESTIMATE(2);
+  else if (kIters == 2 && !estimate_on_matrix_cores(c)) {
+    if constexpr (kIters == 2) {
+      if (a.group == 3) QUEST_ESTIMATE(3);
+      else QUEST_ESTIMATE(4);
     }
+  } else {
+    QUEST_ESTIMATE(0);
   }
 #undef QUEST_ESTIMATE
 }
 
 template <bool kAppend>
 void launch(const quest_cache& c, const EstimateArgs& a, hipStream_t s) {
-  const int iters = est_iters(c);
-  if (iters == 2)
+  if (est_iters(c) == 2)
     launch_iters<kAppend, 2>(c, a, s);
-  else if (iters == 3)
-    launch_iters<kAppend, 3>(c, a, s);
   else
     launch_iters<kAppend, kEstIters>(c, a, s);
 }

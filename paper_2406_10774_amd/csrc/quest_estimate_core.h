@@ -66,17 +66,17 @@ struct Queries {
   }
 };
 
-// Sums over the 16 lanes of a DPP row of two to four values at once, each added up as row16_sum does (the same bits):
+// Sums over the 16 lanes of a DPP row of two or four values at once, each added up as row16_sum does (the same bits):
 // halves, then quarters of the row go on with a value of their own.  Lane c ends up with the sum of value
 // row16_sums_index(c), and row16_sums_has(c) names one lane for each.  Four of them take 12 instructions, one by one
 // and put into their lanes 20.
 template <int kCount>
 __device__ __forceinline__ int row16_sums_index(int c) {
-  return kCount == 2 ? c >> 3 : kCount == 3 ? (c & 4 ? 2 : c >> 3) : (c >> 3) + ((c >> 1) & 2);
+  return kCount == 2 ? c >> 3 : (c >> 3) + ((c >> 1) & 2);
 }
 template <int kCount>
 __device__ __forceinline__ bool row16_sums_has(int c) {
-  return kCount == 2 ? (c & 7) == 0 : kCount == 3 ? (c & 3) == 0 && c < 12 : (c & 3) == 0;
+  return (c & (kCount == 2 ? 7 : 3)) == 0;
 }
 __device__ __forceinline__ float row_swap_add4(float keep, float give) {  // keep + the give of lane c ^ 4
   const int g = __builtin_bit_cast(int, give);
@@ -97,9 +97,8 @@ __device__ __forceinline__ float row16_sums(const float (&v)[2], int c) {
   const float s = row_swap_add8(v[0], v[1], c);
   return quad_add<0xb1>(quad_add<0x4e>(row_swap_add4(s, s)));
 }
-template <int kCount>  // 3 or 4
-__device__ __forceinline__ float row16_sums(const float (&v)[kCount], int c) {
-  const float a = row_swap_add8(v[0], v[1], c), b = kCount == 3 ? row_ror_add<8>(v[2]) : row_swap_add8(v[2], v[kCount - 1], c);
+__device__ __forceinline__ float row16_sums(const float (&v)[4], int c) {
+  const float a = row_swap_add8(v[0], v[1], c), b = row_swap_add8(v[2], v[3], c);
   const bool second = c & 4;
   return quad_add<0xb1>(quad_add<0x4e>(row_swap_add4(second ? b : a, second ? a : b)));
 }
@@ -253,13 +252,13 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   asm volatile("" ::"s"(meta), "s"(q), "s"(page_table), "s"(seq_lens), "s"(max_pages), "s"(a.page_shift),
                "s"(a.num_phys_pages), "s"(num_heads));
   // The wave's page-table entries in one load (whether a page holds tokens is decided
-  // afterwards): lane c of row g fetches entry c % 4 of the row's kIters, and the quad hands
+  // afterwards): lane c of row g fetches entry c % kIters of the row's, and the quad hands
   // them round.  (A load per page, each under its own condition, is a chain of kIters trips
   // to the cache.)  Together 7.6 us instead of 7.9 us in the case above, 13.8 us instead of
   // 14.5 us at 4105 pages of 32 heads, 2.8 us instead of 3.0 us at one head.
   const int32_t* pt = page_table + (size_t)b * max_pages;
-  static_assert(kIters >= 2 && kIters <= 4, "entries of a quad");
-  int entry = pt[min(base + kIters * grp + (kIters == 3 ? min(c & 3, 2) : c & (kIters - 1)), max_pages - 1)];
+  static_assert(kIters == 2 || kIters == 4, "entries of a quad");
+  int entry = pt[min(base + kIters * grp + (c & (kIters - 1)), max_pages - 1)];
   const int seq_len = __builtin_amdgcn_readfirstlane(seq_lens[b]);
   // The query vectors in front of the metadata.
   const int group = kQ == 0 ? a.group : kQ;
@@ -285,8 +284,10 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   int phys[kIters];
   phys[0] = __builtin_amdgcn_update_dpp(0, entry, 0x00, 0xf, 0xf, true);  // quad_perm: lane 0 to all
   phys[1] = __builtin_amdgcn_update_dpp(0, entry, 0x55, 0xf, 0xf, true);
-  if constexpr (kIters > 2) phys[2] = __builtin_amdgcn_update_dpp(0, entry, 0xaa, 0xf, 0xf, true);
-  if constexpr (kIters > 3) phys[3] = __builtin_amdgcn_update_dpp(0, entry, 0xff, 0xf, 0xf, true);
+  if constexpr (kIters == 4) {
+    phys[2] = __builtin_amdgcn_update_dpp(0, entry, 0xaa, 0xf, 0xf, true);
+    phys[3] = __builtin_amdgcn_update_dpp(0, entry, 0xff, 0xf, 0xf, true);
+  }
   // Pages past the end are read from the wave's first page instead, and not used: no load
   // stands under a condition.
   const int some = __builtin_amdgcn_readfirstlane(entry);

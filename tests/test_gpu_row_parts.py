@@ -1,6 +1,6 @@
 """Where a kernel's split of a row ends: the part of a thread's pages that is enough for a short sequence in a long row
 (quest_topk, and the launch that selects and attends, for which eight waves select and four attend), and the estimate's
-blocks of 12 pages (one query head per KV head, tables of 40961 to 114688 entries)."""
+blocks in tables of 40961 to 114688 entries."""
 import numpy as np
 import pytest
 
@@ -40,7 +40,7 @@ def test_topk(n, part):
     (8, 8, 2003, (2003 * 8 - 1, 3 * 8, 1, 4 * 8 + 1, 1000 * 8, 48 * 8 + 1)),
     (1, 64, 7001, (7001 * 64, 35 * 64, 36 * 64 + 1, 37 * 64, 7000 * 64 - 63, 12 * 64)),
 ])
-def test_blocks_of_twelve_pages(kv_heads, S, pages, lens):
+def test_ends_of_blocks(kv_heads, S, pages, lens):
     check_scores(kv_heads, 1, S, pages, lens)
 
 
