@@ -61,7 +61,7 @@ struct Queries {
     const int grp = lane >> 4, c = lane & 15;
 #pragma unroll
     for (int i = 0; i < kRegs; ++i)
-      v[i] = kMatrix ? ld16(first + (size_t)min(g0 + c, group - 1) * (kHeadDim * 2) + i * 64 + grp * 16)
+      v[i] = kMatrix ? ld16(first + (uint32_t)(min(g0 + c, group - 1) * (kHeadDim * 2) + i * 64 + grp * 16))
                      : ld16(first + (kUpTo && kQ > 1 ? min(i, group - 1) : i) * (kHeadDim * 2) + c * 16);
   }
 };
@@ -165,7 +165,7 @@ __device__ __forceinline__ void score_wave(Queries<kQ>& q, uint4 (&mn)[kIters], 
       float z[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) z[i] = (s[0][i] + s[1][i]) + (s[2][i] + s[3][i]);
-      odd |= page < pages && !((z[0] + z[1]) + (z[2] + z[3]) > -INFINITY);
+      odd |= !((z[0] + z[1]) + (z[2] + z[3]) > -INFINITY);
       keep = fmaxf(keep, fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));  // heads 4g .. 4g + 3
     };
     score_heads();
@@ -176,7 +176,7 @@ __device__ __forceinline__ void score_wave(Queries<kQ>& q, uint4 (&mn)[kIters], 
     }
     // An infinite entry, or one that is no number, may have met a zero.  Such pages, which a cache
     // hardly ever holds, are scored head by head.
-    if (__ballot(odd) == 0) {
+    if (__ballot(odd & (page < pages)) == 0) {
       LanePair s = pair_across16(__builtin_bit_cast(uint32_t, keep));
       s = pair_across32(__builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second))));
       keep = fmaxf(__builtin_bit_cast(float, s.first), __builtin_bit_cast(float, s.second));
@@ -331,7 +331,7 @@ __device__ __forceinline__ void estimate_wave(const EstimateArgs& a, int b, int 
   }
 
   score_wave<kIters, kQ>(queries, mn, mx, num_pages - base, stage, lane, [&](bool has, int page, float score) {
-    if (has && base + page < num_pages) row[base + page] = score;
+    if (has & (base + page < num_pages)) row[base + page] = score;  // (&: one branch, not two)
   });
 }
 
