@@ -21,6 +21,39 @@ def kernel_launches(call):
     return count.value
 
 
+def check_attention(out, lse, q, k_pool, v_pool, table, lens, lists, sm_scale, what=""):
+    """fp32 out [B][H][D] and lse [B][H] against float64 attention over the listed pages (any device).
+    The limit, per (sequence, head): a logit is a sum of D products that are exact, a weight an exp2 and a division
+    (2^-21), out and lse sums over n tokens.  Roundings are as often up as down, so N of them make
+    sqrt(N) * 2^-24 of what is summed; eight times that.  A token of ordinary weight that is missing or
+    attended twice is beyond it up to several thousand tokens."""
+    import torch
+    B, H, D = q.shape
+    Hkv, S = k_pool.shape[1:3]
+    G = H // Hkv
+    for b in range(B):
+        pages = lists[b].long()                                                     # [Hkv][K]
+        phys = table[b].long()[pages.clamp(min=0)]
+        at = pages[..., None] * S + torch.arange(S, device=pages.device)
+        valid = ((pages[..., None] >= 0) & (at < int(lens[b]))).flatten(1)          # [Hkv][K S]
+        head = torch.arange(Hkv, device=pages.device)[:, None]
+        for g in range(G):
+            qb = q[b].view(Hkv, G, D)[:, g].double()
+            k, v = (torch.where(valid[..., None], pool[phys, head].flatten(1, 2).double(), 0.0) for pool in (k_pool, v_pool))
+            products = k * qb[:, None] * sm_scale
+            logits = torch.where(valid, products.sum(-1), -math.inf)
+            want_lse = logits.logsumexp(-1)
+            p = (logits - want_lse[:, None]).exp()
+            want = (p[..., None] * v).sum(1)
+            size = products.abs().sum(-1).max(-1).values
+            n = valid.sum(-1)
+            limit = 8 * (math.sqrt(D) * 2.0 ** -24 * size + 2.0 ** -21 + n.sqrt() * 2.0 ** -24)
+            err = (out[b].view(Hkv, G, D)[:, g] - want).abs() / (p[..., None] * v.abs()).sum(1)
+            err_lse = (lse[b].view(Hkv, G)[:, g] - want_lse).abs() / want_lse.abs().clamp(min=1.0)
+            assert bool((err.max(-1).values <= limit).all()), (what, b, g, float((err.max(-1).values / limit).max()))
+            assert bool((err_lse <= limit).all()), (what, b, g, float((err_lse / limit).max()))
+
+
 class Layer:
     """Device copy of one layer's paged KV cache plus the buffers of a decode step."""
 
