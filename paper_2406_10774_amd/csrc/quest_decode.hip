@@ -46,7 +46,7 @@ constexpr int kDecWaves = 4;
 // them, and the longest row.
 constexpr int kSelListCap = 2048;
 constexpr int kLookAhead = 8;
-constexpr int kMostSelected = 256 * 34, kMostSelectedOfGroup = 256 * 20;
+constexpr int kMostSelected = 512 * 17, kMostSelectedOfGroup = 512 * 10;
 
 struct DecodeArgs : AttnArgs {
   const int32_t* topk_idx;  // the page list [B][kv heads][k_pages] (nullptr: selected inside the launch, or every page)
@@ -650,7 +650,8 @@ int launch_decode(const quest_cache& c, const void* q, const int32_t* topk_idx, 
     // group's: a list of 16 pages of 8 tokens, 256 of them 8.1 us with four, 7.5 with eight, but 264 10.7 and 14.7, 384
     // 11.7 and 15.9; 64 pages of 16 tokens, 264 35.1 and 45.3, 512 48.3 and 53.8.  One query head's: 16 pages
     // of 8 tokens, 512 11.8 and 11.2, but 640 15.1 and 17.6, 1024 18.5 and 21.5 (other row lengths 0 to 3 % less);
-    // 64 pages of 16 tokens, 320 items of three splits 32.5 and 35.1.
+    // 64 pages of 16 tokens, 320 items of three splits 32.5 and 35.1; 16 ragged sequences of 32 heads and up to 4099 pages
+    // (512), 128 pages in the list, 88.6 and 88.2.
 #define QUEST_SELECT_CASES(C)     \
   QUEST_SELECT_CASE(false, C, 4, 2) \
   QUEST_SELECT_CASE(false, C, 4, 4) \
@@ -715,14 +716,12 @@ bool selected_whole(const quest_cache& c) {
 
 // Selection and attention in one launch: while a row of scores fits the in-register selection
 // and the list fits in LDS.  Every split of a head repeats the selection, which costs less than the
-// launches it saves.  Where the longest tiling ends, us a call over rows of 8704 pages this way / with candidates
-// picked by a launch of their own: 32 heads, lists of 64 pages 12.7 / 12.5, 256 20.8 / 20.9, 1024 52.5 /
-// 54.1; 16 sequences of them, 64 pages 53.2 / 61.0, 256 180 / 188; with 2611 pages of the row in use 10.6 /
-// 12.3 and 18.6 / 20.9, with 435 10.5 / 11.0 and 18.3 / 19.2.  Full rows of 6913 pages on in one sequence of
-// few heads with short lists are the worst of it (8 heads, 64 pages 11.4 / 10.9); the host does not know
-// how full they are.  (Rows of 8193 pages with a Top-K launch 47.8 us a step, 44.4 this way.)  Groups of query heads have less to stream that hides it: 3 sequences of 6799 pages, 32
-// query / 8 KV heads, 26.7 us a step, 25.9 with candidates, 6 of 8210 pages, 64 / 8 heads, 64.5 and 63.1;
-// 2 of 4627 pages 26.4, 28.1 with a Top-K launch.
+// launches it saves.  The lines lie where the tilings end, us a call this way / with candidates picked by a launch of
+// their own, rows of 8704 pages: 32 heads, lists of 64 pages 11.8 / 12.2, 256 18.1 / 19.4, 1024 47.5 / 50.9; 16
+// sequences of them 50.0 / 59.7 and 169 / 180; with 2611 pages of the row in use 10.1 / 12.3 and 17.5 / 20.1, with
+// 435 and 256 in the list 16.7 / 17.6; 8 heads, 64 pages 10.2 / 10.9.  Rows of 5120 pages of 32 query / 8 KV heads, lists
+// of 64: 10.1 / 12.3, 3 sequences 10.9 / 13.4, 32 26.9 / 30.5, 40 40.2 / 50.5.  (Tilings for longer rows would gain as
+// well: 2 to 18 % at 8720 to 10240 pages, groups 2 to 20 % at 5200 to 8210.)
 bool select_decode_supported(const quest_cache& c, int k_pages) {
   return !(c.flags & QUEST_FLAG_SEPARATE_LAUNCHES) && k_pages <= kSelListCap && selected_whole(c);
 }
@@ -761,8 +760,9 @@ size_t selection_workspace_bytes(const quest_cache& c) {
 //   9 to 112 rows, 192 pages: 32 heads of 61 9.7 / 8.1, of 124 11.0 / 9.5; but 32 of 249, all attended, 12.0 / 13.0, of 257
 //   17.0 / 19.0; 38 of 288 8.9 / 9.6; with more than half of the pages in the list 128: 64 rows of 161, all
 //   attended, 13.6 / 14.4;
-//   113 to 160 rows, 512 pages: 144 of 434 16.5 / 14.3, 128 of 507 18.2 / 17.5; but 120 of 740 16.6 / 18.3, 160 of 881 19.5 / 20.7; more rows up to 256, 1024 pages: 6 sequences of 32 heads, 434 pages
-//   27.8 / 26.6, 996 36.5 / 34.3; but 5 to 8 of 1500 to 2000 pages, 2 to 10 % slower;
+//   113 to 160 rows, 512 pages: 144 of 434 16.5 / 14.3, 128 of 507 18.2 / 17.5; but 120 of 740 16.6 / 18.3, 160
+//   of 881 19.5 / 20.7; more rows up to 256, 1024 pages: 6 sequences of 32 heads, 434 pages 27.8 / 26.6, 996
+//   36.5 / 34.3; but 5 to 8 of 1500 to 2000 pages, 2 to 10 % slower;
 //   257 to 384 rows, which leave the second round of units half empty, 256 pages: 280 of 315 15.1 / 16.9, 336 of
 //   305 18.0 / 19.8; up to 512 rows, 512 pages: 12 sequences of 32 heads, 434 49.5 / 47.3;
 //   three splits of a row, or more rows, 256 pages: 640 rows of 500 up to 8 % slower; thousands of rows of a few pages

@@ -40,15 +40,17 @@ __global__ __launch_bounds__(kEstWaves* kWave, kQ == 0 ? (kIters == 2 ? 7 : 4) :
   estimate_wave<kAppend, kIters, kQ>(a, blockIdx.y, blockIdx.z, base, stage + (kQ == 0 ? wave * 4 * kIters * kMetaBytes : 0));
 }
 
+}  // namespace
+
 // The matrix cores score groups.  Two query heads meet the metadata of 16 sequences of up to 32k tokens
 // in 14.7 us on the vector unit (one in 14.4), of 4 sequences in 6.1: no longer than four on the matrix
 // cores (14.2 and 6.4).  Nor do three or four over small tables, where the turn through LDS shows: 2.85
 // against 2.98 us at 8100 entries, but 4.08 against 3.75 at 16400.  Five and more are faster there in every
 // table: five 3.00 and 2.83 at 256 entries, 4.03 and 3.73 at 9600; eight 3.17 and 2.93, 4.64 and 3.86.
-}  // namespace
 bool estimate_on_matrix_cores(const quest_cache& c) {
   return group_size(c) > ((long)c.batch * kv_heads(c) * c.max_pages_per_seq <= (3l << 12) ? 4 : 2);
 }
+
 namespace {
 
 // Pages per wave: 16 (eight wave-wide loads in flight) once the table is large; a smaller

@@ -346,7 +346,8 @@ struct RowOfPages {
 // pages go to LDS.  A row has at most kWaves * kPasses * 4 kIters pages;
 // wave w takes blocks w, w + kWaves, .. of 4 kIters pages, with the entries of up to four blocks in flight, and
 // folds them in the order they come.  What bounds it: the launch's start and two trips to memory, 1.5 us, then
-// 64 bytes a clock from L2 or, where few compute units share a row, about 27 KiB per us from memory.
+// 64 bytes a clock from L2 or, where few compute units share a row, about 27 KiB per us from memory.  (A row
+// is fetched into L2 once: in eight splits of 124 or 188 pages, 32 heads, a step fetches 1.02 times its bytes.)
 // Nobody has inserted the newest token yet: every work-group of the row stores its key and value (the
 // same bytes; each later reads what it stored itself) and folds the key into the entry it scores, and
 // one of them writes that entry back (store_row).  Another work-group may find the entry as it was or with the key folded in,
